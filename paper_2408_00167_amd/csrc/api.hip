@@ -315,7 +315,8 @@ bool owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n) {
   if (ctx->repos.order == FINCH_ORDER_RANK) {
     size_t npad = 64;
     while (npad < static_cast<size_t>(pl.r_max)) npad <<= 1;
-    if (static_cast<size_t>(pl.r_max) * 4 + 8 + npad * 8 > finch::kOwnerSelectBytes || ctx->layer_group > 1)
+    if (npad > static_cast<size_t>(finch::kOwnerRankRows) ||
+        static_cast<size_t>(pl.r_max) * 4 + 8 + npad * 8 > finch::kOwnerSelectBytes || ctx->layer_group > 1)
       return false;
   }
   // the workgroups of a layer wait for each other: all of them must be on the chip at once
@@ -395,8 +396,8 @@ finch_status run_select(finch_ctx* ctx, const LaunchParams& p, const Plan& pl, v
     ProfScope ps(ctx, FINCH_KERNEL_SELECT, s);
     e = ctx->layer_group > 1
             ? finch::launch_select_layer(p, ctx->layer_group,
-                                         reinterpret_cast<float*>(static_cast<char*>(ws) + pl.off_layer), s)
-            : finch::launch_select(p, s);
+                                         reinterpret_cast<float*>(static_cast<char*>(ws) + pl.off_layer), pl.n_max, s)
+            : finch::launch_select(p, pl.n_max, s);
   }
   return e == hipSuccess ? FINCH_OK : hip_fail(ctx, e);
 }
@@ -604,6 +605,7 @@ finch_status finch_create(const finch_config* cfg, finch_ctx** out) {
   if (e == hipSuccess && cfg->dtype == FINCH_BF16) e = finch::set_max_lds_owner(ctx->max_lds);
   if (e == hipSuccess && cfg->dtype == FINCH_BF16) e = finch::set_max_lds_owner_doc(ctx->max_lds);
   if (e == hipSuccess && cfg->dtype == FINCH_F32) e = finch::set_max_lds_owner_f32(ctx->max_lds);
+  if (e == hipSuccess) e = finch::set_max_lds_select(ctx->max_lds);
   // the re-positioning kernel also has a little static LDS
   if (e == hipSuccess) e = finch::set_max_lds_reposition(ctx->max_lds - 1024);
   if (e != hipSuccess) {

@@ -23,9 +23,15 @@ __host__ __device__ inline int stream_slices(int n_keys, int slice_keys) {
 // One-workgroup-per-problem path: most prompt rows staged per pass over the keys.
 constexpr int kOwnerMaxRowChunk = 256;
 // LDS the one-workgroup-per-problem kernels keep behind their selection scratch (kept indices etc.).
-constexpr size_t kOwnerSelectBytes = 24 * 1024;
+// (a workgroup has the compute unit to itself anyway, so what the prompt rows leave is free: kept
+// indices and order keys of a step with 12000 candidates fit beside 256 prompt rows of 256 bytes)
+constexpr size_t kOwnerSelectBytes = 60 * 1024;
+// Most kept rows a workgroup of these kernels ranks by score (a bitonic network in registers).
+constexpr int kOwnerRankRows = 2048;
 // Most problems per layer run that the one-workgroup-per-problem kernels select for together.
 constexpr int kOwnerMaxLayer = 16;
+// Most LDS a workgroup of the selection kernels asks for.
+constexpr size_t kSelLdsBytes = 144 * 1024;
 // Rows copied by one workgroup of the compaction kernels.
 constexpr int kGatherRows = 64;
 // Most kept rows per problem when slots go by score rank (their order keys are held
@@ -72,8 +78,9 @@ hipError_t launch_colsum_bf16(int head_dim, const LaunchParams& p, size_t lds, h
 hipError_t launch_rowstats_f32(int head_dim, const LaunchParams& p, size_t lds, hipStream_t s);
 hipError_t launch_colsum_f32(int head_dim, const LaunchParams& p, size_t lds, hipStream_t s);
 hipError_t launch_lse(const LaunchParams& p, hipStream_t s);
-hipError_t launch_select(const LaunchParams& p, hipStream_t s);
-hipError_t launch_select_layer(const LaunchParams& p, int group, float* layer_scores, hipStream_t s);
+hipError_t launch_select(LaunchParams p, int n_max, hipStream_t s);
+hipError_t launch_select_layer(LaunchParams p, int group, float* layer_scores, int n_max, hipStream_t s);
+hipError_t set_max_lds_select(size_t bytes);
 hipError_t launch_gather(const LaunchParams& p, int row_bytes, int r_max, hipStream_t s);
 size_t owner_lds_bytes(int head_dim, int row_chunk);
 hipError_t launch_prompt_lse(const LaunchParams& p, int head_dim, bool bf16, int rows_max, hipStream_t s);

@@ -8,7 +8,7 @@ namespace finch {
 // at most kOwnerMaxRowChunk).
 size_t owner_lds_bytes(int head_dim, int row_chunk) {
   // staged prompt rows, then the larger of {pass-1 statistics + lse + block counter}
-  // and the selection scratch with room for about 6000 kept indices
+  // and the selection scratch
   const size_t q = static_cast<size_t>(row_chunk) * (head_dim * 2 + 16);
   const size_t scoring = static_cast<size_t>(row_chunk) * (kOwnWaves * 8 + 4) + 16;
   const size_t selection = sizeof(SelLds) + kOwnerSelectBytes;

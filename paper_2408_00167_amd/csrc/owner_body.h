@@ -251,14 +251,26 @@ __device__ __forceinline__ void own_rank_kept(unsigned long long* ranked, int r,
   }
 }
 
+// Where the candidates' order keys go in the LDS scratch `sel` of sel_bytes: behind the
+// selection's own words and the kept indices, and behind the first `busy` bytes (what is still
+// in use while scores are being written).  Null if there is no room.
+__device__ __forceinline__ unsigned* own_sel_keys(char* sel, size_t sel_bytes, size_t busy, int N, int r) {
+  const size_t mine = sizeof(SelLds) + (static_cast<size_t>(r) + kSelIdxPad) * 4;
+  const size_t off = ((mine > busy ? mine : busy) + 15) & ~size_t{15};
+  if (N > kOwnThreads * kSelRegKeys || off + static_cast<size_t>(N) * 4 > sel_bytes) return nullptr;
+  return reinterpret_cast<unsigned*>(sel + off);
+}
+
 // The rest of a step once this workgroup's scores are in memory (and a barrier has been
 // passed since): top-r (Method: t = top-r(A_agg, r); with `layered` on the sum over the
 // layer's heads) and compaction (Method: Managing the Cache) of rows of SEGS 16-byte
 // pieces with E elements each.  `sel` is LDS scratch of sel_bytes (>= sizeof(SelLds) +
-// kOwnerSelectBytes); `dst` the scores of this problem.
+// kOwnerSelectBytes); `dst` the scores of this problem; `lkeys` what own_sel_keys said, with
+// the order keys of these scores in it already unless `layered` or keys_staged is false.
 template <int SEGS, int E, bool ROT>
 __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const finch_problem& pb, int slot, int N,
                                                 FINCH_GLOBAL float* dst, char* sel, size_t sel_bytes,
+                                                unsigned* lkeys, bool keys_staged,
                                                 const finch_problem* step_probs, int epoch, bool layered,
                                                 int* sync_words, int tid) {
   const int lane = tid & 63, wave = tid >> 6;
@@ -274,11 +286,8 @@ __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const f
   if (identity) {
     for (int i = tid; i < N; i += kOwnThreads) gidx[i] = i;
   } else {
-    size_t used = sizeof(SelLds);
-    if (used + static_cast<size_t>(r) * 4 <= sel_bytes) {
-      lidx = reinterpret_cast<int*>(sel + used);
-      used += static_cast<size_t>(r) * 4;
-    }
+    if (sizeof(SelLds) + (static_cast<size_t>(r) + kSelIdxPad) * 4 <= sel_bytes)
+      lidx = reinterpret_cast<int*>(sel + sizeof(SelLds));
     if (layered) {
       // this workgroup's scores are out (stored past the caches, and every thread has waited
       // for its own stores at the barrier after pass 2); wait until all L workgroups of the
@@ -315,20 +324,21 @@ __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const f
     }
     const LayerScores layer_sum = {fl->layer_src, L};
     const OneScoreVector own = {dst};
-    if (N <= kOwnThreads * kSelRegKeys) {
-      if (layered) select_regs<kOwnThreads>(layer_sum, N, r, gidx, lidx, fl, tid, lane, wave);
-      else select_regs<kOwnThreads>(own, N, r, gidx, lidx, fl, tid, lane, wave);
-    } else {
-      unsigned* lkeys = nullptr;
-      if (used + static_cast<size_t>(N) * 4 <= sel_bytes) {
-        lkeys = reinterpret_cast<unsigned*>(sel + used);
-        for (int i = tid; i < N; i += kOwnThreads) lkeys[i] = order_key(layered ? layer_sum(i) : own(i));
+    if (lkeys) {  // (then there is room for the indices as well)
+      if (layered || !keys_staged) {
+        if (layered) sel_stage_keys<kOwnThreads>(layer_sum, N, lkeys, tid);
+        else sel_stage_keys<kOwnThreads>(own, N, lkeys, tid);
+        __syncthreads();
       }
+      select_keys_any<kOwnThreads, true>(lkeys, N, r, gidx, lidx, fl, tid, lane, wave);
+    } else {
       __syncthreads();
-      if (layered) select_generic<kOwnThreads>(lkeys, layer_sum, N, r, gidx, lidx, fl, tid, lane, wave);
-      else select_generic<kOwnThreads>(lkeys, own, N, r, gidx, lidx, fl, tid, lane, wave);
+      if (layered) select_generic<kOwnThreads>(nullptr, layer_sum, N, r, gidx, lidx, fl, tid, lane, wave);
+      else select_generic<kOwnThreads>(nullptr, own, N, r, gidx, lidx, fl, tid, lane, wave);
     }
-    __syncthreads();  // idx (LDS and memory) complete
+    __syncthreads();  // idx complete
+    if (lkeys)
+      for (int t = tid; t < r; t += kOwnThreads) gidx[t] = lidx[t];
     // (the other workgroups' scores have been read for the last time)
     if (layered && tid == 0) __hip_atomic_fetch_add(sync_words + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -397,6 +407,13 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   FINCH_GLOBAL float* dst = as_global_mut<float>(gscores);
   const int L = prm.layer_group;
   const bool layered = stages && L > 1 && pb.r > 0 && pb.r < N;  // the same in every workgroup of the run
+  // selection scratch lies behind the staged prompt rows, over the statistics of pass 1; the
+  // scores' order keys go there from pass 2 (past what pass 2 still reads)
+  char* const sel = smem + RC * kStride;
+  const size_t sel_bytes = prm.lds_bytes - static_cast<size_t>(RC) * kStride;
+  unsigned* const lkeys = (stages && pb.r > 0 && pb.r < N)
+                              ? own_sel_keys(sel, sel_bytes, static_cast<size_t>(RC) * (kOwnWaves * 8 + 4) + 16, N, pb.r)
+                              : nullptr;
   int* const sync_words = (stages && L > 1) ? prm.layer_sync + 2 * (slot / L) : nullptr;
   if (sync_words && epoch > 0) {
     // nobody of the run may still be adding up the scores of the step before when this
@@ -623,6 +640,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
           // (scores other workgroups will read go out past this compute unit's caches)
           if (layered) __hip_atomic_store(gscores + key, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           else dst[key] = val;
+          if (lkeys) lkeys[key] = order_key(val);
         }
       };
       if (b >= 0) {
@@ -649,11 +667,9 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   staged_rows = Rp;
   if (!stages) return false;
 
-  // ---- top-r and compaction; selection scratch behind the staged prompt rows (the pass-1
-  // statistics are dead)
-  own_finish_step<D / 8, 8, ROT>(prm, pb, slot, N, dst, smem + RC * kStride,
-                                 prm.lds_bytes - static_cast<size_t>(RC) * kStride, step_probs, epoch, layered,
-                                 sync_words, tid);
+  // ---- top-r and compaction (the pass-1 statistics are dead)
+  own_finish_step<D / 8, 8, ROT>(prm, pb, slot, N, dst, sel, sel_bytes, lkeys, /*keys_staged=*/true, step_probs, epoch,
+                                 layered, sync_words, tid);
   return layered;
 }
 

@@ -186,8 +186,10 @@ __device__ __forceinline__ bool own_step_body_f32(const LaunchParams& prm, const
     __syncthreads();  // the staged rows may be replaced; after the last chunk: the scores are out
   }
   if (!stages) return false;
-  own_finish_step<D / 4, 4, ROT>(prm, pb, slot, N, dst, l.sel, prm.lds_bytes - static_cast<size_t>(l.sel - smem),
-                                 step_probs, epoch, layered, sync_words, tid);
+  const size_t sel_bytes = prm.lds_bytes - static_cast<size_t>(l.sel - smem);
+  unsigned* const lkeys = (pb.r > 0 && pb.r < N) ? own_sel_keys(l.sel, sel_bytes, 0, N, pb.r) : nullptr;
+  own_finish_step<D / 4, 4, ROT>(prm, pb, slot, N, dst, l.sel, sel_bytes, lkeys, /*keys_staged=*/false, step_probs,
+                                 epoch, layered, sync_words, tid);
   return layered;
 }
 

@@ -1,15 +1,41 @@
 // Selection kernel: exact top-r of the per-key scores of one problem (Method:
 // t = top-r(A_agg, r)), ties to the lower index, output in ascending index order.
 //
-// One workgroup per problem; the algorithm is in select_common.h.  Up to 16384
-// candidates are held in registers; larger problems re-read their scores (L2) in
-// every round.
+// One workgroup per problem; the algorithm is in select_common.h.  Problems whose order keys
+// fit into the launch's LDS (prm.lds_bytes) take it there; larger ones re-read their
+// scores (L2) in every round.
 #include "select_common.h"
 
 namespace finch {
 
+namespace {
+
+// LDS of a selection over at most n_max candidates: scratch and order keys, or the scratch
+// alone if they do not fit.
+size_t select_lds_bytes(int n_max) {
+  const size_t all = sizeof(SelLds) + static_cast<size_t>(n_max) * 4;
+  return n_max <= kSelThreads * kSelRegKeys && all <= kSelLdsBytes ? all : sizeof(SelLds);
+}
+
+// Top-r of `score_of` into idx by the whole workgroup, 0 < r < N.
+__device__ __forceinline__ void select_problem(const LaunchParams& prm, char* smem, const FINCH_GLOBAL float* scores, int N,
+                                               int r, FINCH_GLOBAL int* idx, int tid, int lane, int wave) {
+  SelLds* lds = reinterpret_cast<SelLds*>(smem);
+  const OneScoreVector src = {scores};
+  if (sizeof(SelLds) + static_cast<size_t>(N) * 4 <= prm.lds_bytes && N <= kSelThreads * kSelRegKeys) {
+    unsigned* keys = reinterpret_cast<unsigned*>(smem + sizeof(SelLds));
+    sel_stage_keys<kSelThreads>(src, N, keys, tid);
+    __syncthreads();
+    select_keys_any<kSelThreads, false>(keys, N, r, idx, nullptr, lds, tid, lane, wave);
+  } else {
+    select_generic<kSelThreads>(nullptr, src, N, r, idx, nullptr, lds, tid, lane, wave);
+  }
+}
+
+}  // namespace
+
 __global__ __launch_bounds__(kSelThreads) void select_topr(LaunchParams prm) {
-  __shared__ SelLds lds;
+  extern __shared__ __align__(16) char smem[];
   const int p = blockIdx.x;
   const finch_problem pb = prm.probs[p];
   const int N = pb.c + pb.m;
@@ -23,11 +49,7 @@ __global__ __launch_bounds__(kSelThreads) void select_topr(LaunchParams prm) {
     for (int i = tid; i < N; i += kSelThreads) idx[i] = i;
     return;
   }
-  if (N <= kSelThreads * kSelRegKeys) {
-    select_regs<kSelThreads>(OneScoreVector{scores}, N, r, idx, nullptr, &lds, tid, lane, wave);
-  } else {
-    select_generic<kSelThreads>(nullptr, OneScoreVector{scores}, N, r, idx, nullptr, &lds, tid, lane, wave);
-  }
+  select_problem(prm, smem, scores, N, r, idx, tid, lane, wave);
 }
 
 // Layer-wise selection (Method: "Sum over heads" - the scores of all heads of a layer
@@ -38,7 +60,7 @@ __global__ __launch_bounds__(kSelThreads) void select_topr(LaunchParams prm) {
 // per run), selects on it and writes the same indices to every problem of the run.
 __global__ __launch_bounds__(kSelThreads) void select_layer(LaunchParams prm, int group,
                                                             float* layer_scores) {
-  __shared__ SelLds lds;
+  extern __shared__ __align__(16) char smem[];
   const int run = blockIdx.x;
   const int p0 = run * group;
   const finch_problem pb0 = prm.probs[p0];
@@ -62,11 +84,7 @@ __global__ __launch_bounds__(kSelThreads) void select_layer(LaunchParams prm, in
   }
   __syncthreads();  // the sums this workgroup wrote are read back by other threads below
   FINCH_GLOBAL int* idx0 = as_global_mut<int>(pb0.idx);
-  if (N <= kSelThreads * kSelRegKeys) {
-    select_regs<kSelThreads>(OneScoreVector{total}, N, r, idx0, nullptr, &lds, tid, lane, wave);
-  } else {
-    select_generic<kSelThreads>(nullptr, OneScoreVector{total}, N, r, idx0, nullptr, &lds, tid, lane, wave);
-  }
+  select_problem(prm, smem, total, N, r, idx0, tid, lane, wave);
   __syncthreads();
   for (int g = 1; g < group; ++g) {
     FINCH_GLOBAL int* idx = as_global_mut<int>(prm.probs[p0 + g].idx);
@@ -74,17 +92,28 @@ __global__ __launch_bounds__(kSelThreads) void select_layer(LaunchParams prm, in
   }
 }
 
-hipError_t launch_select_layer(const LaunchParams& p, int group, float* layer_scores, hipStream_t s) {
+hipError_t launch_select_layer(LaunchParams p, int group, float* layer_scores, int n_max, hipStream_t s) {
   if (p.n_problems == 0) return hipSuccess;
-  hipLaunchKernelGGL(select_layer, dim3(p.n_problems / group), dim3(kSelThreads), 0, s, p, group,
+  p.lds_bytes = static_cast<uint32_t>(select_lds_bytes(n_max));
+  hipLaunchKernelGGL(select_layer, dim3(p.n_problems / group), dim3(kSelThreads), p.lds_bytes, s, p, group,
                      layer_scores);
   return hipGetLastError();
 }
 
-hipError_t launch_select(const LaunchParams& p, hipStream_t s) {
+hipError_t launch_select(LaunchParams p, int n_max, hipStream_t s) {
   if (p.n_problems == 0) return hipSuccess;
-  hipLaunchKernelGGL(select_topr, dim3(p.n_problems), dim3(kSelThreads), 0, s, p);
+  p.lds_bytes = static_cast<uint32_t>(select_lds_bytes(n_max));
+  hipLaunchKernelGGL(select_topr, dim3(p.n_problems), dim3(kSelThreads), p.lds_bytes, s, p);
   return hipGetLastError();
+}
+
+hipError_t set_max_lds_select(size_t bytes) {
+  if (bytes < kSelLdsBytes) return hipErrorInvalidValue;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_topr),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kSelLdsBytes));
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&select_layer), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             static_cast<int>(kSelLdsBytes));
 }
 
 }  // namespace finch

@@ -3,11 +3,13 @@
 // ascending index order.  Shared by the selection kernel and the
 // one-workgroup-per-problem step kernel.
 //
-// The r-th largest value T is found by a radix select over order-preserving 32-bit
-// keys, 8 bits per round, histogramming in LDS.  The kept set is { key > T } plus
-// the first (r - #greater) candidates with key == T in index order, and an ordered
-// scan gives each kept index its output slot, so nothing is sorted.
+// The r-th largest value T is found over order-preserving 32-bit keys with LDS histograms.
+// The kept set is { key > T } plus the first (r - #greater) candidates with key == T in
+// index order, and an ordered scan gives each kept index its output slot, so nothing is
+// sorted.
 #pragma once
+
+#include <type_traits>
 
 #include "finch_internal.h"
 
@@ -15,8 +17,16 @@ namespace finch {
 
 constexpr int kSelThreads = 1024;          // threads of the selection kernel
 constexpr int kSelMaxWaves = 16;           // most waves of any workgroup that selects
-// select_regs keeps up to this many candidates per thread in registers
-constexpr int kSelRegKeys = 16;
+// select_keys keeps up to this many candidates per thread in registers
+constexpr int kSelRegKeys = 31;
+// its histograms: 2048 bins, 32 per lane; a lane's bins stand together, 4 words apart from
+// the next lane's, so that the 16-byte reads of neighbouring lanes fall into different banks
+constexpr int kSelBinBits = 11;
+constexpr int kSelLaneWords = 36;
+constexpr int kSelHistWords = 64 * kSelLaneWords;
+constexpr int kSelIdxPad = 32;
+constexpr int kSelCand = 16;  // a bin with at most this many candidates is resolved directly
+__device__ __forceinline__ int sel_hist_at(unsigned bin) { return static_cast<int>(bin + (bin >> 5) * 4u); }
 
 // Monotone map float -> uint32 (larger float <=> larger key); -0 counts as +0.
 __device__ __forceinline__ unsigned order_key(float f) {
@@ -38,11 +48,27 @@ __device__ __forceinline__ int wave_inclusive_scan(int x) {
   return v;
 }
 
+// Maximum over the 64 lanes of a wave, the same way.
+__device__ __forceinline__ unsigned wave_max_u32(unsigned x) {
+  int v = static_cast<int>(x);
+  auto mx = [](int a, int b) { return static_cast<unsigned>(a) > static_cast<unsigned>(b) ? a : b; };
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true));
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true));
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true));
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true));
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
+  v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
+  return static_cast<unsigned>(__builtin_amdgcn_readlane(v, 63));
+}
+
 constexpr int kSelMaxLayer = 16;  // most score vectors a selection inside a workgroup adds up
 
 struct SelLds {  // LDS scratch of a selection
-  int hist[4][256];
+  alignas(16) int hist[2][kSelHistWords];
+  alignas(16) unsigned cand[kSelCand];
   int wave_tot[2][kSelMaxWaves];
+  unsigned wave_max[2][kSelMaxWaves];  // largest key and largest complement of a key per wave
+  int n_cand;
   int digit[4], remaining[4];
   const float* layer_src[kSelMaxLayer];  // LayerScores: the score vectors of a layer's heads
   int layer_gave_up;                     // the wait for the layer's other workgroups expired
@@ -103,36 +129,35 @@ __device__ __forceinline__ void sel_pick_digit(const int* hist, int remaining, i
   }
 }
 
-// The same by every wave for itself (all waves read the same histogram and get the same
-// answer, so nothing has to be handed round through LDS and no barrier follows): the bin
-// where the count from the top reaches `remaining`, and the rank left inside it.
-__device__ __forceinline__ void sel_pick_digit_wave(const int* hist, int remaining, int lane, int& digit_out,
-                                                    int& left_out) {
-  const int h0 = hist[4 * lane], h1 = hist[4 * lane + 1], h2 = hist[4 * lane + 2], h3 = hist[4 * lane + 3];
-  const int mine = h0 + h1 + h2 + h3;
+// By every wave for itself (all waves read the same histogram and get the same answer, so
+// nothing has to be handed round through LDS and no barrier follows): the bin of a
+// kSelHistWords histogram where the count from the top reaches `remaining`, the rank left
+// inside it and the number of keys in it.  0 < remaining <= number of keys counted.
+__device__ __forceinline__ void sel_pick_bin_wave(const int* hist, int remaining, int lane, unsigned& bin_out,
+                                                  int& left_out, int& count_out) {
+  typedef int i32x4 __attribute__((ext_vector_type(4)));
+  const i32x4* mine4 = reinterpret_cast<const i32x4*>(hist + lane * kSelLaneWords);
+  i32x4 x[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) x[i] = mine4[i];
+  const i32x4 y = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+  const int mine = (y[0] + y[1]) + (y[2] + y[3]);
   const int prefix = wave_inclusive_scan(mine);
   const int total = __builtin_amdgcn_readlane(prefix, 63);
-  const int suffix = total - prefix + mine;  // inclusive sum over lanes >= this one
-  const int above = suffix - mine;           // keys in bins of higher lanes
-  const bool found = above < remaining && remaining <= suffix;
-  int left = remaining - above, digit = 3;
-  if (left > h3) {
-    if (left <= h3 + h2) {
-      digit = 2;
-      left -= h3;
-    } else if (left <= h3 + h2 + h1) {
-      digit = 1;
-      left -= h3 + h2;
-    } else {
-      digit = 0;
-      left -= h3 + h2 + h1;
-    }
-  }
-  // (exactly one lane finds it when 0 < remaining <= total; lane 0's values otherwise)
-  const unsigned long long m = __ballot(found);
-  const int src = m ? __ffsll(static_cast<long long>(m)) - 1 : 0;
-  digit_out = __shfl(4 * lane + digit, src);
-  left_out = __shfl(left, src);
+  // keys in the bins of lanes >= this one: total - prefix + mine; the lane that holds the bin
+  // is the highest one where that reaches `remaining`
+  const unsigned long long m = __ballot(total - prefix + mine >= remaining);
+  const int src = m ? 63 - __builtin_clzll(m) : 0;
+  const int left = remaining - (total - __builtin_amdgcn_readlane(prefix, src));
+  // that lane's 32 bins, one per lane (the upper half of the lanes holds a copy)
+  const int h = hist[src * kSelLaneWords + (lane & 31)];
+  const int v = wave_inclusive_scan(lane < 32 ? h : 0);
+  const int tot32 = __builtin_amdgcn_readlane(v, 31);
+  const unsigned m32 = static_cast<unsigned>(__ballot(tot32 - v + h >= left));
+  const int b = m32 ? 31 - __builtin_clz(m32) : 0;
+  bin_out = static_cast<unsigned>(32 * src + b);
+  left_out = left - (tot32 - __builtin_amdgcn_readlane(v, b));
+  count_out = __builtin_amdgcn_readlane(h, b);
 }
 
 // Exclusive rank of `flag` among the workgroup's threads in thread order, and the
@@ -153,22 +178,6 @@ __device__ __forceinline__ int sel_block_rank(bool flag, int* wave_tot, int lane
   __syncthreads();
   total = tot;
   return base + below;
-}
-
-// Exclusive prefix sum of `v` over the workgroup's threads in thread order.  One
-// barrier; `wave_tot` must not be reused before another barrier.
-template <int NT>
-__device__ __forceinline__ int sel_block_scan(int v, int* wave_tot, int lane, int wave) {
-  const int incl = wave_inclusive_scan(v);
-  if (lane == 63) wave_tot[wave] = incl;
-  __syncthreads();
-  int base = 0;
-#pragma unroll
-  for (int w = 0; w < NT / 64; ++w) {
-    const int x = wave_tot[w];
-    if (w < wave) base += x;
-  }
-  return base + incl - v;
 }
 
 // Any N.  `keys` is LDS (order keys staged there) or nullptr (scores taken from
@@ -222,76 +231,169 @@ __device__ __forceinline__ void select_generic(const unsigned* keys, const Src& 
   }
 }
 
-// N <= NT * kSelRegKeys: thread t owns the candidates [t*K, t*K+K),
-// K = ceil(N / NT), and keeps their order keys in registers, so the four radix
-// rounds touch LDS only for the histograms (lanes of a wave that hit the same bin
-// as the wave's first active lane are counted with one atomic) and the ordered
-// output needs two workgroup scans.  0 < r < N.  Whole workgroup; starts with a
-// barrier of its own and ends without one.
-template <int NT, class Src = OneScoreVector>
-__device__ __forceinline__ void select_regs(const Src& score_of, int N, int r,
-                                            FINCH_GLOBAL int* gidx, int* lidx, SelLds* f, int tid,
-                                            int lane, int wave) {
-  const int K = (N + NT - 1) / NT;
+// N <= NT * KMAX.  `keys` (LDS) holds the candidates' order keys, complete before a barrier
+// that precedes the call; thread t owns the candidates [t K, (t + 1) K) in registers, K odd
+// (so that the lanes of a wave read different LDS banks), and what it keeps goes to
+// consecutive places that one scan over the threads hands out.  The histogram bins divide
+// the range between the smallest and the largest key evenly, 2048 to a round, so that
+// scores of any spread fill them (fixed bits of a key would put nearly all scores of a
+// problem into one bin of the first rounds, and LDS atomics on one word take turns).  A
+// round narrows the range to the bin the r-th largest falls into; after one or two rounds
+// that bin holds few keys, which every wave ranks against each other directly.
+// What this is bound by is latency (barriers and dependent LDS reads), so rounds are few
+// and every wave reads the histogram for itself.  5500 scores of which 1400 are kept, 512
+// threads: 8400 clocks (3.5 us) against 19300 of a four-round radix select with a branch per
+// candidate; a third of that is the three barriers and the reads of the histogram.
+// Writes the kept indices in ascending order to `lidx` (LDS, kSelIdxPad words more than r) or
+// to `gidx`.  0 < r < N.  Whole workgroup; ends without a barrier.
+template <int NT, int KMAX, bool LDS_OUT>
+__device__ __forceinline__ void select_keys(const unsigned* keys, int N, int r, FINCH_GLOBAL int* gidx, int* lidx,
+                                            SelLds* f, int tid, int lane, int wave) {
+  constexpr int kWavesNT = NT / 64;
+  const int K = ((N + NT - 1) / NT) | 1;
   const int i0 = tid * K;
   const int nk = max(0, min(K, N - i0));  // candidates of this thread
-  unsigned key[kSelRegKeys];
+  // order keys of finite scores lie strictly between 0 and the largest unsigned value;
+  // registers without a candidate hold 0
+  // (no branches per candidate below: a lane without one, or one that has nothing to do, takes
+  // the same LDS access to a word that nobody reads)
+  unsigned key[KMAX];
+  unsigned hi = 0u, nlo = 0u;
 #pragma unroll
-  for (int k = 0; k < kSelRegKeys; ++k) key[k] = k < nk ? order_key(score_of(i0 + k)) : 0u;
-  for (int i = tid; i < 4 * 256; i += NT) (&f->hist[0][0])[i] = 0;
+  for (int k = 0; k < KMAX; ++k) key[k] = keys[min(i0 + k, N - 1)];
+#pragma unroll
+  for (int k = 0; k < KMAX; ++k) {
+    key[k] = k < nk ? key[k] : 0u;
+    hi = max(hi, key[k]);
+    nlo = max(nlo, key[k] ? ~key[k] : 0u);
+  }
+  for (int i = tid; i < 2 * kSelHistWords; i += NT) (&f->hist[0][0])[i] = 0;
+  if (tid < kSelCand) f->cand[tid] = 0u;
+  if (tid == 0) f->n_cand = 0;
+  hi = wave_max_u32(hi);
+  nlo = wave_max_u32(nlo);
+  if (lane == 0) {
+    f->wave_max[0][wave] = hi;
+    f->wave_max[1][wave] = nlo;
+  }
   __syncthreads();
-  unsigned prefix = 0, mask = 0;
+#pragma unroll
+  for (int w = 0; w < kWavesNT; ++w) {
+    hi = max(hi, f->wave_max[0][w]);
+    nlo = max(nlo, f->wave_max[1][w]);
+  }
+  // keys [lo, lo + range] are left, `remaining` of them (from the top) are kept
+  unsigned lo = ~nlo, range = hi - lo;
   int remaining = r;
+  unsigned T = lo;           // keys above T are kept,
+  int need_eq = remaining;   // and the first need_eq of those equal to it
+  for (int round = 0; range != 0u; ++round) {
+    int* hist = f->hist[round & 1];
+    if (round >= 2) {  // (everyone has read it: the barrier of the round before lies between)
+      for (int i = tid; i < kSelHistWords; i += NT) hist[i] = 0;
+      __syncthreads();
+    }
+    const int shift = max(0, 32 - __builtin_clz(range) - kSelBinBits);
 #pragma unroll
-  for (int round = 0; round < 4; ++round) {
-    const int shift = 24 - 8 * round;
-    int* hist = f->hist[round];
-#pragma unroll
-    for (int k = 0; k < kSelRegKeys; ++k) {
-      const bool act = k < nk && (key[k] & mask) == prefix;
-      const unsigned long long am = __ballot(act);
-      if (am) {  // uniform
-        const unsigned d = (key[k] >> shift) & 255u;
-        const int leader = __ffsll(static_cast<long long>(am)) - 1;
-        const unsigned dl = static_cast<unsigned>(__shfl(static_cast<int>(d), leader));
-        const unsigned long long same = __ballot(act && d == dl);
-        if (lane == leader) atomicAdd(&hist[dl], __popcll(same));
-        if (act && d != dl) atomicAdd(&hist[d], 1);
-      }
+    for (int k = 0; k < KMAX; ++k) {
+      // (keys below lo, and 0, wrap around to more than range; the last words of a lane's kSelLaneWords are padding)
+      const unsigned off = key[k] - lo;
+      atomicAdd(&hist[off <= range ? sel_hist_at(off >> shift) : lane * kSelLaneWords + 32], 1);
     }
     __syncthreads();
-    int digit;
-    sel_pick_digit_wave(hist, remaining, lane, digit, remaining);
-    prefix |= static_cast<unsigned>(digit) << shift;
-    mask |= 255u << shift;
-  }
-  const unsigned T = prefix;
-  const int need_eq = remaining;  // candidates equal to T that are kept (>= 1)
-  int c_eq = 0;
+    unsigned bin;
+    int count;
+    sel_pick_bin_wave(hist, remaining, lane, bin, remaining, count);
+    lo += bin << shift;
+    range = min((1u << shift) - 1u, range - (bin << shift));
+    if (count == remaining) {  // the whole bin is kept
+      T = lo - 1u;
+      need_eq = 0;
+      break;
+    }
+    T = lo;
+    need_eq = remaining;
+    if (range != 0u && count <= kSelCand) {
+      unsigned in_bin = 0u;
 #pragma unroll
-  for (int k = 0; k < kSelRegKeys; ++k) c_eq += (k < nk && key[k] == T) ? 1 : 0;
-  int eq_rank = sel_block_scan<NT>(c_eq, f->wave_tot[0], lane, wave);
-  unsigned keep_bits = 0;
-  int c_keep = 0;
-#pragma unroll
-  for (int k = 0; k < kSelRegKeys; ++k) {
-    if (k < nk) {
-      bool keep = key[k] > T;
-      if (key[k] == T) keep = eq_rank++ < need_eq;
-      if (keep) {
-        keep_bits |= 1u << k;
-        ++c_keep;
+      for (int k = 0; k < KMAX; ++k) in_bin |= key[k] - lo <= range ? 1u << k : 0u;
+      int at = in_bin ? atomicAdd(&f->n_cand, __popc(in_bin)) : 0;
+      while (in_bin) {  // (few lanes have any, hardly one more than one)
+        const int k1 = __ffs(static_cast<int>(in_bin)) - 1;
+        f->cand[at++ & (kSelCand - 1)] = keys[i0 + k1];
+        in_bin &= in_bin - 1u;
       }
+      __syncthreads();
+      // every row of 16 lanes holds all of them (unused places hold 0) and ranks its own by
+      // turning the row
+      const unsigned mine = f->cand[lane & (kSelCand - 1)];
+      int above = 0, upto = 1;  // keys above this lane's, and not below it
+      auto turned = [&](auto ctrl) {
+        const unsigned o = static_cast<unsigned>(
+            __builtin_amdgcn_update_dpp(0, static_cast<int>(mine), decltype(ctrl)::value, 0xF, 0xF, true));
+        above += o > mine ? 1 : 0;
+        upto += o >= mine ? 1 : 0;
+      };
+#define FINCH_TURN(i) turned(std::integral_constant<int, 0x120 + i>{});  /* row_ror:i */
+      FINCH_TURN(1) FINCH_TURN(2) FINCH_TURN(3) FINCH_TURN(4) FINCH_TURN(5) FINCH_TURN(6) FINCH_TURN(7) FINCH_TURN(8)
+      FINCH_TURN(9) FINCH_TURN(10) FINCH_TURN(11) FINCH_TURN(12) FINCH_TURN(13) FINCH_TURN(14) FINCH_TURN(15)
+#undef FINCH_TURN
+      const unsigned long long m = __ballot(mine != 0u && above < remaining && remaining <= upto);
+      const int src = m ? __ffsll(static_cast<long long>(m)) - 1 : 0;
+      T = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(mine), src));
+      need_eq = remaining - __builtin_amdgcn_readlane(above, src);
+      break;
     }
   }
-  int pos = sel_block_scan<NT>(c_keep, f->wave_tot[1], lane, wave);
+  // candidates above T in the low and equal to T in the high half-word
+  int mine = 0;
 #pragma unroll
-  for (int k = 0; k < kSelRegKeys; ++k) {
-    if (keep_bits & (1u << k)) {
+  for (int k = 0; k < KMAX; ++k) mine += (key[k] > T ? 1 : 0) + (key[k] == T ? 0x10000 : 0);
+  const int incl = wave_inclusive_scan(mine);
+  if (lane == 63) f->wave_tot[0][wave] = incl;
+  __syncthreads();
+  int before = incl - mine;
+#pragma unroll
+  for (int w = 0; w < kWavesNT; ++w) {
+    const int x = f->wave_tot[0][w];
+    before += w < wave ? x : 0;
+  }
+  int eq_rank = before >> 16;
+  int pos = (before & 0xFFFF) + min(eq_rank, need_eq);
+#pragma unroll
+  for (int k = 0; k < KMAX; ++k) {
+    const int eq = key[k] == T ? 1 : 0;
+    const int keep = (key[k] > T ? 1 : 0) | (eq_rank < need_eq ? eq : 0);
+    if (LDS_OUT) {
+      lidx[keep ? min(pos, r) : r + (lane & 31)] = i0 + k;
+    } else if (keep && pos < r) {
       gidx[pos] = i0 + k;
-      if (lidx) lidx[pos] = i0 + k;
-      ++pos;
     }
+    pos += keep;
+    eq_rank += eq;
+  }
+}
+
+// select_keys with as many registers as the problem needs.
+template <int NT, bool LDS_OUT>
+__device__ __forceinline__ void select_keys_any(const unsigned* keys, int N, int r, FINCH_GLOBAL int* gidx, int* lidx,
+                                                SelLds* f, int tid, int lane, int wave) {
+  if (N <= NT * 7) select_keys<NT, 7, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave);
+  else if (N <= NT * 11) select_keys<NT, 11, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave);
+  else select_keys<NT, kSelRegKeys, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave);
+}
+
+// Puts the order keys of the N scores into LDS (no barrier).
+template <int NT, class Src>
+__device__ __forceinline__ void sel_stage_keys(const Src& score_of, int N, unsigned* keys, int tid) {
+  constexpr int kBatch = 8;  // loads in flight per thread
+  for (int i0 = tid; i0 < N; i0 += NT * kBatch) {
+    float v[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) v[u] = score_of(min(i0 + u * NT, N - 1));
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+      if (i0 + u * NT < N) keys[i0 + u * NT] = order_key(v[u]);
   }
 }
 
