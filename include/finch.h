@@ -258,7 +258,9 @@ finch_status finch_schedule_mode(int64_t n_cont, int32_t m, int64_t k, int32_t m
  * fp32: the vector ALU, meant for small problems); batches it cannot run fail with
  * FINCH_ERR_UNSUPPORTED.  AUTO (default) takes OWNER for bf16 when the batch has enough
  * problems to fill the chip's compute units in whole rounds, for fp32 when no problem
- * has more than 4096 candidates or 64 prompt rows, else SEPARATE. */
+ * has more than 4096 candidates or 64 prompt rows; for bf16 batches of at most half as many
+ * problems as compute units, a launch per step in which several workgroups share a problem;
+ * else SEPARATE. */
 typedef enum {
   FINCH_OPT_STEP_PATH = 1,
   /* tuning: target number of keys one workgroup of the two-pass bf16 scoring
@@ -283,7 +285,9 @@ typedef enum {
    * leaves that step's indices and cache rows unwritten and the launch goes on to its
    * end: nothing is written outside its buffers, but indices and caches of that call are
    * not to be used.  0 makes the first workgroup of every layer give up at once: the way
-   * to exercise the error path. */
+   * to exercise the error path.  Launches that put several workgroups on a problem (AUTO,
+   * small bf16 batches) never give up: a workgroup that has waited for the others for this
+   * long, or 0.1 ms if that is less, does what is missing itself, with the same results. */
   FINCH_OPT_LAYER_WAIT_TICKS = 5
 } finch_option;
 typedef enum { FINCH_PATH_AUTO = 0, FINCH_PATH_SEPARATE = 1, FINCH_PATH_OWNER = 3 } finch_path;
@@ -303,7 +307,7 @@ typedef enum {
   FINCH_KERNEL_COLSUM = 2,   /* scoring pass 2: per-key sums of the weights  */
   FINCH_KERNEL_SELECT = 3,   /* top-r                                        */
   FINCH_KERNEL_GATHER = 4,   /* compaction                                   */
-  FINCH_KERNEL_OWNER = 5,    /* all stages, one workgroup per problem        */
+  FINCH_KERNEL_OWNER = 5,    /* all stages in one launch                     */
   FINCH_KERNEL_PROMPT_LSE = 6, /* finch_prompt_lse                             */
   FINCH_KERNEL_COUNT = 7
 } finch_kernel;

@@ -29,6 +29,7 @@ struct finch_ctx {
   finch_reposition repos;  // {OFF, ASCENDING}: plain copies
   int layer_group;         // > 1: runs of that many problems share one selection
   int64_t layer_wait_ticks;  // bound of a workgroup's wait for its layer, 100 MHz ticks
+  int32_t* meet;             // meeting words of the launches with several workgroups per problem
   void* static_scratch;    // this device's copy of the file-scope scratch array (finch_step_static)
   // finch_loop: fingerprint of the last descriptor set whose slots were found free of
   // overlaps (the check is repeated only when the descriptors change)
@@ -60,6 +61,11 @@ struct Plan {
   bool has_doc = false;   // some problem takes rows from the chunk's own tokens (q_doc)
   int32_t own_row_chunk = 32;
   size_t own_lds = 0;
+  // several workgroups per problem in one launch: slices per problem (0: not for this batch)
+  int32_t cluster_slices = 0, cluster_row_chunk = 32;
+  size_t cluster_lds = 0;
+  size_t off_cluster = 0;   // statistics of its slices, behind everything else
+  size_t base_total = 0;    // workspace without that part
   size_t lds_bytes = 0;
   size_t off_stats = 0, off_lse = 0, off_scores = 0, off_layer = 0, off_sync = 0, total = 0;
   int32_t sync_words = 0;  // counters of the layer runs (workspace word 0 is the status word)
@@ -81,6 +87,29 @@ size_t score_lds(const finch_ctx* ctx, int row_chunk) {
   if (ctx->cfg.dtype == FINCH_BF16)
     return static_cast<size_t>(row_chunk) * (d * 2 + 16 + (finch::kStreamThreads / 64) * sizeof(float2)) + 16;
   return static_cast<size_t>(row_chunk) * (d * 4 + 4 * sizeof(float2));
+}
+
+// Whether a launch with several workgroups per problem could run a batch of n problems,
+// and its sizes.
+void plan_cluster(const finch_ctx* ctx, int32_t n, Plan& pl) {
+  pl.cluster_slices = 0;
+  const int cu = ctx->n_cu < finch::kMaxClusterGrid ? ctx->n_cu : finch::kMaxClusterGrid;
+  if (ctx->cfg.dtype != FINCH_BF16 || pl.has_doc || n <= 0 || pl.n_max == 0 || n > cu / 2 ||
+      pl.n_max > finch::kClusterMaxKeys || pl.rpad_max > finch::kClusterMaxRows)
+    return;
+  const int blocks = (pl.n_max + 31) / 32;
+  int s = cu / n;
+  if (s > blocks) s = blocks;
+  if (s < 2) return;
+  const int slice_blocks = (blocks + s - 1) / s;
+  if (slice_blocks > finch::kClusterSliceBlocks) return;
+  int rc = pl.rpad_max < finch::kOwnerMaxRowChunk ? pl.rpad_max : finch::kOwnerMaxRowChunk;
+  if (rc < 32) rc = 32;
+  const size_t lds = finch::cluster_lds_bytes(ctx->cfg.head_dim, rc, slice_blocks, pl.n_max, pl.r_max);
+  if (lds > ctx->max_lds) return;
+  pl.cluster_slices = s;
+  pl.cluster_row_chunk = rc;
+  pl.cluster_lds = lds;
 }
 
 // Sizes launches for the n descriptors of `hd`; the workspace is laid out for
@@ -159,7 +188,13 @@ finch_status make_plan(const finch_ctx* ctx, const finch_problem* hd, int32_t n_
     pl.sync_words = static_cast<int32_t>(2 * (na / ctx->layer_group + 1));
     off = align_up(off + static_cast<size_t>(pl.sync_words) * sizeof(int32_t), 256);
   }
+  pl.base_total = off;
+  pl.off_cluster = off;
+  // (room for a full grid of slices, so that a batch of fewer or smaller problems needs no more)
+  if (ctx->cfg.dtype == FINCH_BF16 && n_max > 0)
+    off += static_cast<size_t>(finch::kMaxClusterGrid) * std::min(pl.rpad_max, finch::kClusterMaxRows) * sizeof(float2);
   pl.total = off;
+  plan_cluster(ctx, n, pl);
   return FINCH_OK;
 }
 
@@ -250,6 +285,8 @@ LaunchParams make_params(const finch_ctx* ctx, const finch_problem* dd, int32_t 
   p.layer_sync = base ? reinterpret_cast<int32_t*>(base + pl.off_sync) : nullptr;
   p.layer_err = reinterpret_cast<int32_t*>(base);
   p.spin_ticks = ctx->layer_wait_ticks;
+  p.meet = ctx->meet;
+  p.help_ticks = std::min(finch::kClusterHelpTicks, ctx->layer_wait_ticks);
   return p;
 }
 
@@ -335,6 +372,27 @@ bool owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n) {
   return static_cast<int64_t>(n) * 100 >= rounds * cu * 85;
 }
 
+// Several workgroups per problem in one launch: for batches that leave at least half of the
+// chip without a workgroup otherwise (two slices a problem and more).  A caller who has set
+// the slices of the two-pass kernels wants those.  Slots by score rank are not built there.
+bool cluster_wanted(const finch_ctx* ctx, const Plan& pl, bool stages) {
+  return pl.cluster_slices > 1 && ctx->step_path == FINCH_PATH_AUTO && ctx->slice_keys == finch::kDefaultSliceKeys &&
+         (!stages || (ctx->repos.order == FINCH_ORDER_ASCENDING && ctx->layer_group <= finch::kOwnerMaxLayer));
+}
+
+finch_status run_cluster(finch_ctx* ctx, LaunchParams p, const Plan& pl, void* ws, int stages, hipStream_t s) {
+  p.row_chunk = pl.cluster_row_chunk;
+  p.lds_bytes = static_cast<uint32_t>(pl.cluster_lds);
+  p.cluster_slices = pl.cluster_slices;
+  p.stats = reinterpret_cast<float2*>(static_cast<char*>(ws) + pl.off_cluster);
+  hipError_t e;
+  {
+    ProfScope ps(ctx, FINCH_KERNEL_OWNER, s);
+    e = finch::launch_cluster_bf16(ctx->cfg.head_dim, p, stages, s);
+  }
+  return e == hipSuccess ? FINCH_OK : hip_fail(ctx, e);
+}
+
 finch_status run_owner(finch_ctx* ctx, LaunchParams p, const Plan& pl, int stages, hipStream_t s) {
   p.row_chunk = pl.own_row_chunk;
   p.lds_bytes = static_cast<uint32_t>(pl.own_lds);
@@ -351,12 +409,13 @@ finch_status run_owner(finch_ctx* ctx, LaunchParams p, const Plan& pl, int stage
   return e == hipSuccess ? FINCH_OK : hip_fail(ctx, e);
 }
 
-finch_status run_score(finch_ctx* ctx, const LaunchParams& p, const Plan& pl, hipStream_t s) {
+finch_status run_score(finch_ctx* ctx, const LaunchParams& p, const Plan& pl, void* ws, hipStream_t s) {
   if (p.n_problems == 0 || pl.tiles_max == 0) return FINCH_OK;
   hipError_t e = hipSuccess;
   const int d = ctx->cfg.head_dim;
   const bool bf16 = ctx->cfg.dtype == FINCH_BF16;
   if (owner_wanted(ctx, pl, p.n_problems)) return run_owner(ctx, p, pl, /*stages=*/0, s);
+  if (cluster_wanted(ctx, pl, false)) return run_cluster(ctx, p, pl, ws, /*stages=*/0, s);
   if (ctx->step_path == FINCH_PATH_OWNER || pl.has_doc) return FINCH_ERR_UNSUPPORTED;
   {
     ProfScope ps(ctx, FINCH_KERNEL_ROWSTATS, s);
@@ -543,13 +602,15 @@ finch_status step_planned(finch_ctx* ctx, const finch_problem* host_desc, const 
   if (n == 0) return FINCH_OK;
   const LaunchParams p = make_params(ctx, dev_desc, n, pl, ws);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (ctx->layer_group > 1) {  // the status word starts every such call at zero, whatever path it takes
+  // (with layer groups the status word starts every call at zero: these two see to it themselves)
+  if (pl.tiles_max > 0 && owner_wanted(ctx, pl, n)) return run_owner(ctx, p, pl, /*stages=*/1, s);
+  if (cluster_wanted(ctx, pl, true)) return run_cluster(ctx, p, pl, ws, /*stages=*/1, s);
+  if (ctx->layer_group > 1) {
     const hipError_t e = finch::launch_zero_words(nullptr, 0, p.layer_err, s);
     if (e != hipSuccess) return hip_fail(ctx, e);
   }
-  if (pl.tiles_max > 0 && owner_wanted(ctx, pl, n)) return run_owner(ctx, p, pl, /*stages=*/1, s);
   if ((ctx->step_path == FINCH_PATH_OWNER || pl.has_doc) && pl.tiles_max > 0) return FINCH_ERR_UNSUPPORTED;
-  if ((st = run_score(ctx, p, pl, s)) != FINCH_OK) return st;
+  if ((st = run_score(ctx, p, pl, ws, s)) != FINCH_OK) return st;
   if (pl.r_max == 0) return FINCH_OK;
   if ((st = run_select(ctx, p, pl, ws, s)) != FINCH_OK) return st;
   return run_gather(ctx, p, pl.r_max, s);
@@ -588,6 +649,7 @@ finch_status finch_create(const finch_config* cfg, finch_ctx** out) {
   ctx->static_scratch = nullptr;
   ctx->loop_checked = false;
   ctx->loop_checked_hash = 0;
+  ctx->meet = nullptr;
   hipError_t e = hipGetDevice(&ctx->device);
   if (e == hipSuccess) e = static_scratch_address(ctx->device, &ctx->static_scratch);
   if (e == hipSuccess) {
@@ -605,6 +667,13 @@ finch_status finch_create(const finch_config* cfg, finch_ctx** out) {
   if (e == hipSuccess && cfg->dtype == FINCH_BF16) e = finch::set_max_lds_owner(ctx->max_lds);
   if (e == hipSuccess && cfg->dtype == FINCH_BF16) e = finch::set_max_lds_owner_doc(ctx->max_lds);
   if (e == hipSuccess && cfg->dtype == FINCH_F32) e = finch::set_max_lds_owner_f32(ctx->max_lds);
+  if (e == hipSuccess && cfg->dtype == FINCH_BF16) e = finch::set_max_lds_cluster(ctx->max_lds);
+  if (e == hipSuccess && cfg->dtype == FINCH_BF16) {
+    // cleared once: the launches keep them in order themselves
+    e = hipMalloc(reinterpret_cast<void**>(&ctx->meet), finch::cluster_meet_bytes());
+    if (e == hipSuccess) e = hipMemset(ctx->meet, 0, finch::cluster_meet_bytes());
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+  }
   if (e == hipSuccess) e = finch::set_max_lds_select(ctx->max_lds);
   // the re-positioning kernel also has a little static LDS
   if (e == hipSuccess) e = finch::set_max_lds_reposition(ctx->max_lds - 1024);
@@ -613,6 +682,7 @@ finch_status finch_create(const finch_config* cfg, finch_ctx** out) {
     std::fprintf(stderr, "finch_create: HIP error %d (%s)\n", static_cast<int>(e),
                  hipGetErrorString(e));
     (void)hipGetLastError();
+    if (ctx->meet) (void)hipFree(ctx->meet);
     delete ctx;
     return FINCH_ERR_HIP;
   }
@@ -621,7 +691,10 @@ finch_status finch_create(const finch_config* cfg, finch_ctx** out) {
 }
 
 finch_status finch_destroy(finch_ctx* ctx) {
-  if (ctx) (void)finch_profile(ctx, 0);
+  if (ctx) {
+    (void)finch_profile(ctx, 0);
+    if (ctx->meet) (void)hipFree(ctx->meet);  // (waits for the device)
+  }
   delete ctx;
   return FINCH_OK;
 }
@@ -730,7 +803,7 @@ finch_status finch_score(finch_ctx* ctx, const finch_problem* host_desc,
   if ((st = validate(ctx, host_desc, n, kNeedQK | kNeedScoresOut)) != FINCH_OK) return st;
   if ((st = check_workspace(pl, ws, ws_bytes)) != FINCH_OK) return st;
   const LaunchParams p = make_params(ctx, dev_desc, n, pl, ws);
-  return run_score(ctx, p, pl, static_cast<hipStream_t>(stream));
+  return run_score(ctx, p, pl, ws, static_cast<hipStream_t>(stream));
 }
 
 finch_status finch_prompt_lse(finch_ctx* ctx, const finch_problem* host_desc,
@@ -803,14 +876,18 @@ finch_status finch_step_static(finch_ctx* ctx, const finch_problem* host_desc,
   if (st != FINCH_OK) return st;
   Plan pl;
   if ((st = make_plan(ctx, host_desc, n, pl)) != FINCH_OK) return st;
-  if (pl.total > kStaticScratchBytes) {
+  if (pl.base_total > kStaticScratchBytes) {
     std::fprintf(stderr,
                  "finch_step_static: this batch needs %zu bytes of scratch, the library holds %zu; "
                  "use finch_step with a workspace\n",
-                 pl.total, kStaticScratchBytes);
+                 pl.base_total, kStaticScratchBytes);
     return FINCH_ERR_CAPACITY;
   }
   if (!ctx->static_scratch) return FINCH_ERR_WORKSPACE;
+  if (pl.total > kStaticScratchBytes) {  // no room for slices of a problem on several workgroups
+    pl.cluster_slices = 0;
+    pl.total = pl.base_total;
+  }
   // No part of the scratch has to start at zero: each region (row statistics, row
   // log-sum-exps, scores, layer sums) is written by the step before it is read.
   return step_planned(ctx, host_desc, dev_desc, n, pl, ctx->static_scratch, kStaticScratchBytes, stream);
@@ -860,10 +937,6 @@ finch_status finch_loop(finch_ctx* ctx, const finch_problem* host_desc, const fi
   if ((st = check_workspace(pl, ws, ws_bytes)) != FINCH_OK) return st;
   if (n_desc == 0 || pl.tiles_max == 0) return FINCH_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (ctx->layer_group > 1) {
-    const hipError_t e = finch::launch_zero_words(nullptr, 0, static_cast<int32_t*>(ws), s);
-    if (e != hipSuccess) return hip_fail(ctx, e);
-  }
   if (owner_wanted(ctx, pl, n_slots)) {
     LaunchParams p = make_params(ctx, dev_desc, n_desc, pl, ws);
     p.row_chunk = pl.own_row_chunk;

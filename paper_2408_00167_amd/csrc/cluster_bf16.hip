@@ -1,0 +1,505 @@
+// Several workgroups per problem for a whole prefill step in ONE launch, bf16 Q/K/V on
+// gfx950: for batches with far fewer problems than the chip has compute units - the KV heads
+// of one layer, which is what a model's forward pass has in hand at a time.  Such a step
+// moves few bytes; what it costs is latency: launches (3.7 us each, back to back), chains of
+// dependent loads, and compute units that have no workgroup.  So a problem's keys are cut
+// into S slices, S * problems <= compute units, and one workgroup takes a slice through all
+// stages (Method: attention of the prompt rows over cache + chunk keys, sum over heads and
+// prompt rows; t = top-r(A_agg, r); Managing the Cache):
+//   pass 1   (max, sum exp2) of every prompt row over the slice's keys  -> memory
+//   meeting  all slices of the problem have published theirs (1-2 us; a launch would cost 4)
+//   pass 2   every row's log-sum-exp from the S records, the slice's scores -> memory
+//   meeting  all slices (of the problem; with layer groups, of the layer) have published
+//   top-r    by every workgroup for itself on all scores (the same answer everywhere, which
+//            is cheaper than a third meeting), then its S-th part of the compaction.
+// One layer of 8 KV heads, 192 prompt rows, 4800 candidates: 26.5 us a step, where one kernel
+// per stage took 80.9 us (16 workgroups in each of its two passes, and four launches).
+//
+// Meetings.  A slice's workgroup sets a flag per meeting; the others poll the flags, at most
+// prm.help_ticks in all.  When the time is up (other work keeps some of the workgroups from
+// starting), a workgroup does what is missing ITSELF - the same instructions on the same
+// inputs, hence the same bits, written to the same places - so every workgroup can finish
+// whatever the others do, and no wait depends on all of them being on the chip at once.
+// A flag is set when it holds the launch's number, generation + 1.  The generation is a
+// word of memory that the last workgroup to be through with its waits advances, so a launch
+// needs no cleared memory and a captured one can be replayed.
+//
+// Data that crosses workgroups goes through agent-scope relaxed atomics (past the caches
+// that are not shared), and is complete before the flag: each thread waits for its own
+// stores, then a barrier, then the flag.
+#include "owner_body.h"
+
+namespace finch {
+
+namespace {
+
+constexpr int kCluThreads = kOwnThreads;
+constexpr int kCluWaves = kOwnWaves;
+
+// words of the meeting area (LaunchParams::meet)
+constexpr int kMeetGen = 0, kMeetExit = 16, kMeetExitOf = 32;   // (one word per 64-byte line, except:)
+constexpr int kMeetFlags = kMeetExitOf + 16 * kMaxClusterGrid;  // [2][kMaxClusterGrid]
+
+template <typename T>
+__device__ __forceinline__ T agent_load(const T* p) {
+  return __hip_atomic_load((const FINCH_GLOBAL T*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void agent_store(T* p, T v) {
+  __hip_atomic_store((FINCH_GLOBAL T*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Every thread's stores are out; then one thread sets the flag.  Whole workgroup.
+__device__ __forceinline__ void meet_set(int* flag, int target, int tid) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) agent_store(flag, target);
+}
+
+// Waits until flags[0 .. n) all hold `target`; -1, or the first missing one once `deadline` has
+// passed.  Whole workgroup; a barrier at the end.
+__device__ __forceinline__ int meet_wait(const int* flags, int n, int target, long long deadline, int* sh, int tid,
+                                         int lane) {
+  if (tid < 64) {
+    int missing = -1;
+    while (true) {
+      missing = -1;
+      for (int i0 = 0; i0 < n && missing < 0; i0 += 64) {
+        const bool there = i0 + lane >= n || agent_load(flags + min(i0 + lane, n - 1)) == target;
+        const unsigned long long m = __ballot(!there);
+        if (m) missing = i0 + __ffsll(static_cast<long long>(m)) - 1;
+      }
+      if (missing < 0 || wall_clock64() > deadline) break;
+      __builtin_amdgcn_s_sleep(1);
+    }
+    if (lane == 0) *sh = missing;
+  }
+  __syncthreads();
+  const int r = *sh;
+  __syncthreads();  // (*sh may be written again)
+  return r;
+}
+
+// Scores other workgroups have written.
+struct AgentScoreVector {
+  const float* p;
+  __device__ __forceinline__ float operator()(int i) const { return agent_load(p + i); }
+};
+
+// Key blocks [b0, b1) of slice s of `per` blocks each.
+struct Slice {
+  int b0, b1;
+};
+__device__ __forceinline__ Slice slice_of(int nb, int per, int s) { return Slice{min(nb, s * per), min(nb, (s + 1) * per)}; }
+
+// How the 8 waves share a slice of kb key blocks and qb row blocks: groups of rs waves (a
+// power of two) take the same keys and different rows.  The split with the shortest longest
+// wave, loading a key block counted like one tile of work; of equal ones the one that loads
+// each key least often.  Slices of more than kSplitBlocks are not split by rows: their waves
+// have keys enough.
+constexpr int kSplitBlocks = 2 * kCluWaves;
+__device__ __forceinline__ int row_split(int kb, int qb) {
+  int best = 1, cost = 1 << 30;
+#pragma unroll
+  for (int rs = 1; rs <= kCluWaves; rs <<= 1) {
+    if (rs > 1 && kb > kSplitBlocks) break;
+    const int lanes = kCluWaves / rs;
+    const int c = ((kb + lanes - 1) / lanes) * ((qb + rs - 1) / rs + 1);
+    if (c < cost) {
+      cost = c;
+      best = rs;
+    }
+  }
+  return best;
+}
+
+// 64 keys x 32 rows of raw dot products, or the first 32 keys only.  The prompt rows' operands
+// are read once for both halves.
+template <int D>
+__device__ __forceinline__ void mfma_two(const bf16x8 (&k0)[D / 16], const bf16x8 (&k1)[D / 16], const char* qrow, bool two,
+                                         f32x16& a0, f32x16& a1) {
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  bf16x8 qf[D / 16];
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qrow + 32 * s);
+  a0 = zero;
+  a1 = zero;
+  if (two) {
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) {
+      a0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[s], qf[s], a0, 0, 0, 0);
+      a1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[s], qf[s], a1, 0, 0, 0);
+    }
+  } else {
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) a0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[s], qf[s], a0, 0, 0, 0);
+  }
+}
+
+__device__ __forceinline__ void mask_keys(f32x16& a, int kbase, int h, int lim) {
+  if (kbase + 32 > lim) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      if (kbase + acc_key(v, h) >= lim) a[v] = -kInf;
+  }
+}
+
+}  // namespace
+
+// stages: 0 = scores only, 1 = scores, top-r and compaction.  ROT: the compaction
+// re-positions the kept keys (ascending slots).
+template <int D, bool ROT>
+__global__ __launch_bounds__(kCluThreads) void cluster_step_bf16(LaunchParams prm, int stages) {
+  extern __shared__ __align__(16) char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int t = lane & 31, h = lane >> 5;
+  constexpr int kStride = D * 2 + 16;
+  const int S = prm.cluster_slices, RC = prm.row_chunk;
+  const int L = stages ? prm.layer_group : 1;
+  // a problem's workgroups (and a layer's) stand together on one of the chip's dies where the
+  // numbers allow it
+  const int role = own_slot_of(blockIdx.x, gridDim.x, 2);
+  const int my_p = role / S, my_s = role - my_p * S;
+  const int p_first = my_p / L * L;  // the problems that select together
+  int* const meet = prm.meet;
+  const int target = agent_load(meet + kMeetGen) + 1;
+  int* const stat_flags = meet + kMeetFlags;
+  int* const score_flags = stat_flags + kMaxClusterGrid;
+  const long long deadline = wall_clock64() + prm.help_ticks;
+  const finch_problem mine = prm.probs[my_p];
+  const int N = mine.c + mine.m;
+  const float sc = prm.scale_log2;
+
+  char* lds_q = smem;
+  float2* wstats = reinterpret_cast<float2*>(smem + RC * kStride);                             // [waves][RC]
+  float* lds_lse = reinterpret_cast<float*>(smem + RC * (kStride + kCluWaves * 8));             // [RC]
+  int* sh_miss = reinterpret_cast<int*>(smem + RC * (kStride + kCluWaves * 8 + 4));
+  float* ksum = reinterpret_cast<float*>(smem + RC * (kStride + kCluWaves * 8 + 4) + 16);       // [row split][keys of the slice]
+
+  // What this workgroup is working on: a slice of its own problem, or - after a wait that has
+  // run out - one that is missing.
+  finch_problem pb = mine;
+  int wp = my_p, ws = my_s;
+  const void* staged_q = nullptr;  // prompt rows that are in LDS
+  int staged_row0 = 0;
+  while (true) {
+    const int n = pb.c + pb.m, nb = (n + 31) >> 5, R = prm.group * pb.n_que;
+    const int per = max(1, (nb + S - 1) / S);
+    const int used = (nb + per - 1) / per;  // slices that have keys
+    const KeySource ks = {static_cast<const char*>(pb.k_cache), static_cast<const char*>(pb.k_chunk), pb.c};
+    unsigned long long* const stats =
+        reinterpret_cast<unsigned long long*>(prm.stats) + static_cast<size_t>(wp) * S * prm.rpad_max;
+    auto stage = [&](int row0, int rows) {
+      if (staged_q == pb.q && staged_row0 == row0) return;
+      stage_q<D, kCluThreads>(pb.q, R, row0, rows, lds_q, tid);
+      staged_q = pb.q;
+      staged_row0 = row0;
+    };
+    if (ws < used) {
+      bf16x8 k0[D / 16], k1[D / 16];
+      int held = -1;  // slice whose key blocks are in k0, k1 (if a wave has no more than two)
+      // ---- pass 1, and the first meeting
+      int s1 = ws;
+      while (true) {
+        const Slice sl = slice_of(nb, per, s1);
+        const int kb = sl.b1 - sl.b0, lim = min(n, sl.b1 << 5);
+        for (int row0 = 0; row0 < R; row0 += RC) {
+          const int rows = min(RC, round_up32(R - row0)), QB = rows >> 5;
+          const int rs = row_split(kb, QB), kl = kCluWaves / rs;
+          const int qper = (QB + rs - 1) / rs;
+          const int q_lo = min(QB, (wave & (rs - 1)) * qper), q_hi = min(QB, q_lo + qper);
+          const int kw = wave / rs;
+          float2* const out = wstats + kw * RC;
+          int b = sl.b0 + kw;
+          if (b < sl.b1) load_k_block<D>(ks, lim, b << 5, lane, k0);
+          if (b + kl < sl.b1) load_k_block<D>(ks, lim, (b + kl) << 5, lane, k1);
+          stage(row0, rows);
+          __syncthreads();
+          bool first = true;
+          do {
+            const bool two = b + kl < sl.b1;
+            for (int q = q_lo; q < q_hi; ++q) {
+              float m = -kInf, z = 0.f;
+              if (b < sl.b1) {
+                f32x16 a0, a1;
+                mfma_two<D>(k0, k1, lds_q + (q * 32 + t) * kStride + 16 * h, two, a0, a1);
+                mask_keys(a0, b << 5, h, lim);
+                float bm = fmaxf(a0[0], a0[1]);
+#pragma unroll
+                for (int v = 2; v < 16; v += 2) bm = fmaxf(fmaxf(bm, a0[v]), a0[v + 1]);
+                if (two) {
+                  mask_keys(a1, (b + kl) << 5, h, lim);
+#pragma unroll
+                  for (int v = 0; v < 16; v += 2) bm = fmaxf(fmaxf(bm, a1[v]), a1[v + 1]);
+                }
+                m = bm * sc;
+                const float mu = (m == -kInf) ? 0.f : m;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) z += fast_exp2(__builtin_fmaf(a0[v], sc, -mu));
+                if (two) {
+#pragma unroll
+                  for (int v = 0; v < 16; ++v) z += fast_exp2(__builtin_fmaf(a1[v], sc, -mu));
+                }
+              }
+              const float m2 = __shfl_xor(m, 32);
+              const float z2 = __shfl_xor(z, 32);
+              merge_stats(m, z, m2, z2);
+              if (h == 0) {
+                if (!first) {
+                  const float2 o = out[q * 32 + t];
+                  merge_stats(m, z, o.x, o.y);
+                }
+                out[q * 32 + t] = make_float2(m, z);
+              }
+            }
+            first = false;
+            b += 2 * kl;
+            if (b < sl.b1) {
+              load_k_block<D>(ks, lim, b << 5, lane, k0);
+              if (b + kl < sl.b1) load_k_block<D>(ks, lim, (b + kl) << 5, lane, k1);
+            }
+          } while (b < sl.b1);
+          held = (kb <= 2 * kl && R <= RC) ? s1 : -1;
+          __syncthreads();
+          for (int i = tid; i < rows; i += kCluThreads) {
+            float2 a = wstats[i];
+            for (int w = 1; w < kl; ++w) {
+              const float2 c = wstats[w * RC + i];
+              merge_stats(a.x, a.y, c.x, c.y);
+            }
+            agent_store(stats + static_cast<size_t>(s1) * prm.rpad_max + row0 + i,
+                        static_cast<unsigned long long>(__float_as_uint(a.x)) |
+                            (static_cast<unsigned long long>(__float_as_uint(a.y)) << 32));
+          }
+          if (row0 + RC < R) __syncthreads();  // (the staged rows and the statistics are replaced)
+        }
+        meet_set(stat_flags + wp * S + s1, target, tid);
+        s1 = meet_wait(stat_flags + wp * S, used, target, deadline, sh_miss, tid, lane);
+        if (s1 < 0) break;
+      }
+
+      // ---- pass 2: the scores of slice ws
+      const Slice sl = slice_of(nb, per, ws);
+      const int kb = sl.b1 - sl.b0, lim = min(n, sl.b1 << 5);
+      int rs_used = 1;
+      for (int row0 = 0; row0 < R; row0 += RC) {
+        const int rows = min(RC, round_up32(R - row0)), QB = rows >> 5;
+        // (the split of the largest chunk of rows serves all: the partial sums of the chunks meet in ksum)
+        const int rs = row_split(kb, min(RC, round_up32(R)) >> 5), kl = kCluWaves / rs;
+        rs_used = rs;
+        const int qper = (QB + rs - 1) / rs;
+        const int rq = wave & (rs - 1);
+        const int q_lo = min(QB, rq * qper), q_hi = min(QB, q_lo + qper);
+        int b = sl.b0 + wave / rs;
+        if (held != ws) {
+          if (b < sl.b1) load_k_block<D>(ks, lim, b << 5, lane, k0);
+          if (b + kl < sl.b1) load_k_block<D>(ks, lim, (b + kl) << 5, lane, k1);
+        }
+        stage(row0, rows);
+        // every row's log-sum-exp: parts of the S records side by side, then merged
+        const int parts = min(kCluWaves, kCluThreads / rows);
+        const int part = tid / rows, i = tid - part * rows;
+        if (part < parts) {
+          float m = -kInf, z = 0.f;
+          constexpr int kBatch = 8;  // loads in flight
+          for (int s0 = part; s0 < used; s0 += parts * kBatch) {
+            float2 rec[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+              const int sx = min(s0 + u * parts, used - 1);
+              const unsigned long long w = agent_load(stats + static_cast<size_t>(sx) * prm.rpad_max + row0 + i);
+              rec[u] = make_float2(__uint_as_float(static_cast<unsigned>(w)), __uint_as_float(static_cast<unsigned>(w >> 32)));
+              if (s0 + u * parts >= used) rec[u] = make_float2(-kInf, 0.f);
+            }
+            float mm = m;
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) mm = fmaxf(mm, rec[u].x);
+            if (mm != -kInf) {
+              z *= fast_exp2(m - mm);
+#pragma unroll
+              for (int u = 0; u < kBatch; ++u) z += rec[u].y * fast_exp2(rec[u].x - mm);
+            }
+            m = mm;
+          }
+          wstats[part * RC + i] = make_float2(m, z);
+        }
+        __syncthreads();
+        if (tid < rows) {
+          float l = kInf;  // padding rows add exp2(-inf) = 0
+          if (row0 + tid < R) {
+            float2 a = wstats[tid];
+            for (int w = 1; w < parts; ++w) {
+              const float2 c = wstats[w * RC + tid];
+              merge_stats(a.x, a.y, c.x, c.y);
+            }
+            l = a.x + fast_log2(a.y);
+            if (pb.lse_extra) l = widen_lse(l, as_global<float>(pb.lse_extra)[row0 + tid]);
+          }
+          lds_lse[tid] = l;
+        }
+        __syncthreads();
+        while (b < sl.b1) {
+          const bool two = b + kl < sl.b1;
+          float u0[16], u1[16];
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            u0[v] = 0.f;
+            u1[v] = 0.f;
+          }
+          for (int q = q_lo; q < q_hi; ++q) {
+            f32x16 a0, a1;
+            mfma_two<D>(k0, k1, lds_q + (q * 32 + t) * kStride + 16 * h, two, a0, a1);
+            const float lse = lds_lse[q * 32 + t];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) u0[v] += fast_exp2(__builtin_fmaf(a0[v], sc, -lse));
+            if (two) {
+#pragma unroll
+              for (int v = 0; v < 16; ++v) u1[v] += fast_exp2(__builtin_fmaf(a1[v], sc, -lse));
+            }
+          }
+          float* const o = ksum + (rq * kb + (b - sl.b0)) * 32 + acc_key(t >> 1, h);
+          const float s0 = fold16_over32(u0, t);
+          if ((t & 1) == 0) *o = row0 == 0 ? s0 : *o + s0;
+          if (two) {
+            const float s2 = fold16_over32(u1, t);
+            float* const o1 = o + kl * 32;
+            if ((t & 1) == 0) *o1 = row0 == 0 ? s2 : *o1 + s2;
+          }
+          b += 2 * kl;
+          if (b < sl.b1) {
+            load_k_block<D>(ks, lim, b << 5, lane, k0);
+            if (b + kl < sl.b1) load_k_block<D>(ks, lim, (b + kl) << 5, lane, k1);
+          }
+        }
+        __syncthreads();
+      }
+      float* const dst = pb.scores ? pb.scores : prm.ws_scores + static_cast<size_t>(wp) * prm.score_stride;
+      for (int i = tid; i < kb * 32; i += kCluThreads) {
+        float v = ksum[i];
+        for (int w = 1; w < rs_used; ++w) v += ksum[w * kb * 32 + i];
+        const int key = (sl.b0 << 5) + i;
+        if (key < n) agent_store(dst + key, v);
+      }
+      meet_set(score_flags + wp * S + ws, target, tid);
+    }
+    // ---- the second meeting: the scores of every problem of the run
+    if (!stages) break;
+    int miss = -1;
+    for (int g = 0; g < L && miss < 0; ++g) {
+      const finch_problem* pg = prm.probs + p_first + g;
+      const int ng = (pg->c + pg->m + 31) >> 5;
+      const int per_g = max(1, (ng + S - 1) / S);
+      const int m = meet_wait(score_flags + (p_first + g) * S, (ng + per_g - 1) / per_g, target, deadline, sh_miss, tid, lane);
+      if (m >= 0) miss = g * S + m;
+    }
+    if (miss < 0) break;
+    wp = p_first + miss / S;
+    ws = miss - miss / S * S;
+    pb = prm.probs[wp];
+  }
+
+  // This workgroup waits for nobody any more.  The last one to come here advances the
+  // generation (two levels of counters, so that no word sees all workgroups).  What the
+  // counters answer is looked at further down, when it has arrived.
+  const int cluster = my_p / L, members = L * S;
+  // (the status word of waits that expire: here none does)
+  if (L > 1 && tid == 0 && role == 0) *as_global_mut<int>(prm.layer_err) = 0;
+  int left = 0;
+  if (tid == 0) left = __hip_atomic_fetch_add(meet + kMeetExitOf + 16 * cluster, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  auto leave = [&]() {
+    if (tid == 0 && left == members - 1) {
+      agent_store(meet + kMeetExitOf + 16 * cluster, 0);
+      const int clusters = prm.n_problems / L;
+      if (__hip_atomic_fetch_add(meet + kMeetExit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == clusters - 1) {
+        agent_store(meet + kMeetExit, 0);
+        agent_store(meet + kMeetGen, target);
+      }
+    }
+  };
+  const int r = min(mine.r, N);
+  if (!stages || r <= 0) {
+    leave();
+    return;
+  }
+
+  // ---- top-r
+  FINCH_GLOBAL int* gidx = as_global_mut<int>(mine.idx);
+  const bool identity = r >= N;
+  SelLds* fl = reinterpret_cast<SelLds*>(smem);
+  int* lidx = reinterpret_cast<int*>(smem + sizeof(SelLds));
+  unsigned* lkeys = reinterpret_cast<unsigned*>(lidx + ((r + kSelIdxPad + 3) & ~3));
+  __syncthreads();  // (the scratch lies over what the passes used)
+  if (!identity) {
+    if (L > 1) {
+      if (tid < L) {
+        const finch_problem* pg = prm.probs + p_first + tid;
+        fl->layer_src[tid] = pg->scores ? pg->scores : prm.ws_scores + static_cast<size_t>(p_first + tid) * prm.score_stride;
+      }
+      __syncthreads();
+      sel_stage_keys<kCluThreads>(LayerScores{fl->layer_src, L}, N, lkeys, tid);
+    } else {
+      sel_stage_keys<kCluThreads>(
+          AgentScoreVector{mine.scores ? mine.scores : prm.ws_scores + static_cast<size_t>(my_p) * prm.score_stride}, N, lkeys,
+          tid);
+    }
+    __syncthreads();
+    select_keys_any<kCluThreads, true>(lkeys, N, r, gidx, lidx, fl, tid, lane, wave);
+    __syncthreads();
+  }
+  leave();
+
+  // ---- this workgroup's part of the compaction
+  const int t0 = static_cast<int>(static_cast<long long>(r) * my_s / S);
+  const int t1 = static_cast<int>(static_cast<long long>(r) * (my_s + 1) / S);
+  for (int i = t0 + tid; i < t1; i += kCluThreads) gidx[i] = identity ? i : lidx[i];
+  if (ROT) own_gather_rot<D / 8, kCluThreads, 8>(mine, N, r, lidx, gidx, identity, prm.rope_pairing, prm.rope_log2_base, tid, nullptr, t0, t1);
+  else own_gather<D / 8>(mine, N, lidx, gidx, identity, tid, t0, t1);
+}
+
+namespace {
+
+template <typename F>
+bool with_cluster_kernel(int head_dim, bool rot, F f) {
+  if (head_dim == 128) rot ? f(&cluster_step_bf16<128, true>) : f(&cluster_step_bf16<128, false>);
+  else if (head_dim == 64) rot ? f(&cluster_step_bf16<64, true>) : f(&cluster_step_bf16<64, false>);
+  else return false;
+  return true;
+}
+
+}  // namespace
+
+size_t cluster_meet_bytes() { return sizeof(int) * (kMeetFlags + 2 * kMaxClusterGrid); }
+
+// LDS of a launch: the passes' (row_chunk staged rows, slices of at most slice_blocks key
+// blocks) or the selection's (n_max candidates, r_max kept), whichever is more.
+size_t cluster_lds_bytes(int head_dim, int row_chunk, int slice_blocks, int n_max, int r_max) {
+  // a slice of at most kSplitBlocks may be split by rows, each part with sums of its own
+  const int blocks = kSplitBlocks * kCluWaves > slice_blocks ? kSplitBlocks * kCluWaves : slice_blocks;
+  const size_t sums = static_cast<size_t>(blocks) * 32 * 4;
+  const size_t passes = static_cast<size_t>(row_chunk) * (head_dim * 2 + 16 + kCluWaves * 8 + 4) + 16 + sums;
+  const size_t select = sizeof(SelLds) + (static_cast<size_t>(r_max) + kSelIdxPad + 3 + n_max) * 4;
+  return passes > select ? passes : select;
+}
+
+hipError_t launch_cluster_bf16(int head_dim, const LaunchParams& p, int stages, hipStream_t s) {
+  if (p.n_problems <= 0) return hipSuccess;
+  const dim3 grid(static_cast<unsigned>(p.n_problems) * static_cast<unsigned>(p.cluster_slices)), block(kCluThreads);
+  const bool ok = with_cluster_kernel(head_dim, p.rope_pairing != FINCH_ROPE_OFF, [&](auto kern) {
+    hipLaunchKernelGGL(kern, grid, block, p.lds_bytes, s, p, stages);
+  });
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
+}
+
+hipError_t set_max_lds_cluster(size_t bytes) {
+  hipError_t err = hipSuccess;
+  for (int d = 64; d <= 128; d += 64)
+    for (int rot = 0; rot < 2; ++rot)
+      with_cluster_kernel(d, rot != 0, [&](auto kern) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes));
+        if (e != hipSuccess) err = e;
+      });
+  return err;
+}
+
+}  // namespace finch

@@ -30,6 +30,15 @@ constexpr size_t kOwnerSelectBytes = 60 * 1024;
 constexpr int kOwnerRankRows = 2048;
 // Most problems per layer run that the one-workgroup-per-problem kernels select for together.
 constexpr int kOwnerMaxLayer = 16;
+// Several workgroups per problem in one launch (cluster_bf16.hip): most workgroups of a launch,
+// most key blocks of 32 and candidates per problem, and most prompt rows (their statistics
+// are held per workgroup in the workspace).
+constexpr int kMaxClusterGrid = 256;
+constexpr int kClusterSliceBlocks = 128;
+constexpr int kClusterMaxKeys = 15872;  // what a 512-thread selection holds in registers
+constexpr int kClusterMaxRows = 4096;
+// A workgroup that has waited this long for others in all (100 MHz ticks) does their work itself.
+constexpr int64_t kClusterHelpTicks = 10000;
 // Most LDS a workgroup of the selection kernels asks for.
 constexpr size_t kSelLdsBytes = 144 * 1024;
 // Rows copied by one workgroup of the compaction kernels.
@@ -68,6 +77,11 @@ struct LaunchParams {
   int32_t layer_group;         // L (1: every problem selects for itself)
   int32_t* layer_sync;         // [2 * runs]
   int32_t* layer_err;          // one word behind them
+  // several workgroups per problem (cluster_bf16.hip): slices of a problem, the meeting words of
+  // the context, and how long a workgroup waits before it helps
+  int32_t cluster_slices;
+  int32_t* meet;
+  int64_t help_ticks;
   int64_t spin_ticks;          // longest wait for the other workgroups, in 100 MHz ticks
 };
 
@@ -97,6 +111,11 @@ hipError_t launch_owner_f32(int head_dim, const LaunchParams& p, int stages, hip
 hipError_t launch_owner_loop_f32(int head_dim, const LaunchParams& p, const int* step_first, int n_steps,
                                  int n_slots, hipStream_t s);
 hipError_t set_max_lds_owner_f32(size_t bytes);
+// several workgroups per problem, one launch
+size_t cluster_meet_bytes();
+size_t cluster_lds_bytes(int head_dim, int row_chunk, int slice_blocks, int n_max, int r_max);
+hipError_t launch_cluster_bf16(int head_dim, const LaunchParams& p, int stages, hipStream_t s);
+hipError_t set_max_lds_cluster(size_t bytes);
 hipError_t launch_zero_words(int32_t* words, int n, int32_t* one_more, hipStream_t s);
 // the same with rows of the chunk's own tokens (desc.q_doc)
 hipError_t launch_owner_doc_bf16(int head_dim, const LaunchParams& p, int stages, hipStream_t s);

@@ -61,12 +61,13 @@ __device__ __forceinline__ int own_next_block(int* counter, int lane) {
   return __builtin_amdgcn_readfirstlane(v);
 }
 
-// Copy rows idx[0..r) of [cache ; chunk] of K and V into k_out / v_out by NT threads
-// (`tid` = index among them).  `lidx` (LDS) or `gidx` (memory, written by this
+// Copy rows idx[t0..t1) of [cache ; chunk] of K and V into k_out / v_out by NT threads
+// (`tid` = index among them), t1 <= the rows kept.  `lidx` (LDS) or `gidx` (memory, written by this
 // workgroup) holds the indices; with `identity` row t is simply candidate t.
 template <int SEGS, int NT = kOwnThreads>
-__device__ __forceinline__ void own_gather(const finch_problem& pb, int N, int r, const int* lidx,
-                                           const FINCH_GLOBAL int* gidx, bool identity, int tid) {
+__device__ __forceinline__ void own_gather(const finch_problem& pb, int N, const int* lidx,
+                                           const FINCH_GLOBAL int* gidx, bool identity, int tid, int t0,
+                                           int t1) {
   const FINCH_GLOBAL u32x4* kc = as_global<u32x4>(pb.k_cache);
   const FINCH_GLOBAL u32x4* kk = as_global<u32x4>(pb.k_chunk);
   const FINCH_GLOBAL u32x4* vc = as_global<u32x4>(pb.v_cache);
@@ -76,11 +77,11 @@ __device__ __forceinline__ void own_gather(const finch_problem& pb, int N, int r
   constexpr int kRowsPerIter = NT / SEGS;
   constexpr int kUnroll = 8;
   const int seg = tid % SEGS, sub = tid / SEGS;
-  for (int row0 = 0; row0 < r; row0 += kRowsPerIter * kUnroll) {
+  for (int row0 = t0; row0 < t1; row0 += kRowsPerIter * kUnroll) {
     u32x4 kv[kUnroll], vv[kUnroll];
 #pragma unroll
     for (int it = 0; it < kUnroll; ++it) {
-      const int t = min(row0 + it * kRowsPerIter + sub, r - 1);
+      const int t = min(row0 + it * kRowsPerIter + sub, t1 - 1);
       int j = identity ? t : (lidx ? lidx[t] : gidx[t]);
       j = min(max(j, 0), N - 1);
       const bool cached = j < pb.c;
@@ -91,7 +92,7 @@ __device__ __forceinline__ void own_gather(const finch_problem& pb, int N, int r
 #pragma unroll
     for (int it = 0; it < kUnroll; ++it) {
       const int t = row0 + it * kRowsPerIter + sub;
-      if (t < r) {
+      if (t < t1) {
         ko[static_cast<size_t>(t) * SEGS + seg] = kv[it];
         vo[static_cast<size_t>(t) * SEGS + seg] = vv[it];
       }
@@ -107,8 +108,8 @@ __device__ __forceinline__ void own_gather(const finch_problem& pb, int N, int r
 template <int SEGS, int NT = kOwnThreads, int E = 8>
 __device__ __forceinline__ void own_gather_rot(const finch_problem& pb, int N, int r, const int* lidx,
                                                const FINCH_GLOBAL int* gidx, bool identity, int pairing,
-                                               double log2_base, int tid,
-                                               const unsigned long long* ranked = nullptr) {
+                                               double log2_base, int tid, const unsigned long long* ranked,
+                                               int t0, int t1) {
   constexpr int kHalf = SEGS / 2;
   const FINCH_GLOBAL u32x4* kc = as_global<u32x4>(pb.k_cache);
   const FINCH_GLOBAL u32x4* kk = as_global<u32x4>(pb.k_chunk);
@@ -121,12 +122,12 @@ __device__ __forceinline__ void own_gather_rot(const finch_problem& pb, int N, i
   const int seg = tid % kHalf, sub = tid / kHalf;
   double th[E];
   pair_thetas<E, kHalf>(pairing, seg, log2_base, th);
-  for (int row0 = 0; row0 < r; row0 += kRowsPerIter * kUnroll) {
+  for (int row0 = t0; row0 < t1; row0 += kRowsPerIter * kUnroll) {
     u32x4 ka[kUnroll], kb[kUnroll], va[kUnroll], vb[kUnroll];
     int shift[kUnroll], slot[kUnroll];
 #pragma unroll
     for (int it = 0; it < kUnroll; ++it) {
-      const int p = min(row0 + it * kRowsPerIter + sub, r - 1);
+      const int p = min(row0 + it * kRowsPerIter + sub, t1 - 1);
       const int t = ranked ? min(static_cast<int>(~static_cast<unsigned>(ranked[p])), r - 1) : p;
       int j = identity ? t : (lidx ? lidx[t] : gidx[t]);
       j = min(max(j, 0), N - 1);
@@ -141,7 +142,7 @@ __device__ __forceinline__ void own_gather_rot(const finch_problem& pb, int N, i
     }
 #pragma unroll
     for (int it = 0; it < kUnroll; ++it) {
-      if (row0 + it * kRowsPerIter + sub < r) {
+      if (row0 + it * kRowsPerIter + sub < t1) {
         if (pairing != FINCH_ROPE_OFF && shift[it] != 0) rotate_pieces<E>(pairing, th, shift[it], ka[it], kb[it]);
         const size_t o = static_cast<size_t>(slot[it]) * SEGS + seg;
         ko[o] = ka[it];
@@ -356,9 +357,9 @@ __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const f
       ranked = reinterpret_cast<unsigned long long*>(sel + sizeof(SelLds) + ((static_cast<size_t>(r) * 4 + 7) & ~size_t{7}));
       own_rank_kept(ranked, r, dst, lidx, identity, tid);
     }
-    own_gather_rot<SEGS, kOwnThreads, E>(pb, N, r, lidx, gidx, identity, prm.rope_pairing, prm.rope_log2_base, tid, ranked);
+    own_gather_rot<SEGS, kOwnThreads, E>(pb, N, r, lidx, gidx, identity, prm.rope_pairing, prm.rope_log2_base, tid, ranked, 0, r);
   } else {
-    own_gather<SEGS>(pb, N, r, lidx, gidx, identity, tid);
+    own_gather<SEGS>(pb, N, lidx, gidx, identity, tid, 0, r);
   }
   FINCH_PHASE(7);
 }

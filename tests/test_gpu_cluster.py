@@ -1,0 +1,88 @@
+"""Steps in which several workgroups share a problem (bf16, batches much smaller than the
+chip): sizes at the edges of slices, row chunks, row splits and of the batch sizes that take
+this launch; the waits between workgroups forced to run out (every workgroup then does the
+others' work as well); layer groups, turned keys and the exact denominator; replays of a
+captured graph."""
+import pytest
+import torch
+
+import paper_2408_00167_amd as F
+from tests import gpu_harness as H
+from tests.test_gpu_parity import _which_scoring_kernels
+
+pytestmark = pytest.mark.gpu
+
+# name -> (specs, whether this launch takes them)
+BATCHES = {
+    "tiny": ([dict(n_que=3, c=0, m=1, r=1), dict(n_que=1, c=0, m=0, r=4), dict(n_que=9, c=5, m=26, r=7),
+              dict(n_que=8, c=1, m=31, r=31), dict(n_que=8, c=1, m=32, r=33), dict(n_que=2, c=70, m=0, r=0)], True),
+    "one": ([dict(n_que=48, c=704, m=4096, r=748)], True),
+    "row_chunks": ([dict(n_que=160, c=100, m=500, r=77), dict(n_que=65, c=0, m=300, r=20)], True),
+    "sliced": ([dict(n_que=40 + p, c=37 * p, m=900 + 61 * p, r=100 + p) for p in range(12)], True),
+    "two_slices": ([dict(n_que=5, c=10, m=150 + p % 7, r=60) for p in range(128)], True),
+    "too_many": ([dict(n_que=5, c=10, m=150, r=60)] * 129, False),
+    "longest": ([dict(n_que=6, c=5872, m=10000, r=5000), dict(n_que=6, c=0, m=64, r=9)], True),
+    "too_long": ([dict(n_que=6, c=5873, m=10000, r=5000)], False),
+}
+
+
+@pytest.mark.parametrize("d,group", [(128, 4), (64, 2)])
+@pytest.mark.parametrize("name", list(BATCHES))
+def test_batches(name, d, group):
+    specs, taken = BATCHES[name]
+    fin = F.Finch(F.FINCH_BF16, d, group)
+    batch, ts = H.single_step_case(fin, specs, torch.bfloat16, d, group, seed=31)
+    assert (_which_scoring_kernels(fin, batch) == {"owner"}) == taken
+    H.validate_single_step(ts, f"{name} d={d}")
+    fin.close()
+
+
+@pytest.mark.parametrize("layer,exact", [(1, False), (4, True)])
+def test_work_of_missing_workgroups_is_done_by_the_others(layer, exact):
+    """With a wait of 0 every workgroup finds some of the others missing and does their slices
+    too: the same bits as with the usual wait, at every repetition."""
+    specs = [dict(n_que=33, c=64 * (p // 4), m=700, r=150 + p // 4, prompt_keys=exact) for p in range(8)]
+    want = None
+    for ticks in (20_000_000, 0, 0, 20_000_000):
+        fin = F.Finch(F.FINCH_BF16, 128, 4)
+        F.finch_set_option(fin.ctx, F.FINCH_OPT_LAYER_GROUP, layer)
+        F.finch_set_option(fin.ctx, F.FINCH_OPT_LAYER_WAIT_TICKS, ticks)
+        if exact:
+            fin.set_reposition(F.FINCH_ROPE_HALF, F.FINCH_ORDER_ASCENDING, 10000.0)
+        batch, ts = H.single_step_case(fin, specs, torch.bfloat16, 128, 4, seed=5)
+        if exact:
+            fin.prompt_lse(batch)
+        for _ in range(3):
+            fin.step(batch)
+        assert fin.workspace_status() == 0
+        got = [t[k].clone() for t in ts for k in ("scores", "idx", "k_out", "v_out")]
+        if want is None:
+            want = got
+            if layer == 1:
+                H.validate_single_step(ts, "usual wait")
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
+        fin.close()
+
+
+def test_replays_of_a_captured_step():
+    specs = [dict(n_que=20, c=100, m=600, r=120)] * 8
+    fin = F.Finch(F.FINCH_BF16, 128, 4)
+    batch, ts = H.single_step_case(fin, specs, torch.bfloat16, 128, 4, seed=6)
+    fin.step_static(batch)
+    H.validate_single_step(ts, "eager")
+    want = [t[k].clone() for t in ts for k in ("scores", "idx", "k_out", "v_out")]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        fin.step_static(batch)
+    for i in range(4):
+        for t in ts:
+            t["scores"].fill_(-5.0)
+            t["k_out"].fill_(7.0)
+        g.replay()
+        if i == 1:
+            fin.step_static(batch)  # eager work of the program's own between the replays
+        torch.cuda.synchronize()
+        for a, b in zip([t[k] for t in ts for k in ("scores", "idx", "k_out", "v_out")], want):
+            assert torch.equal(a, b), i
+    fin.close()
