@@ -388,7 +388,7 @@ finch_status run_cluster(finch_ctx* ctx, LaunchParams p, const Plan& pl, void* w
   hipError_t e;
   {
     ProfScope ps(ctx, FINCH_KERNEL_OWNER, s);
-    e = finch::launch_cluster_bf16(ctx->cfg.head_dim, p, stages, s);
+    e = finch::launch_cluster_bf16(ctx->cfg.head_dim, p, pl.n_max, stages, s);
   }
   return e == hipSuccess ? FINCH_OK : hip_fail(ctx, e);
 }

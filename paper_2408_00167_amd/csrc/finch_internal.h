@@ -114,7 +114,7 @@ hipError_t set_max_lds_owner_f32(size_t bytes);
 // several workgroups per problem, one launch
 size_t cluster_meet_bytes();
 size_t cluster_lds_bytes(int head_dim, int row_chunk, int slice_blocks, int n_max, int r_max);
-hipError_t launch_cluster_bf16(int head_dim, const LaunchParams& p, int stages, hipStream_t s);
+hipError_t launch_cluster_bf16(int head_dim, const LaunchParams& p, int n_max, int stages, hipStream_t s);
 hipError_t set_max_lds_cluster(size_t bytes);
 hipError_t launch_zero_words(int32_t* words, int n, int32_t* one_more, hipStream_t s);
 // the same with rows of the chunk's own tokens (desc.q_doc)

@@ -64,7 +64,7 @@ __device__ __forceinline__ int own_next_block(int* counter, int lane) {
 // Copy rows idx[t0..t1) of [cache ; chunk] of K and V into k_out / v_out by NT threads
 // (`tid` = index among them), t1 <= the rows kept.  `lidx` (LDS) or `gidx` (memory, written by this
 // workgroup) holds the indices; with `identity` row t is simply candidate t.
-template <int SEGS, int NT = kOwnThreads>
+template <int SEGS, int NT = kOwnThreads, int kUnroll = 8>
 __device__ __forceinline__ void own_gather(const finch_problem& pb, int N, const int* lidx,
                                            const FINCH_GLOBAL int* gidx, bool identity, int tid, int t0,
                                            int t1) {
@@ -75,7 +75,6 @@ __device__ __forceinline__ void own_gather(const finch_problem& pb, int N, const
   FINCH_GLOBAL u32x4* ko = as_global_mut<u32x4>(pb.k_out);
   FINCH_GLOBAL u32x4* vo = as_global_mut<u32x4>(pb.v_out);
   constexpr int kRowsPerIter = NT / SEGS;
-  constexpr int kUnroll = 8;
   const int seg = tid % SEGS, sub = tid / SEGS;
   for (int row0 = t0; row0 < t1; row0 += kRowsPerIter * kUnroll) {
     u32x4 kv[kUnroll], vv[kUnroll];
@@ -105,7 +104,7 @@ __device__ __forceinline__ void own_gather(const finch_problem& pb, int N, const
 // at place p of the sorted records; the key is turned by p - idx[t] positions while it
 // is copied (not at all with pairing FINCH_ROPE_OFF).  A thread owns two pieces of a
 // row, d/2 channels apart, i.e. both partners of its channel pairs.
-template <int SEGS, int NT = kOwnThreads, int E = 8>
+template <int SEGS, int NT = kOwnThreads, int E = 8, int kUnroll = 4>
 __device__ __forceinline__ void own_gather_rot(const finch_problem& pb, int N, int r, const int* lidx,
                                                const FINCH_GLOBAL int* gidx, bool identity, int pairing,
                                                double log2_base, int tid, const unsigned long long* ranked,
@@ -118,7 +117,6 @@ __device__ __forceinline__ void own_gather_rot(const finch_problem& pb, int N, i
   FINCH_GLOBAL u32x4* ko = as_global_mut<u32x4>(pb.k_out);
   FINCH_GLOBAL u32x4* vo = as_global_mut<u32x4>(pb.v_out);
   constexpr int kRowsPerIter = NT / kHalf;
-  constexpr int kUnroll = 4;
   const int seg = tid % kHalf, sub = tid / kHalf;
   double th[E];
   pair_thetas<E, kHalf>(pairing, seg, log2_base, th);
@@ -323,11 +321,11 @@ __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const f
         return;
       }
     }
-    const LayerScores layer_sum = {fl->layer_src, L};
+    const LayerScores<kSelMaxLayer> layer_sum = {fl->layer_src, L};
     const OneScoreVector own = {dst};
     if (lkeys) {  // (then there is room for the indices as well)
       if (layered || !keys_staged) {
-        if (layered) sel_stage_keys<kOwnThreads>(layer_sum, N, lkeys, tid);
+        if (layered) sel_stage_layer_keys<kOwnThreads>(fl->layer_src, L, N, lkeys, tid);
         else sel_stage_keys<kOwnThreads>(own, N, lkeys, tid);
         __syncthreads();
       }

@@ -41,6 +41,24 @@ __device__ __forceinline__ float widen_lse(float lse2, float extra_ln) {
 // lane-half h.
 __device__ __forceinline__ int acc_key(int v, int h) { return 8 * (v >> 2) + 4 * h + (v & 3); }
 
+// A problem's descriptor through the scalar cache, all of it at once (descriptors do not change
+// during a launch; as ordinary loads the compiler fetches the fields one dependent round trip
+// after the other, where they are used).  `p` must be the same in every lane.
+__device__ __forceinline__ finch_problem load_problem(const finch_problem* p) {
+  typedef const __attribute__((address_space(4))) unsigned long long* words;
+  struct Raw {
+    unsigned long long w[sizeof(finch_problem) / 8];
+  } raw;
+  static_assert(sizeof(Raw) == sizeof(finch_problem), "descriptors are whole 8-byte words");
+  const words src = (words)(unsigned long long)p;
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(finch_problem) / 8; ++i) raw.w[i] = src[i];
+  static_assert(sizeof(finch_problem) / 8 == 14, "all of them are named below");
+  asm volatile("" ::"s"(raw.w[0]), "s"(raw.w[1]), "s"(raw.w[2]), "s"(raw.w[3]), "s"(raw.w[4]), "s"(raw.w[5]), "s"(raw.w[6]),
+               "s"(raw.w[7]), "s"(raw.w[8]), "s"(raw.w[9]), "s"(raw.w[10]), "s"(raw.w[11]), "s"(raw.w[12]), "s"(raw.w[13]));
+  return __builtin_bit_cast(finch_problem, raw);
+}
+
 // One 32-key block of K as MFMA A operands: lane (t, h) holds row kbase + t,
 // elements 16*s + 8*h .. +7 of it for k-step s.  Rows at or past N are zeros.
 template <int D>
@@ -112,12 +130,12 @@ __device__ __forceinline__ void load_k_block(const KeySource& ks, int N, int kba
 // Copy prompt rows [row0, row0+rows) into LDS, rows past R as zeros.  Row stride
 // D*2+16 bytes keeps the 16-byte B-operand reads of 8 consecutive lanes on
 // distinct banks.  NT = threads of the workgroup.
-template <int D, int NT>
+template <int D, int NT, int BATCH = 4>
 __device__ __forceinline__ void stage_q(const void* q, int R, int row0, int rows, char* lds_q,
                                         int tid) {
   constexpr int kSegs = D / 8;
   constexpr int kStride = D * 2 + 16;
-  constexpr int kBatch = 4;  // loads in flight per thread
+  constexpr int kBatch = BATCH;  // loads in flight per thread
   const FINCH_GLOBAL u32x4* src = as_global<u32x4>(q);
   const int total = rows * kSegs;
   for (int i0 = tid; i0 < total; i0 += NT * kBatch) {

@@ -82,19 +82,19 @@ struct OneScoreVector {
 // ... or the sum of the L vectors of a layer's heads, added head by head in fp32 (Method:
 // "Sum over heads"; the order is that of select_layer, so both give the same bits).  The
 // vectors come from other workgroups: they are read past this compute unit's caches.
+// W: at least L; all W loads go out together (those past L repeat the last one), so keep it small.
+template <int W>
 struct LayerScores {
   const float* const* src;  // LDS table of L pointers
   int L;
   __device__ __forceinline__ float operator()(int i) const {
-    // all loads first (they come from far away), then the sum in head order
-    float v[kSelMaxLayer];
+    float v[W];
 #pragma unroll
-    for (int g = 0; g < kSelMaxLayer; ++g)
-      v[g] = g < L ? __hip_atomic_load(src[g] + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
+    for (int g = 0; g < W; ++g)
+      v[g] = __hip_atomic_load((const FINCH_GLOBAL float*)src[min(g, L - 1)] + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     float t = v[0];
 #pragma unroll
-    for (int g = 1; g < kSelMaxLayer; ++g)
-      if (g < L) t = t + v[g];
+    for (int g = 1; g < W; ++g) t = g < L ? t + v[g] : t;
     return t;
   }
 };
@@ -267,7 +267,9 @@ __device__ __forceinline__ void select_keys(const unsigned* keys, int N, int r, 
     hi = max(hi, key[k]);
     nlo = max(nlo, key[k] ? ~key[k] : 0u);
   }
-  for (int i = tid; i < 2 * kSelHistWords; i += NT) (&f->hist[0][0])[i] = 0;
+  typedef int i32x4 __attribute__((ext_vector_type(4)));
+  const i32x4 zero4 = {0, 0, 0, 0};
+  for (int i = tid; i < 2 * kSelHistWords / 4; i += NT) reinterpret_cast<i32x4*>(&f->hist[0][0])[i] = zero4;
   if (tid < kSelCand) f->cand[tid] = 0u;
   if (tid == 0) f->n_cand = 0;
   hi = wave_max_u32(hi);
@@ -378,15 +380,17 @@ __device__ __forceinline__ void select_keys(const unsigned* keys, int N, int r, 
 template <int NT, bool LDS_OUT>
 __device__ __forceinline__ void select_keys_any(const unsigned* keys, int N, int r, FINCH_GLOBAL int* gidx, int* lidx,
                                                 SelLds* f, int tid, int lane, int wave) {
-  if (N <= NT * 7) select_keys<NT, 7, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave);
+  if (N <= NT * 3) select_keys<NT, 3, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave);
+  else if (N <= NT * 7) select_keys<NT, 7, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave);
   else if (N <= NT * 11) select_keys<NT, 11, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave);
   else select_keys<NT, kSelRegKeys, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave);
 }
 
 // Puts the order keys of the N scores into LDS (no barrier).
-template <int NT, class Src>
-__device__ __forceinline__ void sel_stage_keys(const Src& score_of, int N, unsigned* keys, int tid) {
-  constexpr int kBatch = 8;  // loads in flight per thread
+// BATCH: candidates whose loads are in flight per thread.
+template <int NT, int BATCH, class Src>
+__device__ __forceinline__ void sel_stage_keys_batch(const Src& score_of, int N, unsigned* keys, int tid) {
+  constexpr int kBatch = BATCH;
   for (int i0 = tid; i0 < N; i0 += NT * kBatch) {
     float v[kBatch];
 #pragma unroll
@@ -395,6 +399,17 @@ __device__ __forceinline__ void sel_stage_keys(const Src& score_of, int N, unsig
     for (int u = 0; u < kBatch; ++u)
       if (i0 + u * NT < N) keys[i0 + u * NT] = order_key(v[u]);
   }
+}
+
+template <int NT, class Src>
+__device__ __forceinline__ void sel_stage_keys(const Src& score_of, int N, unsigned* keys, int tid) {
+  sel_stage_keys_batch<NT, 8>(score_of, N, keys, tid);
+}
+// The sums over the L vectors of a layer.
+template <int NT>
+__device__ __forceinline__ void sel_stage_layer_keys(const float* const* src, int L, int N, unsigned* keys, int tid) {
+  if (L <= 8) sel_stage_keys_batch<NT, 4>(LayerScores<8>{src, L}, N, keys, tid);
+  else sel_stage_keys_batch<NT, 2>(LayerScores<kSelMaxLayer>{src, L}, N, keys, tid);
 }
 
 }  // namespace finch
