@@ -1,69 +1,87 @@
-// One workgroup per problem for fp32 Q/K/V: both scoring passes on the vector ALU
+// One workgroup per problem for fp32 Q/K/V: both scoring passes
 // (Background, attention equation; Method: prompt-guided sub-matrix, sum over heads and
 // prompt rows), then the top-r and the compaction of owner_body.h, for one step or for
 // the whole chunk loop in one launch (Method: Document Segmentation).  Rows come from the
 // prompt and, with desc.q_doc, from the chunk's own tokens under the causal mask with the
 // Method's normalisation step read per row.
 //
-// One thread owns one key at a time and keeps its K row in registers; the rows of a
-// chunk of kRowChunk rows are broadcast from LDS.  Dot products accumulate in fp64
-// (every fp32 product is exact there), the softmax runs in fp32 in the log2 domain with
-// a running (maximum, sum) per row and thread, merged over the workgroup.  This serves
-// fp32 problems of modest size (C1: 16 prompt rows, a few hundred keys); it is not
-// tuned for large ones, which the kernels per stage spread over the chip.
+// Rows go through in chunks of 16, keys in tiles of 16: a tile of logits is one chain of fp64
+// matrix instructions (v_mfma_f64_16x16x4: every fp32 product is exact there, sums are fp64),
+// which leaves one row and four keys to a lane.  The softmax runs in fp32 in the log2 domain
+// with a running (maximum, sum) per row and lane, merged over the workgroup.  Logits of up to
+// kHeldTiles tiles (1024 candidates) wait in LDS for the second pass; beyond that they are
+// formed again.  This serves fp32 problems of modest size, where a step is
+// latency: 320 candidates and 16 rows of 64 channels take 10 us (40 with a key per thread on the
+// vector ALU, where every fp64 multiply-add came with two conversions); large ones are better
+// off spread over the chip by the kernels per stage.
 #include "owner_body.h"
 
 namespace finch {
 
 namespace {
 
-constexpr int kRowChunk = 16;  // rows staged at a time
+constexpr int kRowChunk = 16;  // rows at a time
+constexpr int kTile = 16;      // keys of a tile
+constexpr int kHeldTiles = 64; // tiles whose logits are kept from pass 1 to pass 2
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 struct F32Lds {
-  float* rows;     // [kRowChunk][D]
-  int* lim;        // [kRowChunk] a row sees the keys below its limit
+  float4* held;    // [kHeldTiles][64 lanes]
   float* lse;      // [kRowChunk]
   float2* wred;    // [waves][kRowChunk]
   char* sel;       // selection scratch
 };
 
-template <int D>
 __device__ __forceinline__ F32Lds f32_lds(char* smem) {
   F32Lds l;
-  size_t off = 0;
-  l.rows = reinterpret_cast<float*>(smem);
-  off += sizeof(float) * kRowChunk * D;
-  l.lim = reinterpret_cast<int*>(smem + off);
-  off += sizeof(int) * kRowChunk;
-  l.lse = reinterpret_cast<float*>(smem + off);
-  off += sizeof(float) * kRowChunk;
-  l.wred = reinterpret_cast<float2*>(smem + off);
-  off += sizeof(float2) * kOwnWaves * kRowChunk;
-  l.sel = smem + ((off + 15) & ~size_t{15});
+  l.held = reinterpret_cast<float4*>(smem);
+  smem += sizeof(float4) * 64 * kHeldTiles;
+  l.lse = reinterpret_cast<float*>(smem);
+  l.wred = reinterpret_cast<float2*>(smem + sizeof(float) * kRowChunk);
+  l.sel = smem + ((sizeof(float) * kRowChunk + sizeof(float2) * kOwnWaves * kRowChunk + 15) & ~size_t{15});
   return l;
 }
 
+// A lane's share of an operand of the fp64 matrix instructions: row `lane & 15` of sixteen, the
+// (lane >> 4)-th quarter of its channels (which k-step takes which channel is free as long as
+// both operands agree).
 template <int D>
-__device__ __forceinline__ void f32_load_k_row(const finch_problem& pb, int key, float (&k)[D]) {
-  const float* row = key < pb.c ? static_cast<const float*>(pb.k_cache) + static_cast<size_t>(key) * D
-                                : static_cast<const float*>(pb.k_chunk) + static_cast<size_t>(key - pb.c) * D;
-  const FINCH_GLOBAL u32x4* rp = as_global<u32x4>(row);
+__device__ __forceinline__ void f32_load_quarter(const float* row, int lane, u32x4 (&x)[D / 16]) {
+  const FINCH_GLOBAL u32x4* rp = as_global<u32x4>(row + (lane >> 4) * (D / 4));
 #pragma unroll
-  for (int s = 0; s < D / 4; ++s) {
-    const u32x4 x = rp[s];
-    k[4 * s] = __uint_as_float(x.x);
-    k[4 * s + 1] = __uint_as_float(x.y);
-    k[4 * s + 2] = __uint_as_float(x.z);
-    k[4 * s + 3] = __uint_as_float(x.w);
-  }
+  for (int s = 0; s < D / 16; ++s) x[s] = rp[s];
+}
+template <int D>
+__device__ __forceinline__ void f32_load_keys(const finch_problem& pb, int N, int tile, int lane, u32x4 (&x)[D / 16]) {
+  const int key = min(tile * kTile + (lane & 15), N - 1);
+  const float* base = static_cast<const float*>(key < pb.c ? pb.k_cache : pb.k_chunk);
+  f32_load_quarter<D>(base + static_cast<size_t>(key < pb.c ? key : key - pb.c) * D, lane, x);
 }
 
+// Dot products of 16 keys and 16 rows: element v of a lane is key 4 v + (lane >> 4), row lane & 15.
 template <int D>
-__device__ __forceinline__ float f32_dot(const float* qrow, const float (&k)[D]) {
-  double acc = 0.0;
+__device__ __forceinline__ void f32_dots(const u32x4 (&k)[D / 16], u32x4 (&q)[D / 16], float (&dot)[4]) {
+  if (D > 64) {  // (128 channels of a row as fp64 would not fit for good: they are widened tile by tile)
 #pragma unroll
-  for (int s = 0; s < D; ++s) acc = __builtin_fma(static_cast<double>(qrow[s]), static_cast<double>(k[s]), acc);
-  return static_cast<float>(acc);
+    for (int s = 0; s < D / 16; ++s) asm volatile("" : "+v"(q[s]));
+  }
+  f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+  for (int s = 0; s < D / 4; ++s)
+    acc[s & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(__uint_as_float(k[s >> 2][s & 3])),
+                                                      static_cast<double>(__uint_as_float(q[s >> 2][s & 3])), acc[s & 1], 0, 0, 0);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) dot[v] = static_cast<float>(acc[0][v] + acc[1][v]);
+}
+
+// Sum over the 16 lanes of a row of lanes (lane ^ 8, ^ 7, ^ 2, ^ 1 through DPP; fixed order).
+__device__ __forceinline__ float sum_over16(float x) {
+  x += from_lane_dpp<0x128>(x);
+  x += from_lane_dpp<0x141>(x);
+  x += from_lane_dpp<0x4E>(x);
+  x += from_lane_dpp<0xB1>(x);
+  return x;
 }
 
 // One step of one problem by the whole workgroup; see own_step_body for `step_probs`,
@@ -74,8 +92,8 @@ __device__ __forceinline__ bool own_step_body_f32(const LaunchParams& prm, const
                                                   int epoch) {
   const int N = pb.c + pb.m;
   if (N == 0) return false;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const F32Lds l = f32_lds<D>(smem);
+  const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
+  const F32Lds l = f32_lds(smem);
   const float sc = prm.scale_log2;
   float* gscores = pb.scores ? pb.scores : prm.ws_scores + static_cast<size_t>(slot) * prm.score_stride;
   FINCH_GLOBAL float* dst = as_global_mut<float>(gscores);
@@ -96,58 +114,54 @@ __device__ __forceinline__ bool own_step_body_f32(const LaunchParams& prm, const
     }
     __syncthreads();
   }
+  const size_t sel_bytes = prm.lds_bytes - static_cast<size_t>(l.sel - smem);
+  unsigned* const lkeys = (stages && pb.r > 0 && pb.r < N) ? own_sel_keys(l.sel, sel_bytes, 0, N, pb.r) : nullptr;
   // rows: the prompt's (they see every key), then those of the chunk's own tokens, head by head
   const int Rp = pb.q ? prm.group * pb.n_que : 0;
   const int Rd = (pb.q_doc && pb.m > 0) ? prm.group * pb.m : 0;
   const int n_rows = Rp + Rd;
+  const int n_tiles = (N + kTile - 1) / kTile;
+  const bool hold = n_tiles <= kHeldTiles;
+  const int col = lane & 15, part = lane >> 4;
+  u32x4 kf[D / 16], kn[D / 16];
   for (int row0 = 0; row0 < n_rows; row0 += kRowChunk) {
     const int rows = min(kRowChunk, n_rows - row0);
-    // stage the rows, their limits and what is added to their denominators
-    for (int i = tid; i < rows * (D / 4); i += kOwnThreads) {
-      const int ri = i / (D / 4), seg = i - ri * (D / 4);
-      const int row = row0 + ri;
-      const float* src = row < Rp ? static_cast<const float*>(pb.q) + static_cast<size_t>(row) * D
-                                  : static_cast<const float*>(pb.q_doc) + static_cast<size_t>(row - Rp) * D;
-      reinterpret_cast<u32x4*>(l.rows)[i] = as_global<u32x4>(src)[seg];
-    }
-    if (tid < kRowChunk) {
-      const int row = row0 + tid;
-      int lim = 0;  // rows past the end see nothing
-      if (tid < rows) lim = row < Rp ? N : min(N, pb.c + (row - Rp) % pb.m + 1);
-      l.lim[tid] = lim;
-    }
-    __syncthreads();
-    // ---- pass 1: running (maximum, sum exp2) per row over this thread's keys
-    float m_run[kRowChunk], z_run[kRowChunk];
+    // this lane's row: its keys end at `lim` (a row past the end sees none)
+    const int row = row0 + min(col, rows - 1);
+    const int lim = col >= rows ? 0 : row < Rp ? N : min(N, pb.c + (row - Rp) % pb.m + 1);
+    if (wave < n_tiles) f32_load_keys<D>(pb, N, wave, lane, kf);
+    u32x4 q[D / 16];
+    f32_load_quarter<D>(row < Rp ? static_cast<const float*>(pb.q) + static_cast<size_t>(row) * D
+                                 : static_cast<const float*>(pb.q_doc) + static_cast<size_t>(row - Rp) * D,
+                        lane, q);
+    // ---- pass 1: running (maximum, sum exp2) of this lane's row over its keys
+    float m = -kInf, z = 0.f;
+    auto tile_stats = [&](const float (&dot)[4], int tile) {
+      float s[4];
 #pragma unroll
-    for (int i = 0; i < kRowChunk; ++i) {
-      m_run[i] = -kInf;
-      z_run[i] = 0.f;
-    }
-    for (int key = tid; key < N; key += kOwnThreads) {
-      float k[D];
-      f32_load_k_row<D>(pb, key, k);
+      for (int v = 0; v < 4; ++v) s[v] = tile * kTile + 4 * v + part < lim ? dot[v] * sc : -kInf;
+      const float mn = fmaxf(fmaxf(fmaxf(m, s[0]), fmaxf(s[1], s[2])), s[3]);
+      const float mu = mn == -kInf ? 0.f : mn;
+      z = z * fast_exp2(m - mu) + (fast_exp2(s[0] - mu) + fast_exp2(s[1] - mu)) + (fast_exp2(s[2] - mu) + fast_exp2(s[3] - mu));
+      m = mn;
+    };
+    for (int tile = wave; tile < n_tiles; tile += kOwnWaves) {
+      if (tile + kOwnWaves < n_tiles) f32_load_keys<D>(pb, N, tile + kOwnWaves, lane, kn);
+      float dot[4];
+      f32_dots<D>(kf, q, dot);
+      if (hold) l.held[tile * 64 + lane] = make_float4(dot[0], dot[1], dot[2], dot[3]);
+      tile_stats(dot, tile);
 #pragma unroll
-      for (int i = 0; i < kRowChunk; ++i) {
-        if (key < l.lim[i]) {
-          const float s = f32_dot<D>(l.rows + i * D, k) * sc;
-          const float mn = fmaxf(m_run[i], s);
-          z_run[i] = z_run[i] * fast_exp2(m_run[i] - mn) + fast_exp2(s - mn);
-          m_run[i] = mn;
-        }
-      }
+      for (int s = 0; s < D / 16; ++s) kf[s] = kn[s];
     }
 #pragma unroll
-    for (int i = 0; i < kRowChunk; ++i) {
-      float m = m_run[i], z = z_run[i];
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) {
-        const float m2 = __shfl_xor(m, o);
-        const float z2 = __shfl_xor(z, o);
-        merge_stats(m, z, m2, z2);
-      }
-      if (lane == 0) l.wred[wave * kRowChunk + i] = make_float2(m, z);
+    for (int o = 16; o <= 32; o <<= 1) {
+      const float m2 = __shfl_xor(m, o);
+      const float z2 = __shfl_xor(z, o);
+      merge_stats(m, z, m2, z2);
     }
+    if (lane < kRowChunk) l.wred[wave * kRowChunk + lane] = make_float2(m, z);
+    if (!hold) f32_load_keys<D>(pb, N, wave, lane, kf);
     __syncthreads();
     if (tid < kRowChunk) {
       float lse = kInf;  // rows past the end add exp2(-inf) = 0
@@ -159,36 +173,54 @@ __device__ __forceinline__ bool own_step_body_f32(const LaunchParams& prm, const
           merge_stats(a.x, a.y, c.x, c.y);
         }
         lse = a.x + fast_log2(a.y);
-        const int row = row0 + tid;
         if (row < Rp) {
           if (pb.lse_extra) lse = widen_lse(lse, as_global<float>(pb.lse_extra)[row]);
         } else {
           // normalisation step: the row's weights times (keys it sees) / (c + m)
-          lse -= fast_log2(static_cast<float>(l.lim[tid]) / static_cast<float>(N));
+          lse -= fast_log2(static_cast<float>(lim) / static_cast<float>(N));
         }
       }
       l.lse[tid] = lse;
     }
     __syncthreads();
-    // ---- pass 2: this chunk's rows added to the scores of this thread's keys
-    for (int key = tid; key < N; key += kOwnThreads) {
-      float k[D];
-      f32_load_k_row<D>(pb, key, k);
-      float u = 0.f;
+    // ---- pass 2: this chunk's rows added to the scores of the keys
+    const float lse = l.lse[col];
+    auto tile_sums = [&](const float (&dot)[4], int tile) {
+      float mine = 0.f;  // lane col == v takes the sum of key 4 v + part
 #pragma unroll
-      for (int i = 0; i < kRowChunk; ++i) {
-        if (key < l.lim[i]) u += fast_exp2(__builtin_fmaf(f32_dot<D>(l.rows + i * D, k), sc, -l.lse[i]));
+      for (int v = 0; v < 4; ++v) {
+        const float w = tile * kTile + 4 * v + part < lim ? fast_exp2(__builtin_fmaf(dot[v], sc, -lse)) : 0.f;
+        const float u = sum_over16(w);
+        mine = col == v ? u : mine;
       }
-      const float val = row0 == 0 ? u : dst[key] + u;
-      if (layered) __hip_atomic_store(gscores + key, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      else dst[key] = val;
+      const int key = tile * kTile + 4 * col + part;
+      if (col < 4 && key < N) {
+        const float val = row0 == 0 ? mine : dst[key] + mine;
+        if (layered) __hip_atomic_store(gscores + key, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else dst[key] = val;
+        if (lkeys) lkeys[key] = order_key(val);
+      }
+    };
+    if (hold) {  // (a wave reads back what it has written itself)
+      for (int tile = wave; tile < n_tiles; tile += kOwnWaves) {
+        const float4 h = l.held[tile * 64 + lane];
+        const float dot[4] = {h.x, h.y, h.z, h.w};
+        tile_sums(dot, tile);
+      }
+    } else {
+      for (int tile = wave; tile < n_tiles; tile += kOwnWaves) {
+        if (tile + kOwnWaves < n_tiles) f32_load_keys<D>(pb, N, tile + kOwnWaves, lane, kn);
+        float dot[4];
+        f32_dots<D>(kf, q, dot);
+        tile_sums(dot, tile);
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s) kf[s] = kn[s];
+      }
     }
-    __syncthreads();  // the staged rows may be replaced; after the last chunk: the scores are out
+    __syncthreads();  // after the last chunk: the scores are out
   }
   if (!stages) return false;
-  const size_t sel_bytes = prm.lds_bytes - static_cast<size_t>(l.sel - smem);
-  unsigned* const lkeys = (pb.r > 0 && pb.r < N) ? own_sel_keys(l.sel, sel_bytes, 0, N, pb.r) : nullptr;
-  own_finish_step<D / 4, 4, ROT>(prm, pb, slot, N, dst, l.sel, sel_bytes, lkeys, /*keys_staged=*/false, step_probs,
+  own_finish_step<D / 4, 4, ROT>(prm, pb, slot, N, dst, l.sel, sel_bytes, lkeys, /*keys_staged=*/true, step_probs,
                                  epoch, layered, sync_words, tid);
   return layered;
 }
@@ -197,7 +229,7 @@ template <int D, bool ROT>
 __global__ __launch_bounds__(kOwnThreads) void owner_step_f32(LaunchParams prm, int stages) {
   extern __shared__ __align__(16) char smem[];
   const int p = own_slot_of(blockIdx.x, gridDim.x, stages ? prm.layer_group : 1);
-  const finch_problem pb = prm.probs[p];
+  const finch_problem pb = load_problem(prm.probs + p);
   own_step_body_f32<D, ROT>(prm, pb, p, stages, smem, prm.probs, 0);
 }
 
@@ -209,7 +241,7 @@ __global__ __launch_bounds__(kOwnThreads) void owner_loop_f32(LaunchParams prm, 
   for (int s = 0; s < n_steps; ++s) {
     const int first = step_first[s];
     if (slot >= step_first[s + 1] - first) break;  // slots are filled from the front
-    const finch_problem pb = prm.probs[first + slot];
+    const finch_problem pb = load_problem(prm.probs + uni(first + slot));
     if (own_step_body_f32<D, ROT>(prm, pb, slot, /*stages=*/1, smem, prm.probs + first, epoch)) ++epoch;
     // the rows this step wrote are the next step's cache: complete before it reads
     __syncthreads();
@@ -234,8 +266,8 @@ bool with_f32_loop_kernel(int head_dim, bool rot, F f) {
 }  // namespace
 
 size_t owner_f32_lds_bytes(int head_dim) {
-  const size_t fixed = sizeof(float) * kRowChunk * head_dim + (sizeof(int) + sizeof(float)) * kRowChunk +
-                       sizeof(float2) * kOwnWaves * kRowChunk + 16;
+  (void)head_dim;
+  const size_t fixed = sizeof(float4) * 64 * kHeldTiles + sizeof(float) * kRowChunk + sizeof(float2) * kOwnWaves * kRowChunk + 16;
   return fixed + sizeof(SelLds) + kOwnerSelectBytes;
 }
 
