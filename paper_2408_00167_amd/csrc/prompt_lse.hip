@@ -11,8 +11,8 @@
 // of 16 prompt keys, and a block's 256 logits are one chain of fp64 matrix instructions
 // (every product is exact, sums are fp64).  Each lane then holds the logits of one key
 // against four rows; maxima and sums stay in fp64.  One layer of 8 KV heads, 256 rows and 64
-// prompt keys each: 38 us with one row per four lanes and the keys one after the other, 5 us
-// now (launch and the first loads' latency).
+// prompt keys each: 38 us with one row per four lanes and the keys one after the other, 6.4 us
+// now (most of it the first loads' latency).
 #include "finch_internal.h"
 
 namespace finch {
