@@ -345,7 +345,9 @@ __global__ __launch_bounds__(kCluThreads) void cluster_step_bf16(LaunchParams pr
                 const float m2 = __shfl_xor(m, 32);
                 const float z2 = __shfl_xor(z, 32);
                 merge_stats(m, z, m2, z2);
-                if (h == 0) wstats[bk * RC + q * 32 + t] = make_float2(m, z);
+                // (tiles formed once more: their statistics are published, and these words are
+                // pass 2's from here on - no barrier lies between)
+                if (h == 0 && !met) wstats[bk * RC + q * 32 + t] = make_float2(m, z);
               }
             }
           } else {

@@ -65,6 +65,37 @@ def test_work_of_missing_workgroups_is_done_by_the_others(layer, exact):
         fin.close()
 
 
+# Slices of several key blocks and row blocks: the tiles a wave holds are formed once more after it
+# has helped, by waves with four tiles beside waves with none; and what is not held in registers.
+HELPED = {
+    "held_5x5": [dict(n_que=40, c=100 + p, m=4900 - 3 * p, r=300 + p) for p in range(8)],
+    "held_5x6": [dict(n_que=48, c=700, m=4096, r=750)] * 8,
+    "held_6x3": [dict(n_que=24, c=0, m=6140 - p, r=90) for p in range(8)],
+}
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("name", list(HELPED))
+def test_helping_over_several_blocks(name, d):
+    """As above, where a slice is several key blocks: bits of the usual wait, which the oracle checks."""
+    want = None
+    for ticks in (20_000_000, 0, 0, 0):
+        fin = F.Finch(F.FINCH_BF16, d, 4)
+        F.finch_set_option(fin.ctx, F.FINCH_OPT_LAYER_WAIT_TICKS, ticks)
+        batch, ts = H.single_step_case(fin, HELPED[name], torch.bfloat16, d, 4, seed=41)
+        for _ in range(4):
+            for t in ts:
+                t["scores"][:-1].fill_(-3.0)
+            fin.step(batch)
+            got = [t[k].clone() for t in ts for k in ("scores", "idx", "k_out", "v_out")]
+            if want is None:
+                want = got
+                H.validate_single_step(ts, f"{name} d={d}")
+            for a, b in zip(got, want):
+                assert torch.equal(a, b), (name, d, ticks)
+        fin.close()
+
+
 def test_replays_of_a_captured_step():
     specs = [dict(n_que=20, c=100, m=600, r=120)] * 8
     fin = F.Finch(F.FINCH_BF16, 128, 4)
