@@ -287,7 +287,8 @@ typedef enum {
    * not to be used.  0 makes the first workgroup of every layer give up at once: the way
    * to exercise the error path.  Launches that put several workgroups on a problem (AUTO,
    * small bf16 batches) never give up: a workgroup that has waited for the others for this
-   * long, or 0.1 ms if that is less, does what is missing itself, with the same results. */
+   * long, or for 0.1 ms and a time that grows with the work if that is less, does what is
+   * missing itself, with the same results. */
   FINCH_OPT_LAYER_WAIT_TICKS = 5
 } finch_option;
 typedef enum { FINCH_PATH_AUTO = 0, FINCH_PATH_SEPARATE = 1, FINCH_PATH_OWNER = 3 } finch_path;

@@ -286,7 +286,6 @@ LaunchParams make_params(const finch_ctx* ctx, const finch_problem* dd, int32_t 
   p.layer_err = reinterpret_cast<int32_t*>(base);
   p.spin_ticks = ctx->layer_wait_ticks;
   p.meet = ctx->meet;
-  p.help_ticks = std::min(finch::kClusterHelpTicks, ctx->layer_wait_ticks);
   return p;
 }
 
@@ -384,6 +383,9 @@ finch_status run_cluster(finch_ctx* ctx, LaunchParams p, const Plan& pl, void* w
   p.row_chunk = pl.cluster_row_chunk;
   p.lds_bytes = static_cast<uint32_t>(pl.cluster_lds);
   p.cluster_slices = pl.cluster_slices;
+  const int64_t slice_blocks = ((pl.n_max + 31) / 32 + pl.cluster_slices - 1) / pl.cluster_slices;
+  p.help_ticks = std::min(finch::kClusterHelpTicks + finch::kClusterHelpTicksPerTile * slice_blocks * (pl.rpad_max / 32),
+                          ctx->layer_wait_ticks);
   p.stats = reinterpret_cast<float2*>(static_cast<char*>(ws) + pl.off_cluster);
   hipError_t e;
   {

@@ -18,8 +18,9 @@
 // a wave issues one every four to five clocks, and 1250 of them stood before the first barrier.
 //
 // Meetings.  A slice's workgroup sets a flag per meeting; the others poll the flags, at most
-// prm.help_ticks in all.  When the time is up (other work keeps some of the workgroups from
-// starting), a workgroup does what is missing ITSELF - the same instructions on the same
+// prm.help_ticks in all: the time spent polling counts, not the time spent working.  When it is
+// up (other work keeps some of the workgroups from starting), a workgroup does what is missing
+// ITSELF - the same instructions on the same
 // inputs, hence the same bits, written to the same places - so every workgroup can finish
 // whatever the others do, and no wait depends on all of them being on the chip at once.
 // A flag is set when it holds the launch's number, generation + 1.  The generation is a
@@ -65,10 +66,11 @@ __device__ __forceinline__ void meet_set(int* flag, int target, int tid) {
 }
 
 // Waits until the flags i < n with i % stride < used all hold `target`; -1, or the first missing
-// one once `deadline` has passed.  Whole workgroup; a barrier at the end.
-__device__ __forceinline__ int meet_wait(const int* flags, int n, int stride, int used, int target, long long deadline,
-                                         int* sh, int tid, int lane) {
-  if (tid < 64) {
+// one once `budget` ticks are used up.  What the wait took is taken from `budget` (wave 0 has
+// it).  Whole workgroup; a barrier at the end.
+__device__ __forceinline__ int meet_wait(const int* flags, int n, int stride, int used, int target, long long& budget,
+                                         int* sh, int lane, int wave) {
+  if (wave == 0) {
     constexpr int kLoads = kMaxClusterGrid / 64;
     bool want[kLoads];
 #pragma unroll
@@ -76,6 +78,7 @@ __device__ __forceinline__ int meet_wait(const int* flags, int n, int stride, in
       const int i = lane + 64 * u;
       want[u] = i < n && i - div_small(i, stride) * stride < used;
     }
+    long long began = -1, waited = 0;
     int missing;
     while (true) {
       missing = -1;
@@ -87,9 +90,14 @@ __device__ __forceinline__ int meet_wait(const int* flags, int n, int stride, in
         const unsigned long long m = __ballot(want[u] && !there[u]);
         if (m) missing = 64 * u + __ffsll(static_cast<long long>(m)) - 1;
       }
-      if (missing < 0 || wall_clock64() > deadline) break;
+      if (missing < 0) break;
+      const long long now = wall_clock64();
+      if (began < 0) began = now;
+      waited = now - began;
+      if (waited >= budget) break;
       __builtin_amdgcn_s_sleep(1);
     }
+    budget = waited < budget ? budget - waited : 0;
     if (lane == 0) *sh = missing;
   }
   __syncthreads();
@@ -246,7 +254,7 @@ __global__ __launch_bounds__(kCluThreads) void cluster_step_bf16(LaunchParams pr
   int gen = agent_load(meet + kMeetGen);  // (looked at when it is needed: it comes from far away)
   int* const stat_flags = meet + kMeetFlags;
   int* const score_flags = stat_flags + kMaxClusterGrid;
-  const long long deadline = wall_clock64() + prm.help_ticks;
+  long long budget = prm.help_ticks;  // how long this workgroup still waits for others
   const finch_problem mine = load_problem(prm.probs + my_p);
   const int N = mine.c + mine.m;
   const float sc = prm.scale_log2;
@@ -411,7 +419,7 @@ __global__ __launch_bounds__(kCluThreads) void cluster_step_bf16(LaunchParams pr
         asm volatile("" : "+v"(gen));
         const int target = uni(gen) + 1;
         meet_set(stat_flags + wp * S + s1, target, tid);
-        s1 = meet_wait(stat_flags + wp * S, used, S, used, target, deadline, sh_miss, tid, lane);
+        s1 = meet_wait(stat_flags + wp * S, used, S, used, target, budget, sh_miss, lane, wave);
         if (s1 < 0) {
           if (!HELD || held == ws) break;
           // others' work has been done in between: this slice's tiles once more
@@ -570,7 +578,7 @@ __global__ __launch_bounds__(kCluThreads) void cluster_step_bf16(LaunchParams pr
     const int nb_mine = (N + 31) >> 5, per_mine = max(1, uni(div_small(nb_mine + S - 1, S)));
     const int used_mine = uni(div_small(nb_mine + per_mine - 1, per_mine));
     if (used_mine == 0) break;
-    const int miss = meet_wait(score_flags + p_first * S, L * S, S, used_mine, uni(gen) + 1, deadline, sh_miss, tid, lane);
+    const int miss = meet_wait(score_flags + p_first * S, L * S, S, used_mine, uni(gen) + 1, budget, sh_miss, lane, wave);
     if (miss < 0) break;
     const int g = div_small(miss, S);
     wp = uni(p_first + g);

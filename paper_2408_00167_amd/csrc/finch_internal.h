@@ -37,8 +37,12 @@ constexpr int kMaxClusterGrid = 256;
 constexpr int kClusterSliceBlocks = 128;
 constexpr int kClusterMaxKeys = 15872;  // what a 512-thread selection holds in registers
 constexpr int kClusterMaxRows = 4096;
-// A workgroup that has waited this long for others in all (100 MHz ticks) does their work itself.
+// A workgroup that has waited for others this long in all (100 MHz ticks) does their work itself:
+// 0.1 ms, and 1 us for every tile of 32 keys x 32 rows of a slice.  Both passes over a tile take
+// 0.22 us (128 channels, 304 tiles: 66 us), so slices that differ in length, or workgroups that
+// start late, do not make the others do work that is being done.
 constexpr int64_t kClusterHelpTicks = 10000;
+constexpr int64_t kClusterHelpTicksPerTile = 100;
 // Most LDS a workgroup of the selection kernels asks for.
 constexpr size_t kSelLdsBytes = 144 * 1024;
 // Rows copied by one workgroup of the compaction kernels.

@@ -96,6 +96,34 @@ def test_helping_over_several_blocks(name, d):
         fin.close()
 
 
+def _fastest(f, repeats=8):
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best = float("inf")
+    for _ in range(repeats):
+        a.record()
+        f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+def test_work_that_is_being_done_is_not_done_twice():
+    """Slices whose passes take longer than the 0.1 ms after which a workgroup that waits in vain
+    helps (here 0.17 ms a pass): nobody is missing, so the launch takes no longer than the kernels
+    per stage do.  0.76 of their time; 1.7 times when the time spent working counted as time waited."""
+    specs = [dict(n_que=256, c=625, m=4375, r=833)] * 85
+    fin = F.Finch(F.FINCH_BF16, 128, 4)
+    batch, _ = H.single_step_case(fin, specs, torch.bfloat16, 128, 4, seed=3)
+    assert _which_scoring_kernels(fin, batch) == {"owner"}
+    shared = _fastest(lambda: fin.step(batch))
+    fin.set_step_path(F.FINCH_PATH_SEPARATE)
+    per_stage = _fastest(lambda: fin.step(batch))
+    print(f"shared {shared * 1e3:.0f} us, per stage {per_stage * 1e3:.0f} us", flush=True)
+    assert shared < 1.25 * per_stage
+    fin.close()
+
+
 def test_replays_of_a_captured_step():
     specs = [dict(n_que=20, c=100, m=600, r=120)] * 8
     fin = F.Finch(F.FINCH_BF16, 128, 4)
