@@ -371,12 +371,33 @@ bool owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n) {
   return static_cast<int64_t>(n) * 100 >= rounds * cu * 85;
 }
 
+// Whether one kernel per stage is the faster launch of a batch that several workgroups per
+// problem could take: when its two passes cut the problems into as many slices (of 2400 keys) and
+// put them on the chip in one round, the meetings save nothing, and a tile costs less there
+// (a moving reference per row instead of every block's maximum).  Measured, AUTO's launch against
+// kernels per stage on 48 to 128 problems: scores alone 1.05 to 1.3 times the time at 64 channels
+// and up to 256 rows, 1.03 to 1.14 at 128; whole steps 1.0 to 1.25 and 0.98 to 1.1.  The other way
+// round: 128 channels with more than 256 rows (the passes per stage hold one workgroup of 512 rows
+// a compute unit) 0.85 to 1.0; layer groups, whose sums and selection per stage have one workgroup a
+// layer, 0.67 to 0.95, except 64 channels with more than 256 rows, 1.0 to 1.18.  Scores alone at 64
+// channels: also with three quarters of the slices (1.0 to 1.11).
+bool stages_faster(const finch_ctx* ctx, const Plan& pl, int32_t n, bool stages) {
+  const int64_t dies = 8, per_die = std::max<int64_t>(1, ctx->n_cu / dies);
+  const int64_t rounds = ((n + dies - 1) / dies * pl.tiles_max + per_die - 1) / per_die;
+  const bool narrow = ctx->cfg.head_dim == 64, many_rows = pl.rpad_max > 256;
+  const int64_t mine = pl.cluster_slices * rounds, theirs = pl.tiles_max;
+  if (stages && ctx->layer_group > 1) return narrow && many_rows && mine <= theirs;
+  if (!narrow) return !many_rows && mine <= theirs;
+  return stages ? mine <= theirs : 3 * mine <= 4 * theirs;
+}
+
 // Several workgroups per problem in one launch: for batches that leave at least half of the
 // chip without a workgroup otherwise (two slices a problem and more).  A caller who has set
 // the slices of the two-pass kernels wants those.  Slots by score rank are not built there.
-bool cluster_wanted(const finch_ctx* ctx, const Plan& pl, bool stages) {
+bool cluster_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n, bool stages) {
   return pl.cluster_slices > 1 && ctx->step_path == FINCH_PATH_AUTO && ctx->slice_keys == finch::kDefaultSliceKeys &&
-         (!stages || (ctx->repos.order == FINCH_ORDER_ASCENDING && ctx->layer_group <= finch::kOwnerMaxLayer));
+         (!stages || (ctx->repos.order == FINCH_ORDER_ASCENDING && ctx->layer_group <= finch::kOwnerMaxLayer)) &&
+         !stages_faster(ctx, pl, n, stages);
 }
 
 finch_status run_cluster(finch_ctx* ctx, LaunchParams p, const Plan& pl, void* ws, int stages, hipStream_t s) {
@@ -417,7 +438,7 @@ finch_status run_score(finch_ctx* ctx, const LaunchParams& p, const Plan& pl, vo
   const int d = ctx->cfg.head_dim;
   const bool bf16 = ctx->cfg.dtype == FINCH_BF16;
   if (owner_wanted(ctx, pl, p.n_problems)) return run_owner(ctx, p, pl, /*stages=*/0, s);
-  if (cluster_wanted(ctx, pl, false)) return run_cluster(ctx, p, pl, ws, /*stages=*/0, s);
+  if (cluster_wanted(ctx, pl, p.n_problems, false)) return run_cluster(ctx, p, pl, ws, /*stages=*/0, s);
   if (ctx->step_path == FINCH_PATH_OWNER || pl.has_doc) return FINCH_ERR_UNSUPPORTED;
   {
     ProfScope ps(ctx, FINCH_KERNEL_ROWSTATS, s);
@@ -606,7 +627,7 @@ finch_status step_planned(finch_ctx* ctx, const finch_problem* host_desc, const 
   hipStream_t s = static_cast<hipStream_t>(stream);
   // (with layer groups the status word starts every call at zero: these two see to it themselves)
   if (pl.tiles_max > 0 && owner_wanted(ctx, pl, n)) return run_owner(ctx, p, pl, /*stages=*/1, s);
-  if (cluster_wanted(ctx, pl, true)) return run_cluster(ctx, p, pl, ws, /*stages=*/1, s);
+  if (cluster_wanted(ctx, pl, n, true)) return run_cluster(ctx, p, pl, ws, /*stages=*/1, s);
   if (ctx->layer_group > 1) {
     const hipError_t e = finch::launch_zero_words(nullptr, 0, p.layer_err, s);
     if (e != hipSuccess) return hip_fail(ctx, e);

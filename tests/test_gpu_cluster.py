@@ -8,6 +8,7 @@ import torch
 
 import paper_2408_00167_amd as F
 from tests import gpu_harness as H
+from tests.test_gpu_layer import validate_layers
 from tests.test_gpu_parity import _which_scoring_kernels
 
 pytestmark = pytest.mark.gpu
@@ -94,6 +95,46 @@ def test_helping_over_several_blocks(name, d):
             for a, b in zip(got, want):
                 assert torch.equal(a, b), (name, d, ticks)
         fin.close()
+
+
+def _kernels_of(fin, call, batch):
+    F.finch_profile(fin.ctx, True)
+    call(batch)
+    torch.cuda.synchronize()
+    prof = F.finch_profile_read(fin.ctx)
+    F.finch_profile(fin.ctx, False)
+    return {k for k, v in prof.items() if v["launches"]}
+
+
+@pytest.mark.parametrize("d,layer,rows,problems,n,taken", [
+    (64, 1, 32, 128, 3599, True), (64, 1, 32, 128, 3600, False), (128, 1, 256, 128, 3600, False),
+    (128, 1, 288, 128, 3600, True), (64, 8, 256, 128, 3600, True), (64, 8, 288, 128, 3600, False),
+    (64, 1, 32, 88, 6000, True), (64, 1, 32, 80, 6000, False)])
+def test_batches_at_the_line_to_one_kernel_per_stage(d, layer, rows, problems, n, taken):
+    """Where the kernels per stage would put as many slices on the chip in one round they take over
+    (128 problems: from 3600 candidates); both sides of the line against the oracle."""
+    specs = [dict(n_que=rows, c=100, m=n - 100, r=77)] * problems
+    fin = F.Finch(F.FINCH_BF16, d, 1)
+    F.finch_set_option(fin.ctx, F.FINCH_OPT_LAYER_GROUP, layer)
+    batch, ts = H.single_step_case(fin, specs, torch.bfloat16, d, 1, seed=77)
+    assert (_kernels_of(fin, fin.step, batch) == {"owner"}) == taken
+    if layer == 1:
+        H.validate_single_step(ts[::9], "line")
+    else:
+        validate_layers(ts[:2 * layer], layer, "line")
+    fin.close()
+
+
+def test_scores_alone_take_the_line_earlier():
+    fin = F.Finch(F.FINCH_BF16, 64, 1)
+    for n, scores_taken in ((5999, True), (6000, False)):  # 64 problems: four slices here, three per stage
+        batch, ts = H.single_step_case(fin, [dict(n_que=32, c=100, m=n - 100, r=77)] * 64, torch.bfloat16, 64, 1, seed=78)
+        assert (_kernels_of(fin, fin.score, batch) == {"owner"}) == scores_taken
+        fin.topk(batch)
+        fin.compact(batch)
+        H.validate_single_step(ts[::9], f"scores alone n={n}")
+        assert _kernels_of(fin, fin.step, batch) == {"owner"}
+    fin.close()
 
 
 def _fastest(f, repeats=8):
