@@ -243,6 +243,10 @@ __global__ __launch_bounds__(kCluThreads) void cluster_step_bf16(LaunchParams pr
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const int t = lane & 31, h = lane >> 5;
   constexpr int kStride = D * 2 + 16;
+  // (what the launch was called with, in one go: left to itself the compiler fetches some of it in
+  // turn before the descriptor, each time with a wait)
+  asm volatile("" ::"s"(prm.probs), "s"(prm.n_problems), "s"(prm.group), "s"(prm.rpad_max), "s"(prm.row_chunk), "s"(prm.layer_group),
+               "s"(prm.cluster_slices), "s"(prm.meet), "s"(prm.help_ticks), "s"(prm.stats), "s"(prm.scale_log2), "s"(stages));
   const int S = prm.cluster_slices, RC = prm.row_chunk;
   const int L = stages ? prm.layer_group : 1;
   // a problem's workgroups (and a layer's) stand together on one of the chip's dies where the
@@ -269,8 +273,7 @@ __global__ __launch_bounds__(kCluThreads) void cluster_step_bf16(LaunchParams pr
   // run out - one that is missing.
   finch_problem pb = mine;
   int wp = my_p, ws = my_s;
-  const void* staged_q = nullptr;  // prompt rows that are in LDS
-  int staged_row0 = 0;
+  int staged_row0 = -1;  // first of the prompt rows of `pb` that are in LDS (-1: none)
   while (true) {
     const int n = pb.c + pb.m, nb = (n + 31) >> 5, R = prm.group * pb.n_que;
     const int per = max(1, uni(div_small(nb + S - 1, S)));
@@ -279,11 +282,10 @@ __global__ __launch_bounds__(kCluThreads) void cluster_step_bf16(LaunchParams pr
     unsigned long long* const stats =
         reinterpret_cast<unsigned long long*>(prm.stats) + static_cast<size_t>(wp) * S * prm.rpad_max;
     auto stage = [&](int row0, int rows) {
-      if (staged_q == pb.q && staged_row0 == row0) return;
+      if (staged_row0 == row0) return;
       int own_tid = tid;  // (opaque: the addresses are not worth keeping through the loops)
       asm volatile("" : "+v"(own_tid));
       stage_rows<D>(pb.q, R, row0, rows >> 5, lds_q, own_tid);
-      staged_q = pb.q;
       staged_row0 = row0;
     };
     if (ws < used) {
@@ -584,6 +586,7 @@ __global__ __launch_bounds__(kCluThreads) void cluster_step_bf16(LaunchParams pr
     wp = uni(p_first + g);
     ws = uni(miss - g * S);
     pb = load_problem(prm.probs + wp);
+    staged_row0 = -1;  // (its rows may lie at the same place and be more or fewer)
   }
 
   // This workgroup waits for nobody any more.  The last one to come here advances the

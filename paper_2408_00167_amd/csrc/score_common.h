@@ -54,8 +54,8 @@ __device__ __forceinline__ finch_problem load_problem(const finch_problem* p) {
 #pragma unroll
   for (unsigned i = 0; i < sizeof(finch_problem) / 8; ++i) raw.w[i] = src[i];
   static_assert(sizeof(finch_problem) / 8 == 14, "all of them are named below");
-  asm volatile("" ::"s"(raw.w[0]), "s"(raw.w[1]), "s"(raw.w[2]), "s"(raw.w[3]), "s"(raw.w[4]), "s"(raw.w[5]), "s"(raw.w[6]),
-               "s"(raw.w[7]), "s"(raw.w[8]), "s"(raw.w[9]), "s"(raw.w[10]), "s"(raw.w[11]), "s"(raw.w[12]), "s"(raw.w[13]));
+  asm volatile("" : "+s"(raw.w[0]), "+s"(raw.w[1]), "+s"(raw.w[2]), "+s"(raw.w[3]), "+s"(raw.w[4]), "+s"(raw.w[5]), "+s"(raw.w[6]),
+               "+s"(raw.w[7]), "+s"(raw.w[8]), "+s"(raw.w[9]), "+s"(raw.w[10]), "+s"(raw.w[11]), "+s"(raw.w[12]), "+s"(raw.w[13]));
   return __builtin_bit_cast(finch_problem, raw);
 }
 

@@ -97,6 +97,31 @@ def test_helping_over_several_blocks(name, d):
         fin.close()
 
 
+def test_helping_where_heads_share_prompt_rows():
+    """Problems of a layer with the same query pointer and different numbers of prompt rows: a
+    workgroup that helps must not go on with the rows it has staged for the shorter prompt."""
+    want = None
+    for ticks in (20_000_000, 0, 0, 0):
+        fin = F.Finch(F.FINCH_BF16, 128, 4)
+        F.finch_set_option(fin.ctx, F.FINCH_OPT_LAYER_GROUP, 4)
+        F.finch_set_option(fin.ctx, F.FINCH_OPT_LAYER_WAIT_TICKS, ticks)
+        _, ts = H.single_step_case(fin, [dict(n_que=40 - p % 4, c=64, m=700, r=150) for p in range(8)], torch.bfloat16,
+                                   128, 4, seed=55)
+        for p, t in enumerate(ts):
+            t["q"] = ts[p - p % 4]["q"][:4 * t["n_que"]]
+        batch = F.Batch([dict(t, scores=t["scores"][:-1], idx=t["idx"][:-1], k_out=t["k_out"][:-1], v_out=t["v_out"][:-1])
+                         for t in ts])
+        for _ in range(4):
+            fin.step(batch)
+            got = [t[k].clone() for t in ts for k in ("scores", "idx", "k_out", "v_out")]
+            if want is None:
+                want = got
+                validate_layers(ts, 4, "shared rows")
+            for a, b in zip(got, want):
+                assert torch.equal(a, b), ticks
+        fin.close()
+
+
 def _kernels_of(fin, call, batch):
     F.finch_profile(fin.ctx, True)
     call(batch)
