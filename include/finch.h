@@ -19,11 +19,16 @@
  * the caller has synchronised the stream.  Results are bit-identical run to run.
  *
  * Threads and streams: one context is for one host thread and one stream at a time (it
- * holds settings, the last HIP error, the profiling pool and the memo of finch_loop's
- * checks, none of them synchronised).  Concurrent use - several host threads, or work in
+ * holds settings, the last HIP error, the profiling pool, the memo of finch_loop's
+ * checks, and device words in which the workgroups of a launch meet, none of them
+ * synchronised).  Concurrent use - several host threads, or work in
  * flight on several streams - takes one context per thread or stream, each with its own
  * workspace.  Calls that share a workspace, or descriptors whose outputs overlap, must
- * be ordered by the caller (same stream, or events).
+ * be ordered by the caller (same stream, or events).  Calls captured into a HIP graph use
+ * nothing of the context: the graph may be replayed after finch_destroy and beside
+ * other work, as long as its workspace, descriptors and buffers live and are its own.
+ * Contexts may be created and destroyed while a stream is being captured; finch_destroy
+ * waits for the work in flight on the device.
  *
  * Errors: every function returns a finch_status.  Argument errors are detected on
  * the host before anything is launched.  Non-finite inputs are undefined
@@ -185,7 +190,8 @@ finch_status finch_step(finch_ctx* ctx, const finch_problem* host_desc,
  * log-sum-exps, scores of descriptors whose `scores` is NULL, layer sums) is a
  * file-scope device array inside the library, finch_static_scratch_bytes() = 16 MiB on
  * every GPU the library is used on, held until the process ends.  A batch that needs
- * more (finch_workspace_size tells) is refused with FINCH_ERR_CAPACITY and a message on
+ * more (of what finch_workspace_size tells it can do without the part for launches that
+ * share problems between workgroups, up to 8 MiB) is refused with FINCH_ERR_CAPACITY and a message on
  * stderr; nothing is launched then.  The call allocates nothing and frees nothing.
  * All calls on one GPU share that GPU's array, which keeps the last call's contents
  * (nothing in it has to start at zero): calls that overlap in time on one GPU - two

@@ -29,8 +29,9 @@ struct finch_ctx {
   finch_reposition repos;  // {OFF, ASCENDING}: plain copies
   int layer_group;         // > 1: runs of that many problems share one selection
   int64_t layer_wait_ticks;  // bound of a workgroup's wait for its layer, 100 MHz ticks
-  int32_t* meet;             // meeting words of the launches with several workgroups per problem
+  int32_t* meet;             // meeting words of this context's launches with several workgroups per problem
   void* static_scratch;    // this device's copy of the file-scope scratch array (finch_step_static)
+  int32_t* static_meet;    // and of the meeting words that go with it
   // finch_loop: fingerprint of the last descriptor set whose slots were found free of
   // overlaps (the check is repeated only when the descriptors change)
   uint64_t loop_checked_hash;
@@ -42,6 +43,7 @@ struct finch_ctx {
 // holds its own copy of the array, at its own address, until the process ends.
 constexpr size_t kStaticScratchBytes = size_t{16} << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) int32_t scratch_meet[finch::kClusterMeetWords];
 
 namespace {
 
@@ -65,7 +67,9 @@ struct Plan {
   int32_t cluster_slices = 0, cluster_row_chunk = 32;
   size_t cluster_lds = 0;
   size_t off_cluster = 0;   // statistics of its slices, behind everything else
-  size_t base_total = 0;    // workspace without that part
+  size_t off_meet = 0;      // meeting words of a launch that is being captured, behind those
+  size_t base_total = 0;    // workspace without either
+  size_t static_total = 0;  // and with the statistics only (finch_step_static brings the words)
   size_t lds_bytes = 0;
   size_t off_stats = 0, off_lse = 0, off_scores = 0, off_layer = 0, off_sync = 0, total = 0;
   int32_t sync_words = 0;  // counters of the layer runs (workspace word 0 is the status word)
@@ -193,6 +197,9 @@ finch_status make_plan(const finch_ctx* ctx, const finch_problem* hd, int32_t n_
   // (room for a full grid of slices, so that a batch of fewer or smaller problems needs no more)
   if (ctx->cfg.dtype == FINCH_BF16 && n_max > 0)
     off += static_cast<size_t>(finch::kMaxClusterGrid) * std::min(pl.rpad_max, finch::kClusterMaxRows) * sizeof(float2);
+  pl.static_total = off;
+  pl.off_meet = off;
+  if (ctx->cfg.dtype == FINCH_BF16 && n_max > 0) off += sizeof(int32_t) * finch::kClusterMeetWords;
   pl.total = off;
   plan_cluster(ctx, n, pl);
   return FINCH_OK;
@@ -285,7 +292,6 @@ LaunchParams make_params(const finch_ctx* ctx, const finch_problem* dd, int32_t 
   p.layer_sync = base ? reinterpret_cast<int32_t*>(base + pl.off_sync) : nullptr;
   p.layer_err = reinterpret_cast<int32_t*>(base);
   p.spin_ticks = ctx->layer_wait_ticks;
-  p.meet = ctx->meet;
   return p;
 }
 
@@ -294,26 +300,64 @@ finch_status hip_fail(finch_ctx* ctx, hipError_t e) {
   return FINCH_ERR_HIP;
 }
 
-// Device address of `scratch` on each GPU.  In host code the array's name only stands
-// for the symbol; the address kernels can use comes from hipGetSymbolAddress, asked once
-// per device with that device current.
+// Device addresses of `scratch` and `scratch_meet` on each GPU.  In host code an array's name
+// only stands for the symbol; the address kernels can use comes from hipGetSymbolAddress, asked
+// once per device with that device current.
 constexpr int kMaxDevices = 64;
-void* g_scratch_addr[kMaxDevices];
-std::mutex g_scratch_mutex;
+struct StaticAddresses {
+  void* scratch;
+  void* meet;
+  hipStream_t stream;  // for what is done while a context is made; kept (one costs 0.1 ms to create)
+};
+StaticAddresses g_static_addr[kMaxDevices];
+std::mutex g_static_mutex;
 
-hipError_t static_scratch_address(int device, void** out) {
-  *out = nullptr;
+hipError_t static_addresses(int device, StaticAddresses* out) {
   if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;
-  std::lock_guard<std::mutex> lock(g_scratch_mutex);
-  if (!g_scratch_addr[device]) {
-    void* p = nullptr;
-    const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+  std::lock_guard<std::mutex> lock(g_static_mutex);
+  if (!g_static_addr[device].scratch) {
+    StaticAddresses a = {nullptr, nullptr, nullptr};
+    hipError_t e = hipGetSymbolAddress(&a.scratch, HIP_SYMBOL(scratch));
+    if (e == hipSuccess) e = hipGetSymbolAddress(&a.meet, HIP_SYMBOL(scratch_meet));
+    if (e == hipSuccess && (!a.scratch || !a.meet)) e = hipErrorInvalidSymbol;
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&a.stream, hipStreamNonBlocking);
     if (e != hipSuccess) return e;
-    if (!p) return hipErrorInvalidSymbol;
-    g_scratch_addr[device] = p;
+    g_static_addr[device] = a;
   }
-  *out = g_scratch_addr[device];
+  *out = g_static_addr[device];
   return hipSuccess;
+}
+
+// While one of these lives, what this thread allocates and frees does not break a capture that
+// some stream of the process is going through (the default mode forbids both meanwhile).
+struct CaptureUnaffected {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  CaptureUnaffected() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~CaptureUnaffected() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// Meeting words for the eager launches of a context, cleared (they keep themselves in order from
+// then on).  On a stream of the library's: the null stream would wait for others.
+hipError_t make_meet(int32_t** out, hipStream_t s) {
+  const CaptureUnaffected guard;
+  hipError_t e = hipMalloc(reinterpret_cast<void**>(out), sizeof(int32_t) * finch::kClusterMeetWords);
+  if (e == hipSuccess) e = finch::launch_zero_words(*out, finch::kClusterMeetWords, nullptr, s);
+  return e == hipSuccess ? hipStreamSynchronize(s) : e;
+}
+void free_meet(int32_t* meet) {  // (waits for the device: launches may still be using them)
+  if (!meet) return;
+  const CaptureUnaffected guard;
+  (void)hipFree(meet);
+}
+
+// Whether what is launched on `s` now is recorded into a graph (or cannot be told).
+bool being_captured(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &status) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return status != hipStreamCaptureStatusNone;
 }
 
 constexpr int kProfPairs = 8192;
@@ -400,7 +444,21 @@ bool cluster_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n, bool stages
          !stages_faster(ctx, pl, n, stages);
 }
 
+// A graph outlives the context it was captured with, and several of them can be replayed side by
+// side: a captured launch must use the caller's memory only.  Its meeting words are in the
+// workspace and cleared by a launch in front of it; an eager launch uses the context's, which
+// need none (15 to 23 us a step, 3 more with it).  finch_step_static's calls are in order on a
+// GPU by contract and use the words beside its scratch, captured or not.
 finch_status run_cluster(finch_ctx* ctx, LaunchParams p, const Plan& pl, void* ws, int stages, hipStream_t s) {
+  if (ws == ctx->static_scratch) {
+    p.meet = ctx->static_meet;
+  } else if (being_captured(s)) {
+    p.meet = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + pl.off_meet);
+    const hipError_t e = finch::launch_zero_words(p.meet, finch::kClusterMeetWords, nullptr, s);
+    if (e != hipSuccess) return hip_fail(ctx, e);
+  } else {
+    p.meet = ctx->meet;
+  }
   p.row_chunk = pl.cluster_row_chunk;
   p.lds_bytes = static_cast<uint32_t>(pl.cluster_lds);
   p.cluster_slices = pl.cluster_slices;
@@ -670,11 +728,17 @@ finch_status finch_create(const finch_config* cfg, finch_ctx** out) {
   ctx->repos.order = FINCH_ORDER_ASCENDING;
   ctx->repos.base = 10000.0;
   ctx->static_scratch = nullptr;
+  ctx->static_meet = nullptr;
   ctx->loop_checked = false;
   ctx->loop_checked_hash = 0;
   ctx->meet = nullptr;
   hipError_t e = hipGetDevice(&ctx->device);
-  if (e == hipSuccess) e = static_scratch_address(ctx->device, &ctx->static_scratch);
+  StaticAddresses a = {nullptr, nullptr, nullptr};
+  if (e == hipSuccess) {
+    e = static_addresses(ctx->device, &a);
+    ctx->static_scratch = a.scratch;
+    ctx->static_meet = static_cast<int32_t*>(a.meet);
+  }
   if (e == hipSuccess) {
     int v = 0;
     e = hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device);
@@ -691,12 +755,7 @@ finch_status finch_create(const finch_config* cfg, finch_ctx** out) {
   if (e == hipSuccess && cfg->dtype == FINCH_BF16) e = finch::set_max_lds_owner_doc(ctx->max_lds);
   if (e == hipSuccess && cfg->dtype == FINCH_F32) e = finch::set_max_lds_owner_f32(ctx->max_lds);
   if (e == hipSuccess && cfg->dtype == FINCH_BF16) e = finch::set_max_lds_cluster(ctx->max_lds);
-  if (e == hipSuccess && cfg->dtype == FINCH_BF16) {
-    // cleared once: the launches keep them in order themselves
-    e = hipMalloc(reinterpret_cast<void**>(&ctx->meet), finch::cluster_meet_bytes());
-    if (e == hipSuccess) e = hipMemset(ctx->meet, 0, finch::cluster_meet_bytes());
-    if (e == hipSuccess) e = hipDeviceSynchronize();
-  }
+  if (e == hipSuccess && cfg->dtype == FINCH_BF16) e = make_meet(&ctx->meet, a.stream);
   if (e == hipSuccess) e = finch::set_max_lds_select(ctx->max_lds);
   // the re-positioning kernel also has a little static LDS
   if (e == hipSuccess) e = finch::set_max_lds_reposition(ctx->max_lds - 1024);
@@ -705,7 +764,7 @@ finch_status finch_create(const finch_config* cfg, finch_ctx** out) {
     std::fprintf(stderr, "finch_create: HIP error %d (%s)\n", static_cast<int>(e),
                  hipGetErrorString(e));
     (void)hipGetLastError();
-    if (ctx->meet) (void)hipFree(ctx->meet);
+    free_meet(ctx->meet);
     delete ctx;
     return FINCH_ERR_HIP;
   }
@@ -716,7 +775,7 @@ finch_status finch_create(const finch_config* cfg, finch_ctx** out) {
 finch_status finch_destroy(finch_ctx* ctx) {
   if (ctx) {
     (void)finch_profile(ctx, 0);
-    if (ctx->meet) (void)hipFree(ctx->meet);  // (waits for the device)
+    free_meet(ctx->meet);
   }
   delete ctx;
   return FINCH_OK;
@@ -906,6 +965,7 @@ finch_status finch_step_static(finch_ctx* ctx, const finch_problem* host_desc,
     return FINCH_ERR_CAPACITY;
   }
   if (!ctx->static_scratch) return FINCH_ERR_WORKSPACE;
+  pl.total = pl.static_total;
   if (pl.total > kStaticScratchBytes) {  // no room for slices of a problem on several workgroups
     pl.cluster_slices = 0;
     pl.total = pl.base_total;

@@ -25,7 +25,9 @@
 // whatever the others do, and no wait depends on all of them being on the chip at once.
 // A flag is set when it holds the launch's number, generation + 1.  The generation is a
 // word of memory that the last workgroup to be through with its waits advances, so a launch
-// needs no cleared memory and a captured one can be replayed.
+// leaves the words ready for the next one on the same stream and nothing has to be cleared
+// in between (a launch that clears them costs 3 us of a step's 15 to 23).  Two launches that
+// overlap in time need words of their own; api.hip sees to that.
 //
 // Data that crosses workgroups goes through agent-scope relaxed atomics (past the caches
 // that are not shared), and is complete before the flag: each thread waits for its own
@@ -42,6 +44,7 @@ constexpr int kCluWaves = kOwnWaves;
 // words of the meeting area (LaunchParams::meet)
 constexpr int kMeetGen = 0, kMeetExit = 16, kMeetExitOf = 32;   // (one word per 64-byte line, except:)
 constexpr int kMeetFlags = kMeetExitOf + 16 * kMaxClusterGrid;  // [2][kMaxClusterGrid]
+static_assert(kMeetFlags + 2 * kMaxClusterGrid == kClusterMeetWords, "size of the meeting area");
 
 template <typename T>
 __device__ __forceinline__ T agent_load(const T* p) {
@@ -673,8 +676,6 @@ bool with_cluster_kernel(int head_dim, bool rot, bool held, F f) {
 }
 
 }  // namespace
-
-size_t cluster_meet_bytes() { return sizeof(int) * (kMeetFlags + 2 * kMaxClusterGrid); }
 
 // LDS of a launch: the passes' (row_chunk staged rows, slices of at most slice_blocks key
 // blocks) or the selection's (n_max candidates, r_max kept), whichever is more.

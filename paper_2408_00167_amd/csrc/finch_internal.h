@@ -37,6 +37,8 @@ constexpr int kMaxClusterGrid = 256;
 constexpr int kClusterSliceBlocks = 128;
 constexpr int kClusterMaxKeys = 15872;  // what a 512-thread selection holds in registers
 constexpr int kClusterMaxRows = 4096;
+// Words in which the workgroups of such a launch meet.
+constexpr int kClusterMeetWords = 32 + 18 * kMaxClusterGrid;
 // A workgroup that has waited for others this long in all (100 MHz ticks) does their work itself:
 // 0.1 ms, and 1 us for every tile of 32 keys x 32 rows of a slice.  Both passes over a tile take
 // 0.22 us (128 channels, 304 tiles: 66 us), so slices that differ in length, or workgroups that
@@ -81,8 +83,8 @@ struct LaunchParams {
   int32_t layer_group;         // L (1: every problem selects for itself)
   int32_t* layer_sync;         // [2 * runs]
   int32_t* layer_err;          // one word behind them
-  // several workgroups per problem (cluster_bf16.hip): slices of a problem, the meeting words of
-  // the context, and how long a workgroup waits before it helps
+  // several workgroups per problem (cluster_bf16.hip): slices of a problem, the meeting words (what
+  // a launch that has ended has left in them, or zeros), and how long a workgroup waits before it helps
   int32_t cluster_slices;
   int32_t* meet;
   int64_t help_ticks;
@@ -116,7 +118,6 @@ hipError_t launch_owner_loop_f32(int head_dim, const LaunchParams& p, const int*
                                  int n_slots, hipStream_t s);
 hipError_t set_max_lds_owner_f32(size_t bytes);
 // several workgroups per problem, one launch
-size_t cluster_meet_bytes();
 size_t cluster_lds_bytes(int head_dim, int row_chunk, int slice_blocks, int n_max, int r_max);
 hipError_t launch_cluster_bf16(int head_dim, const LaunchParams& p, int n_max, int stages, hipStream_t s);
 hipError_t set_max_lds_cluster(size_t bytes);

@@ -190,6 +190,108 @@ def test_work_that_is_being_done_is_not_done_twice():
     fin.close()
 
 
+OUT = ("scores", "idx", "k_out", "v_out")
+
+
+def _clobber(ts):
+    for t in ts:
+        t["scores"][:-1].fill_(-6.0)
+        t["idx"][:-1].fill_(-7)
+        t["k_out"][:-1].fill_(7.0)
+        t["v_out"][:-1].fill_(7.0)
+
+
+@pytest.mark.parametrize("static", [False, True])
+def test_graphs_outlive_their_context(static):
+    """A captured step uses nothing of its context: replays after the context is gone, with other
+    contexts made and used in between, give the eager results."""
+    specs = [dict(n_que=20 + p, c=100, m=600 + 40 * p, r=120) for p in range(8)]
+    fin = F.Finch(F.FINCH_BF16, 128, 4)
+    batch, ts = H.single_step_case(fin, specs, torch.bfloat16, 128, 4, seed=16)
+    call = fin.step_static if static else fin.step
+    call(batch)
+    H.validate_single_step(ts, "eager")
+    want = [t[k].clone() for t in ts for k in OUT]
+    ws = fin.ws  # (the workspace stays with the graph)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call(batch)
+    fin.close()
+    del fin, call
+    others = []
+    for i in range(4):
+        others.append(F.Finch(F.FINCH_BF16, 64, 2))
+        b2, t2 = H.single_step_case(others[-1], specs, torch.bfloat16, 64, 2, seed=17 + i)
+        _clobber(ts)
+        g.replay()
+        others[-1].step(b2)  # eager work of the program's own between the replays
+        if i == 2:
+            others.pop(0).close()
+        torch.cuda.synchronize()
+        for a, b in zip([t[k] for t in ts for k in OUT], want):
+            assert torch.equal(a, b), i
+        H.validate_single_step(t2, f"between {i}")
+    del ws
+
+
+def test_graphs_of_one_context_side_by_side():
+    """Two captured steps of one context, each with a workspace of its own, replayed on two streams
+    at once and beside eager steps of the context."""
+    fin = F.Finch(F.FINCH_BF16, 128, 4)
+    cases, graphs, spaces = [], [], []
+    for i in range(3):
+        specs = [dict(n_que=24, c=50 * i, m=900 + 64 * i, r=130 + i)] * 8
+        cases.append(H.single_step_case(fin, specs, torch.bfloat16, 128, 4, seed=60 + i))
+    for batch, ts in cases:
+        fin.step(batch)
+        H.validate_single_step(ts, "eager")
+    want = [[t[k].clone() for t in ts for k in OUT] for _, ts in cases]
+    for batch, _ in cases[:2]:
+        need = F.finch_workspace_size(fin.ctx, batch.host, batch.n)
+        spaces.append(torch.empty(need, dtype=torch.uint8, device="cuda"))
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            F.finch_step(fin.ctx, batch.host, batch.dev_ptr, batch.n, spaces[-1].data_ptr(), need,
+                         torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for round_ in range(5):
+        for _, ts in cases:
+            _clobber(ts)
+        torch.cuda.synchronize()
+        for _ in range(10):
+            for s, g in zip(streams, graphs):
+                with torch.cuda.stream(s):
+                    g.replay()
+            fin.step(cases[2][0])
+        torch.cuda.synchronize()
+        for (_, ts), w in zip(cases, want):
+            for a, b in zip([t[k] for t in ts for k in OUT], w):
+                assert torch.equal(a, b), round_
+    fin.close()
+
+
+def test_contexts_come_and_go_during_a_capture():
+    specs = [dict(n_que=20, c=100, m=600, r=120)] * 8
+    gone = F.Finch(F.FINCH_BF16, 128, 4)
+    batch, ts = H.single_step_case(gone, specs, torch.bfloat16, 128, 4, seed=18)
+    gone.step(batch)
+    H.validate_single_step(ts, "eager")
+    want = [t[k].clone() for t in ts for k in OUT]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        gone.close()
+        fin = F.Finch(F.FINCH_BF16, 128, 4)
+        fin.step_static(batch)
+        fin.close()
+    for i in range(3):
+        _clobber(ts)
+        g.replay()
+        torch.cuda.synchronize()
+        for a, b in zip([t[k] for t in ts for k in OUT], want):
+            assert torch.equal(a, b), i
+
+
 def test_replays_of_a_captured_step():
     specs = [dict(n_que=20, c=100, m=600, r=120)] * 8
     fin = F.Finch(F.FINCH_BF16, 128, 4)
