@@ -167,6 +167,7 @@ finch_status make_plan(const finch_ctx* ctx, const finch_problem* hd, int32_t n_
   if (gb * n >= (int64_t{1} << 31)) return FINCH_ERR_CAPACITY;
   if (ctx->cfg.dtype == FINCH_BF16 && n_max > 0) {
     int orc = pl.rpad_max < finch::kOwnerMaxRowChunk ? pl.rpad_max : finch::kOwnerMaxRowChunk;
+    if (orc < 32) orc = 32;  // (no rows at all: document rows only, and no chunk)
     while (orc > 32 && finch::owner_lds_bytes(ctx->cfg.head_dim, orc) > ctx->max_lds) orc -= 32;
     pl.own_row_chunk = orc;
     pl.own_lds = finch::owner_lds_bytes(ctx->cfg.head_dim, orc);

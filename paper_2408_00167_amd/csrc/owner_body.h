@@ -260,18 +260,27 @@ __device__ __forceinline__ unsigned* own_sel_keys(char* sel, size_t sel_bytes, s
   return reinterpret_cast<unsigned*>(sel + off);
 }
 
+// Scores of a step without any row (document rows only, and no chunk): empty sums.  Whole
+// workgroup; a barrier at the end.
+__device__ __forceinline__ void own_no_rows(float* scores, unsigned* lkeys, int N, int tid) {
+  for (int i = tid; i < N; i += kOwnThreads) {
+    __hip_atomic_store((FINCH_GLOBAL float*)scores + i, 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lkeys) lkeys[i] = order_key(0.f);
+  }
+  __syncthreads();
+}
+
 // The rest of a step once this workgroup's scores are in memory (and a barrier has been
 // passed since): top-r (Method: t = top-r(A_agg, r); with `layered` on the sum over the
 // layer's heads) and compaction (Method: Managing the Cache) of rows of SEGS 16-byte
 // pieces with E elements each.  `sel` is LDS scratch of sel_bytes (>= sizeof(SelLds) +
 // kOwnerSelectBytes); `dst` the scores of this problem; `lkeys` what own_sel_keys said, with
-// the order keys of these scores in it already unless `layered` or keys_staged is false.
+// the order keys of these scores in it already (not those of the layer's sum).
 template <int SEGS, int E, bool ROT>
 __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const finch_problem& pb, int slot, int N,
                                                 FINCH_GLOBAL float* dst, char* sel, size_t sel_bytes,
-                                                unsigned* lkeys, bool keys_staged,
-                                                const finch_problem* step_probs, int epoch, bool layered,
-                                                int* sync_words, int tid) {
+                                                unsigned* lkeys, const finch_problem* step_probs, int epoch,
+                                                bool layered, int* sync_words, int tid) {
   const int lane = tid & 63, wave = tid >> 6;
   const int L = prm.layer_group;
   FINCH_PHASE_BEGIN();
@@ -324,9 +333,8 @@ __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const f
     const LayerScores<kSelMaxLayer> layer_sum = {fl->layer_src, L};
     const OneScoreVector own = {dst};
     if (lkeys) {  // (then there is room for the indices as well)
-      if (layered || !keys_staged) {
-        if (layered) sel_stage_layer_keys<kOwnThreads>(fl->layer_src, L, N, lkeys, tid);
-        else sel_stage_keys<kOwnThreads>(own, N, lkeys, tid);
+      if (layered) {
+        sel_stage_layer_keys<kOwnThreads>(fl->layer_src, L, N, lkeys, tid);
         __syncthreads();
       }
       select_keys_any<kOwnThreads, true>(lkeys, N, r, gidx, lidx, fl, tid, lane, wave);
@@ -661,14 +669,14 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     __syncthreads();  // scores of this row chunk are out; LDS may be restaged
     FINCH_PHASE(5);
   }
+  if (DOC && n_chunks == 0) own_no_rows(gscores, lkeys, N, tid);
   // what the prompt-row region of LDS holds now (selection scratch lies behind it)
   staged_q = (n_chunks == 1) ? pb.q : nullptr;
   staged_rows = Rp;
   if (!stages) return false;
 
   // ---- top-r and compaction (the pass-1 statistics are dead)
-  own_finish_step<D / 8, 8, ROT>(prm, pb, slot, N, dst, sel, sel_bytes, lkeys, /*keys_staged=*/true, step_probs, epoch,
-                                 layered, sync_words, tid);
+  own_finish_step<D / 8, 8, ROT>(prm, pb, slot, N, dst, sel, sel_bytes, lkeys, step_probs, epoch, layered, sync_words, tid);
   return layered;
 }
 

@@ -147,3 +147,32 @@ def test_paths_without_those_rows_refuse():
     f32.step(batch)
     H.validate_single_step(ts, "fp32 document rows")
     f32.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("beside", [False, True])
+def test_steps_without_any_row(dtype, beside):
+    """Document rows only, and a step without a chunk: no row sees the cache, every score is an
+    empty sum, and equal scores keep the first rows.  In a batch of such steps alone and beside one
+    with rows."""
+    fin = F.Finch(H.finch_dtype(torch.empty(0, dtype=dtype)), 64, 2)
+    specs = [dict(n_que=1, c=300, m=0, r=70), dict(n_que=1, c=33, m=0, r=40), dict(n_que=1, c=1000, m=0, r=999)]
+    if beside:
+        specs.append(dict(n_que=3, c=40, m=100, r=50, doc_rows=True, no_prompt=True))
+    batch, ts = H.single_step_case(fin, specs, dtype, 64, 2, seed=9)
+    rows = torch.zeros(64, 64, dtype=dtype, device="cuda")
+    for t in ts[:3]:
+        t["q"], t["q_doc"], t["n_que"] = None, rows, 0
+    batch = F.Batch(batch_descs(ts))
+    for call in (fin.step, fin.score):
+        for t in ts:
+            t["scores"][:-1].fill_(-4.0)
+        call(batch)
+        torch.cuda.synchronize()
+        for t in ts[:3]:
+            assert (t["scores"][:-1] == 0.0).all() and float(t["scores"][-1]) == -5.0
+            r = min(t["r"], t["c"])
+            assert torch.equal(t["idx"][:r], torch.arange(r, dtype=torch.int32, device="cuda"))
+            assert torch.equal(t["k_out"][:r], t["k_cache"][:r]) and torch.equal(t["v_out"][:r], t["v_cache"][:r])
+    H.validate_single_step(ts[3:], "beside")
+    fin.close()
