@@ -62,7 +62,8 @@ struct Plan {
   bool own_ok = false;    // the batch can run with one workgroup per problem
   bool has_doc = false;   // some problem takes rows from the chunk's own tokens (q_doc)
   int32_t own_row_chunk = 32;
-  size_t own_lds = 0;
+  size_t own_lds = 0;        // of a step
+  size_t own_score_lds = 0;  // of its scores alone
   // several workgroups per problem in one launch: slices per problem (0: not for this batch)
   int32_t cluster_slices = 0, cluster_row_chunk = 32;
   size_t cluster_lds = 0;
@@ -168,13 +169,16 @@ finch_status make_plan(const finch_ctx* ctx, const finch_problem* hd, int32_t n_
   if (ctx->cfg.dtype == FINCH_BF16 && n_max > 0) {
     int orc = pl.rpad_max < finch::kOwnerMaxRowChunk ? pl.rpad_max : finch::kOwnerMaxRowChunk;
     if (orc < 32) orc = 32;  // (no rows at all: document rows only, and no chunk)
-    while (orc > 32 && finch::owner_lds_bytes(ctx->cfg.head_dim, orc) > ctx->max_lds) orc -= 32;
+    const bool rank = ctx->repos.order == FINCH_ORDER_RANK;
+    // (the same rows at a time for every batch: the largest selection's scratch beside them)
+    while (orc > 32 && finch::owner_lds_bytes(ctx->cfg.head_dim, orc, INT32_MAX, pl.r_max, rank, true) > ctx->max_lds) orc -= 32;
     pl.own_row_chunk = orc;
-    pl.own_lds = finch::owner_lds_bytes(ctx->cfg.head_dim, orc);
+    pl.own_lds = finch::owner_lds_bytes(ctx->cfg.head_dim, orc, pl.n_max, pl.r_max, rank, true);
+    pl.own_score_lds = finch::owner_lds_bytes(ctx->cfg.head_dim, orc, pl.n_max, pl.r_max, rank, false);
     pl.own_ok = pl.own_lds <= ctx->max_lds;
   }
   if (ctx->cfg.dtype == FINCH_F32 && n_max > 0) {
-    pl.own_lds = finch::owner_f32_lds_bytes(ctx->cfg.head_dim);
+    pl.own_lds = pl.own_score_lds = finch::owner_f32_lds_bytes(ctx->cfg.head_dim);
     pl.own_ok = pl.own_lds <= ctx->max_lds;
   }
   size_t off = 256;  // the first word of the workspace is the status word of the launches (finch_workspace_status)
@@ -477,7 +481,7 @@ finch_status run_cluster(finch_ctx* ctx, LaunchParams p, const Plan& pl, void* w
 
 finch_status run_owner(finch_ctx* ctx, LaunchParams p, const Plan& pl, int stages, hipStream_t s) {
   p.row_chunk = pl.own_row_chunk;
-  p.lds_bytes = static_cast<uint32_t>(pl.own_lds);
+  p.lds_bytes = static_cast<uint32_t>(stages ? pl.own_lds : pl.own_score_lds);
   hipError_t e;
   if (stages && ctx->layer_group > 1) {
     if ((e = finch::launch_zero_words(p.layer_sync, pl.sync_words, p.layer_err, s)) != hipSuccess) return hip_fail(ctx, e);

@@ -22,9 +22,8 @@ __host__ __device__ inline int stream_slices(int n_keys, int slice_keys) {
 }
 // One-workgroup-per-problem path: most prompt rows staged per pass over the keys.
 constexpr int kOwnerMaxRowChunk = 256;
-// LDS the one-workgroup-per-problem kernels keep behind their selection scratch (kept indices etc.).
-// (a workgroup has the compute unit to itself anyway, so what the prompt rows leave is free: kept
-// indices and order keys of a step with 12000 candidates fit beside 256 prompt rows of 256 bytes)
+// Most LDS the one-workgroup-per-problem kernels keep behind their selection scratch: kept indices
+// and order keys of a step with 12000 candidates fit beside 256 prompt rows of 256 bytes.
 constexpr size_t kOwnerSelectBytes = 60 * 1024;
 // Most kept rows a workgroup of these kernels ranks by score (a bitonic network in registers).
 constexpr int kOwnerRankRows = 2048;
@@ -102,7 +101,7 @@ hipError_t launch_select(LaunchParams p, int n_max, hipStream_t s);
 hipError_t launch_select_layer(LaunchParams p, int group, float* layer_scores, int n_max, hipStream_t s);
 hipError_t set_max_lds_select(size_t bytes);
 hipError_t launch_gather(const LaunchParams& p, int row_bytes, int r_max, hipStream_t s);
-size_t owner_lds_bytes(int head_dim, int row_chunk);
+size_t owner_lds_bytes(int head_dim, int row_chunk, int n_max, int r_max, bool rank_order, bool stages);
 hipError_t launch_prompt_lse(const LaunchParams& p, int head_dim, bool bf16, int rows_max, hipStream_t s);
 hipError_t launch_reposition(const LaunchParams& p, int row_bytes, bool bf16, int r_max, int pairing,
                              bool rank, double base, hipStream_t s);

@@ -273,8 +273,7 @@ __device__ __forceinline__ void own_no_rows(float* scores, unsigned* lkeys, int 
 // The rest of a step once this workgroup's scores are in memory (and a barrier has been
 // passed since): top-r (Method: t = top-r(A_agg, r); with `layered` on the sum over the
 // layer's heads) and compaction (Method: Managing the Cache) of rows of SEGS 16-byte
-// pieces with E elements each.  `sel` is LDS scratch of sel_bytes (>= sizeof(SelLds) +
-// kOwnerSelectBytes); `dst` the scores of this problem; `lkeys` what own_sel_keys said, with
+// pieces with E elements each.  `sel` is LDS scratch of sel_bytes (owner_lds_bytes); `dst` the scores of this problem; `lkeys` what own_sel_keys said, with
 // the order keys of these scores in it already (not those of the layer's sum).
 template <int SEGS, int E, bool ROT>
 __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const finch_problem& pb, int slot, int N,
@@ -692,8 +691,9 @@ __device__ __forceinline__ int own_slot_of(int b, int n, int L) {
 
 // One launch = one step of every problem of a batch; workgroup b owns problem b.
 // ROT: the compaction re-positions the kept keys (prm.rope_pairing, ascending slots).
+// (Few rows of 64 channels: 128 registers are enough, and two workgroups share a compute unit.)
 template <int D, int QBT, bool ROT, bool DOC>
-__global__ __launch_bounds__(kOwnThreads) void owner_step_bf16(LaunchParams prm, int stages) {
+__global__ __launch_bounds__(kOwnThreads, (D == 64 && QBT == 2 && !ROT && !DOC) ? 4 : 2) void owner_step_bf16(LaunchParams prm, int stages) {
   extern __shared__ __align__(16) char smem[];
   const int p = own_slot_of(blockIdx.x, gridDim.x, stages ? prm.layer_group : 1);
   const finch_problem pb = prm.probs[p];
