@@ -261,12 +261,12 @@ finch_status finch_schedule_mode(int64_t n_cont, int32_t m, int64_t k, int32_t m
  * one kernel per stage: row statistics, merge, per-key sums, top-r, compaction.
  * OWNER gives every problem to one workgroup of 8 waves that runs all stages of the
  * step - or, in finch_loop, of all steps - back to back (bf16: matrix instructions;
- * fp32: the vector ALU, meant for small problems); batches it cannot run fail with
+ * fp32: fp64 matrix instructions, meant for small problems); batches it cannot run fail with
  * FINCH_ERR_UNSUPPORTED.  AUTO (default) takes OWNER for bf16 when the batch has enough
  * problems to fill the chip's compute units in whole rounds, for fp32 when no problem
- * has more than 4096 candidates or 64 prompt rows; for bf16 batches of at most half as many
- * problems as compute units, a launch per step in which several workgroups share a problem;
- * else SEPARATE. */
+ * has more than 4096 candidates or 64 prompt rows (few problems of head_dim 64 with at most 5
+ * rows: 1024 candidates); for bf16 batches of at most half as many problems as compute units,
+ * mostly, a launch per step in which several workgroups share a problem; else SEPARATE. */
 typedef enum {
   FINCH_OPT_STEP_PATH = 1,
   /* tuning: target number of keys one workgroup of the two-pass bf16 scoring

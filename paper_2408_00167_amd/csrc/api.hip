@@ -412,9 +412,17 @@ bool owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n) {
   if (ctx->step_path == FINCH_PATH_OWNER) return true;
   if (pl.has_doc) return ctx->step_path == FINCH_PATH_AUTO;  // the only kernels with those rows
   if (ctx->step_path != FINCH_PATH_AUTO) return false;
-  // fp32 (vector ALU): one workgroup per problem saves launches while problems are small;
-  // large ones are better spread over the chip by the kernels per stage
-  if (ctx->cfg.dtype == FINCH_F32) return pl.n_max <= 4096 && pl.rows_max <= 64;
+  // fp32: one workgroup per problem saves launches while problems are small; large ones are
+  // better spread over the chip by the kernels per stage.  So are, from 1025 candidates on (whose
+  // logits are no longer kept between the passes), the few problems of up to 5 rows of 64
+  // channels: the fp64 matrix tiles of 16 rows are then mostly padding.  4 rows, 4096 candidates:
+  // 1 problem 100 us with one workgroup and 27 per stage, 128 problems 116 and 87, 256
+  // problems 139 and 158.
+  if (ctx->cfg.dtype == FINCH_F32) {
+    const bool padding = ctx->cfg.head_dim == 64 && pl.rows_max <= 5;
+    const bool few = int64_t{4} * n <= int64_t{3} * ctx->n_cu && pl.n_max > int64_t{15} * n;
+    return pl.n_max <= 4096 && pl.rows_max <= 64 && !(padding && few && pl.n_max > 1024);
+  }
   const int64_t cu = ctx->n_cu > 0 ? ctx->n_cu : 256;
   const int64_t rounds = (n + cu - 1) / cu;
   return static_cast<int64_t>(n) * 100 >= rounds * cu * 85;

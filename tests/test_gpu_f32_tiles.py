@@ -6,6 +6,7 @@ import torch
 
 import paper_2408_00167_amd as F
 from tests import gpu_harness as H
+from tests.test_gpu_parity import _which_scoring_kernels
 
 pytestmark = pytest.mark.gpu
 
@@ -21,4 +22,16 @@ def test_tile_edges(d, group, rows):
     batch, ts = H.single_step_case(fin, specs, torch.float32, d, group, seed=12)
     fin.step(batch)
     H.validate_single_step(ts, f"tiles d={d} {rows}")
+    fin.close()
+
+
+@pytest.mark.parametrize("d,rows,problems,n,owner", [
+    (64, 5, 1, 1024, True), (64, 5, 1, 1025, False), (64, 6, 1, 4096, True), (128, 1, 1, 4096, True),
+    (64, 1, 100, 1500, True), (64, 1, 100, 1501, False), (64, 4, 192, 2881, False), (64, 1, 193, 4096, True)])
+def test_few_rows_and_many_candidates(d, rows, problems, n, owner):
+    """Which launch AUTO takes where the tiles of 16 rows are mostly padding; both against the oracle."""
+    fin = F.Finch(F.FINCH_F32, d, 1)
+    batch, ts = H.single_step_case(fin, [dict(n_que=rows, c=100, m=n - 100, r=60)] * problems, torch.float32, d, 1, seed=14)
+    assert (_which_scoring_kernels(fin, batch) == {"owner"}) == owner
+    H.validate_single_step(ts[::20], f"d={d} rows={rows} n={n}")
     fin.close()
