@@ -226,8 +226,8 @@ finch_status finch_loop(finch_ctx* ctx, const finch_problem* host_desc,
 /* The first word of a workspace is the status word of the launches that used it last.
  * Only one thing sets it: with FINCH_OPT_LAYER_GROUP > 1 the workgroups of a layer wait
  * for each other inside the one-workgroup-per-problem kernels, at most about 0.2 s each
- * time; a workgroup whose wait runs out sets the word and goes on with the scores it
- * finds, so the launch always ends, but its selection is then not the layer's.  This
+ * time; a workgroup whose wait runs out sets the word and leaves that step's indices and
+ * cache rows unwritten, so the launch always ends, but without the layer's selection.  This
  * call waits for `stream`, copies the word to *flags and returns FINCH_ERR_TIMEOUT if it
  * is not zero (which takes a chip on which other work keeps some of the batch's
  * workgroups from starting).  While FINCH_OPT_LAYER_GROUP > 1 every finch_step and

@@ -385,13 +385,13 @@ struct ProfScope {
   }
 };
 
-// One workgroup per problem pays when the problems fill the chip's CUs in whole
-// rounds (one 16-wave workgroup per CU at a time): AUTO takes that path when the
-// last round would be at least 85 % full.
 bool repositioning(const finch_ctx* ctx) {
   return ctx->repos.pairing != FINCH_ROPE_OFF || ctx->repos.order != FINCH_ORDER_ASCENDING;
 }
 
+// One workgroup per problem pays when the problems fill the chip's CUs in whole
+// rounds (mostly one workgroup per CU at a time): AUTO takes that path when the
+// last round would be at least 85 % full.
 bool owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n) {
   if (!pl.own_ok || n <= 0) return false;
   // slots by score rank: the workgroup sorts its kept rows in LDS (their indices and one

@@ -5,9 +5,10 @@
 // workgroup that owns the problem.
 //
 // Nothing is exchanged between workgroups, so there are no kernel boundaries, no
-// atomics on device memory and no waits: the row statistics are merged in LDS, the
-// scores a workgroup wrote are read back by itself (top-r), and so are the indices
-// (compaction).  The keys are read a second time right after the first pass, while
+// atomics on device memory and no waits (but for layer groups, whose workgroups exchange
+// scores): the row statistics are merged in LDS, and the scores' order keys and the kept
+// indices stay there for top-r and compaction where they fit; else the workgroup reads back
+// what it wrote itself.  The keys are read a second time right after the first pass, while
 // the memory-side cache still holds most of them.  Workgroups are 8 waves (two per
 // SIMD, up to 256 registers each), one per CU; the batch should have about as many problems as the chip has CUs (or a
 // multiple), which the host checks before it picks this path.
@@ -273,8 +274,9 @@ __device__ __forceinline__ void own_no_rows(float* scores, unsigned* lkeys, int 
 // The rest of a step once this workgroup's scores are in memory (and a barrier has been
 // passed since): top-r (Method: t = top-r(A_agg, r); with `layered` on the sum over the
 // layer's heads) and compaction (Method: Managing the Cache) of rows of SEGS 16-byte
-// pieces with E elements each.  `sel` is LDS scratch of sel_bytes (owner_lds_bytes); `dst` the scores of this problem; `lkeys` what own_sel_keys said, with
-// the order keys of these scores in it already (not those of the layer's sum).
+// pieces with E elements each.  `sel` is LDS scratch of sel_bytes (owner_lds_bytes); `dst` the
+// scores of this problem; `lkeys` what own_sel_keys said, with the order keys of these scores
+// in it already (not those of the layer's sum).
 template <int SEGS, int E, bool ROT>
 __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const finch_problem& pb, int slot, int N,
                                                 FINCH_GLOBAL float* dst, char* sel, size_t sel_bytes,
@@ -339,8 +341,8 @@ __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const f
       select_keys_any<kOwnThreads, true>(lkeys, N, r, gidx, lidx, fl, tid, lane, wave);
     } else {
       __syncthreads();
-      if (layered) select_generic<kOwnThreads>(nullptr, layer_sum, N, r, gidx, lidx, fl, tid, lane, wave);
-      else select_generic<kOwnThreads>(nullptr, own, N, r, gidx, lidx, fl, tid, lane, wave);
+      if (layered) select_generic<kOwnThreads>(layer_sum, N, r, gidx, lidx, fl, tid, lane, wave);
+      else select_generic<kOwnThreads>(own, N, r, gidx, lidx, fl, tid, lane, wave);
     }
     __syncthreads();  // idx complete
     if (lkeys)
@@ -379,8 +381,8 @@ __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const f
 // another step must put a barrier in between.
 // With prm.layer_group = L > 1 the L workgroups of a run of slots (a layer's KV heads)
 // select together (Method: "Sum over heads", then one top-r per layer): each publishes
-// its scores, waits for the others (bounded: a wait that runs out sets the error word
-// and the workgroup goes on with what it finds), adds the L vectors up in the same order
+// its scores, waits for the others (bounded: a wait that runs out sets the error word and
+// the workgroup leaves the step's indices and rows unwritten), adds the L vectors up in the same order
 // and selects on the sum, so that all L arrive at the same indices on their own.
 // `step_probs` are the descriptors of this step, `epoch` counts the exchanges this
 // workgroup has been through in this launch; returns true if the step made one.

@@ -28,7 +28,7 @@ __device__ __forceinline__ void select_problem(const LaunchParams& prm, char* sm
     __syncthreads();
     select_keys_any<kSelThreads, false>(keys, N, r, idx, nullptr, lds, tid, lane, wave);
   } else {
-    select_generic<kSelThreads>(nullptr, src, N, r, idx, nullptr, lds, tid, lane, wave);
+    select_generic<kSelThreads>(src, N, r, idx, nullptr, lds, tid, lane, wave);
   }
 }
 

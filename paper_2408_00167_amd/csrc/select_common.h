@@ -180,14 +180,12 @@ __device__ __forceinline__ int sel_block_rank(bool flag, int* wave_tot, int lane
   return base + below;
 }
 
-// Any N.  `keys` is LDS (order keys staged there) or nullptr (scores taken from
-// `score_of` again each round).  Writes idx to `gidx` and, if `lidx` is not null, also to
-// LDS.  0 < r < N.  Whole workgroup; starts and ends without a barrier.
+// Any N: scores are taken from `score_of` again each round.  Writes idx to `gidx` and, if `lidx` is
+// not null, also to LDS.  0 < r < N.  Whole workgroup; starts and ends without a barrier.
 template <int NT, class Src = OneScoreVector>
-__device__ __forceinline__ void select_generic(const unsigned* keys, const Src& score_of,
-                                               int N, int r, FINCH_GLOBAL int* gidx, int* lidx, SelLds* f,
+__device__ __forceinline__ void select_generic(const Src& score_of, int N, int r, FINCH_GLOBAL int* gidx, int* lidx, SelLds* f,
                                                int tid, int lane, int wave) {
-  auto key_at = [&](int i) -> unsigned { return keys ? keys[i] : order_key(score_of(i)); };
+  auto key_at = [&](int i) -> unsigned { return order_key(score_of(i)); };
   unsigned prefix = 0, mask = 0;
   int remaining = r;
   int* hist = f->hist[0];

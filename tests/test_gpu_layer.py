@@ -17,7 +17,8 @@ LAYERS = [
     dict(n_que=16, c=64, m=0, r=10),
     dict(n_que=16, c=100, m=156, r=0),
     dict(n_que=16, c=100, m=156, r=256),      # keep everything
-    dict(n_que=3, c=0, m=17000, r=700),       # more candidates than the register select holds
+    dict(n_que=3, c=0, m=17000, r=700),       # more candidates than 512 threads hold in registers
+    dict(n_que=2, c=0, m=32000, r=400),       # than 1024 threads do
 ]
 
 

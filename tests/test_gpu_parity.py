@@ -72,7 +72,8 @@ def test_both_step_paths(d, group, path):
     cap = 512 // group
     specs = [dict(s, n_que=min(s["n_que"], cap)) for s in RAGGED_SPECS]
     specs += [dict(n_que=cap, c=1364, m=4096, r=1408), dict(n_que=max(1, cap // 3), c=5, m=130, r=64),
-              dict(n_que=2, c=100, m=9000, r=900)]   # more candidates than a workgroup's registers hold
+              dict(n_que=2, c=100, m=9000, r=900),
+              dict(n_que=2, c=100, m=15900, r=900)]   # more candidates than a workgroup's registers hold
     batch, ts = H.single_step_case(fin, specs, torch.bfloat16, d, group, seed=300 + d + group)
     fin.step(batch)
     st = H.validate_single_step(ts, f"{path} d={d} G={group}")
@@ -93,7 +94,7 @@ FP32_SPECS = [dict(n_que=16, c=48, m=256, r=64), dict(n_que=4, c=0, m=64, r=8), 
 
 @pytest.mark.parametrize("d,group", [(64, 1), (128, 2), (64, 5)])
 def test_fp32_one_workgroup_per_problem(d, group):
-    """fp32 inputs through the one-workgroup-per-problem kernels (vector ALU): the same
+    """fp32 inputs through the one-workgroup-per-problem kernels: the same
     results as the kernels per stage, to the oracle's tolerance."""
     say(f"fp32 owner d={d} G={group}")
     fin = F.Finch(F.FINCH_F32, d, group)
