@@ -81,7 +81,8 @@ __device__ __forceinline__ int meet_wait(const int* flags, int n, int stride, in
       const int i = lane + 64 * u;
       want[u] = i < n && i - div_small(i, stride) * stride < used;
     }
-    long long began = -1, waited = 0;
+    const long long end = wall_clock64() + budget;
+    long long now = end - budget;
     int missing;
     while (true) {
       missing = -1;
@@ -94,13 +95,11 @@ __device__ __forceinline__ int meet_wait(const int* flags, int n, int stride, in
         if (m) missing = 64 * u + __ffsll(static_cast<long long>(m)) - 1;
       }
       if (missing < 0) break;
-      const long long now = wall_clock64();
-      if (began < 0) began = now;
-      waited = now - began;
-      if (waited >= budget) break;
+      now = wall_clock64();
+      if (now >= end) break;
       __builtin_amdgcn_s_sleep(1);
     }
-    budget = waited < budget ? budget - waited : 0;
+    budget = max(0ll, end - now);
     if (lane == 0) *sh = missing;
   }
   __syncthreads();
