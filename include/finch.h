@@ -211,7 +211,10 @@ size_t finch_static_scratch_bytes(void);
  * memory that a descriptor in another slot writes: slots are processed
  * independently, each through all of its steps, possibly by one kernel launch for
  * the whole loop (one workgroup per slot; picked under FINCH_PATH_AUTO when the
- * slots fill the chip, forced by FINCH_PATH_OWNER), otherwise step by step.
+ * slots fill the chip, forced by FINCH_PATH_OWNER), otherwise step by step.  Rows of
+ * k_out / v_out that a later step of the same call overwrites need not be written
+ * before; all of them hold what the last step that writes them leaves when the call's
+ * work is done.
  * host_step_first is host memory, dev_step_first a device copy of it.  The
  * workspace must hold finch_loop_workspace_size bytes (never more than
  * finch_workspace_size of all descriptors taken as one batch). */

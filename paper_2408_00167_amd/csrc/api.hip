@@ -36,6 +36,7 @@ struct finch_ctx {
   // overlaps (the check is repeated only when the descriptors change)
   uint64_t loop_checked_hash;
   bool loop_checked;
+  bool loop_rows_may_stay;  // what check_slot_overlaps said of that set
 };
 
 // Scratch of finch_step_static: the workspace of a step, held by the library itself so
@@ -596,10 +597,19 @@ struct Span {
   int32_t slot;
 };
 
+// (a span that continues one of the last two, or starts where it does, is joined to it: chunks of
+// a document follow each other, and caches alternate between two places)
 void add_span(std::vector<Span>& v, const void* p, size_t bytes, int32_t slot) {
   if (!p || bytes == 0) return;
-  const uintptr_t a = reinterpret_cast<uintptr_t>(p);
-  v.push_back(Span{a, a + bytes, slot});
+  const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = a + bytes;
+  for (size_t k = 1; k <= 2 && k <= v.size(); ++k) {
+    Span& l = v[v.size() - k];
+    if (l.slot == slot && a >= l.lo && a <= l.hi) {
+      if (b > l.hi) l.hi = b;
+      return;
+    }
+  }
+  v.push_back(Span{a, b, slot});
 }
 
 // Sorts by start and merges spans of one slot that touch or overlap (the ping-pong
@@ -615,6 +625,16 @@ void merge_own(std::vector<Span>& v) {
     }
   }
   v.resize(out);
+}
+
+// Whether a span of `a` and one of `b` share a byte; both as merge_own leaves them.
+bool spans_meet(const std::vector<Span>& a, const std::vector<Span>& b) {
+  for (size_t i = 0, j = 0; i < a.size() && j < b.size();) {
+    if (a[i].lo < b[j].hi && b[j].lo < a[i].hi) return true;
+    if (a[i].hi <= b[j].hi) ++i;
+    else ++j;
+  }
+  return false;
 }
 
 uint64_t fingerprint(const void* data, size_t bytes, uint64_t seed) {
@@ -634,40 +654,77 @@ uint64_t fingerprint(const void* data, size_t bytes, uint64_t seed) {
   return r;
 }
 
+// Whether the places of all rows of a slot, `p` to p + bytes among them, can be told in 32 bits as
+// 16-byte pieces from `base` (kernels add a row's offset to a start of up to this size).
+bool in_reach(const void* p, size_t bytes, const void* base) {
+  if (!p || bytes == 0) return true;
+  const int64_t limit = int64_t{1} << 34;  // 16 GiB: 2^30 pieces
+  const int64_t lo = static_cast<int64_t>(reinterpret_cast<uintptr_t>(p)) - static_cast<int64_t>(reinterpret_cast<uintptr_t>(base));
+  return lo >= -limit && lo + static_cast<int64_t>(bytes) <= limit;
+}
+
 // The rule of finch_loop: a slot runs through its steps without regard to the other
 // slots, so nothing a slot writes (k_out, v_out, scores, idx of any of its steps) may
 // overlap what another slot writes or reads (q, q_doc, k_*, v_*, lse_extra, scores).
+// *rows_may_stay: whether a slot's caches are memory that only its own steps use, and only as
+// caches.  The loop then need not move kept rows whose place a later step of the slot overwrites:
+// nothing but the next step's k_cache / v_cache reads k_out / v_out before, and nothing
+// writes to the chunks (and the first cache) in which the rows lie.
 finch_status check_slot_overlaps(const finch_ctx* ctx, const finch_problem* hd, const int32_t* first,
-                                 int32_t n_steps, int32_t n_slots) {
-  if (n_slots <= 1) return FINCH_OK;
+                                 int32_t n_steps, int32_t n_slots, bool* rows_may_stay) {
+  *rows_may_stay = true;
   const size_t rb = static_cast<size_t>(ctx->row_bytes);
   const int G = ctx->cfg.group_size;
-  std::vector<Span> writes, reads, own_w, own_r;
+  std::vector<Span> writes, reads, rows, notes, own_r;  // rows: k_out, v_out; notes: scores, idx
   for (int32_t slot = 0; slot < n_slots; ++slot) {
-    own_w.clear();
+    int32_t steps = 0;
+    while (steps < n_steps && slot < first[steps + 1] - first[steps]) ++steps;
+    rows.clear();
+    notes.clear();
     own_r.clear();
-    for (int32_t s = 0; s < n_steps; ++s) {
-      if (slot >= first[s + 1] - first[s]) break;
-      const finch_problem& pb = hd[first[s] + slot];
-      const size_t N = static_cast<size_t>(pb.c) + static_cast<size_t>(pb.m);
-      const size_t rr = static_cast<size_t>(pb.r) < N ? static_cast<size_t>(pb.r) : N;
-      add_span(own_w, pb.k_out, rr * rb, slot);
-      add_span(own_w, pb.v_out, rr * rb, slot);
-      add_span(own_w, pb.scores, N * sizeof(float), slot);
-      add_span(own_w, pb.idx, rr * sizeof(int32_t), slot);
-      add_span(own_r, pb.q, static_cast<size_t>(G) * pb.n_que * rb, slot);
-      add_span(own_r, pb.q_doc, static_cast<size_t>(G) * pb.m * rb, slot);
-      add_span(own_r, pb.k_cache, static_cast<size_t>(pb.c) * rb, slot);
-      add_span(own_r, pb.v_cache, static_cast<size_t>(pb.c) * rb, slot);
-      add_span(own_r, pb.k_chunk, static_cast<size_t>(pb.m) * rb, slot);
-      add_span(own_r, pb.v_chunk, static_cast<size_t>(pb.m) * rb, slot);
-      add_span(own_r, pb.lse_extra, static_cast<size_t>(G) * pb.n_que * sizeof(float), slot);
-    }
-    merge_own(own_w);
+    // (field by field, so that add_span finds the neighbours)
+    auto each = [&](auto f) {
+      for (int32_t s = 0; s < steps; ++s) f(hd[first[s] + slot], s);
+    };
+    auto total = [](const finch_problem& pb) { return static_cast<size_t>(pb.c) + static_cast<size_t>(pb.m); };
+    auto kept = [&](const finch_problem& pb) { return std::min(static_cast<size_t>(pb.r), total(pb)); };
+    each([&](const finch_problem& pb, int32_t) { add_span(rows, pb.k_out, kept(pb) * rb, slot); });
+    each([&](const finch_problem& pb, int32_t) { add_span(rows, pb.v_out, kept(pb) * rb, slot); });
+    each([&](const finch_problem& pb, int32_t) { add_span(notes, pb.scores, total(pb) * sizeof(float), slot); });
+    each([&](const finch_problem& pb, int32_t) { add_span(notes, pb.idx, kept(pb) * sizeof(int32_t), slot); });
+    each([&](const finch_problem& pb, int32_t) { add_span(own_r, pb.q, static_cast<size_t>(G) * pb.n_que * rb, slot); });
+    each([&](const finch_problem& pb, int32_t) { add_span(own_r, pb.q_doc, static_cast<size_t>(G) * pb.m * rb, slot); });
+    each([&](const finch_problem& pb, int32_t) { add_span(own_r, pb.k_chunk, static_cast<size_t>(pb.m) * rb, slot); });
+    each([&](const finch_problem& pb, int32_t) { add_span(own_r, pb.v_chunk, static_cast<size_t>(pb.m) * rb, slot); });
+    each([&](const finch_problem& pb, int32_t) { add_span(own_r, pb.lse_extra, static_cast<size_t>(G) * pb.n_que * sizeof(float), slot); });
+    // caches that are not what the step before has kept count as inputs
+    each([&](const finch_problem& pb, int32_t s) {
+      const finch_problem* prev = s > 0 ? &hd[first[s - 1] + slot] : nullptr;
+      const size_t bytes = static_cast<size_t>(pb.c) * rb;
+      if (!prev || pb.k_cache != prev->k_out || bytes > kept(*prev) * rb) add_span(own_r, pb.k_cache, bytes, slot);
+      if (!prev || pb.v_cache != prev->v_out || bytes > kept(*prev) * rb) add_span(own_r, pb.v_cache, bytes, slot);
+    });
+    merge_own(rows);
+    merge_own(notes);
     merge_own(own_r);
-    writes.insert(writes.end(), own_w.begin(), own_w.end());
+    if (steps > 0 && *rows_may_stay) {
+      const finch_problem& p0 = hd[first[0] + slot];
+      const void* k0 = p0.m > 0 ? p0.k_chunk : p0.k_cache;
+      const void* v0 = p0.m > 0 ? p0.v_chunk : p0.v_cache;
+      if (spans_meet(own_r, rows) || spans_meet(own_r, notes) || spans_meet(rows, notes)) *rows_may_stay = false;
+      const size_t cb = static_cast<size_t>(p0.c) * rb;
+      if (!in_reach(p0.k_cache, cb, k0) || !in_reach(p0.v_cache, cb, v0)) *rows_may_stay = false;
+      each([&](const finch_problem& pb, int32_t) {
+        const size_t mb = static_cast<size_t>(pb.m) * rb;
+        if (!in_reach(pb.k_chunk, mb, k0) || !in_reach(pb.v_chunk, mb, v0)) *rows_may_stay = false;
+      });
+    }
+    rows.insert(rows.end(), notes.begin(), notes.end());
+    merge_own(rows);
+    writes.insert(writes.end(), rows.begin(), rows.end());
     reads.insert(reads.end(), own_r.begin(), own_r.end());
   }
+  if (n_slots <= 1) return FINCH_OK;
   std::sort(writes.begin(), writes.end(), [](const Span& a, const Span& b) { return a.lo < b.lo; });
   // spans of one slot are disjoint now, so two neighbours that overlap belong to two slots;
   // `reach` carries the furthest end seen so far and the slot it belongs to
@@ -744,6 +801,7 @@ finch_status finch_create(const finch_config* cfg, finch_ctx** out) {
   ctx->static_meet = nullptr;
   ctx->loop_checked = false;
   ctx->loop_checked_hash = 0;
+  ctx->loop_rows_may_stay = false;
   ctx->meet = nullptr;
   hipError_t e = hipGetDevice(&ctx->device);
   StaticAddresses a = {nullptr, nullptr, nullptr};
@@ -1024,8 +1082,10 @@ finch_status finch_loop(finch_ctx* ctx, const finch_problem* host_desc, const fi
     uint64_t h = fingerprint(host_desc, static_cast<size_t>(n_desc) * sizeof(finch_problem), 1);
     h = fingerprint(host_step_first, static_cast<size_t>(n_steps + 1) * sizeof(int32_t), h);
     if (!ctx->loop_checked || ctx->loop_checked_hash != h) {
-      if ((st = check_slot_overlaps(ctx, host_desc, host_step_first, n_steps, n_slots)) != FINCH_OK) return st;
+      bool may_stay = false;
+      if ((st = check_slot_overlaps(ctx, host_desc, host_step_first, n_steps, n_slots, &may_stay)) != FINCH_OK) return st;
       ctx->loop_checked = true;
+      ctx->loop_rows_may_stay = may_stay;
       ctx->loop_checked_hash = h;
     }
   }
@@ -1036,6 +1096,10 @@ finch_status finch_loop(finch_ctx* ctx, const finch_problem* host_desc, const fi
     LaunchParams p = make_params(ctx, dev_desc, n_desc, pl, ws);
     p.row_chunk = pl.own_row_chunk;
     p.lds_bytes = static_cast<uint32_t>(pl.own_lds);
+    // notes of where kept rows lie: as many as fit beside the rest of the LDS (the kernels that move
+    // every row are fp32's, and slots by rank put the rows in another order)
+    if (ctx->cfg.dtype == FINCH_BF16 && ctx->loop_rows_may_stay && ctx->repos.order == FINCH_ORDER_ASCENDING)
+      p.stay_rows = static_cast<int32_t>(std::min(static_cast<size_t>(pl.r_max), (ctx->max_lds - pl.own_lds) / 8));
     hipError_t e;
     if (ctx->layer_group > 1) {
       if ((e = finch::launch_zero_words(p.layer_sync, pl.sync_words, p.layer_err, s)) != hipSuccess) return hip_fail(ctx, e);
@@ -1094,7 +1158,8 @@ finch_status finch_loop_check(const finch_config* cfg, const finch_problem* host
     if (static_cast<int64_t>(pb.c) + pb.m > (1 << 24)) return FINCH_ERR_CAPACITY;
   }
   if ((st = validate(&tmp, host_desc, n_desc, kNeedQK | kNeedIdx | kNeedGather)) != FINCH_OK) return st;
-  return check_slot_overlaps(&tmp, host_desc, host_step_first, n_steps, n_slots);
+  bool may_stay = false;
+  return check_slot_overlaps(&tmp, host_desc, host_step_first, n_steps, n_slots, &may_stay);
 }
 
 finch_status finch_schedule(int64_t n_cont, int32_t m, int64_t k, int32_t* r_out, int32_t r_len) {

@@ -87,6 +87,8 @@ struct LaunchParams {
   int32_t cluster_slices;
   int32_t* meet;
   int64_t help_ticks;
+  int32_t stay_rows;           // whole loop: most kept rows a step may leave where they are (0: none; room for as many notes, 8
+                               // bytes each, follows the lds_bytes)
   int64_t spin_ticks;          // longest wait for the other workgroups, in 100 MHz ticks
 };
 

@@ -62,16 +62,32 @@ __device__ __forceinline__ int own_next_block(int* counter, int lane) {
   return __builtin_amdgcn_readfirstlane(v);
 }
 
+// Rows that stay where they are.  Inside the whole-loop kernels a step need not move the rows it
+// keeps if a later step overwrites all of its k_out / v_out and the step in between is the only
+// one to read them (owner_loop_bf16 decides; the host has checked that nothing else of the
+// slot touches those buffers): it only notes in LDS where each kept row lies, and the next step
+// reads its cache there.  Kept rows are moved when they are wanted in their place, at the end of
+// the loop.  With re-positioning that holds for the values only: a key is rounded every time
+// it moves.
+struct KeptRows {
+  int* at = nullptr;         // LDS: kept row t lies at[t] 16-byte pieces behind k0, and at[cap + t] behind v0
+  int cap = 0;
+  const char* k0 = nullptr;
+  const char* v0 = nullptr;
+  bool mapped = false;       // the cache rows of this step are where `at` says, not in k_cache / v_cache
+  bool stay = false;         // this step leaves its kept rows where they are
+};
+
 // Copy rows idx[t0..t1) of [cache ; chunk] of K and V into k_out / v_out by NT threads
 // (`tid` = index among them), t1 <= the rows kept.  `lidx` (LDS) or `gidx` (memory, written by this
 // workgroup) holds the indices; with `identity` row t is simply candidate t.
 template <int SEGS, int NT = kOwnThreads, int kUnroll = 8>
 __device__ __forceinline__ void own_gather(const finch_problem& pb, int N, const int* lidx,
                                            const FINCH_GLOBAL int* gidx, bool identity, int tid, int t0,
-                                           int t1) {
-  const FINCH_GLOBAL u32x4* kc = as_global<u32x4>(pb.k_cache);
+                                           int t1, const KeptRows& kept = KeptRows{}) {
+  const FINCH_GLOBAL u32x4* kc = as_global<u32x4>(kept.mapped ? kept.k0 : pb.k_cache);
   const FINCH_GLOBAL u32x4* kk = as_global<u32x4>(pb.k_chunk);
-  const FINCH_GLOBAL u32x4* vc = as_global<u32x4>(pb.v_cache);
+  const FINCH_GLOBAL u32x4* vc = as_global<u32x4>(kept.mapped ? kept.v0 : pb.v_cache);
   const FINCH_GLOBAL u32x4* vk = as_global<u32x4>(pb.v_chunk);
   FINCH_GLOBAL u32x4* ko = as_global_mut<u32x4>(pb.k_out);
   FINCH_GLOBAL u32x4* vo = as_global_mut<u32x4>(pb.v_out);
@@ -85,6 +101,16 @@ __device__ __forceinline__ void own_gather(const finch_problem& pb, int N, const
       int j = identity ? t : (lidx ? lidx[t] : gidx[t]);
       j = min(max(j, 0), N - 1);
       const bool cached = j < pb.c;
+      if (kept.mapped) {
+        long long ko_at = static_cast<long long>(j - pb.c) * SEGS, vo_at = ko_at;
+        if (cached) {
+          ko_at = kept.at[j];
+          vo_at = kept.at[kept.cap + j];
+        }
+        kv[it] = (cached ? kc : kk)[ko_at + seg];
+        vv[it] = (cached ? vc : vk)[vo_at + seg];
+        continue;
+      }
       const size_t off = static_cast<size_t>(cached ? j : j - pb.c) * SEGS + seg;
       kv[it] = (cached ? kc : kk)[off];
       vv[it] = (cached ? vc : vk)[off];
@@ -104,16 +130,17 @@ __device__ __forceinline__ void own_gather(const finch_problem& pb, int N, const
 // order), or, with `ranked` (LDS; see own_rank_kept), the kept row whose record stands
 // at place p of the sorted records; the key is turned by p - idx[t] positions while it
 // is copied (not at all with pairing FINCH_ROPE_OFF).  A thread owns two pieces of a
-// row, d/2 channels apart, i.e. both partners of its channel pairs.
+// row, d/2 channels apart, i.e. both partners of its channel pairs.  (Values may stay where
+// they are; keys do not.)
 template <int SEGS, int NT = kOwnThreads, int E = 8, int kUnroll = 4>
 __device__ __forceinline__ void own_gather_rot(const finch_problem& pb, int N, int r, const int* lidx,
                                                const FINCH_GLOBAL int* gidx, bool identity, int pairing,
                                                double log2_base, int tid, const unsigned long long* ranked,
-                                               int t0, int t1) {
+                                               int t0, int t1, const KeptRows& kept = KeptRows{}) {
   constexpr int kHalf = SEGS / 2;
   const FINCH_GLOBAL u32x4* kc = as_global<u32x4>(pb.k_cache);
   const FINCH_GLOBAL u32x4* kk = as_global<u32x4>(pb.k_chunk);
-  const FINCH_GLOBAL u32x4* vc = as_global<u32x4>(pb.v_cache);
+  const FINCH_GLOBAL u32x4* vc = as_global<u32x4>(kept.mapped ? kept.v0 : pb.v_cache);
   const FINCH_GLOBAL u32x4* vk = as_global<u32x4>(pb.v_chunk);
   FINCH_GLOBAL u32x4* ko = as_global_mut<u32x4>(pb.k_out);
   FINCH_GLOBAL u32x4* vo = as_global_mut<u32x4>(pb.v_out);
@@ -136,8 +163,12 @@ __device__ __forceinline__ void own_gather_rot(const finch_problem& pb, int N, i
       const size_t off = static_cast<size_t>(cached ? j : j - pb.c) * SEGS + seg;
       ka[it] = (cached ? kc : kk)[off];
       kb[it] = (cached ? kc : kk)[off + kHalf];
-      va[it] = (cached ? vc : vk)[off];
-      vb[it] = (cached ? vc : vk)[off + kHalf];
+      if (!kept.stay) {
+        long long voff = static_cast<long long>(off);
+        if (kept.mapped && cached) voff = static_cast<long long>(kept.at[kept.cap + j]) + seg;
+        va[it] = (cached ? vc : vk)[voff];
+        vb[it] = (cached ? vc : vk)[voff + kHalf];
+      }
     }
 #pragma unroll
     for (int it = 0; it < kUnroll; ++it) {
@@ -146,9 +177,38 @@ __device__ __forceinline__ void own_gather_rot(const finch_problem& pb, int N, i
         const size_t o = static_cast<size_t>(slot[it]) * SEGS + seg;
         ko[o] = ka[it];
         ko[o + kHalf] = kb[it];
-        vo[o] = va[it];
-        vo[o + kHalf] = vb[it];
+        if (!kept.stay) {
+          vo[o] = va[it];
+          vo[o + kHalf] = vb[it];
+        }
       }
+    }
+  }
+}
+
+// Notes where the r rows that this step keeps lie (KeptRows::stay).  In place: kept row t is candidate
+// idx[t] >= t, so that a turn of NT rows only reads places that no turn before it has written.
+// Whole workgroup; the notes are complete at the next barrier.
+template <int SEGS>
+__device__ __forceinline__ void own_note_rows(const finch_problem& pb, int r, const int* lidx, const FINCH_GLOBAL int* gidx,
+                                              bool identity, int tid, const KeptRows& kept) {
+  auto pieces = [](const void* p, const char* base) { return static_cast<int>((static_cast<const char*>(p) - base) / 16); };
+  const int kc = pieces(pb.k_cache, kept.k0), vc = pieces(pb.v_cache, kept.v0);
+  const int kk = pieces(pb.k_chunk, kept.k0), vk = pieces(pb.v_chunk, kept.v0);
+  for (int t0 = 0; t0 < r; t0 += kOwnThreads) {
+    const int t = t0 + tid, u = min(t, r - 1);
+    const int j = identity ? u : (lidx ? lidx[u] : gidx[u]);
+    const bool cached = j < pb.c;
+    const int off = (cached ? j : j - pb.c) * SEGS;
+    int k_at = (cached ? kc : kk) + off, v_at = (cached ? vc : vk) + off;
+    if (kept.mapped && cached) {
+      k_at = kept.at[j];
+      v_at = kept.at[kept.cap + j];
+    }
+    __syncthreads();
+    if (t < r) {
+      kept.at[t] = k_at;
+      kept.at[kept.cap + t] = v_at;
     }
   }
 }
@@ -281,12 +341,14 @@ template <int SEGS, int E, bool ROT>
 __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const finch_problem& pb, int slot, int N,
                                                 FINCH_GLOBAL float* dst, char* sel, size_t sel_bytes,
                                                 unsigned* lkeys, const finch_problem* step_probs, int epoch,
-                                                bool layered, int* sync_words, int tid) {
+                                                bool layered, int* sync_words, int tid, KeptRows& kept) {
   const int lane = tid & 63, wave = tid >> 6;
   const int L = prm.layer_group;
   FINCH_PHASE_BEGIN();
   // ---- top-r on the scores this workgroup has just written
   const int r = min(pb.r, N);
+  KeptRows mine = kept;
+  kept.mapped = false;  // (of the next step's cache; a step that gives up leaves none)
   if (r <= 0) return;
   FINCH_GLOBAL int* gidx = as_global_mut<int>(pb.idx);
   const bool identity = r >= N;
@@ -364,9 +426,14 @@ __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const f
       ranked = reinterpret_cast<unsigned long long*>(sel + sizeof(SelLds) + ((static_cast<size_t>(r) * 4 + 7) & ~size_t{7}));
       own_rank_kept(ranked, r, dst, lidx, identity, tid);
     }
-    own_gather_rot<SEGS, kOwnThreads, E>(pb, N, r, lidx, gidx, identity, prm.rope_pairing, prm.rope_log2_base, tid, ranked, 0, r);
-  } else {
-    own_gather<SEGS>(pb, N, lidx, gidx, identity, tid, 0, r);
+    own_gather_rot<SEGS, kOwnThreads, E>(pb, N, r, lidx, gidx, identity, prm.rope_pairing, prm.rope_log2_base, tid, ranked, 0, r,
+                                         mine);
+  } else if (!mine.stay) {
+    own_gather<SEGS>(pb, N, lidx, gidx, identity, tid, 0, r, mine);
+  }
+  if (mine.stay) {
+    own_note_rows<SEGS>(pb, r, lidx, gidx, identity, tid, mine);
+    kept.mapped = true;
   }
   FINCH_PHASE(7);
 }
@@ -389,10 +456,13 @@ __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const f
 template <int D, int QBT, bool ROT, bool DOC>
 __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const finch_problem& pb, int slot,
                                               int stages, char* smem, const void*& staged_q,
-                                              int& staged_rows, const finch_problem* step_probs = nullptr,
-                                              int epoch = 0) {
+                                              int& staged_rows, const finch_problem* step_probs,
+                                              int epoch, KeptRows& kept) {
   const int N = pb.c + pb.m;
-  if (N == 0) return false;
+  if (N == 0) {
+    kept.mapped = false;
+    return false;
+  }
   FINCH_PHASE_BEGIN();
   const int Rp = (DOC && !pb.q) ? 0 : prm.group * pb.n_que;  // prompt rows
   // (the thread index goes through an empty asm: in the whole-loop kernel the compiler
@@ -408,7 +478,10 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   float2* wstats = reinterpret_cast<float2*>(smem + RC * kStride);                 // [waves][RC]
   float* lds_lse = reinterpret_cast<float*>(smem + RC * (kStride + kOwnWaves * 8));  // [RC]
   int* sh_next = reinterpret_cast<int*>(smem + RC * (kStride + kOwnWaves * 8 + 4));
-  const KeySource ks = {static_cast<const char*>(pb.k_cache), static_cast<const char*>(pb.k_chunk), pb.c};
+  // (keys that are re-positioned lie in the cache)
+  const bool mapped = !ROT && kept.mapped;
+  const KeySource ks = {mapped ? kept.k0 : static_cast<const char*>(pb.k_cache), static_cast<const char*>(pb.k_chunk), pb.c,
+                        mapped, kept.at};
   const int nb = (N + 31) >> 5;
   const float sc = prm.scale_log2;
   float* gscores = pb.scores ? pb.scores : prm.ws_scores + static_cast<size_t>(slot) * prm.score_stride;
@@ -677,7 +750,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   if (!stages) return false;
 
   // ---- top-r and compaction (the pass-1 statistics are dead)
-  own_finish_step<D / 8, 8, ROT>(prm, pb, slot, N, dst, sel, sel_bytes, lkeys, step_probs, epoch, layered, sync_words, tid);
+  own_finish_step<D / 8, 8, ROT>(prm, pb, slot, N, dst, sel, sel_bytes, lkeys, step_probs, epoch, layered, sync_words, tid, kept);
   return layered;
 }
 
@@ -691,6 +764,15 @@ __device__ __forceinline__ int own_slot_of(int b, int n, int L) {
   return x * (n >> 3) + min(x, n & 7) + j;
 }
 
+// Whether a step may leave the rows it keeps where they are: the next step's cache is exactly
+// these rows, and the step after that writes as many at the same place.
+__device__ __forceinline__ bool own_rows_may_stay(const finch_problem& pb, const finch_problem* next, const finch_problem* after,
+                                                  int cap) {
+  const int r = min(pb.r, pb.c + pb.m);
+  return r > 0 && r <= cap && next->c == r && next->k_cache == pb.k_out && next->v_cache == pb.v_out &&
+         after->k_out == pb.k_out && after->v_out == pb.v_out && min(after->r, after->c + after->m) >= r;
+}
+
 // One launch = one step of every problem of a batch; workgroup b owns problem b.
 // ROT: the compaction re-positions the kept keys (prm.rope_pairing, ascending slots).
 // (Few rows of 64 channels: 128 registers are enough, and two workgroups share a compute unit.)
@@ -701,7 +783,8 @@ __global__ __launch_bounds__(kOwnThreads, (D == 64 && QBT == 2 && !ROT && !DOC) 
   const finch_problem pb = prm.probs[p];
   const void* staged_q = nullptr;
   int staged_rows = 0;
-  own_step_body<D, QBT, ROT, DOC>(prm, pb, p, stages, smem, staged_q, staged_rows, prm.probs, 0);
+  KeptRows kept;
+  own_step_body<D, QBT, ROT, DOC>(prm, pb, p, stages, smem, staged_q, staged_rows, prm.probs, 0, kept);
 }
 
 // One launch = the whole chunk loop (Method: Document Segmentation): workgroup b
@@ -709,6 +792,10 @@ __global__ __launch_bounds__(kOwnThreads, (D == 64 && QBT == 2 && !ROT && !DOC) 
 // are prm.probs[step_first[s] + slot] for slot < step_first[s+1] - step_first[s].
 // Slots do not depend on each other, so workgroups drift apart and the copy-bound
 // and arithmetic-bound stages of different problems overlap.
+// Kept rows are moved in a slot's last two steps; before that a step only notes where they lie
+// (KeptRows) if own_rows_may_stay says so.  256 problems, 4096-token chunks, up to 1408 kept rows:
+// the copies were 20 of 187 us a step, the loop takes 5533 us in place of 6080; 1024 problems of
+// 32 rows, 512-token chunks and up to 1024 kept rows, where they were 18 of 42 us: 999 in place of 1354.
 template <int D, int QBT, bool ROT, bool DOC>
 __global__ __launch_bounds__(kOwnThreads) void owner_loop_bf16(LaunchParams prm, const int* step_first,
                                                                int n_steps) {
@@ -717,12 +804,24 @@ __global__ __launch_bounds__(kOwnThreads) void owner_loop_bf16(LaunchParams prm,
   const void* staged_q = nullptr;
   int staged_rows = 0;
   int epoch = 0;
+  KeptRows kept;
+  kept.at = reinterpret_cast<int*>(smem + prm.lds_bytes);
+  kept.cap = prm.stay_rows;
+  if (prm.stay_rows > 0) {
+    const finch_problem* p0 = prm.probs + slot;
+    kept.k0 = static_cast<const char*>(p0->m > 0 ? p0->k_chunk : p0->k_cache);
+    kept.v0 = static_cast<const char*>(p0->m > 0 ? p0->v_chunk : p0->v_cache);
+  }
   for (int s = 0; s < n_steps; ++s) {
     const int first = step_first[s];
     if (slot >= step_first[s + 1] - first) break;  // slots are filled from the front
     const finch_problem pb = prm.probs[first + slot];
+    kept.stay = false;
+    // (rows in a cache that an earlier step has moved would be overwritten while they are still wanted)
+    if (prm.stay_rows > 0 && s + 2 < n_steps && slot < step_first[s + 3] - step_first[s + 2] && (s == 0 || pb.c == 0 || kept.mapped))
+      kept.stay = own_rows_may_stay(pb, prm.probs + step_first[s + 1] + slot, prm.probs + step_first[s + 2] + slot, prm.stay_rows);
     if (own_step_body<D, QBT, ROT, DOC>(prm, pb, slot, /*stages=*/1, smem, staged_q, staged_rows, prm.probs + first,
-                                        epoch))
+                                        epoch, kept))
       ++epoch;
     // the rows this step wrote are the next step's cache: complete before it reads
     __syncthreads();
@@ -789,8 +888,8 @@ hipError_t launch_owner_loop_impl(int head_dim, const LaunchParams& p, const int
   const dim3 grid(static_cast<unsigned>(n_slots)), block(kOwnThreads);
   const bool ok = with_loop_kernel<DOC>(head_dim, own_qbt(p.row_chunk), p.rope_pairing != FINCH_ROPE_OFF || p.rank_order,
                                         [&](auto kern) {
-                                          hipLaunchKernelGGL(kern, grid, block, p.lds_bytes, s, p, step_first,
-                                                             n_steps);
+                                          hipLaunchKernelGGL(kern, grid, block, p.lds_bytes + 8u * static_cast<unsigned>(p.stay_rows), s,
+                                                             p, step_first, n_steps);
                                         });
   return ok ? hipGetLastError() : hipErrorInvalidValue;
 }

@@ -221,7 +221,8 @@ __device__ __forceinline__ bool own_step_body_f32(const LaunchParams& prm, const
   }
   if (n_rows == 0) own_no_rows(gscores, lkeys, N, tid);
   if (!stages) return false;
-  own_finish_step<D / 4, 4, ROT>(prm, pb, slot, N, dst, l.sel, sel_bytes, lkeys, step_probs, epoch, layered, sync_words, tid);
+  KeptRows kept;
+  own_finish_step<D / 4, 4, ROT>(prm, pb, slot, N, dst, l.sel, sel_bytes, lkeys, step_probs, epoch, layered, sync_words, tid, kept);
   return layered;
 }
 

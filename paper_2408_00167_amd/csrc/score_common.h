@@ -98,11 +98,14 @@ __device__ __forceinline__ T* uni(T* p) {
   return reinterpret_cast<T*>((static_cast<unsigned long long>(hi) << 32) | lo);
 }
 
-// Where the keys of a problem live: rows [0, c) in `cache`, the rest in `chunk`.
+// Where the keys of a problem live: rows [0, c) in `cache`, the rest in `chunk`.  With `mapped` row
+// j < c stands at[j] 16-byte pieces behind `cache` (`at` in LDS).
 struct KeySource {
   const char* cache;
   const char* chunk;
   int c;
+  bool mapped = false;
+  const int* at = nullptr;
 };
 
 // load_k_block with the three descriptor fields it needs passed directly.
@@ -114,6 +117,7 @@ __device__ __forceinline__ void load_k_block(const KeySource& ks, int N, int kba
   if (key < N) {
     const char* row = key < ks.c ? ks.cache + static_cast<size_t>(key) * (D * 2)
                                  : ks.chunk + static_cast<size_t>(key - ks.c) * (D * 2);
+    if (ks.mapped && key < ks.c) row = ks.cache + static_cast<long long>(ks.at[key]) * 16;
     const FINCH_GLOBAL u32x4* rp = as_global<u32x4>(row);
 #pragma unroll
     for (int s = 0; s < D / 16; ++s) {
