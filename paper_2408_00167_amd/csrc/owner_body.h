@@ -543,7 +543,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     auto lim_mine = [&](int q) { return min(N, lim0 + lim_step * (q * 32 + t)); };
     bf16x8 ka[D / 16], kb[D / 16];
     int b = wave;
-    if (b < nbc) load_k_block<D>(ks, N, b << 5, lane, ka);  // requested before Q is staged
+    load_k_block<D>(ks, N, b << 5, lane, ka);  // requested before Q is staged
     if (!(R <= RC && staged_q == qsrc && staged_rows == R)) {
       stage_q<D, kOwnThreads>(qsrc, R, row0, rows, lds_q, tid);
       __syncthreads();
@@ -627,11 +627,11 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
       };
       if (b < nbc) {
         while (true) {
-          if (b + kOwnWaves < nbc) load_k_block<D>(ks, N, (b + kOwnWaves) << 5, lane, kb);
+          if (!DOC || b + kOwnWaves < nbc) load_k_block<D>(ks, N, (b + kOwnWaves) << 5, lane, kb);
           process(ka, b);
           b += kOwnWaves;
           if (b >= nbc) break;
-          if (b + kOwnWaves < nbc) load_k_block<D>(ks, N, (b + kOwnWaves) << 5, lane, ka);
+          if (!DOC || b + kOwnWaves < nbc) load_k_block<D>(ks, N, (b + kOwnWaves) << 5, lane, ka);
           process(kb, b);
           b += kOwnWaves;
           if (b >= nbc) break;
@@ -653,7 +653,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     // ---- pass 2 walks the keys from the end (what pass 1 read last is what the
     // caches most likely still hold); its first block is requested before the merge
     b = nbc - 1 - wave;
-    if (b >= 0) load_k_block<D>(ks, N, b << 5, lane, ka);
+    load_k_block<D>(ks, N, b * 32, lane, ka);
     if (tid == 0) *sh_next = kOwnWaves;
     __syncthreads();
     FINCH_PHASE(2);
@@ -719,7 +719,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
         if ((t & 1) == 0 && key < N) {
           const float val = first_chunk ? tot : dst[key] + tot;
           // (scores other workgroups will read go out past this compute unit's caches)
-          if (layered) __hip_atomic_store(gscores + key, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (layered) __hip_atomic_store(dst + key, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           else dst[key] = val;
           if (lkeys) lkeys[key] = order_key(val);
         }
@@ -727,12 +727,12 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
       if (b >= 0) {
         while (true) {
           int bn = nbc - 1 - own_next_block(sh_next, lane);
-          if (bn >= 0) load_k_block<D>(ks, N, bn << 5, lane, kb);
+          if (!DOC || bn >= 0) load_k_block<D>(ks, N, bn * 32, lane, kb);
           process(ka, b);
           b = bn;
           if (b < 0) break;
           bn = nbc - 1 - own_next_block(sh_next, lane);
-          if (bn >= 0) load_k_block<D>(ks, N, bn << 5, lane, ka);
+          if (!DOC || bn >= 0) load_k_block<D>(ks, N, bn * 32, lane, ka);
           process(kb, b);
           b = bn;
           if (b < 0) break;

@@ -18,3 +18,14 @@ hipError_t launch_owner_loop_doc_bf16(int head_dim, const LaunchParams& p, const
 hipError_t set_max_lds_owner_doc(size_t bytes) { return set_max_lds_owner_impl<true>(bytes); }
 
 }  // namespace finch
+
+#ifdef FINCH_PHASE_TIMERS
+// Phase-timer build only: as finch_debug_phases, for the kernels of this file.
+extern "C" int finch_debug_phases_doc(unsigned long long* out, int reset) {
+  if (reset) {
+    const unsigned long long zero[8] = {0};
+    return static_cast<int>(hipMemcpyToSymbol(HIP_SYMBOL(finch::finch_phase_ticks), zero, sizeof(zero)));
+  }
+  return static_cast<int>(hipMemcpyFromSymbol(out, HIP_SYMBOL(finch::finch_phase_ticks), sizeof(unsigned long long) * 8));
+}
+#endif

@@ -196,7 +196,7 @@ __device__ __forceinline__ bool own_step_body_f32(const LaunchParams& prm, const
       const int key = tile * kTile + 4 * col + part;
       if (col < 4 && key < N) {
         const float val = row0 == 0 ? mine : dst[key] + mine;
-        if (layered) __hip_atomic_store(gscores + key, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (layered) __hip_atomic_store(dst + key, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         else dst[key] = val;
         if (lkeys) lkeys[key] = order_key(val);
       }
