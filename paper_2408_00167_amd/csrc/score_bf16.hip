@@ -79,6 +79,7 @@ __global__ __launch_bounds__(kThreads, 4) void rowstats_bf16(LaunchParams prm) {
   float2* wstats = reinterpret_cast<float2*>(smem + prm.row_chunk * kStride);  // [kWaves][rows]
   float2* out = prm.stats + (static_cast<size_t>(p) * prm.tiles_max + slice) * prm.rpad_max;
   const float sc = prm.scale_log2;
+  const KeySource ks = {static_cast<const char*>(pb.k_cache), static_cast<const char*>(pb.k_chunk), pb.c};
 
   for (int row0 = 0; row0 < R; row0 += prm.row_chunk) {
     const int rows = min(prm.row_chunk, round_up32(R - row0));
@@ -144,16 +145,18 @@ __global__ __launch_bounds__(kThreads, 4) void rowstats_bf16(LaunchParams prm) {
 
     // key blocks of this wave (a fixed assignment: the order in which a row's sums
     // are added up must not depend on timing), two register sets in ping-pong
+    // (what is requested past the slice's last row repeats that)
     bf16x8 ka[D / 16], kb[D / 16];
+    const int lim = min(N, b1 << 5);
     int b = b0 + wave;
     if (b < b1) {
-      load_k_block<D>(pb, N, b << 5, lane, ka);
+      load_k_block<D>(ks, lim, b << 5, lane, ka);
       while (true) {
-        if (b + kWaves < b1) load_k_block<D>(pb, N, (b + kWaves) << 5, lane, kb);
+        load_k_block<D>(ks, lim, (b + kWaves) << 5, lane, kb);
         process(ka, b);
         b += kWaves;
         if (b >= b1) break;
-        if (b + kWaves < b1) load_k_block<D>(pb, N, (b + kWaves) << 5, lane, ka);
+        load_k_block<D>(ks, lim, (b + kWaves) << 5, lane, ka);
         process(kb, b);
         b += kWaves;
         if (b >= b1) break;
@@ -205,6 +208,7 @@ __global__ __launch_bounds__(kThreads, 4) void colsum_bf16(LaunchParams prm) {
   int* sh_next = reinterpret_cast<int*>(smem + prm.row_chunk * (kStride + kWaves * 8));
   const float* lse = prm.lse + static_cast<size_t>(p) * prm.rpad_max;
   const float sc = prm.scale_log2;
+  const KeySource ks = {static_cast<const char*>(pb.k_cache), static_cast<const char*>(pb.k_chunk), pb.c};
   FINCH_GLOBAL float* dst = as_global_mut<float>(
       pb.scores ? pb.scores : prm.ws_scores + static_cast<size_t>(p) * prm.score_stride);
 
@@ -262,15 +266,15 @@ __global__ __launch_bounds__(kThreads, 4) void colsum_bf16(LaunchParams prm) {
     bf16x8 ka[D / 16], kb[D / 16];
     int b = b1 - 1 - next_block(sh_next, lane);
     if (b >= b0) {
-      load_k_block<D>(pb, N, b << 5, lane, ka);
+      load_k_block<D>(ks, N, b << 5, lane, ka);
       while (true) {
         int bn = b1 - 1 - next_block(sh_next, lane);
-        if (bn >= b0) load_k_block<D>(pb, N, bn << 5, lane, kb);
+        load_k_block<D>(ks, N, bn >= b0 ? bn * 32 : -32, lane, kb);
         process(ka, b);
         b = bn;
         if (b < b0) break;
         bn = b1 - 1 - next_block(sh_next, lane);
-        if (bn >= b0) load_k_block<D>(pb, N, bn << 5, lane, ka);
+        load_k_block<D>(ks, N, bn >= b0 ? bn * 32 : -32, lane, ka);
         process(kb, b);
         b = bn;
         if (b < b0) break;

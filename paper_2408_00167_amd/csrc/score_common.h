@@ -59,31 +59,6 @@ __device__ __forceinline__ finch_problem load_problem(const finch_problem* p) {
   return __builtin_bit_cast(finch_problem, raw);
 }
 
-// One 32-key block of K as MFMA A operands: lane (t, h) holds row kbase + t,
-// elements 16*s + 8*h .. +7 of it for k-step s.  Rows at or past N are zeros.
-template <int D>
-__device__ __forceinline__ void load_k_block(const finch_problem& pb, int N, int kbase, int lane,
-                                             bf16x8 (&kf)[D / 16]) {
-  const int key = kbase + (lane & 31);
-  const int h = lane >> 5;
-  if (key < N) {
-    const char* row = key < pb.c
-                          ? static_cast<const char*>(pb.k_cache) + static_cast<size_t>(key) * (D * 2)
-                          : static_cast<const char*>(pb.k_chunk) +
-                                static_cast<size_t>(key - pb.c) * (D * 2);
-    const FINCH_GLOBAL u32x4* rp = as_global<u32x4>(row);
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) {
-      const u32x4 raw = rp[2 * s + h];
-      kf[s] = __builtin_bit_cast(bf16x8, raw);
-    }
-  } else {
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) kf[s] = __builtin_bit_cast(bf16x8, zero);
-  }
-}
-
 // Values that are the same in every lane, moved into scalar registers (used where
 // the compiler cannot see the uniformity, e.g. arguments of non-inlined functions).
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -108,7 +83,8 @@ struct KeySource {
   const int* at = nullptr;
 };
 
-// load_k_block with the three descriptor fields it needs passed directly.  Rows before the first and
+// One 32-key block of K as MFMA A operands: lane (t, h) holds row kbase + t,
+// elements 16*s + 8*h .. +7 of it for k-step s.  Rows before the first and
 // past the last (N > 0) repeat that one: their logits are masked, or their sums not used.  No branch
 // around the loads: a wave that may have skipped them cannot tell how many of its loads are newer
 // than the block it waits for, and waits for all of them - the block that is to come included.
