@@ -438,6 +438,18 @@ __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const f
   FINCH_PHASE(7);
 }
 
+// Few rows of 64 channels: 128 registers are enough for a step, and two workgroups share a compute unit.
+constexpr bool own_lean(int d, int qbt, bool rot, bool doc) { return d == 64 && qbt == 2 && !rot && !doc; }
+
+// Calls f(number of row blocks) with the number as a constant if it is one of those a kernel for up
+// to QBT has the code without branches for; what f says, or false.
+template <int QBT, typename F>
+__device__ __forceinline__ bool own_whole(int qb, F f) {
+  if (qb == QBT) return f(std::integral_constant<int, QBT>{});
+  if (qb == QBT - 1) return f(std::integral_constant<int, QBT - 1>{});
+  return false;
+}
+
 // One step of one problem by the whole workgroup.  QBT = row blocks (of 32 prompt
 // rows) per pass over the keys the code is compiled for; prm.row_chunk <= 32 * QBT.
 // stages: 0 = scores only, 1 = scores, top-r and compaction.  `staged_q` names the
@@ -453,7 +465,7 @@ __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const f
 // and selects on the sum, so that all L arrive at the same indices on their own.
 // `step_probs` are the descriptors of this step, `epoch` counts the exchanges this
 // workgroup has been through in this launch; returns true if the step made one.
-template <int D, int QBT, bool ROT, bool DOC>
+template <int D, int QBT, bool ROT, bool DOC, bool LOOP>
 __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const finch_problem& pb, int slot,
                                               int stages, char* smem, const void*& staged_q,
                                               int& staged_rows, const finch_problem* step_probs,
@@ -511,6 +523,10 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     }
     __syncthreads();
   }
+
+  // (two workgroups a compute unit have no registers for it)
+  constexpr bool WHOLE = !own_lean(D, QBT, ROT, DOC) || LOOP;
+  auto whole = [](int qb, auto f) { return own_whole<QBT>(qb, f); };
 
   // Row chunks: the prompt rows first (they see every key, so they initialise all
   // scores), then, in DOC kernels, the rows of the chunk's own tokens, head by head
@@ -604,8 +620,25 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
       // In DOC kernels a pair none of whose rows sees the key block is left out (the
       // limits grow with the row, and a wave's key blocks come in ascending order, so a
       // row block that is left out once stays out).
+      // A block every row sees all of, once there are references (false: some logits lie too far
+      // above them; nothing has been added).
+      auto whole_block = [&](const bf16x8(&kf)[D / 16], auto qb) {
+        constexpr int QBC = decltype(qb)::value;
+        float z[QBC];
+#pragma unroll
+        for (int q = 0; q < QBC; ++q) z[q] = 0.f;
+        for_block_logits<D, QBC>(kf, lds_q, lane, [&](int q, int, float a) { z[q] += fast_exp2(__builtin_fmaf(a, sc, -m_run[q])); });
+        bool far = false;
+#pragma unroll
+        for (int q = 0; q < QBC; ++q) far |= !(z[q] <= 0x1p64f);
+        if (__any(far)) return false;
+#pragma unroll
+        for (int q = 0; q < QBC; ++q) z_run[q] += z[q];
+        return true;
+      };
       auto process = [&](const bf16x8(&kf)[D / 16], int blk) {
         const int kbase = blk << 5;
+        if (WHOLE && seeded && kbase + 32 <= min(N, lim0) && whole(QB, [&](auto qb) { return whole_block(kf, qb); })) return;
         auto pair_visible = [&](int q) { return !DOC || kbase < lim_hi(q + 1 < QB ? q + 1 : q); };
         f32x16 acc[QBT];
 #pragma unroll
@@ -695,23 +728,33 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
 #pragma unroll
           for (int v = 0; v < 16; ++v) u[v] += fast_exp2(__builtin_fmaf(a[v], sc, -L));
         };
-        auto pair_visible = [&](int q) { return !DOC || kbase < lim_hi(q + 1 < QB ? q + 1 : q); };
-        // pairs of row blocks, the vector work one pair behind the matrix work
-        f32x16 acc[QBT];
+        auto whole_block = [&](auto qb) {
+          constexpr int QBC = decltype(qb)::value;
+          float L[QBC];
 #pragma unroll
-        for (int q = 0; q < QBT + 2; q += 2) {
-          if (q < QBT && q < QB && pair_visible(q)) {
-            if (q + 1 < QB) {
-              mfma_block_pair_lds<D>(kf, lds_q, q, lane, acc[q], acc[q + 1]);
-            } else {
-              bf16x8 qf0[D / 16];
-              load_q_frags<D>(lds_q, q, lane, qf0);
-              acc[q] = mfma_block<D>(kf, qf0);
+          for (int q = 0; q < QBC; ++q) L[q] = lds_lse[q * 32 + t];
+          for_block_logits<D, QBC>(kf, lds_q, lane, [&](int q, int v, float a) { u[v] += fast_exp2(__builtin_fmaf(a, sc, -L[q])); });
+          return true;
+        };
+        if (!WHOLE || kbase + 32 > min(N, lim0) || !whole(QB, whole_block)) {
+          auto pair_visible = [&](int q) { return !DOC || kbase < lim_hi(q + 1 < QB ? q + 1 : q); };
+          // pairs of row blocks, the vector work one pair behind the matrix work
+          f32x16 acc[QBT];
+#pragma unroll
+          for (int q = 0; q < QBT + 2; q += 2) {
+            if (q < QBT && q < QB && pair_visible(q)) {
+              if (q + 1 < QB) {
+                mfma_block_pair_lds<D>(kf, lds_q, q, lane, acc[q], acc[q + 1]);
+              } else {
+                bf16x8 qf0[D / 16];
+                load_q_frags<D>(lds_q, q, lane, qf0);
+                acc[q] = mfma_block<D>(kf, qf0);
+              }
             }
-          }
-          if (q >= 2 && q - 2 < QB && pair_visible(q - 2)) {
-            tile_sums(acc[q - 2], q - 2);
-            if (q - 1 < QB) tile_sums(acc[q - 1], q - 1);
+            if (q >= 2 && q - 2 < QB && pair_visible(q - 2)) {
+              tile_sums(acc[q - 2], q - 2);
+              if (q - 1 < QB) tile_sums(acc[q - 1], q - 1);
+            }
           }
         }
         const float tot = fold16_over32(u, t);
@@ -775,16 +818,15 @@ __device__ __forceinline__ bool own_rows_may_stay(const finch_problem& pb, const
 
 // One launch = one step of every problem of a batch; workgroup b owns problem b.
 // ROT: the compaction re-positions the kept keys (prm.rope_pairing, ascending slots).
-// (Few rows of 64 channels: 128 registers are enough, and two workgroups share a compute unit.)
 template <int D, int QBT, bool ROT, bool DOC>
-__global__ __launch_bounds__(kOwnThreads, (D == 64 && QBT == 2 && !ROT && !DOC) ? 4 : 2) void owner_step_bf16(LaunchParams prm, int stages) {
+__global__ __launch_bounds__(kOwnThreads, own_lean(D, QBT, ROT, DOC) ? 4 : 2) void owner_step_bf16(LaunchParams prm, int stages) {
   extern __shared__ __align__(16) char smem[];
   const int p = own_slot_of(blockIdx.x, gridDim.x, stages ? prm.layer_group : 1);
   const finch_problem pb = prm.probs[p];
   const void* staged_q = nullptr;
   int staged_rows = 0;
   KeptRows kept;
-  own_step_body<D, QBT, ROT, DOC>(prm, pb, p, stages, smem, staged_q, staged_rows, prm.probs, 0, kept);
+  own_step_body<D, QBT, ROT, DOC, false>(prm, pb, p, stages, smem, staged_q, staged_rows, prm.probs, 0, kept);
 }
 
 // One launch = the whole chunk loop (Method: Document Segmentation): workgroup b
@@ -820,7 +862,7 @@ __global__ __launch_bounds__(kOwnThreads) void owner_loop_bf16(LaunchParams prm,
     // (rows in a cache that an earlier step has moved would be overwritten while they are still wanted)
     if (prm.stay_rows > 0 && s + 2 < n_steps && slot < step_first[s + 3] - step_first[s + 2] && (s == 0 || pb.c == 0 || kept.mapped))
       kept.stay = own_rows_may_stay(pb, prm.probs + step_first[s + 1] + slot, prm.probs + step_first[s + 2] + slot, prm.stay_rows);
-    if (own_step_body<D, QBT, ROT, DOC>(prm, pb, slot, /*stages=*/1, smem, staged_q, staged_rows, prm.probs + first,
+    if (own_step_body<D, QBT, ROT, DOC, true>(prm, pb, slot, /*stages=*/1, smem, staged_q, staged_rows, prm.probs + first,
                                         epoch, kept))
       ++epoch;
     // the rows this step wrote are the next step's cache: complete before it reads
