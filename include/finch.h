@@ -266,7 +266,8 @@ finch_status finch_schedule_mode(int64_t n_cont, int32_t m, int64_t k, int32_t m
  * step - or, in finch_loop, of all steps - back to back (bf16: matrix instructions;
  * fp32: fp64 matrix instructions, meant for small problems); batches it cannot run fail with
  * FINCH_ERR_UNSUPPORTED.  AUTO (default) takes OWNER for bf16 when the batch has enough
- * problems to fill the chip's compute units in whole rounds, for fp32 when no problem
+ * problems to fill the chip's compute units in whole rounds, at least 69 % of them (finch_loop of
+ * four steps and more with few candidates: from a quarter of them on), for fp32 when no problem
  * has more than 4096 candidates or 64 prompt rows (few problems of head_dim 64 with at most 5
  * rows: 1024 candidates); for bf16 batches of at most half as many problems as compute units,
  * mostly, a launch per step in which several workgroups share a problem; else SEPARATE. */

@@ -392,7 +392,11 @@ bool repositioning(const finch_ctx* ctx) {
 
 // One workgroup per problem pays when the problems fill the chip's CUs in whole
 // rounds (mostly one workgroup per CU at a time): AUTO takes that path when the
-// last round would be at least 85 % full.
+// rounds would be at least 69 % full (layer groups, slots by rank, and several rounds of more than
+// 2048 candidates - 360 problems of 192 rows, 5120 candidates 366 us, 342 per stage -: 85 %).  One step of 192
+// problems of 192 rows, 512 / 1024 / 2048 candidates: 29 / 41 / 69 us, and 38 / 55 / 83 with one
+// kernel per stage; 64 rows of 64 channels 16 / 21 / 32 and 24 / 29 / 42; 128 problems (50 %) of 192
+// rows, 1024 candidates 38 and 35.
 bool owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n) {
   if (!pl.own_ok || n <= 0) return false;
   // slots by score rank: the workgroup sorts its kept rows in LDS (their indices and one
@@ -426,7 +430,34 @@ bool owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n) {
   }
   const int64_t cu = ctx->n_cu > 0 ? ctx->n_cu : 256;
   const int64_t rounds = (n + cu - 1) / cu;
-  return static_cast<int64_t>(n) * 100 >= rounds * cu * 85;
+  const bool early = ctx->layer_group <= 1 && ctx->repos.order == FINCH_ORDER_ASCENDING && (rounds == 1 || pl.n_max <= 2048);
+  const int fill = early ? 69 : 85;
+  return static_cast<int64_t>(n) * 100 >= rounds * cu * fill;
+}
+
+// Whether a whole loop that does not fill the chip is still faster as one launch with one workgroup
+// per slot, where kept rows stay in place and there is one launch instead of one and more a step, than
+// step by step; `slots` = problems of a step, `steps` = steps of a slot, both on average.  In one
+// round of workgroups a problem takes as long as it takes, however few there are, and step by step a
+// step gets cheaper with fewer problems, so the line moves with the length of a step, its candidates,
+// and with the steps before the last two, which alone leave rows in place.  Measured (us here : step by
+// step).  Loops over 16384 tokens, 192 rows of 128 channels, up to 1024 candidates, 32 / 64 / 96 slots
+// 773:612, 788:846, 794:1148; 4608 candidates, 96 / 128 slots 395:364, 423:411; 32 rows of 128, 4096
+// candidates and 1024 kept, 64 / 96 slots 482:382, 509:543; 640 rows (several chunks), 1536
+// candidates, 96 / 128 slots 1757:1703, 1765:1816.  Four steps of 512, 1024, 2048 tokens, 128 slots,
+// 192 rows 100:139, 159:190, 301:323, 32 rows 69:86, 113:129, 227:236; 64 slots, 192 rows 94:89,
+// 146:131, 255:186; 72 slots of 64 channels, 64 rows 49:68, 71:82, 116:122.  One step, 128 slots
+// 38:35, 62:59.  (Layer groups keep to the launches that wait for nobody.)
+bool loop_owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n_slots, int32_t slots, int32_t steps) {
+  const int64_t cu = ctx->n_cu > 0 ? ctx->n_cu : 256;
+  if (ctx->cfg.dtype != FINCH_BF16 || ctx->step_path != FINCH_PATH_AUTO || ctx->layer_group > 1 ||
+      ctx->slice_keys != finch::kDefaultSliceKeys || !pl.own_ok || ctx->repos.order != FINCH_ORDER_ASCENDING || steps < 4)
+    return false;
+  const int64_t rounds = (n_slots + cu - 1) / cu;
+  if (rounds > 1) return int64_t{100} * slots >= rounds * cu * 69;  // (384 slots of 64 channels 961:1486)
+  const bool many_rows = pl.rows_max > finch::kOwnerMaxRowChunk, narrow = ctx->cfg.head_dim == 64;
+  const int64_t few = many_rows ? cu * 5 / 8 : narrow || steps >= 10 ? cu / 4 : cu * 3 / 8;
+  return slots >= std::max<int64_t>(few, pl.n_max / 32);
 }
 
 // Whether one kernel per stage is the faster launch of a batch that several workgroups per
@@ -1092,7 +1123,7 @@ finch_status finch_loop(finch_ctx* ctx, const finch_problem* host_desc, const fi
   if ((st = check_workspace(pl, ws, ws_bytes)) != FINCH_OK) return st;
   if (n_desc == 0 || pl.tiles_max == 0) return FINCH_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (owner_wanted(ctx, pl, n_slots)) {
+  if (owner_wanted(ctx, pl, n_slots) || loop_owner_wanted(ctx, pl, n_slots, n_desc / n_steps, n_desc / std::max(1, n_slots))) {
     LaunchParams p = make_params(ctx, dev_desc, n_desc, pl, ws);
     p.row_chunk = pl.own_row_chunk;
     p.lds_bytes = static_cast<uint32_t>(pl.own_lds);

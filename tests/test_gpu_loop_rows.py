@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import paper_2408_00167_amd as F
+from paper_2408_00167_amd.driver import ChunkLoop
 
 pytestmark = pytest.mark.gpu
 
@@ -98,3 +99,28 @@ def test_loop_leaves_what_single_steps_leave(name, d, group, n_que):
         fin.close()
     for n, (a, b) in enumerate(zip(*left)):
         assert torch.equal(a.contiguous().view(torch.uint8), b.contiguous().view(torch.uint8)), f"{name}: buffer {n} differs"
+
+
+@pytest.mark.parametrize("slots,lengths", [(63, [4]), (64, [4]), (64, [4, 2]), (160, [3]), (177, [3, 1]), (300, [2])])
+def test_routes_of_loops_that_do_not_fill_the_chip(slots, lengths):
+    """AUTO takes the one-launch loop from some number of slots on: the same results either side."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(slots)
+    d, group, n_que, chunk, steps = 64, 2, 5, 160, max(lengths)
+    rand = lambda *shape: torch.randn(*shape, generator=g, device="cuda", dtype=torch.bfloat16)
+    problems = [dict(Q=rand(group * n_que, d), K=rand(chunk * lengths[p % len(lengths)] - 7, d), V=rand(chunk * lengths[p % len(lengths)] - 7, d),
+                     n_que=n_que, budget=60) for p in range(slots)]
+    left = []
+    for path in (F.FINCH_PATH_AUTO, F.FINCH_PATH_OWNER):
+        fin = F.Finch(F.FINCH_BF16, d, group)
+        fin.set_step_path(path)
+        loop = ChunkLoop(fin, problems, chunk)
+        loop.run()
+        torch.cuda.synchronize()
+        left.append([t.cpu() for t in (*loop.kbuf, *loop.vbuf, loop.scores, loop.idx)])
+        fin.close()
+    worst = float(((left[0][4] - left[1][4]).abs() / left[1][4].clamp_min(1e-30)).max())
+    assert worst < 1e-5, f"scores of the routes differ by {worst:.1e}"  # fp32 sums in another order
+    for a, b in zip(left[0][:4] + left[0][5:], left[1][:4] + left[1][5:]):
+        rows = (a != b).reshape(a.shape[0], -1).any(dim=1).float().mean() if a.dim() == 2 and a.shape[0] > 1 else (a != b).float().mean()
+        assert float(rows) < 1e-3  # (two nearly equal scores may change places)
