@@ -137,6 +137,40 @@ __device__ __forceinline__ void stage_q(const void* q, int R, int row0, int rows
   }
 }
 
+// The same in two halves, for chunks of at most 256 rows of 8 waves: a thread's pieces are requested into
+// the registers of a key block, and go to LDS when the chunk's turn has come.  Pieces past row R
+// repeat the last one (R > row0) and are zeros in LDS.
+template <int D, int NT>
+__device__ __forceinline__ void hold_q(const void* q, int R, int row0, int RC, int tid, bf16x8 (&held)[D / 16]) {
+  constexpr int kSegs = D / 8;
+  static_assert(256 * kSegs <= NT * (D / 16), "a key block's registers hold the chunk");
+  const FINCH_GLOBAL u32x4* src = as_global<u32x4>(q) + static_cast<size_t>(row0) * kSegs;
+  const int last = min(RC, R - row0) * kSegs - 1;
+#pragma unroll
+  for (int u = 0; u < D / 16; ++u) {
+    const u32x4 raw = src[min(tid + u * NT, last)];
+    held[u] = __builtin_bit_cast(bf16x8, raw);
+  }
+}
+template <int D, int NT>
+__device__ __forceinline__ void stage_q_held(const bf16x8 (&held)[D / 16], int R, int row0, int rows, char* lds_q, int tid) {
+  constexpr int kSegs = D / 8;
+  constexpr int kStride = D * 2 + 16;
+#pragma unroll
+  for (int u = 0; u < D / 16; ++u) {
+    const int i = tid + u * NT, row = i / kSegs, seg = i - row * kSegs;
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    const u32x4 raw = __builtin_bit_cast(u32x4, held[u]);
+    if (row < rows) *reinterpret_cast<u32x4*>(lds_q + row * kStride + seg * 16) = row0 + row < R ? raw : zero;
+  }
+}
+
+template <int D>
+__device__ __forceinline__ void copy_block(const bf16x8 (&from)[D / 16], bf16x8 (&to)[D / 16]) {
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) to[s] = from[s];
+}
+
 // B operands (prompt rows qb*32 .. +31) from LDS.
 template <int D>
 __device__ __forceinline__ void load_q_frags(const char* lds_q, int qb, int lane,

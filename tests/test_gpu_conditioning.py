@@ -176,3 +176,19 @@ def test_steps_without_any_row(dtype, beside):
             assert torch.equal(t["k_out"][:r], t["k_cache"][:r]) and torch.equal(t["v_out"][:r], t["v_cache"][:r])
     H.validate_single_step(ts[3:], "beside")
     fin.close()
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("m,n_que", [(20, 3), (32, 140), (130, 1), (257, 3), (511, 40), (769, 65)])
+def test_rows_held_from_chunk_to_chunk(m, n_que, d):
+    """The next chunk's rows are requested while the last key block of the present chunk is worked on:
+    chunks of 32 to 256 rows, ragged last ones, from prompt to document rows and from head to head,
+    passes of fewer key blocks than waves and of more."""
+    fin = F.Finch(F.FINCH_BF16, d, 4)
+    specs = [dict(n_que=n_que, c=0, m=m, r=max(1, m // 3), doc_rows=True),
+             dict(n_que=n_que, c=291, m=m, r=100, doc_rows=True),
+             dict(n_que=n_que, c=3, m=max(1, m - 1), r=3, doc_rows=True, no_prompt=True)]
+    batch, ts = H.single_step_case(fin, specs, torch.bfloat16, d, 4, seed=31 * m + d)
+    fin.step(batch)
+    H.validate_single_step(ts, f"held rows d={d} m={m} n_que={n_que}")
+    fin.close()
