@@ -201,28 +201,30 @@ __device__ __forceinline__ float2 merge_records(const float2* rec, int stride, i
   return make_float2(m, z);
 }
 
-// 64 keys x 32 rows of raw dot products, or the first 32 keys only.  The prompt rows' operands
-// are read once for both halves.
-template <int D>
-__device__ __forceinline__ void mfma_two(const bf16x8 (&k0)[D / 16], const bf16x8 (&k1)[D / 16], const char* qrow, bool two,
-                                         f32x16& a0, f32x16& a1) {
+// 64 keys x 32 rows of raw dot products, or (not TWO) the first 32 keys only.  The prompt rows'
+// operands are read once for both halves.
+template <int D, bool TWO>
+__device__ __forceinline__ void mfma_rows(const bf16x8 (&k0)[D / 16], const bf16x8 (&k1)[D / 16], const char* qrow, f32x16& a0,
+                                          f32x16& a1) {
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   bf16x8 qf[D / 16];
 #pragma unroll
   for (int s = 0; s < D / 16; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qrow + 32 * s);
   a0 = zero;
   a1 = zero;
-  if (two) {
 #pragma unroll
-    for (int s = 0; s < D / 16; ++s) {
-      a0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[s], qf[s], a0, 0, 0, 0);
-      a1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[s], qf[s], a1, 0, 0, 0);
-    }
-  } else {
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) a0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[s], qf[s], a0, 0, 0, 0);
+  for (int s = 0; s < D / 16; ++s) {
+    a0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[s], qf[s], a0, 0, 0, 0);
+    if (TWO) a1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[s], qf[s], a1, 0, 0, 0);
   }
 }
+
+// Key blocks a wave takes at a time, of a slice of kb that kl waves share: three where that is all it
+// has - a third one loaded when the first two were done with stood in both passes' way, as its
+// first two had to be loaded again in pass 2 - else two, which read the rows' operands once.
+// (32 problems of 128 channels and 256 rows, 2944 candidates: 37.0 us a step, 41.7 by twos; 4992: 46.7
+// and 50.6.  Five blocks a wave, 10192 candidates: 85.5 by threes, 82.3 by twos.)
+__device__ __forceinline__ int blocks_at_a_time(int kb, int kl) { return kb <= 3 * kl ? 3 : 2; }
 
 __device__ __forceinline__ void mask_keys(f32x16& a, int kbase, int h, int lim) {
   if (kbase + 32 > lim) {
@@ -291,8 +293,8 @@ __global__ __launch_bounds__(kCluThreads) void cluster_step_bf16(LaunchParams pr
       staged_row0 = row0;
     };
     if (ws < used) {
-      bf16x8 k0[D / 16], k1[D / 16];
-      // slice whose key blocks are in k0, k1 (if a wave has no more than two), or whose tiles are held
+      bf16x8 k0[D / 16], k1[D / 16], k2[D / 16];
+      // slice whose key blocks are in k0, k1, k2 (if a wave has no more than three), or whose tiles are held
       int held = -1;
       f32x16 tile[HELD ? kHeldTiles : 1];     // exp2(logit - tile_ref), tile_ref per lane
       float tile_ref[HELD ? kHeldTiles : 1];
@@ -320,6 +322,7 @@ __global__ __launch_bounds__(kCluThreads) void cluster_step_bf16(LaunchParams pr
           } else {
             if (b < sl.b1) load_k_rows<D>(ks, lim, b << 5, lane, k0);
             if (b + kl < sl.b1) load_k_rows<D>(ks, lim, (b + kl) << 5, lane, k1);
+            if (kb <= 3 * kl && b + 2 * kl < sl.b1) load_k_rows<D>(ks, lim, (b + 2 * kl) << 5, lane, k2);
           }
           stage(row0, rows);
           __syncthreads();
@@ -363,52 +366,61 @@ __global__ __launch_bounds__(kCluThreads) void cluster_step_bf16(LaunchParams pr
               }
             }
           } else {
-            bool first = true;
-            do {
-              const bool two = b + kl < sl.b1;
+            auto keep = [&](int q, float m, float z, bool first) {
+              const float m2 = __shfl_xor(m, 32);
+              const float z2 = __shfl_xor(z, 32);
+              merge_stats(m, z, m2, z2);
+              if (h == 0) {
+                if (!first) {
+                  const float2 o = out[q * 32 + t];
+                  merge_stats(m, z, o.x, o.y);
+                }
+                out[q * 32 + t] = make_float2(m, z);
+              }
+            };
+            // key block blk (and blk + kl) against this wave's row blocks
+            auto blocks = [&](const bf16x8(&kx)[D / 16], const bf16x8(&ky)[D / 16], int blk, bool first, auto two) {
+              constexpr bool TWO = decltype(two)::value;
+              const bool ragged = (blk + (TWO ? kl : 0) + 1) << 5 > lim;
               for (int q = q_lo; q < q_hi; ++q) {
-                float m = -kInf, z = 0.f;
-                if (b < sl.b1) {
-                  f32x16 a0, a1;
-                  mfma_two<D>(k0, k1, lds_q + (q * 32 + t) * kStride + 16 * h, two, a0, a1);
-                  mask_keys(a0, b << 5, h, lim);
-                  float bm = fmaxf(a0[0], a0[1]);
-#pragma unroll
-                  for (int v = 2; v < 16; v += 2) bm = fmaxf(fmaxf(bm, a0[v]), a0[v + 1]);
-                  if (two) {
-                    mask_keys(a1, (b + kl) << 5, h, lim);
-#pragma unroll
-                    for (int v = 0; v < 16; v += 2) bm = fmaxf(fmaxf(bm, a1[v]), a1[v + 1]);
-                  }
-                  m = bm * sc;
-                  const float mu = (m == -kInf) ? 0.f : m;
-#pragma unroll
-                  for (int v = 0; v < 16; ++v) z += fast_exp2(__builtin_fmaf(a0[v], sc, -mu));
-                  if (two) {
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) z += fast_exp2(__builtin_fmaf(a1[v], sc, -mu));
-                  }
+                f32x16 a0, a1;
+                mfma_rows<D, TWO>(kx, ky, lds_q + (q * 32 + t) * kStride + 16 * h, a0, a1);
+                if (ragged) {
+                  mask_keys(a0, blk << 5, h, lim);
+                  if (TWO) mask_keys(a1, (blk + kl) << 5, h, lim);
                 }
-                const float m2 = __shfl_xor(m, 32);
-                const float z2 = __shfl_xor(z, 32);
-                merge_stats(m, z, m2, z2);
-                if (h == 0) {
-                  if (!first) {
-                    const float2 o = out[q * 32 + t];
-                    merge_stats(m, z, o.x, o.y);
-                  }
-                  out[q * 32 + t] = make_float2(m, z);
+                float bm = fmaxf(a0[0], a0[1]);
+#pragma unroll
+                for (int v = 2; v < 16; v += 2) bm = fmaxf(fmaxf(bm, a0[v]), a0[v + 1]);
+                if (TWO) {
+#pragma unroll
+                  for (int v = 0; v < 16; v += 2) bm = fmaxf(fmaxf(bm, a1[v]), a1[v + 1]);
                 }
+                const float m = bm * sc;
+                const float mu = (m == -kInf) ? 0.f : m;
+                float z = 0.f;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) z += fast_exp2(__builtin_fmaf(a0[v], sc, -mu));
+                if (TWO) {
+#pragma unroll
+                  for (int v = 0; v < 16; ++v) z += fast_exp2(__builtin_fmaf(a1[v], sc, -mu));
+                }
+                keep(q, m, z, first);
               }
-              first = false;
-              b += 2 * kl;
-              if (b < sl.b1) {
-                load_k_rows<D>(ks, lim, b << 5, lane, k0);
-                if (b + kl < sl.b1) load_k_rows<D>(ks, lim, (b + kl) << 5, lane, k1);
-              }
-            } while (b < sl.b1);
+            };
+            if (b >= sl.b1)
+              for (int q = q_lo; q < q_hi; ++q) keep(q, -kInf, 0.f, true);
+            const int turn = blocks_at_a_time(kb, kl) * kl;
+            for (bool first = true; b < sl.b1; first = false) {
+              if (b + kl < sl.b1) blocks(k0, k1, b, first, std::true_type{});
+              else blocks(k0, k0, b, first, std::false_type{});
+              if (turn == 3 * kl && b + 2 * kl < sl.b1) blocks(k2, k2, b + 2 * kl, false, std::false_type{});
+              b += turn;
+              if (b < sl.b1) load_k_rows<D>(ks, lim, b << 5, lane, k0);
+              if (b + kl < sl.b1) load_k_rows<D>(ks, lim, (b + kl) << 5, lane, k1);
+            }
           }
-          held = (HELD || (kb <= 2 * kl && R <= RC)) ? s1 : -1;
+          held = (HELD || (kb <= 3 * kl && R <= RC)) ? s1 : -1;
           if (met) break;  // (only the tiles were wanted)
           __syncthreads();
           for (int i = tid; i < rows; i += kCluThreads) {
@@ -448,6 +460,7 @@ __global__ __launch_bounds__(kCluThreads) void cluster_step_bf16(LaunchParams pr
         if (!HELD && held != ws) {
           if (b < sl.b1) load_k_rows<D>(ks, lim, b << 5, lane, k0);
           if (b + kl < sl.b1) load_k_rows<D>(ks, lim, (b + kl) << 5, lane, k1);
+          if (kb <= 3 * kl && b + 2 * kl < sl.b1) load_k_rows<D>(ks, lim, (b + 2 * kl) << 5, lane, k2);
         }
         stage(row0, rows);
         // every row's log-sum-exp: parts of the S records side by side, then merged
@@ -524,8 +537,8 @@ __global__ __launch_bounds__(kCluThreads) void cluster_step_bf16(LaunchParams pr
           const float tot = fold16_over32(u, t);
           if (nt > 0 && (t & 1) == 0) o[nt > j1 ? 32 : 0] = tot;
         } else {
-        while (b < sl.b1) {
-            const bool two = b + kl < sl.b1;
+          auto blocks = [&](const bf16x8(&kx)[D / 16], const bf16x8(&ky)[D / 16], int blk, auto two) {
+            constexpr bool TWO = decltype(two)::value;
             float u0[16], u1[16];
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -534,28 +547,31 @@ __global__ __launch_bounds__(kCluThreads) void cluster_step_bf16(LaunchParams pr
             }
             for (int q = q_lo; q < q_hi; ++q) {
               f32x16 a0, a1;
-              mfma_two<D>(k0, k1, lds_q + (q * 32 + t) * kStride + 16 * h, two, a0, a1);
+              mfma_rows<D, TWO>(kx, ky, lds_q + (q * 32 + t) * kStride + 16 * h, a0, a1);
               const float lse = lds_lse[q * 32 + t];
 #pragma unroll
-              for (int v = 0; v < 16; ++v) u0[v] += fast_exp2(__builtin_fmaf(a0[v], sc, -lse));
-              if (two) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) u1[v] += fast_exp2(__builtin_fmaf(a1[v], sc, -lse));
+              for (int v = 0; v < 16; ++v) {
+                u0[v] += fast_exp2(__builtin_fmaf(a0[v], sc, -lse));
+                if (TWO) u1[v] += fast_exp2(__builtin_fmaf(a1[v], sc, -lse));
               }
             }
-            float* const o = ksum + (rq * kb + (b - sl.b0)) * 32 + acc_key(t >> 1, h);
+            float* const o = ksum + (rq * kb + (blk - sl.b0)) * 32 + acc_key(t >> 1, h);
             const float s0 = fold16_over32(u0, t);
             if ((t & 1) == 0) *o = row0 == 0 ? s0 : *o + s0;
-            if (two) {
+            if (TWO) {
               const float s2 = fold16_over32(u1, t);
               float* const o1 = o + kl * 32;
               if ((t & 1) == 0) *o1 = row0 == 0 ? s2 : *o1 + s2;
             }
-            b += 2 * kl;
-            if (b < sl.b1) {
-              load_k_rows<D>(ks, lim, b << 5, lane, k0);
-              if (b + kl < sl.b1) load_k_rows<D>(ks, lim, (b + kl) << 5, lane, k1);
-            }
+          };
+          const int turn = blocks_at_a_time(kb, kl) * kl;
+          while (b < sl.b1) {
+            if (b + kl < sl.b1) blocks(k0, k1, b, std::true_type{});
+            else blocks(k0, k0, b, std::false_type{});
+            if (turn == 3 * kl && b + 2 * kl < sl.b1) blocks(k2, k2, b + 2 * kl, std::false_type{});
+            b += turn;
+            if (b < sl.b1) load_k_rows<D>(ks, lim, b << 5, lane, k0);
+            if (b + kl < sl.b1) load_k_rows<D>(ks, lim, (b + kl) << 5, lane, k1);
           }
         }
         __syncthreads();

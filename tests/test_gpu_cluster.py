@@ -313,3 +313,27 @@ def test_replays_of_a_captured_step():
         for a, b in zip([t[k] for t in ts for k in ("scores", "idx", "k_out", "v_out")], want):
             assert torch.equal(a, b), i
     fin.close()
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("blocks,n_que", [(12, 64), (17, 64), (24, 50), (24, 96), (25, 64)])
+def test_three_key_blocks_a_wave(blocks, n_que, d):
+    """Eight slices of 12 to 25 key blocks: waves with three blocks in registers beside waves with two,
+    one chunk of rows and two (where pass 2 loads them again), the first size past it, and ragged
+    ends; the same bits where workgroups do others' slices in between."""
+    n = 8 * 32 * blocks
+    specs = [dict(n_que=n_que, c=100, m=n - 100 - 33 * (p % 5), r=200 + p) for p in range(32)]
+    want = None
+    for ticks in (20_000_000, 0):
+        fin = F.Finch(F.FINCH_BF16, d, 4)
+        F.finch_set_option(fin.ctx, F.FINCH_OPT_LAYER_WAIT_TICKS, ticks)
+        batch, ts = H.single_step_case(fin, specs, torch.bfloat16, d, 4, seed=blocks)
+        fin.step(batch)
+        assert fin.workspace_status() == 0
+        got = [t[k].clone() for t in ts for k in ("scores", "idx", "k_out", "v_out")]
+        if want is None:
+            want = got
+            H.validate_single_step(ts, f"{blocks} blocks, {n_que} prompt tokens, d={d}")
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
+        fin.close()
