@@ -40,7 +40,7 @@ MEASURED_TRAFFIC = {"C4": {
     "colsum": 2.0 * 159516.2 * 1024 + 4780.0 * 1024,
     "select": 2.0 * 2557.3 * 1024 + 728.0 * 1024,
     "gather": 2.0 * 47163.0 * 1024 + 92928.0 * 1024,
-    "owner": 2.0 * 11133278.1 * 1024 + 3149952.0 * 1024,   # one launch = the whole loop
+    "owner": 2.0 * 9503102.2 * 1024 + 531072.0 * 1024,   # one launch = the whole loop
 }}
 
 
