@@ -482,7 +482,13 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   // keep it in registers through every phase)
   int tid_ = threadIdx.x;
   asm volatile("" : "+v"(tid_));
-  const int tid = tid_, lane = tid & 63, wave = tid >> 6;
+  const int tid = tid_, lane = tid & 63;
+  // (DOC kernels: in a scalar register, so that the loops over a wave's key blocks are uniform.  A key buffer
+  // there lives on past both exits of such a loop; with a loop that lanes may leave at different times the
+  // compiler keeps what either exit hands on in registers of its own, 32 more than there are: up to
+  // 56 spilled, 789 us in place of 604 for the loop of 256 problems, 200-token chunks, with
+  // re-positioning, 808 and 743 for a step of 256 problems of 512 + 1024 candidates.)
+  const int wave = DOC ? uni(tid >> 6) : tid >> 6;
   const int t = lane & 31, h = lane >> 5;
   constexpr int kStride = D * 2 + 16;
   const int RC = prm.row_chunk;
@@ -551,8 +557,8 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   // blocks long, a buffer is never left idle: beside the last key block of pass 1 the first of
   // pass 2 is under way, beside the last of pass 2 this thread's pieces of the next chunk's
   // rows (a thread's share of 256 rows is exactly as large as its share of a key block).
-  // 256 problems, 1024-token chunks, 17 chunks of rows a step: staging them was 67 of 617 us
-  // a step, the loop takes 2180 us in place of 2260.
+  // 256 problems of 192 rows, 1024-token chunks, 17 chunks of rows a step: the loop takes 2216 us,
+  // 2346 where every chunk asks for its rows when its turn has come (64 channels, 256 rows: 1569 and 1669).
   bf16x8 ka[D / 16], kb[D / 16];
   for (int ch = 0; ch < n_chunks; ++ch) {
     const RowChunk rc = row_chunk(ch);

@@ -192,3 +192,20 @@ def test_rows_held_from_chunk_to_chunk(m, n_que, d):
     fin.step(batch)
     H.validate_single_step(ts, f"held rows d={d} m={m} n_que={n_que}")
     fin.close()
+
+
+@pytest.mark.parametrize("pairing", ["half", "interleaved"])
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("m,n_que", [(40, 3), (100, 30), (180, 40), (301, 64), (700, 17)])
+def test_document_rows_with_repositioned_keys(m, n_que, d, pairing):
+    """Both options in one step, in the kernels for 2, 4, 6 and 8 row blocks: chunks of rows held ahead in
+    registers beside the compaction that turns keys."""
+    fin = F.Finch(F.FINCH_BF16, d, 4)
+    fin.set_reposition({"half": F.FINCH_ROPE_HALF, "interleaved": F.FINCH_ROPE_INTERLEAVED}[pairing], F.FINCH_ORDER_ASCENDING, 10000.0)
+    specs = [dict(n_que=n_que, c=0, m=m, r=max(1, m // 3), doc_rows=True),
+             dict(n_que=n_que, c=150, m=m, r=100, doc_rows=True),
+             dict(n_que=n_que, c=33, m=m - 9, r=30, doc_rows=True, no_prompt=True)]
+    batch, ts = H.single_step_case(fin, specs, torch.bfloat16, d, 4, seed=17 * m + d)
+    fin.step(batch)
+    H.validate_single_step(ts, f"document rows, turned keys d={d} m={m}", repos=(pairing, "ascending", 10000.0))
+    fin.close()

@@ -27,7 +27,14 @@ FORMS = {
     "rank": dict(slots=GROWING, rope=(F.FINCH_ROPE_INTERLEAVED, F.FINCH_ORDER_RANK)),
     "layer": dict(slots=GROWING[:1] * 4, layer=2),
     "doc_rows": dict(slots=GROWING, doc=True),
+    "doc_rows_rope": dict(slots=GROWING, doc=True, rope=(F.FINCH_ROPE_HALF, F.FINCH_ORDER_ASCENDING)),
+    "layer_rope": dict(slots=GROWING[:1] * 4, layer=2, rope=(F.FINCH_ROPE_INTERLEAVED, F.FINCH_ORDER_ASCENDING)),
 }
+# (kernels for 2, 4 and 6 row blocks; GROWING's chunks take the one for 8)
+for _m in (40, 100, 180):
+    FORMS[f"doc_rows_rope_{_m}"] = dict(slots=[(17, [(_m, 20), (_m, 41), (_m, 45), (_m - 7, 66)])], doc=True,
+                                        rope=(F.FINCH_ROPE_HALF, F.FINCH_ORDER_ASCENDING))
+
 
 
 def _case(form, d, group, n_que, seed):
