@@ -58,7 +58,7 @@ enum Need : unsigned {
 };
 
 struct Plan {
-  int32_t n_max = 0, rows_max = 0, rpad_max = 0, r_max = 0, tiles_max = 0, row_chunk = 32;
+  int32_t n_max = 0, m_max = 0, rows_max = 0, rpad_max = 0, r_max = 0, tiles_max = 0, row_chunk = 32;
   int32_t score_stride = 0;
   bool own_ok = false;    // the batch can run with one workgroup per problem
   bool has_doc = false;   // some problem takes rows from the chunk's own tokens (q_doc)
@@ -143,6 +143,7 @@ finch_status make_plan(const finch_ctx* ctx, const finch_problem* hd, int32_t n_
       if (dr > R) R = dr;
     }
     if (N > n_max) n_max = N;
+    if (pb.m > pl.m_max) pl.m_max = pb.m;
     if (R > rows_max) rows_max = R;
     const int64_t rr = pb.r < N ? pb.r : N;
     if (rr > r_max) r_max = rr;
@@ -392,12 +393,32 @@ bool repositioning(const finch_ctx* ctx) {
 
 // One workgroup per problem pays when the problems fill the chip's CUs in whole
 // rounds (mostly one workgroup per CU at a time): AUTO takes that path when the
-// rounds would be at least 69 % full (layer groups, slots by rank, and several rounds of more than
-// 2048 candidates - 360 problems of 192 rows, 5120 candidates 366 us, 342 per stage -: 85 %).  One step of 192
-// problems of 192 rows, 512 / 1024 / 2048 candidates: 29 / 41 / 69 us, and 38 / 55 / 83 with one
-// kernel per stage; 64 rows of 64 channels 16 / 21 / 32 and 24 / 29 / 42; 128 problems (50 %) of 192
-// rows, 1024 candidates 38 and 35.
-bool owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n) {
+// rounds would be at least 85 % full, and from 69 % on (this) for
+//  - one round of up to 8192 candidates, 12288 from 78 % on: beyond, the slices of the kernels per stage fill
+//    the chip better.  Time here : per stage, whole steps, 32 to 256 rows: 0.53 to 0.97 up to 8192; 177
+//    problems of 9600 0.93 to 1.15, of 16384 1.04 to 1.24; 205 problems of 12000 0.79 to 1.01.  Any number
+//    for 225 to 256 and more than 384 rows of 128 channels, of which the kernels per stage hold one
+//    workgroup a CU or spill: 9600 to 16384 candidates 0.62 to 0.98;
+//  - several rounds of up to 2048 candidates: 0.52 to 1.04; 354 problems, 192 rows, 4096 candidates 1.08.
+//    Scores alone, without top-r and copies to save launches of, not with 65 to 256 rows of 64 channels:
+//    0.94 to 1.14;
+//  - where rows come in two chunks of which the second is short and the kernels per stage take them in one (257 to
+//    320, 384 of 64 channels): one round of whole steps of up to 1024 candidates, 0.70 to 0.96; 2048 1.0 to 1.06, 8192 1.04
+//    to 1.17.  Several rounds and scores alone, 128 channels, up to 600 0.72 to 0.98; 64 channels 1.05 to 1.42.
+// (Layer groups and slots by rank: 85 %.)
+bool owner_from_69(const finch_ctx* ctx, const Plan& pl, int32_t n, int64_t rounds, int64_t cu, bool stages) {
+  if (ctx->layer_group > 1 || ctx->repos.order != FINCH_ORDER_ASCENDING) return false;
+  const bool narrow = ctx->cfg.head_dim == 64, one_chunk = pl.rows_max <= finch::kOwnerMaxRowChunk;
+  if (!one_chunk && pl.rows_max <= (narrow ? 384 : 320)) {
+    if (rounds == 1 && stages) return pl.n_max <= 1024;
+    return !narrow && pl.n_max <= 600;
+  }
+  if (rounds > 1) return pl.n_max <= 2048 && (stages || !narrow || pl.rows_max <= 64 || !one_chunk);
+  if (!narrow && (one_chunk ? pl.rows_max > 224 : pl.rows_max > 384)) return true;
+  return pl.n_max <= (int64_t{100} * n >= cu * 78 && (one_chunk || !narrow) ? 12288 : 8192);
+}
+
+bool owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n, bool stages) {
   if (!pl.own_ok || n <= 0) return false;
   // slots by score rank: the workgroup sorts its kept rows in LDS (their indices and one
   // 64-bit record each, padded to a power of two of at least 64, behind the selection scratch), and a
@@ -430,34 +451,60 @@ bool owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n) {
   }
   const int64_t cu = ctx->n_cu > 0 ? ctx->n_cu : 256;
   const int64_t rounds = (n + cu - 1) / cu;
-  const bool early = ctx->layer_group <= 1 && ctx->repos.order == FINCH_ORDER_ASCENDING && (rounds == 1 || pl.n_max <= 2048);
-  const int fill = early ? 69 : 85;
-  return static_cast<int64_t>(n) * 100 >= rounds * cu * fill;
+  return static_cast<int64_t>(n) * 100 >= rounds * cu * (owner_from_69(ctx, pl, n, rounds, cu, stages) ? 69 : 85);
 }
 
 // Whether a whole loop that does not fill the chip is still faster as one launch with one workgroup
-// per slot, where kept rows stay in place and there is one launch instead of one and more a step, than
-// step by step; `slots` = problems of a step, `steps` = steps of a slot, both on average.  In one
-// round of workgroups a problem takes as long as it takes, however few there are, and step by step a
-// step gets cheaper with fewer problems, so the line moves with the length of a step, its candidates,
-// and with the steps before the last two, which alone leave rows in place.  Measured (us here : step by
-// step).  Loops over 16384 tokens, 192 rows of 128 channels, up to 1024 candidates, 32 / 64 / 96 slots
-// 773:612, 788:846, 794:1148; 4608 candidates, 96 / 128 slots 395:364, 423:411; 32 rows of 128, 4096
-// candidates and 1024 kept, 64 / 96 slots 482:382, 509:543; 640 rows (several chunks), 1536
-// candidates, 96 / 128 slots 1757:1703, 1765:1816.  Four steps of 512, 1024, 2048 tokens, 128 slots,
-// 192 rows 100:139, 159:190, 301:323, 32 rows 69:86, 113:129, 227:236; 64 slots, 192 rows 94:89,
-// 146:131, 255:186; 72 slots of 64 channels, 64 rows 49:68, 71:82, 116:122.  One step, 128 slots
-// 38:35, 62:59.  (Layer groups keep to the launches that wait for nobody.)
+// per slot, where kept rows stay in place (with re-positioning their values only) and there is one
+// launch instead of one and more a step, than step by step; `slots` = problems of a step, `steps` =
+// steps of a slot, both on average.  In one round of workgroups a problem takes as long as it takes, however
+// few there are, and step by step a step gets cheaper with fewer problems, so the line moves with
+// the length of a step, its candidates, and with the steps before the last two, which alone leave
+// rows in place.  Time here : step by step, without / with re-positioning, for "tokens a chunk (candidates of the
+// last)" and 32 to 256 rows unless said otherwise:
+//  - from 69 % of the rounds on, by the tokens of a chunk where kept rows stay, else by candidates.  128 channels, one round: 512 (992) to
+//    4096 (5376) 0.50 to 0.84 / 0.56 to 0.88, 12000 (13125) 0.79 to 0.95 / 0.80 to 0.98, 16384 up to 1.02 / 1.04; several: 4096
+//    (5376) 0.67 to 0.92 / 0.74 to 0.97, 6000 (6749) 0.76 to 1.00 / 0.79 to 1.04, 8192 (10752) 0.85 to 1.07 / 0.94 to 1.10 at 69 %,
+//    0.80 to 0.97 / 0.84 to 0.99 from 75 % on.  64 channels, 65 to 256 rows, one round: 6000 0.85 to 0.93 / 0.88 to
+//    0.93, 8192 up to 1.04 / 1.08, 12000 1.09; several: 3000 (3656) 0.83 to 0.98 / 0.85 to 1.02, 4096 (5376) up to 1.10 / 1.12; up to
+//    64 rows 0.46 to 0.96 / 0.53 to 1.00 at all of these.  384 rows, 128 channels, one round: 6000 0.88 to 0.93 / 0.88 to 0.92, 8192 up to
+//    1.03 / 1.06; several: 2048 (2944) 0.91 to 0.97 / 0.92 to 1.00, 4096 up to 1.11 / 1.14; 64 channels: 2048 0.93 / 0.97, 1.03 to 1.13.
+//    More than 384, 128 channels: 7280 (12200) 0.76;
+//  - from half a round on, where step by step a problem has no second workgroup: up to 32 candidates a slot
+//    (2048 (2944), 130 to 160 slots) 0.64 to 0.80 / 0.70 to 0.82;
+//  - from a third on, where it has two: with 8 steps and more 0.63 to 0.99 / 0.68 to 1.05 up to 32 candidates a
+//    slot, with fewer 20 (800 (1600) in 5 steps 0.71 to 0.97 / 0.83 to 1.06, 3000 (3312) in 6 up to 1.12 / 1.14); 193 to 256 rows
+//    of 64 channels 16 (0.82 to 1.0; 2048 (2432) in 4 steps 1.07 to 1.14); up to 64 rows of them 32 and 24;
+//  - from a quarter on (three and four of them), counted in the same way: 512 (992) and up to 128 rows, of 64
+//    channels 192, 0.67 to 0.95 / 0.77 to 1.05; 64 channels and 64 rows 1024 (1472 and 2944) 0.80 to 0.92 / 0.87 to 0.91
+//    and 1.18; 1024 (1472), 128 channels 0.96 to 1.29, 64 channels, 256 rows 1.25.
+// (Layer groups keep to the launches that wait for nobody.)
 bool loop_owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n_slots, int32_t slots, int32_t steps) {
   const int64_t cu = ctx->n_cu > 0 ? ctx->n_cu : 256;
   if (ctx->cfg.dtype != FINCH_BF16 || ctx->step_path != FINCH_PATH_AUTO || ctx->layer_group > 1 ||
       ctx->slice_keys != finch::kDefaultSliceKeys || !pl.own_ok || ctx->repos.order != FINCH_ORDER_ASCENDING || steps < 4)
     return false;
-  const int64_t rounds = (n_slots + cu - 1) / cu;
-  if (rounds > 1) return int64_t{100} * slots >= rounds * cu * 69;  // (384 slots of 64 channels 961:1486)
-  const bool many_rows = pl.rows_max > finch::kOwnerMaxRowChunk, narrow = ctx->cfg.head_dim == 64;
-  const int64_t few = many_rows ? cu * 5 / 8 : narrow || steps >= 10 ? cu / 4 : cu * 3 / 8;
-  return slots >= std::max<int64_t>(few, pl.n_max / 32);
+  const int64_t rounds = (n_slots + cu - 1) / cu, percent = int64_t{100} * slots / (rounds * cu);
+  const bool narrow = ctx->cfg.head_dim == 64, few_rows = narrow && pl.rows_max <= 64;
+  const bool many_rows = pl.rows_max > finch::kOwnerMaxRowChunk, turned = ctx->repos.pairing != FINCH_ROPE_OFF;
+  const bool stay = !turned && ctx->loop_rows_may_stay;
+  const int32_t keys = stay ? std::max(pl.m_max, pl.n_max - pl.r_max) : pl.n_max;
+  if (percent >= 69) {
+    if (many_rows && pl.rows_max <= 384) return keys <= (narrow ? (rounds > 1 ? 0 : 2048) : rounds > 1 ? 2560 : 6144);
+    if (narrow && !few_rows) return keys <= (rounds > 1 ? 3072 : 7168);
+    return keys <= (few_rows || many_rows || rounds == 1 ? 13312 : percent >= 75 ? 11264 : 7168);
+  }
+  if (rounds > 1 || slots < (many_rows ? cu * 5 / 8 : narrow || steps >= 10 ? cu / 4 : cu * 3 / 8)) return false;
+  if (slots <= cu / 3) {
+    if (turned && !narrow && slots < cu * 9 / 32) return false;
+    return keys <= (stay ? 512 : 1024) + (few_rows ? 512 : 0) && pl.n_max <= 32 * slots && pl.rows_max <= (narrow ? 192 : 128);
+  }
+  int64_t per_slot = 32;
+  if (slots <= cu / 2) {
+    if (narrow && pl.rows_max > 192) per_slot = 16;
+    else if (steps < 8) per_slot = !few_rows ? 20 : turned ? 24 : 32;
+  }
+  return pl.n_max <= per_slot * slots;
 }
 
 // Whether one kernel per stage is the faster launch of a batch that several workgroups per
@@ -540,7 +587,7 @@ finch_status run_score(finch_ctx* ctx, const LaunchParams& p, const Plan& pl, vo
   hipError_t e = hipSuccess;
   const int d = ctx->cfg.head_dim;
   const bool bf16 = ctx->cfg.dtype == FINCH_BF16;
-  if (owner_wanted(ctx, pl, p.n_problems)) return run_owner(ctx, p, pl, /*stages=*/0, s);
+  if (owner_wanted(ctx, pl, p.n_problems, false)) return run_owner(ctx, p, pl, /*stages=*/0, s);
   if (cluster_wanted(ctx, pl, p.n_problems, false)) return run_cluster(ctx, p, pl, ws, /*stages=*/0, s);
   if (ctx->step_path == FINCH_PATH_OWNER || pl.has_doc) return FINCH_ERR_UNSUPPORTED;
   {
@@ -785,7 +832,7 @@ finch_status step_planned(finch_ctx* ctx, const finch_problem* host_desc, const 
   const LaunchParams p = make_params(ctx, dev_desc, n, pl, ws);
   hipStream_t s = static_cast<hipStream_t>(stream);
   // (with layer groups the status word starts every call at zero: these two see to it themselves)
-  if (pl.tiles_max > 0 && owner_wanted(ctx, pl, n)) return run_owner(ctx, p, pl, /*stages=*/1, s);
+  if (pl.tiles_max > 0 && owner_wanted(ctx, pl, n, true)) return run_owner(ctx, p, pl, /*stages=*/1, s);
   if (cluster_wanted(ctx, pl, n, true)) return run_cluster(ctx, p, pl, ws, /*stages=*/1, s);
   if (ctx->layer_group > 1) {
     const hipError_t e = finch::launch_zero_words(nullptr, 0, p.layer_err, s);
@@ -1123,7 +1170,7 @@ finch_status finch_loop(finch_ctx* ctx, const finch_problem* host_desc, const fi
   if ((st = check_workspace(pl, ws, ws_bytes)) != FINCH_OK) return st;
   if (n_desc == 0 || pl.tiles_max == 0) return FINCH_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (owner_wanted(ctx, pl, n_slots) || loop_owner_wanted(ctx, pl, n_slots, n_desc / n_steps, n_desc / std::max(1, n_slots))) {
+  if (owner_wanted(ctx, pl, n_slots, true) || loop_owner_wanted(ctx, pl, n_slots, n_desc / n_steps, n_desc / std::max(1, n_slots))) {
     LaunchParams p = make_params(ctx, dev_desc, n_desc, pl, ws);
     p.row_chunk = pl.own_row_chunk;
     p.lds_bytes = static_cast<uint32_t>(pl.own_lds);
