@@ -1214,8 +1214,10 @@ finch_status finch_workspace_status(finch_ctx* ctx, const void* workspace, void*
   return *flags == 0 ? FINCH_OK : FINCH_ERR_TIMEOUT;
 }
 
-finch_status finch_loop_check(const finch_config* cfg, const finch_problem* host_desc,
-                              const int32_t* host_step_first, int32_t n_steps) {
+// What finch_loop checks before it launches anything, and (not in finch.h: for tests of what the kernels
+// are then told) whether the rows a step keeps may stay where they are.
+finch_status finch_debug_loop_rows_may_stay(const finch_config* cfg, const finch_problem* host_desc,
+                                            const int32_t* host_step_first, int32_t n_steps, int32_t* rows_may_stay) {
   if (!cfg) return FINCH_ERR_INVALID_ARG;
   if (cfg->dtype != FINCH_F32 && cfg->dtype != FINCH_BF16) return FINCH_ERR_UNSUPPORTED;
   if (cfg->head_dim != 64 && cfg->head_dim != 128) return FINCH_ERR_UNSUPPORTED;
@@ -1237,7 +1239,14 @@ finch_status finch_loop_check(const finch_config* cfg, const finch_problem* host
   }
   if ((st = validate(&tmp, host_desc, n_desc, kNeedQK | kNeedIdx | kNeedGather)) != FINCH_OK) return st;
   bool may_stay = false;
-  return check_slot_overlaps(&tmp, host_desc, host_step_first, n_steps, n_slots, &may_stay);
+  st = check_slot_overlaps(&tmp, host_desc, host_step_first, n_steps, n_slots, &may_stay);
+  if (rows_may_stay) *rows_may_stay = may_stay ? 1 : 0;
+  return st;
+}
+
+finch_status finch_loop_check(const finch_config* cfg, const finch_problem* host_desc,
+                              const int32_t* host_step_first, int32_t n_steps) {
+  return finch_debug_loop_rows_may_stay(cfg, host_desc, host_step_first, n_steps, nullptr);
 }
 
 finch_status finch_schedule(int64_t n_cont, int32_t m, int64_t k, int32_t* r_out, int32_t r_len) {

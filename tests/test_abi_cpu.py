@@ -133,6 +133,44 @@ def test_loop_check_accepts_disjoint_slots_and_rejects_overlaps_between_slots():
     assert F.finch_loop_check(F.FINCH_BF16, 96, 1, hd, first, n_steps) == F.FINCH_ERR_UNSUPPORTED
 
 
+def _rows_may_stay(hd, first, n_steps):
+    cfg, said = F.finch_config(F.FINCH_BF16, 128, 1, 0), ctypes.c_int32(-1)
+    assert F.load_library().finch_debug_loop_rows_may_stay(ctypes.byref(cfg), hd, first, n_steps, ctypes.byref(said)) == F.FINCH_OK
+    return bool(said.value)
+
+
+def test_rows_stay_only_within_reach_and_in_memory_of_their_own():
+    """Kept rows are left where they are only if 32-bit notes can name their places (chunks and the first cache
+    within 16 GiB of the first chunk) and nothing else of the slot touches that memory."""
+    n_slots, n_steps, rb, m = 3, 4, 256, 64
+    reach = 1 << 34
+    hd, first = _loop_descs(n_slots, n_steps)
+    assert _rows_may_stay(hd, first, n_steps)
+    for field in ("k_chunk", "v_chunk"):
+        for ahead, stays in [(reach - m * rb, True), (reach - m * rb + 16, False)]:
+            hd, first = _loop_descs(n_slots, n_steps)
+            setattr(hd[2 * n_slots + 1], field, getattr(hd[1], field) + ahead)
+            assert _rows_may_stay(hd, first, n_steps) == stays, (field, ahead)
+        # (the first chunk above the others: step 1's is the one furthest below)
+        for above, stays in [(reach, True), (reach + 16, False)]:
+            hd, first = _loop_descs(n_slots, n_steps)
+            setattr(hd[1], field, getattr(hd[n_slots + 1], field) + above)
+            assert _rows_may_stay(hd, first, n_steps) == stays, (field, above)
+    for field in ("k_cache", "v_cache"):
+        for ahead, stays in [(reach - 5 * rb, True), (reach - 5 * rb + 16, False)]:
+            hd, first = _loop_descs(n_slots, n_steps)
+            hd[1].c = 5
+            hd[1].k_cache, hd[1].v_cache = hd[1].k_chunk - (1 << 24), hd[1].v_chunk - (1 << 24) - (1 << 16)
+            setattr(hd[1], field, getattr(hd[1], field.replace("cache", "chunk")) + ahead)
+            assert _rows_may_stay(hd, first, n_steps) == stays, (field, ahead)
+    # scores in a chunk that has been read, a chunk that lies in a cache, indices over a cache
+    for field, where in [("scores", lambda: hd[1].k_chunk), ("k_chunk", lambda: hd[n_slots + 1].k_out), ("idx", lambda: hd[n_slots + 1].v_out)]:
+        hd, first = _loop_descs(n_slots, n_steps)
+        hd[2 * n_slots + 1].m = 8  # (few enough rows for one cache)
+        setattr(hd[2 * n_slots + 1], field, where())
+        assert not _rows_may_stay(hd, first, n_steps), field
+
+
 def test_loop_check_many_slots_is_fast():
     import time
     hd, first = _loop_descs(1024, 8)
