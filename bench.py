@@ -44,10 +44,13 @@ MEASURED_TRAFFIC = {"C4": {
 }}
 
 
-def algorithmic_bytes(w, loop):
+def algorithmic_bytes(w, loop, rows_stay=False, turned=False):
     """Bytes the method must move, per kernel class and in total, summed over one
     full chunk loop: every candidate key read once for scoring, Q once per step,
-    every kept K and V row read once and written once."""
+    every kept K and V row read once and written once.  With `rows_stay` (one call for the
+    whole loop) kept rows have to be in their place only after a problem's last two steps, what
+    the caches of the call hold in the end; with `turned` keys are re-positioned, and
+    rounded, at every step all the same."""
     e, d = w.elem_bytes, w.head_dim
     per = dict(score_pass=0, select=0, gather=0)
     keys = 0
@@ -58,7 +61,8 @@ def algorithmic_bytes(w, loop):
             keys += N
             per["score_pass"] += N * d * e + R * d * e
             per["select"] += 4 * N + 4 * min(r, N)
-            per["gather"] += min(r, N) * d * e * 4
+            stays = rows_stay and i + 2 < loop.n_steps and p in loop.active[i + 2]
+            per["gather"] += min(r, N) * d * e * ((2 if turned else 0) if stays else 4)
     total = per["score_pass"] + per["gather"]
     return per, total, keys
 
@@ -204,7 +208,10 @@ def main() -> int:
                      constant_budget=args.constant_budget)
     torch.cuda.synchronize()
     t_gen = time.perf_counter() - t_gen
-    per_kernel_bytes, total_bytes, keys = algorithmic_bytes(w, loop)
+    # (kernels that run one step per launch move every kept row)
+    per_kernel_bytes, every_row_bytes, keys = algorithmic_bytes(w, loop)
+    _, total_bytes, _ = algorithmic_bytes(w, loop, rows_stay=not args.per_step and args.order == "ascending",
+                                          turned=args.reposition != "off")
     n_tokens = sum(r.n_cont for r in w.requests)
 
     for _ in range(args.warmup):
@@ -280,8 +287,8 @@ def main() -> int:
         klass = {"prompt_lse": "prompt_lse","rowstats": "score_pass", "colsum": "score_pass", "owner": "step",
                  "select": "select", "gather": "gather", "lse": "select"}[dom]
         launches = kernels[dom]["launches_per_step"]
-        # a launch that runs all stages: everything the method has to move (keys once)
-        per_kernel_bytes["step"] = total_bytes
+        # a launch that runs all stages, of the whole loop or of a step: everything it has to move (keys once)
+        per_kernel_bytes["step"] = total_bytes if launches == 1 else every_row_bytes
         bytes_per_launch = per_kernel_bytes[klass] / launches
         achieved = bytes_per_launch / (kernels[dom]["avg_us"] * 1e-6) / 1e9
         roofline = dict(bound="hbm", kernel=dom, achieved=achieved, peak=HBM_PEAK_GBPS, unit="GB/s",

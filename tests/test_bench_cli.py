@@ -34,3 +34,22 @@ def test_byte_and_flop_accounting():
     assert per["gather"] == (10 + 50 + 20) * row * 4
     assert total == per["score_pass"] + per["gather"]
     assert bench.logit_flops(w, loop) == 2 * 2 * 128 * (100 * 12 + 50 * 20 + 110 * 12)
+
+
+def test_bytes_of_a_whole_loop_leave_out_rows_that_may_stay():
+    sys.path.insert(0, ROOT)
+    import bench
+    w = types.SimpleNamespace(elem_bytes=2, head_dim=64, group=1)
+    loop = types.SimpleNamespace(
+        n_steps=4, active=[[1, 0], [1, 0], [1, 0], [1]],
+        step_shapes=[[(0, 90, 7), (0, 100, 10)], [(7, 90, 14), (10, 100, 20)], [(14, 90, 21), (20, 40, 24)], [(21, 90, 28)]],
+        problems=[dict(n_que=3), dict(n_que=5)])
+    row = 64 * 2
+    every, total, keys = bench.algorithmic_bytes(w, loop)
+    per, less, same = bench.algorithmic_bytes(w, loop, rows_stay=True)
+    # rows move in the last two steps of problem 0 (20, 24 rows) and of problem 1 (21, 28)
+    assert per["gather"] == (20 + 24 + 21 + 28) * row * 4 and per["score_pass"] == every["score_pass"] and same == keys
+    assert less == total - (10 + 7 + 14) * row * 4
+    # keys that are turned move at every step
+    per, _, _ = bench.algorithmic_bytes(w, loop, rows_stay=True, turned=True)
+    assert per["gather"] == (20 + 24 + 21 + 28) * row * 4 + (10 + 7 + 14) * row * 2
