@@ -220,7 +220,8 @@ def main() -> int:
     phase_fn = None
     if args.phases:
         import ctypes
-        phase_fn = F.load_library().finch_debug_phases
+        lib = F.load_library()  # (the totals of the kernels that also take document rows are their own)
+        phase_fn = lib.finch_debug_phases_doc if args.doc_rows else lib.finch_debug_phases
         phase_fn.argtypes = [ctypes.POINTER(ctypes.c_ulonglong), ctypes.c_int]
         phase_fn.restype = ctypes.c_int
         phase_buf = (ctypes.c_ulonglong * 8)()
