@@ -60,9 +60,13 @@ __device__ __forceinline__ int next_block(int* counter, int lane) {
 }  // namespace
 
 // ---------------------------------------------------------------- pass 1
-// QBT = row blocks (of 32 prompt rows) the kernel is compiled for.
+// QBT = row blocks (of 32 prompt rows) the kernel is compiled for.  Two workgroups share a compute unit, with
+// 128 registers a wave; more than 256 rows of 128 channels fill more than half of its LDS, so a second workgroup
+// finds no place and the registers of a key block on its way and of 12 or 16 row blocks' statistics need not be spilled
+// (33 were).  256 problems of 512 rows, 256 / 1024 / 4096 candidates: 25 / 59 / 193 us, 41 / 82 / 269 with 128
+// registers.
 template <int D, int QBT>
-__global__ __launch_bounds__(kThreads, 4) void rowstats_bf16(LaunchParams prm) {
+__global__ __launch_bounds__(kThreads, D == 128 && QBT >= 12 ? 2 : 4) void rowstats_bf16(LaunchParams prm) {
   extern __shared__ __align__(16) char smem[];
   int p, slice;
   if (!decode_slice(prm, p, slice)) return;

@@ -56,3 +56,14 @@ def test_document_row_kernels_keep_their_key_buffers_in_registers():
             seen += 1
             assert meta[".vgpr_spill_count"] <= 4, f"{m.groups()}: {meta['.vgpr_spill_count']} spilled"
     assert seen == 32  # step and loop, 2 head sizes, 4 numbers of row blocks, with re-positioning and without
+
+
+def test_row_statistics_of_many_rows_are_not_spilled():
+    """More than 256 rows of 128 channels leave room for one workgroup a compute unit: twice the registers."""
+    seen = 0
+    for name, meta in kernels().items():
+        m = re.search(r"rowstats_bf16ILi(\d+)ELi(12|16)E", name)
+        if m:
+            seen += 1
+            assert meta[".vgpr_spill_count"] == 0, f"{m.groups()}: {meta['.vgpr_spill_count']} spilled"
+    assert seen == 4
