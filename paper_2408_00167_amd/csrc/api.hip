@@ -391,30 +391,38 @@ bool repositioning(const finch_ctx* ctx) {
   return ctx->repos.pairing != FINCH_ROPE_OFF || ctx->repos.order != FINCH_ORDER_ASCENDING;
 }
 
+// Rows that are two whole chunks here and that the kernels per stage, whose LDS holds fewer, take in two as
+// well, the second one short (481 to 512 rows of 128 channels).
+bool rest_per_stage(const Plan& pl) {
+  return pl.rows_max > pl.row_chunk && pl.rows_max <= 2 * finch::kOwnerMaxRowChunk;
+}
+
 // One workgroup per problem pays when the problems fill the chip's CUs in whole
 // rounds (mostly one workgroup per CU at a time): AUTO takes that path when the
 // rounds would be at least 85 % full, and from 69 % on (this) for
 //  - one round of up to 8192 candidates, 12288 from 78 % on: beyond, the slices of the kernels per stage fill
 //    the chip better.  Time here : per stage, whole steps, 32 to 256 rows: 0.53 to 0.97 up to 8192; 177
 //    problems of 9600 0.93 to 1.15, of 16384 1.04 to 1.24; 205 problems of 12000 0.79 to 1.01.  Any number
-//    for 225 to 256 and more than 384 rows of 128 channels, of which the kernels per stage hold one
-//    workgroup a CU or spill: 9600 to 16384 candidates 0.62 to 0.98;
+//    for rows of 128 channels of which the kernels per stage hold one workgroup a CU (225 to 256) or which they take
+//    in one chunk more (481 to 512): 9600 to 16384 candidates 0.76 to 0.95.  More than 320 rows otherwise 0.73 to 1.06, beyond
+//    8192 up to 1.18 (from 78 % up to 12288 0.85 to 1.02);
 //  - several rounds of up to 2048 candidates: 0.52 to 1.04; 354 problems, 192 rows, 4096 candidates 1.08.
 //    Scores alone, without top-r and copies to save launches of, not with 65 to 256 rows of 64 channels:
 //    0.94 to 1.14;
 //  - where rows come in two chunks of which the second is short and the kernels per stage take them in one (257 to
-//    320, 384 of 64 channels): one round of whole steps of up to 1024 candidates, 0.70 to 0.96; 2048 1.0 to 1.06, 8192 1.04
-//    to 1.17.  Several rounds and scores alone, 128 channels, up to 600 0.72 to 0.98; 64 channels 1.05 to 1.42.
+//    320, 384 of 64 channels): one round of whole steps of up to 1024 candidates, 0.70 to 0.99; 2048 1.0 to 1.09, 8192 1.04
+//    to 1.17.  128 channels, several rounds of up to 300 0.80 to 1.01 (600 up to 1.06), scores alone of up to 128 0.86 to 0.93
+//    (600 up to 1.09); 64 channels 1.05 to 1.42.
 // (Layer groups and slots by rank: 85 %.)
 bool owner_from_69(const finch_ctx* ctx, const Plan& pl, int32_t n, int64_t rounds, int64_t cu, bool stages) {
   if (ctx->layer_group > 1 || ctx->repos.order != FINCH_ORDER_ASCENDING) return false;
   const bool narrow = ctx->cfg.head_dim == 64, one_chunk = pl.rows_max <= finch::kOwnerMaxRowChunk;
   if (!one_chunk && pl.rows_max <= (narrow ? 384 : 320)) {
     if (rounds == 1 && stages) return pl.n_max <= 1024;
-    return !narrow && pl.n_max <= 600;
+    return !narrow && pl.n_max <= (stages ? 300 : 128);
   }
   if (rounds > 1) return pl.n_max <= 2048 && (stages || !narrow || pl.rows_max <= 64 || !one_chunk);
-  if (!narrow && (one_chunk ? pl.rows_max > 224 : pl.rows_max > 384)) return true;
+  if (!narrow && (one_chunk ? pl.rows_max > 224 : rest_per_stage(pl))) return true;
   return pl.n_max <= (int64_t{100} * n >= cu * 78 && (one_chunk || !narrow) ? 12288 : 8192);
 }
 
@@ -467,9 +475,11 @@ bool owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n, bool stages) 
 //    (5376) 0.67 to 0.92 / 0.74 to 0.97, 6000 (6749) 0.76 to 1.00 / 0.79 to 1.04, 8192 (10752) 0.85 to 1.07 / 0.94 to 1.10 at 69 %,
 //    0.80 to 0.97 / 0.84 to 0.99 from 75 % on.  64 channels, 65 to 256 rows, one round: 6000 0.85 to 0.93 / 0.88 to
 //    0.93, 8192 up to 1.04 / 1.08, 12000 1.09; several: 3000 (3656) 0.83 to 0.98 / 0.85 to 1.02, 4096 (5376) up to 1.10 / 1.12; up to
-//    64 rows 0.46 to 0.96 / 0.53 to 1.00 at all of these.  384 rows, 128 channels, one round: 6000 0.88 to 0.93 / 0.88 to 0.92, 8192 up to
-//    1.03 / 1.06; several: 2048 (2944) 0.91 to 0.97 / 0.92 to 1.00, 4096 up to 1.11 / 1.14; 64 channels: 2048 0.93 / 0.97, 1.03 to 1.13.
-//    More than 384, 128 channels: 7280 (12200) 0.76;
+//    64 rows 0.46 to 0.96 / 0.53 to 1.00 at all of these.  More than
+//    256 rows, 128 channels: 257 to 320 1024 (1472) 0.89 to 1.02 / 0.89 to 1.02, 2048 up to 1.09 / 1.12; 321 and more, one round, 6000 0.81
+//    to 0.95 / 0.83 to 0.96, 8192 up to 1.07 / 1.06, several 2048 (2944) 0.88 to 1.01 / 0.90 to 1.05, 4096 1.01 to 1.15 / 1.02 to 1.17, at
+//    83 % 6000 0.86 to 0.97 / 0.85 to 0.98; 481 to 512 as one chunk of rows (one round 0.65 to 0.89, several 4096 0.76 to 0.95,
+//    8192 up to 1.03).  64 channels, 384 rows: one round 2048 0.93 / 0.97, several 1.03 to 1.13;
 //  - from half a round on, where step by step a problem has no second workgroup: up to 32 candidates a slot
 //    (2048 (2944), 130 to 160 slots) 0.64 to 0.80 / 0.70 to 0.82;
 //  - from a third on, where it has two: with 8 steps and more 0.63 to 0.99 / 0.68 to 1.05 up to 32 candidates a
@@ -490,9 +500,10 @@ bool loop_owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n_slots, in
   const bool stay = !turned && ctx->loop_rows_may_stay;
   const int32_t keys = stay ? std::max(pl.m_max, pl.n_max - pl.r_max) : pl.n_max;
   if (percent >= 69) {
-    if (many_rows && pl.rows_max <= 384) return keys <= (narrow ? (rounds > 1 ? 0 : 2048) : rounds > 1 ? 2560 : 6144);
+    if (many_rows && pl.rows_max <= (narrow ? 384 : 320)) return keys <= (!narrow ? 1536 : rounds > 1 ? 0 : 2048);
+    if (many_rows && !narrow && !rest_per_stage(pl)) return keys <= (rounds == 1 ? 7168 : percent >= 80 ? 6144 : 2560);
     if (narrow && !few_rows) return keys <= (rounds > 1 ? 3072 : 7168);
-    return keys <= (few_rows || many_rows || rounds == 1 ? 13312 : percent >= 75 ? 11264 : 7168);
+    return keys <= (few_rows || rounds == 1 ? 13312 : percent >= 75 ? 11264 : 7168);
   }
   if (rounds > 1 || slots < (many_rows ? cu * 5 / 8 : narrow || steps >= 10 ? cu / 4 : cu * 3 / 8)) return false;
   if (slots <= cu / 3) {

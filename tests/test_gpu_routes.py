@@ -28,13 +28,13 @@ STEPS = [
     (176, 128, 192, 512, False, False), (177, 128, 192, 512, False, True),           # 69 % of a round
     (177, 64, 256, 8192, False, True), (177, 64, 256, 8193, False, False),           # candidates of one round
     (199, 128, 192, 8193, False, False), (200, 128, 192, 12288, False, True), (200, 128, 192, 12289, False, False),
-    (177, 128, 224, 9000, False, False), (177, 128, 225, 9000, False, True), (177, 128, 385, 9000, True, True),
+    (177, 128, 224, 9000, False, False), (177, 128, 225, 9000, False, True), (177, 128, 480, 9000, True, False), (177, 128, 481, 9000, True, True),
     (200, 128, 384, 9000, False, True), (200, 64, 385, 9000, False, False), (218, 128, 192, 12289, False, True),  # 85 %
-    (177, 128, 257, 1024, False, True), (177, 128, 257, 1025, False, False), (177, 128, 257, 600, True, True),
-    (177, 128, 320, 601, True, False), (177, 128, 321, 1025, False, True), (177, 64, 384, 1025, False, False),
+    (177, 128, 257, 1024, False, True), (177, 128, 257, 1025, False, False), (177, 128, 257, 128, True, True),
+    (177, 128, 320, 129, True, False), (177, 128, 321, 1025, False, True), (177, 64, 384, 1025, False, False),
     (177, 64, 385, 1025, False, True), (177, 64, 384, 300, True, False), (354, 64, 384, 300, False, False),
     (354, 128, 192, 2048, False, True), (354, 128, 192, 2049, False, False), (353, 128, 192, 2048, False, False),
-    (354, 64, 65, 300, False, True), (354, 64, 65, 300, True, False), (354, 64, 64, 300, True, True), (354, 128, 300, 601, False, False),
+    (354, 64, 65, 300, False, True), (354, 64, 65, 300, True, False), (354, 64, 64, 300, True, True), (354, 128, 300, 300, False, True), (354, 128, 300, 301, False, False),
 ]
 
 
@@ -69,7 +69,9 @@ LOOPS = [
     (177, 128, 192, 13300, 4, 400, False, True), (177, 128, 192, 13500, 4, 400, False, False), (177, 128, 192, 13100, 4, 400, True, False),
     (177, 64, 256, 7100, 4, 2000, False, True), (177, 64, 256, 7100, 4, 2000, True, False), (177, 64, 256, 8400, 4, 400, False, False),
     (354, 128, 192, 7100, 4, 400, False, True), (354, 128, 192, 7200, 4, 400, False, False), (354, 128, 192, 7100, 4, 400, True, False),
-    (384, 128, 192, 7200, 4, 400, False, True), (354, 128, 385, 7200, 4, 400, True, True), (354, 128, 192, 2100, 16, 8400, False, True), (354, 128, 192, 2100, 16, 8400, True, False),
+    (384, 128, 192, 7200, 4, 400, False, True), (354, 128, 481, 6700, 4, 400, True, True),
+    (177, 128, 480, 7100, 4, 2000, False, True), (177, 128, 480, 7200, 4, 2000, False, False), (410, 128, 480, 6100, 4, 400, False, True),
+    (354, 128, 300, 1500, 4, 100, False, True), (354, 128, 300, 1600, 4, 100, False, False), (354, 128, 192, 2100, 16, 8400, False, True), (354, 128, 192, 2100, 16, 8400, True, False),
     (354, 64, 256, 3050, 4, 400, False, True), (354, 64, 256, 3200, 4, 400, False, False), (354, 64, 64, 13000, 4, 400, False, True),
     (354, 128, 384, 2500, 4, 400, False, True), (354, 128, 384, 2700, 4, 400, False, False), (354, 64, 257, 300, 4, 40, False, False),
 ]
