@@ -210,8 +210,8 @@ size_t finch_static_scratch_bytes(void);
  * v_cache at step s+1 are its k_out / v_out of step s), and no descriptor may read
  * memory that a descriptor in another slot writes: slots are processed
  * independently, each through all of its steps, possibly by one kernel launch for
- * the whole loop (one workgroup per slot; picked under FINCH_PATH_AUTO when the
- * slots fill the chip, forced by FINCH_PATH_OWNER), otherwise step by step.  Rows of
+ * the whole loop (one workgroup per slot; forced by FINCH_PATH_OWNER, picked under
+ * FINCH_PATH_AUTO where it is the faster way, see there), otherwise step by step.  Rows of
  * k_out / v_out that a later step of the same call overwrites need not be written
  * before; all of them hold what the last step that writes them leaves when the call's
  * work is done.
@@ -265,12 +265,13 @@ finch_status finch_schedule_mode(int64_t n_cont, int32_t m, int64_t k, int32_t m
  * OWNER gives every problem to one workgroup of 8 waves that runs all stages of the
  * step - or, in finch_loop, of all steps - back to back (bf16: matrix instructions;
  * fp32: fp64 matrix instructions, meant for small problems); batches it cannot run fail with
- * FINCH_ERR_UNSUPPORTED.  AUTO (default) takes OWNER for bf16 when the batch has enough
- * problems to fill the chip's compute units in whole rounds, at least 69 % of them (finch_loop of
- * four steps and more with few candidates: from a quarter of them on), for fp32 when no problem
+ * FINCH_ERR_UNSUPPORTED.  AUTO (default) takes whichever was measured as faster: OWNER for bf16 when
+ * the batch fills the chip's compute units in whole rounds to 85 %, from 69 % on and for whole loops
+ * from a quarter of a round on depending on rows, candidates, steps, head_dim and options; for fp32 when no problem
  * has more than 4096 candidates or 64 prompt rows (few problems of head_dim 64 with at most 5
  * rows: 1024 candidates); for bf16 batches of at most half as many problems as compute units,
- * mostly, a launch per step in which several workgroups share a problem; else SEPARATE. */
+ * mostly, a launch per step in which several workgroups share a problem; else SEPARATE.  Where the lines lie is
+ * no part of the interface.  Scores of different ways can differ in their last bits (sums in another order). */
 typedef enum {
   FINCH_OPT_STEP_PATH = 1,
   /* tuning: target number of keys one workgroup of the two-pass bf16 scoring

@@ -521,13 +521,14 @@ bool loop_owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n_slots, in
 // Whether one kernel per stage is the faster launch of a batch that several workgroups per
 // problem could take: when its two passes cut the problems into as many slices (of 2400 keys) and
 // put them on the chip in one round, the meetings save nothing, and a tile costs less there
-// (a moving reference per row instead of every block's maximum).  Measured, AUTO's launch against
-// kernels per stage on 48 to 128 problems: scores alone 1.05 to 1.3 times the time at 64 channels
-// and up to 256 rows, 1.03 to 1.14 at 128; whole steps 1.0 to 1.25 and 0.98 to 1.1.  The other way
-// round: 128 channels with more than 256 rows (the passes per stage hold one workgroup of 512 rows
-// a compute unit) 0.85 to 1.0; layer groups, whose sums and selection per stage have one workgroup a
-// layer, 0.67 to 0.95, except 64 channels with more than 256 rows, 1.0 to 1.18.  Scores alone at 64
-// channels: also with three quarters of the slices (1.0 to 1.11).
+// (a moving reference per row instead of every block's maximum).  Time per stage : one launch, 24 to 128 problems of
+// 1500 to 12000 candidates, up to 256 rows: scores alone 0.71 to 1.02 at 64 channels, 0.78 to 1.02 at 128; whole
+// steps 0.81 to 1.06 and 0.86 to 1.05.  More rows: 64 channels 0.70 to 1.03; 128 channels stay with
+// one launch, though 0.68 to 1.03 but for 481 to 512 rows (0.95 to 1.08).  Layer groups, whose sums and selection per
+// stage have one workgroup a layer: 0.96 to 1.5, with more than 256 rows of 64 channels 0.90 to 1.07, of 128 0.85 to
+// 1.04 (481 to 512 1.19).  Scores alone at 64 channels: also with
+// three quarters of the slices (0.79 to 1.03 in one round of the passes per stage, up to 1.17 in two); whole steps and 128 channels
+// would be 0.79 to 1.1 there in one round, 0.85 to 1.31 in two.
 bool stages_faster(const finch_ctx* ctx, const Plan& pl, int32_t n, bool stages) {
   const int64_t dies = 8, per_die = std::max<int64_t>(1, ctx->n_cu / dies);
   const int64_t rounds = ((n + dies - 1) / dies * pl.tiles_max + per_die - 1) / per_die;
