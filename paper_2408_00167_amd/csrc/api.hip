@@ -518,6 +518,23 @@ bool loop_owner_wanted(const finch_ctx* ctx, const Plan& pl, int32_t n_slots, in
   return pl.n_max <= per_slot * slots;
 }
 
+// Whether the one launch of a loop keeps notes of rows that stay in place.  Two steps lie ahead of
+// one whose rows may stay: shorter loops only pay for the notes (1 or 2 steps, chunks of 64 to 1024:
+// 1.01 of the time without them).  Where keys are turned at each step only values stay, and what a
+// step reads of the next descriptors and writes as notes has to be less than moving them: loops of
+// 64 to 512 problems take, by kept rows, of the time without notes,
+//   128 channels, 3 to 8 steps: 16 to 128 rows 1.01 to 1.07; 256 0.99 to 1.03; 512 0.95 to 1.02;
+//       768 0.93 to 1.01; 2048 0.88 to 1.01;
+//   64 channels: 16 to 128 rows 1.02 to 1.08; 256 1.01 to 1.05; 512 0.99 to 1.04; 768 0.97 to 1.02;
+//       1024 0.95 to 1.01; 2048 0.90 to 1.01.
+// The line is at 96 KB of values.  Rows whose keys stay too pay from 3 steps on (16 rows 0.97 to 1.00,
+// 512 rows 0.85 to 1.00).
+bool rows_pay_to_stay(const finch_ctx* ctx, const Plan& pl, int32_t n_steps) {
+  if (ctx->cfg.dtype != FINCH_BF16 || !ctx->loop_rows_may_stay || ctx->repos.order != FINCH_ORDER_ASCENDING || n_steps < 3)
+    return false;
+  return ctx->repos.pairing == FINCH_ROPE_OFF || int64_t{pl.r_max} * ctx->cfg.head_dim >= 48 * 1024;
+}
+
 // Whether one kernel per stage is the faster launch of a batch that several workgroups per
 // problem could take: when its two passes cut the problems into as many slices (of 2400 keys) and
 // put them on the chip in one round, the meetings save nothing, and a tile costs less there
@@ -1188,7 +1205,7 @@ finch_status finch_loop(finch_ctx* ctx, const finch_problem* host_desc, const fi
     p.lds_bytes = static_cast<uint32_t>(pl.own_lds);
     // notes of where kept rows lie: as many as fit beside the rest of the LDS (the kernels that move
     // every row are fp32's, and slots by rank put the rows in another order)
-    if (ctx->cfg.dtype == FINCH_BF16 && ctx->loop_rows_may_stay && ctx->repos.order == FINCH_ORDER_ASCENDING)
+    if (rows_pay_to_stay(ctx, pl, n_steps))
       p.stay_rows = static_cast<int32_t>(std::min(static_cast<size_t>(pl.r_max), (ctx->max_lds - pl.own_lds) / 8));
     hipError_t e;
     if (ctx->layer_group > 1) {

@@ -30,10 +30,22 @@ FORMS = {
     "doc_rows_rope": dict(slots=GROWING, doc=True, rope=(F.FINCH_ROPE_HALF, F.FINCH_ORDER_ASCENDING)),
     "layer_rope": dict(slots=GROWING[:1] * 4, layer=2, rope=(F.FINCH_ROPE_INTERLEAVED, F.FINCH_ORDER_ASCENDING)),
 }
+# (turned keys: the values stay from 384 rows of 128 channels and 768 rows of 64 on; both sides of the line,
+# enough rows for the values to stay with either width, and with as many document rows, and too few steps to stay)
+for _d, _r in ((128, 384), (64, 768)):
+    for _off in (-1, 0):
+        FORMS[f"rope_line_{_d}_{_off}"] = dict(slots=[(9, [(900, _r // 2), (300, _r + _off), (257, _r - 40), (31, _r + _off), (64, _r - 1)])],
+                                              rope=(F.FINCH_ROPE_INTERLEAVED, F.FINCH_ORDER_ASCENDING))
+LONG = [(0, [(1025, 300), (513, 700), (257, 800), (257, 811), (100, 830)]), (0, [(900, 64), (900, 820), (31, 830)]), (0, [(5, 3)])]
+for _name, _more in (("", {}), ("doc_rows_", dict(doc=True)), ("layer_", dict(slots=LONG[:1] * 4, layer=2)), ("three_buffers_", dict(buffers=3))):
+    FORMS[f"{_name}rope_long"] = dict(dict(slots=LONG, rope=(F.FINCH_ROPE_HALF, F.FINCH_ORDER_ASCENDING)), **_more)
+FORMS["two_steps"] = dict(slots=[(0, [(257, 40), (257, 80)]), (9, [(257, 64)])])
 # (kernels for 2, 4 and 6 row blocks; GROWING's chunks take the one for 8)
 for _m in (40, 100, 180):
     FORMS[f"doc_rows_rope_{_m}"] = dict(slots=[(17, [(_m, 20), (_m, 41), (_m, 45), (_m - 7, 66)])], doc=True,
                                         rope=(F.FINCH_ROPE_HALF, F.FINCH_ORDER_ASCENDING))
+    FORMS[f"doc_rows_rope_long_{_m}"] = dict(slots=[(900, [(_m, 800), (_m, 810), (_m, 811), (_m - 7, 820)])], doc=True,
+                                             rope=(F.FINCH_ROPE_HALF, F.FINCH_ORDER_ASCENDING))
 
 
 
