@@ -212,7 +212,7 @@ size_t finch_static_scratch_bytes(void);
  * independently, each through all of its steps, possibly by one kernel launch for
  * the whole loop (one workgroup per slot; forced by FINCH_PATH_OWNER, picked under
  * FINCH_PATH_AUTO where it is the faster way, see there), otherwise step by step.  Rows of
- * k_out / v_out that a later step of the same call overwrites need not be written
+ * k_out / v_out and scores that a later step of the same call overwrites need not be written
  * before; all of them hold what the last step that writes them leaves when the call's
  * work is done.
  * host_step_first is host memory, dev_step_first a device copy of it.  The

@@ -535,6 +535,14 @@ bool rows_pay_to_stay(const finch_ctx* ctx, const Plan& pl, int32_t n_steps) {
   return ctx->repos.pairing == FINCH_ROPE_OFF || int64_t{pl.r_max} * ctx->cfg.head_dim >= 48 * 1024;
 }
 
+// Whether a whole loop may leave out a step's scores where the next step overwrites them (owner_loop_bf16 decides
+// step by step): nothing else of the slot touches them, every problem selects for itself, and the
+// order of the kept rows does not depend on them.
+bool scores_may_be_bounds(const finch_ctx* ctx, const Plan& pl, int32_t n_steps) {
+  return ctx->cfg.dtype == FINCH_BF16 && !pl.has_doc && ctx->loop_rows_may_stay && ctx->layer_group == 1 &&
+         ctx->repos.order == FINCH_ORDER_ASCENDING && n_steps >= 3;
+}
+
 // Whether one kernel per stage is the faster launch of a batch that several workgroups per
 // problem could take: when its two passes cut the problems into as many slices (of 2400 keys) and
 // put them on the chip in one round, the meetings save nothing, and a tile costs less there
@@ -1205,8 +1213,12 @@ finch_status finch_loop(finch_ctx* ctx, const finch_problem* host_desc, const fi
     p.lds_bytes = static_cast<uint32_t>(pl.own_lds);
     // notes of where kept rows lie: as many as fit beside the rest of the LDS (the kernels that move
     // every row are fp32's, and slots by rank put the rows in another order)
+    const size_t est_words = static_cast<size_t>(pl.own_row_chunk) + finch::kEstExtraWords;
+    if (scores_may_be_bounds(ctx, pl, n_steps) && pl.own_lds + est_words * 4 <= ctx->max_lds)
+      p.est_words = static_cast<int32_t>(est_words);
     if (rows_pay_to_stay(ctx, pl, n_steps))
-      p.stay_rows = static_cast<int32_t>(std::min(static_cast<size_t>(pl.r_max), (ctx->max_lds - pl.own_lds) / 8));
+      p.stay_rows = static_cast<int32_t>(
+          std::min(static_cast<size_t>(pl.r_max), (ctx->max_lds - pl.own_lds - 4 * static_cast<size_t>(p.est_words)) / 8));
     hipError_t e;
     if (ctx->layer_group > 1) {
       if ((e = finch::launch_zero_words(p.layer_sync, pl.sync_words, p.layer_err, s)) != hipSuccess) return hip_fail(ctx, e);

@@ -89,6 +89,7 @@ struct LaunchParams {
   int64_t help_ticks;
   int32_t stay_rows;           // whole loop: most kept rows a step may leave where they are (0: none; room for as many notes, 8
                                // bytes each, follows the lds_bytes)
+  int32_t est_words;           // whole loop: 4-byte words of LDS for RowEstimates, behind the notes (0: every step makes both passes)
   int64_t spin_ticks;          // longest wait for the other workgroups, in 100 MHz ticks
 };
 
@@ -103,6 +104,7 @@ hipError_t launch_select(LaunchParams p, int n_max, hipStream_t s);
 hipError_t launch_select_layer(LaunchParams p, int group, float* layer_scores, int n_max, hipStream_t s);
 hipError_t set_max_lds_select(size_t bytes);
 hipError_t launch_gather(const LaunchParams& p, int row_bytes, int r_max, hipStream_t s);
+constexpr int kEstExtraWords = 32;  // words of RowEstimates beside one per staged prompt row
 size_t owner_lds_bytes(int head_dim, int row_chunk, int n_max, int r_max, bool rank_order, bool stages);
 hipError_t launch_prompt_lse(const LaunchParams& p, int head_dim, bool bf16, int rows_max, hipStream_t s);
 hipError_t launch_reposition(const LaunchParams& p, int row_bytes, bool bf16, int r_max, int pairing,
@@ -112,6 +114,9 @@ hipError_t launch_owner_bf16(int head_dim, const LaunchParams& p, int stages, hi
 hipError_t launch_owner_loop_bf16(int head_dim, const LaunchParams& p, const int* step_first,
                                   int n_steps, int n_slots, hipStream_t s);
 hipError_t set_max_lds_owner(size_t bytes);
+hipError_t launch_owner_loop_once_bf16(int head_dim, const LaunchParams& p, const int* step_first,
+                                       int n_steps, int n_slots, hipStream_t s);
+hipError_t set_max_lds_owner_once(size_t bytes);
 // one workgroup per problem for fp32 inputs (prompt rows and rows of the chunk's own tokens)
 size_t owner_f32_lds_bytes(int head_dim);
 hipError_t launch_owner_f32(int head_dim, const LaunchParams& p, int stages, hipStream_t s);

@@ -34,21 +34,32 @@ hipError_t launch_owner_bf16(int head_dim, const LaunchParams& p, int stages, hi
 
 hipError_t launch_owner_loop_bf16(int head_dim, const LaunchParams& p, const int* step_first, int n_steps,
                                   int n_slots, hipStream_t s) {
-  return launch_owner_loop_impl<false>(head_dim, p, step_first, n_steps, n_slots, s);
+  if (p.est_words > 0) return launch_owner_loop_once_bf16(head_dim, p, step_first, n_steps, n_slots, s);
+  return launch_owner_loop_impl<false, false>(head_dim, p, step_first, n_steps, n_slots, s);
 }
 
-hipError_t set_max_lds_owner(size_t bytes) { return set_max_lds_owner_impl<false>(bytes); }
+hipError_t set_max_lds_owner(size_t bytes) {
+  const hipError_t e = set_max_lds_owner_impl<false>(bytes);
+  return e == hipSuccess ? set_max_lds_owner_once(bytes) : e;
+}
 
 }  // namespace finch
 
 #ifdef FINCH_PHASE_TIMERS
-// Phase-timer build only: the totals of the kernels of this file (prompt rows only) on the
-// current device, 8 words of wall-clock ticks (10 ns); reset != 0 clears them instead.
+extern "C" int finch_debug_phases_once(unsigned long long* out, int reset);
+// Phase-timer build only: the totals of the kernels for prompt rows only (of this file and of
+// owner_once_bf16.hip together) on the current device, 8 words of wall-clock ticks (10 ns); reset != 0
+// clears them instead.
 extern "C" int finch_debug_phases(unsigned long long* out, int reset) {
   if (reset) {
     const unsigned long long zero[8] = {0};
-    return static_cast<int>(hipMemcpyToSymbol(HIP_SYMBOL(finch::finch_phase_ticks), zero, sizeof(zero)));
+    const int e = finch_debug_phases_once(out, reset);
+    return e ? e : static_cast<int>(hipMemcpyToSymbol(HIP_SYMBOL(finch::finch_phase_ticks), zero, sizeof(zero)));
   }
-  return static_cast<int>(hipMemcpyFromSymbol(out, HIP_SYMBOL(finch::finch_phase_ticks), sizeof(unsigned long long) * 8));
+  unsigned long long once[8];
+  int e = finch_debug_phases_once(once, 0);
+  if (!e) e = static_cast<int>(hipMemcpyFromSymbol(out, HIP_SYMBOL(finch::finch_phase_ticks), sizeof(unsigned long long) * 8));
+  for (int i = 0; !e && i < 8; ++i) out[i] += once[i];
+  return e;
 }
 #endif

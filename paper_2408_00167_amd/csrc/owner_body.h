@@ -56,6 +56,15 @@ static __device__ unsigned long long finch_phase_ticks[8];
 constexpr int kOwnThreads = 512;
 constexpr int kOwnWaves = kOwnThreads / 64;
 
+// The thread's index, through an empty asm: in the whole-loop kernels the compiler would otherwise compute
+// everything that depends only on it once for all steps, and keep it in registers through every
+// phase.  So each phase asks for it anew.
+__device__ __forceinline__ int own_thread() {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  return tid;
+}
+
 __device__ __forceinline__ int own_next_block(int* counter, int lane) {
   int v = 0;
   if (lane == 0) v = atomicAdd(counter, 1);
@@ -76,6 +85,41 @@ struct KeptRows {
   const char* v0 = nullptr;
   bool mapped = false;       // the cache rows of this step are where `at` says, not in k_cache / v_cache
   bool stay = false;         // this step leaves its kept rows where they are
+};
+
+// Keys that stay open cost their part of the second pass, and as much as kEstFixed keys of one row block more: finding
+// them, and another selection.  One pass saves most of the other: worth trying up to half of that.
+constexpr int kEstFixed = 300;
+constexpr float kEstRoom = 1.15f;      // factor around the r-th largest score in which a slot without experience looks for others
+constexpr float kEstSpread = 16.f;     // log2 of the largest spread that is of use
+constexpr float kEstLeast = 0x1p-60f;  // smaller scores may have lost terms below the least exponent
+
+// Selection on one pass over the keys.  The weight of row i at key j is exp2(logit - lse_i), and lse_i is only known
+// when all keys have been seen: hence two passes.  But with any guess g_i of it, one pass gives S_j = sum_i
+// exp2(logit - g_i) for every key and z_i = 2^(lse_i - g_i) for every row; all terms are
+// positive, so the true score of every key lies between S_j / max_i z_i and S_j / min_i z_i.  Keys
+// further from the r-th largest S than that spread are in or out whatever their exact scores
+// are; only the others, often none, are scored exactly and chosen among.  The selection is that of the exact scores.
+// As guesses serve the log-sum-exps of the slot's step before (the same rows over most of the same heavy
+// keys).  The scores themselves are not formed, so this is for steps whose scores nobody can see:
+// the next step of the call overwrites all of them (the host has checked that nothing else of the
+// slot touches them), or there is no place to put them.
+// What bounds these loops is the chip's power: with 192 rows a launch runs at 1.72 GHz, at 1.92 GHz with the same
+// cycles when its keys come from L2, at 2.13 GHz without key loads.  So what counts is work not done: one
+// pass has half the matrix instructions, LDS operands and key bytes of two and two thirds of their
+// vector instructions.  Both sides of the loop of 256 problems, 128 channels: 192 rows, 4096-token chunks of 131072
+// tokens, no key near the line 4700 -> 2880 us, keys spread evenly 4850 -> 3610 (open keys scored
+// exactly); 256 rows, 2048-token chunks 1945 -> 1290; 32 rows, 512-token chunks, 1024 problems 957 -> 877.  Steps that do
+// not pay (kEstFixed) make both passes, 1 % slower than the kernels without this.
+struct RowEstimates {
+  float* lse = nullptr;      // LDS: one guess per staged row ...
+  int* words = nullptr;      // ... and kEstExtraWords words behind them: [0, 16) extremes per wave, [16] counter
+  const void* q = nullptr;   // the rows they are for
+  int rows = 0;
+  float room = kEstRoom;     // how far from the r-th largest score keys are taken to stay open: as in the last step that tried, less with every one that does not
+  bool dense = true;         // too many keys are that close (by the last step's scores): not worth trying
+  bool hidden = false;       // this step's scores are not seen by anybody
+  const int* ask = nullptr;  // (no estimate: memory that a later step begins with)
 };
 
 // Copy rows idx[t0..t1) of [cache ; chunk] of K and V into k_out / v_out by NT threads
@@ -331,32 +375,32 @@ __device__ __forceinline__ void own_no_rows(float* scores, unsigned* lkeys, int 
   __syncthreads();
 }
 
-// The rest of a step once this workgroup's scores are in memory (and a barrier has been
-// passed since): top-r (Method: t = top-r(A_agg, r); with `layered` on the sum over the
-// layer's heads) and compaction (Method: Managing the Cache) of rows of SEGS 16-byte
-// pieces with E elements each.  `sel` is LDS scratch of sel_bytes (owner_lds_bytes); `dst` the
+// What a step keeps: its rows' indices in LDS (null: only in pb.idx), all rows in their order
+// (identity), nothing (a wait has expired, or r is 0).
+struct Selected {
+  int* lidx;
+  bool identity, ok;
+};
+
+// Top-r (Method: t = top-r(A_agg, r); with `layered` on the sum over the
+// layer's heads) once this workgroup's scores are in memory (and a barrier has been passed since).
+// `sel` is LDS scratch of sel_bytes (owner_lds_bytes); `dst` the
 // scores of this problem; `lkeys` what own_sel_keys said, with the order keys of these scores
-// in it already (not those of the layer's sum).
-template <int SEGS, int E, bool ROT>
-__device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const finch_problem& pb, int slot, int N,
-                                                FINCH_GLOBAL float* dst, char* sel, size_t sel_bytes,
-                                                unsigned* lkeys, const finch_problem* step_probs, int epoch,
-                                                bool layered, int* sync_words, int tid, KeptRows& kept) {
+// in it already (not those of the layer's sum).  The indices are in LDS at the end (a barrier has been
+// passed), and in memory already if they were not chosen by `lkeys`.
+__device__ __forceinline__ Selected own_select(const LaunchParams& prm, const finch_problem& pb, int slot, int N,
+                                               FINCH_GLOBAL float* dst, char* sel, size_t sel_bytes,
+                                               unsigned* lkeys, const finch_problem* step_probs, int epoch,
+                                               bool layered, int* sync_words, int tid, SelBand* band = nullptr) {
   const int lane = tid & 63, wave = tid >> 6;
   const int L = prm.layer_group;
-  FINCH_PHASE_BEGIN();
-  // ---- top-r on the scores this workgroup has just written
   const int r = min(pb.r, N);
-  KeptRows mine = kept;
-  kept.mapped = false;  // (of the next step's cache; a step that gives up leaves none)
-  if (r <= 0) return;
+  if (r <= 0) return {nullptr, false, false};
   FINCH_GLOBAL int* gidx = as_global_mut<int>(pb.idx);
   const bool identity = r >= N;
   SelLds* fl = reinterpret_cast<SelLds*>(sel);
   int* lidx = nullptr;
-  if (identity) {
-    for (int i = tid; i < N; i += kOwnThreads) gidx[i] = i;
-  } else {
+  if (!identity) {
     if (sizeof(SelLds) + (static_cast<size_t>(r) + kSelIdxPad) * 4 <= sel_bytes)
       lidx = reinterpret_cast<int*>(sel + sizeof(SelLds));
     if (layered) {
@@ -390,7 +434,7 @@ __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const f
         // workgroup leaves the step's indices and cache rows unwritten.  It still says
         // that it will not read the others' scores any more.
         if (tid == 0) __hip_atomic_fetch_add(sync_words + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return;
+        return {nullptr, false, false};
       }
     }
     const LayerScores<kSelMaxLayer> layer_sum = {fl->layer_src, L};
@@ -400,21 +444,37 @@ __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const f
         sel_stage_layer_keys<kOwnThreads>(fl->layer_src, L, N, lkeys, tid);
         __syncthreads();
       }
-      select_keys_any<kOwnThreads, true>(lkeys, N, r, gidx, lidx, fl, tid, lane, wave);
+      select_keys_any<kOwnThreads, true>(lkeys, N, r, gidx, lidx, fl, tid, lane, wave, band);
     } else {
       __syncthreads();
       if (layered) select_generic<kOwnThreads>(layer_sum, N, r, gidx, lidx, fl, tid, lane, wave);
       else select_generic<kOwnThreads>(own, N, r, gidx, lidx, fl, tid, lane, wave);
     }
     __syncthreads();  // idx complete
-    if (lkeys)
-      for (int t = tid; t < r; t += kOwnThreads) gidx[t] = lidx[t];
     // (the other workgroups' scores have been read for the last time)
     if (layered && tid == 0) __hip_atomic_fetch_add(sync_words + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  FINCH_PHASE(6);
+  return {lidx, identity, true};
+}
 
-  // ---- compaction
+// The rest of a step once it is known what it keeps: the indices, and compaction (Method: Managing the
+// Cache) of rows of SEGS 16-byte pieces with E elements each.
+template <int SEGS, int E, bool ROT>
+__device__ __forceinline__ void own_compact(const LaunchParams& prm, const finch_problem& pb, int N, const Selected& chosen,
+                                            FINCH_GLOBAL float* dst, char* sel, bool in_lds, int tid, KeptRows& kept) {
+  const int r = min(pb.r, N);
+  KeptRows mine = kept;
+  kept.mapped = false;  // (of the next step's cache; a step that gives up leaves none)
+  if (!chosen.ok) return;
+  FINCH_PHASE_BEGIN();
+  FINCH_GLOBAL int* gidx = as_global_mut<int>(pb.idx);
+  const bool identity = chosen.identity;
+  int* const lidx = chosen.lidx;
+  if (identity) {
+    for (int i = tid; i < N; i += kOwnThreads) gidx[i] = i;
+  } else if (in_lds) {
+    for (int t = tid; t < r; t += kOwnThreads) gidx[t] = lidx[t];
+  }
   if (ROT) {
     // slots by relevance (Method: Managing the Cache, the worked example): the rank of a kept
     // row's score among the kept ones, highest first, equal scores by index.  The host
@@ -438,6 +498,18 @@ __device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const f
   FINCH_PHASE(7);
 }
 
+// Both.
+template <int SEGS, int E, bool ROT>
+__device__ __forceinline__ void own_finish_step(const LaunchParams& prm, const finch_problem& pb, int slot, int N,
+                                                FINCH_GLOBAL float* dst, char* sel, size_t sel_bytes,
+                                                unsigned* lkeys, const finch_problem* step_probs, int epoch,
+                                                bool layered, int* sync_words, int tid, KeptRows& kept) {
+  FINCH_PHASE_BEGIN();
+  const Selected chosen = own_select(prm, pb, slot, N, dst, sel, sel_bytes, lkeys, step_probs, epoch, layered, sync_words, tid);
+  FINCH_PHASE(6);
+  own_compact<SEGS, E, ROT>(prm, pb, N, chosen, dst, sel, lkeys != nullptr, tid, kept);
+}
+
 // Few rows of 64 channels: 128 registers are enough for a step, and two workgroups share a compute unit.
 constexpr bool own_lean(int d, int qbt, bool rot, bool doc) { return d == 64 && qbt == 2 && !rot && !doc; }
 
@@ -448,6 +520,14 @@ __device__ __forceinline__ bool own_whole(int qb, F f) {
   if (qb == QBT) return f(std::integral_constant<int, QBT>{});
   if (qb == QBT - 1) return f(std::integral_constant<int, QBT - 1>{});
   return false;
+}
+
+// The same for every number of row blocks up to QBT.
+template <int QBT, typename F>
+__device__ __forceinline__ bool own_any(int qb, F f) {
+  if (qb == QBT) return f(std::integral_constant<int, QBT>{});
+  if constexpr (QBT > 1) return own_any<QBT - 1>(qb, f);
+  else return false;
 }
 
 // One step of one problem by the whole workgroup.  QBT = row blocks (of 32 prompt
@@ -465,11 +545,12 @@ __device__ __forceinline__ bool own_whole(int qb, F f) {
 // and selects on the sum, so that all L arrive at the same indices on their own.
 // `step_probs` are the descriptors of this step, `epoch` counts the exchanges this
 // workgroup has been through in this launch; returns true if the step made one.
-template <int D, int QBT, bool ROT, bool DOC, bool LOOP>
+// ONCE: steps whose scores nobody sees may select on one pass (RowEstimates).
+template <int D, int QBT, bool ROT, bool DOC, bool LOOP, bool ONCE>
 __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const finch_problem& pb, int slot,
                                               int stages, char* smem, const void*& staged_q,
                                               int& staged_rows, const finch_problem* step_probs,
-                                              int epoch, KeptRows& kept) {
+                                              int epoch, KeptRows& kept, RowEstimates& est) {
   const int N = pb.c + pb.m;
   if (N == 0) {
     kept.mapped = false;
@@ -477,18 +558,13 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   }
   FINCH_PHASE_BEGIN();
   const int Rp = (DOC && !pb.q) ? 0 : prm.group * pb.n_que;  // prompt rows
-  // (the thread index goes through an empty asm: in the whole-loop kernel the compiler
-  // would otherwise compute everything that depends only on it once for all steps and
-  // keep it in registers through every phase)
-  int tid_ = threadIdx.x;
-  asm volatile("" : "+v"(tid_));
-  const int tid = tid_, lane = tid & 63;
+  const int tid = own_thread(), lane = tid & 63;
   // (DOC kernels: in a scalar register, so that the loops over a wave's key blocks are uniform.  A key buffer
   // there lives on past both exits of such a loop; with a loop that lanes may leave at different times the
   // compiler keeps what either exit hands on in registers of its own, 32 more than there are: up to
   // 56 spilled, 789 us in place of 604 for the loop of 256 problems, 200-token chunks, with
   // re-positioning, 808 and 743 for a step of 256 problems of 512 + 1024 candidates.)
-  const int wave = DOC ? uni(tid >> 6) : tid >> 6;
+  const int wave = DOC || ONCE ? uni(tid >> 6) : tid >> 6;
   const int t = lane & 31, h = lane >> 5;
   constexpr int kStride = D * 2 + 16;
   const int RC = prm.row_chunk;
@@ -560,7 +636,12 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   // 256 problems of 192 rows, 1024-token chunks, 17 chunks of rows a step: the loop takes 2216 us,
   // 2346 where every chunk asks for its rows when its turn has come (64 channels, 256 rows: 1569 and 1669).
   bf16x8 ka[D / 16], kb[D / 16];
+  static_assert(!ONCE || (LOOP && !DOC));
+  bool once = ONCE && est.hidden && est.q == pb.q && est.rows == Rp && n_chunks == 1 && lkeys && !est.dense;
+  Selected chosen = {nullptr, false, false};
+  int asked;  // (asked for beside the first key block)
   for (int ch = 0; ch < n_chunks; ++ch) {
+    const int tid = own_thread(), lane = tid & 63, t = lane & 31, h = lane >> 5;
     const RowChunk rc = row_chunk(ch);
     const void* const qsrc = rc.qsrc;
     const int R = rc.R, row0 = rc.row0, lim0 = rc.lim0, lim_step = rc.lim_step;
@@ -580,6 +661,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
       __syncthreads();
     } else {
       load_k_block<D>(ks, N, b << 5, lane, ka);  // requested before Q is staged
+      if (LOOP && ch == 0) asked = *as_global<int>(est.ask);
       if (!(R <= RC && staged_q == qsrc && staged_rows == R)) {
         stage_q<D, kOwnThreads>(qsrc, R, row0, rows, lds_q, tid);
         __syncthreads();
@@ -588,6 +670,125 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     staged_q = nullptr;
     FINCH_PHASE(0);
 
+    // ---- the only pass (RowEstimates): row sums and key sums of exp2(logit - guess), fixed block assignment
+    float spread = 0.f;  // log2 of max_i z_i / min_i z_i
+    if (ONCE && once) {
+      const int tid = own_thread(), lane = tid & 63, t = lane & 31, h = lane >> 5;
+      float z_run[QBT], g[QBT];
+#pragma unroll
+      for (int q = 0; q < QBT; ++q) {
+        z_run[q] = 0.f;
+        g[q] = q < QB ? est.lse[q * 32 + t] : kInf;
+      }
+      auto put = [&](float tot, int kbase) {
+        const int key = kbase + acc_key(t >> 1, h);
+        if ((t & 1) == 0 && key < N) lkeys[key] = order_key(tot);
+      };
+      auto process = [&](const bf16x8(&kf)[D / 16], int blk) {
+        const int kbase = blk << 5;
+        float u[16];
+        auto whole_block = [&](auto qb) {
+          constexpr int QBC = decltype(qb)::value;
+          float z[QBC];
+          for_block_logits<D, QBC>(kf, lds_q, lane, [&](int q, int v, float a) {
+            const float e = fast_exp2(__builtin_fmaf(a, sc, -g[q]));
+            z[q] = v == 0 ? e : z[q] + e;
+            u[v] = q == 0 ? e : u[v] + e;
+          });
+#pragma unroll
+          for (int q = 0; q < QBC; ++q) z_run[q] += z[q];
+          return true;
+        };
+        if (kbase + 32 > N) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) u[v] = 0.f;
+#pragma unroll
+          for (int q = 0; q < QBT; ++q) {
+            if (q < QB) {
+              bf16x8 qf[D / 16];
+              load_q_frags<D>(lds_q, q, lane, qf);
+              const f32x16 a = mfma_block<D>(kf, qf);
+              float z = 0.f;
+#pragma unroll
+              for (int v = 0; v < 16; ++v) {
+                const float e = kbase + acc_key(v, h) < N ? fast_exp2(__builtin_fmaf(a[v], sc, -g[q])) : 0.f;
+                z += e;
+                u[v] += e;
+              }
+              z_run[q] += z;
+            }
+          }
+        } else {
+          own_any<QBT>(QB, whole_block);
+        }
+        put(fold16_over32(u, t), kbase);
+      };
+      if (b < nb) {
+        while (true) {
+          load_k_block<D>(ks, N, (b + kOwnWaves) << 5, lane, kb);
+          process(ka, b);
+          b += kOwnWaves;
+          if (b >= nb) break;
+          load_k_block<D>(ks, N, (b + kOwnWaves) << 5, lane, ka);
+          process(kb, b);
+          b += kOwnWaves;
+          if (b >= nb) break;
+        }
+        // (neither buffer is of use to what follows)
+        forget<D>(ka);
+        forget<D>(kb);
+      }
+      float* const wsum = reinterpret_cast<float*>(wstats);  // [waves][RC]
+#pragma unroll
+      for (int q = 0; q < QBT; ++q) {
+        if (q < QB) {
+          const float z = z_run[q] + __shfl_xor(z_run[q], 32);
+          if (h == 0) wsum[wave * RC + q * 32 + t] = z;
+        }
+      }
+      FINCH_PHASE(1);
+      if (tid == 0) est.words[16] = 0;
+      __syncthreads();
+      FINCH_PHASE(2);
+      // every row's log-sum-exp takes the place of its guess
+      unsigned most = 0u, least = 0u;  // order keys of log2 z_i, the least one's complement
+      if (tid < rows) {
+        float l = kInf;
+        if (tid < R) {
+          float z = wsum[tid];
+#pragma unroll
+          for (int w = 1; w < kOwnWaves; ++w) z += wsum[w * RC + tid];
+          const float guess = est.lse[tid];
+          l = guess + fast_log2(z);
+          if (pb.lse_extra) l = widen_lse(l, as_global<float>(pb.lse_extra)[tid]);
+          most = order_key(l - guess);
+          least = ~most;
+        }
+        est.lse[tid] = l;
+      }
+      most = wave_max_u32(most);
+      least = wave_max_u32(least);
+      if (lane == 0) {
+        est.words[2 * wave] = static_cast<int>(most);
+        est.words[2 * wave + 1] = static_cast<int>(least);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < kOwnWaves; ++w) {
+        most = max(most, static_cast<unsigned>(est.words[2 * w]));
+        least = max(least, static_cast<unsigned>(est.words[2 * w + 1]));
+      }
+      spread = uni(order_value(most) - order_value(~least));
+      FINCH_PHASE(3);
+      // (rows that are not numbers, or whose sum has moved out of range)
+      if (!(spread <= kEstSpread)) {
+        once = false;
+        b = wave;
+        load_k_block<D>(ks, N, b << 5, lane, ka);
+      }
+    }
+
+    if (!ONCE || !once) {
     // ---- pass 1: running (reference, sum exp2) per prompt row, fixed block assignment
     {
       float m_run[QBT], z_run[QBT];
@@ -715,7 +916,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     if (tid == 0) *sh_next = kOwnWaves;
     __syncthreads();
     FINCH_PHASE(2);
-    for (int i = tid; i < rows; i += kOwnThreads) {
+    for (int i = own_thread(); i < rows; i += kOwnThreads) {
       float l = kInf;  // padding rows add exp2(-inf) = 0
       if (row0 + i < R) {
         float2 a = wstats[i];
@@ -733,10 +934,20 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
         }
       }
       lds_lse[i] = l;
+      if (ONCE && n_chunks == 1) est.lse[i] = l;
     }
     __syncthreads();
     FINCH_PHASE(3);
-    {
+    }
+
+    // ---- pass 2, and the selection behind the last chunk of rows.  After the only pass it comes
+    // first, and pass 2 is for the keys that it leaves open (`list`; null: all).
+    if (LOOP) asm volatile("" ::"v"(asked));
+    int n2 = N, nb2 = nbc;
+    KeySource ks2 = ks;
+    for (int turn = ONCE && once ? 1 : 0; turn < 3; ++turn) {
+    if (turn != 1) {
+      const int tid = own_thread(), lane = tid & 63, t = lane & 31, h = lane >> 5;
       auto process = [&](const bf16x8(&kf)[D / 16], int blk) {
         const int kbase = blk << 5;
         float u[16];
@@ -761,7 +972,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
           for_block_logits<D, QBC>(kf, lds_q, lane, [&](int q, int v, float a) { u[v] += fast_exp2(__builtin_fmaf(a, sc, -L[q])); });
           return true;
         };
-        if (!WHOLE || kbase + 32 > min(N, lim0) || !whole(QB, whole_block)) {
+        if (!WHOLE || kbase + 32 > min(n2, lim0) || !whole(QB, whole_block)) {
           auto pair_visible = [&](int q) { return !DOC || kbase < lim_hi(q + 1 < QB ? q + 1 : q); };
           // pairs of row blocks, the vector work one pair behind the matrix work
           f32x16 acc[QBT];
@@ -783,8 +994,13 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
           }
         }
         const float tot = fold16_over32(u, t);
-        const int key = kbase + acc_key(t >> 1, h);
-        if ((t & 1) == 0 && key < N) {
+        int key = kbase + acc_key(t >> 1, h);
+        if ((t & 1) == 0 && key < n2) {
+          if (ONCE && once) {
+            if (ks2.list) key = ks2.list[key];
+            lkeys[key] = order_key(tot);
+            return;
+          }
           const float val = first_chunk ? tot : dst[key] + tot;
           // (scores other workgroups will read go out past this compute unit's caches)
           if (layered) __hip_atomic_store(dst + key, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -795,7 +1011,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
       // the next key block, or the next chunk's rows when there is none
       auto load_next = [&](int bn, bf16x8(&kf)[D / 16]) {
         if (!DOC || bn >= 0) {
-          load_k_block<D>(ks, N, bn * 32, lane, kf);
+          load_k_block<D>(ks2, n2, bn * 32, lane, kf);
         } else {
           const RowChunk nx = row_chunk(min(ch + 1, n_chunks - 1));
           hold_q<D, kOwnThreads>(nx.qsrc, nx.R, nx.row0, RC, tid, kf);
@@ -803,12 +1019,12 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
       };
       if (b >= 0) {
         while (true) {
-          int bn = nbc - 1 - own_next_block(sh_next, lane);
+          int bn = nb2 - 1 - own_next_block(sh_next, lane);
           load_next(bn, kb);
           process(ka, b);
           b = bn;
           if (b < 0) break;
-          bn = nbc - 1 - own_next_block(sh_next, lane);
+          bn = nb2 - 1 - own_next_block(sh_next, lane);
           load_next(bn, ka);
           process(kb, b);
           b = bn;
@@ -820,19 +1036,72 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
       } else {
         load_next(b, kb);
       }
-      if (DOC) load_k_block<D>(ks, N, wave << 5, lane, ka);  // the next chunk's first
-    }
+      if (DOC) {
+        load_k_block<D>(ks, N, wave << 5, lane, ka);  // the next chunk's first
+      } else if (LOOP) {
+        // (What is still on its way is awaited here, with few stores behind it.  Left to itself the compiler
+        // waits where it takes the registers again, at the next step's start, and there for all stores
+        // of the step: 45 of 1020 us in the loop of 1024 problems, 32 rows, 512-token chunks.)
+        forget<D>(ka);
+        forget<D>(kb);
+      }
     FINCH_PHASE(4);
     __syncthreads();  // scores of this row chunk are out; LDS may be restaged
     FINCH_PHASE(5);
+    }
+    if (!ONCE || !stages || ch + 1 < n_chunks) break;
+    const int tid = own_thread(), lane = tid & 63, wave = uni(tid >> 6);
+    SelBand band = {turn == 1 ? fast_exp2(spread) * 1.004f : est.room};
+    chosen = own_select(prm, pb, slot, N, dst, sel, sel_bytes, lkeys, step_probs, epoch, layered, sync_words, tid, &band);
+    FINCH_PHASE(6);
+    const int n_lo = uni(band.n_lo), open = n_lo - uni(band.n_hi);
+    if (turn < 2) est.dense = !lkeys || (n_lo > pb.r && 2 * (open * QB + kEstFixed) > N * QB);
+    est.room = fmaxf(kEstRoom, turn == 1 ? uni(band.room) : 0.5f + 0.5f * est.room);
+    if (turn != 1) break;
+    // Keys below band.thr_lo are out and those above band.thr_hi are in whatever their exact scores are.
+    // (The 0.4 % beside the spread are far more than what fp32 sums of exponentials differ by.)
+    if (n_lo == pb.r && band.least >= kEstLeast) break;
+    // ---- the others one by one
+    const unsigned thr_lo = band.thr_lo, thr_hi = band.thr_hi;
+    n2 = open;
+    unsigned short* const list = reinterpret_cast<unsigned short*>(sel + static_cast<size_t>(RC) * (kOwnWaves * 8 + 4) + 16);
+    if (!(band.least >= kEstLeast) || n2 <= 0 || reinterpret_cast<char*>(list + n2) > reinterpret_cast<char*>(lkeys)) {
+      n2 = N;
+    } else {
+      for (int i0 = 0; i0 < N; i0 += kOwnThreads) {
+        const int i = i0 + tid;
+        const unsigned key = i < N ? lkeys[i] : 0u;
+        const bool mine = i < N && key >= thr_lo && key <= thr_hi;
+        const unsigned long long m = __ballot(mine);
+        int at = 0;
+        if (lane == 0 && m) at = atomicAdd(est.words + 16, __popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & ((1ull << lane) - 1ull));
+        if (mine) list[at] = static_cast<unsigned short>(i);
+        else if (i < N) lkeys[i] = order_key(key > thr_hi ? 3.4028234e38f : 0.f);
+      }
+      ks2.list = list;
+    }
+    nb2 = (n2 + 31) >> 5;
+    if (tid < rows) lds_lse[tid] = est.lse[tid];
+    if (tid == 0) *sh_next = kOwnWaves;
+    __syncthreads();
+    b = nb2 - 1 - wave;
+    load_k_block<D>(ks2, n2, b * 32, lane, ka);
+    }
   }
   if (DOC && n_chunks == 0) own_no_rows(gscores, lkeys, N, tid);
   // what the prompt-row region of LDS holds now (selection scratch lies behind it)
   staged_q = (n_chunks == 1) ? pb.q : nullptr;
   staged_rows = Rp;
+  est.q = staged_q;
+  est.rows = Rp;
   if (!stages) return false;
 
   // ---- top-r and compaction (the pass-1 statistics are dead)
+  if (ONCE) {
+    own_compact<D / 8, 8, ROT>(prm, pb, N, chosen, dst, sel, lkeys != nullptr, tid, kept);
+    return layered;
+  }
   own_finish_step<D / 8, 8, ROT>(prm, pb, slot, N, dst, sel, sel_bytes, lkeys, step_probs, epoch, layered, sync_words, tid, kept);
   return layered;
 }
@@ -849,11 +1118,14 @@ __device__ __forceinline__ int own_slot_of(int b, int n, int L) {
 
 // Whether a step may leave the rows it keeps where they are: the next step's cache is exactly
 // these rows, and the step after that writes as many at the same place.
-__device__ __forceinline__ bool own_rows_may_stay(const finch_problem& pb, const finch_problem* next, const finch_problem* after,
-                                                  int cap) {
-  const int r = min(pb.r, pb.c + pb.m);
-  return r > 0 && r <= cap && next->c == r && next->k_cache == pb.k_out && next->v_cache == pb.v_out &&
-         after->k_out == pb.k_out && after->v_out == pb.v_out && min(after->r, after->c + after->m) >= r;
+typedef const __attribute__((address_space(4))) finch_problem* DescriptorPtr;  // (read through the scalar cache, as load_problem does)
+typedef const __attribute__((address_space(4))) int* StepTablePtr;
+__device__ __forceinline__ bool own_rows_may_stay(DescriptorPtr pb, DescriptorPtr next, DescriptorPtr after, int cap) {
+  // (no short cuts: all of it is asked for at once)
+  const int r = min(pb->r, pb->c + pb->m), r_after = min(after->r, after->c + after->m);
+  const bool rows = (r > 0) & (r <= cap) & (next->c == r) & (r_after >= r);
+  const bool places = (next->k_cache == pb->k_out) & (next->v_cache == pb->v_out) & (after->k_out == pb->k_out) & (after->v_out == pb->v_out);
+  return rows & places;
 }
 
 // One launch = one step of every problem of a batch; workgroup b owns problem b.
@@ -866,7 +1138,8 @@ __global__ __launch_bounds__(kOwnThreads, own_lean(D, QBT, ROT, DOC) ? 4 : 2) vo
   const void* staged_q = nullptr;
   int staged_rows = 0;
   KeptRows kept;
-  own_step_body<D, QBT, ROT, DOC, false>(prm, pb, p, stages, smem, staged_q, staged_rows, prm.probs, 0, kept);
+  RowEstimates est;
+  own_step_body<D, QBT, ROT, DOC, false, false>(prm, pb, p, stages, smem, staged_q, staged_rows, prm.probs, 0, kept, est);
 }
 
 // One launch = the whole chunk loop (Method: Document Segmentation): workgroup b
@@ -878,7 +1151,7 @@ __global__ __launch_bounds__(kOwnThreads, own_lean(D, QBT, ROT, DOC) ? 4 : 2) vo
 // (KeptRows) if own_rows_may_stay says so.  256 problems, 4096-token chunks, up to 1408 kept rows:
 // the copies were 20 of 187 us a step, the loop takes 5533 us in place of 6080; 1024 problems of
 // 32 rows, 512-token chunks and up to 1024 kept rows, where they were 18 of 42 us: 999 in place of 1354.
-template <int D, int QBT, bool ROT, bool DOC>
+template <int D, int QBT, bool ROT, bool DOC, bool ONCE>
 __global__ __launch_bounds__(kOwnThreads) void owner_loop_bf16(LaunchParams prm, const int* step_first,
                                                                int n_steps) {
   extern __shared__ __align__(16) char smem[];
@@ -889,21 +1162,46 @@ __global__ __launch_bounds__(kOwnThreads) void owner_loop_bf16(LaunchParams prm,
   KeptRows kept;
   kept.at = reinterpret_cast<int*>(smem + prm.lds_bytes);
   kept.cap = prm.stay_rows;
+  const DescriptorPtr probs = (DescriptorPtr)(unsigned long long)prm.probs;
+  const StepTablePtr table = (StepTablePtr)(unsigned long long)step_first;
   if (prm.stay_rows > 0) {
-    const finch_problem* p0 = prm.probs + slot;
+    const DescriptorPtr p0 = probs + slot;
     kept.k0 = static_cast<const char*>(p0->m > 0 ? p0->k_chunk : p0->k_cache);
     kept.v0 = static_cast<const char*>(p0->m > 0 ? p0->v_chunk : p0->v_cache);
   }
+  RowEstimates est;
+  if (ONCE) {
+    est.lse = reinterpret_cast<float*>(smem + prm.lds_bytes + 8u * static_cast<unsigned>(prm.stay_rows));
+    est.words = reinterpret_cast<int*>(est.lse) + prm.row_chunk;
+  }
+  // Descriptors come from memory that this launch has not touched yet, 1 to 2 us away, and a step begins with
+  // what it and the two after it say.  So each step asks for the one three steps on (once its own first
+  // loads are on their way), to have it in the L2 by then.
+  auto descriptor_at = [&](int s) {
+    const int at = table[min(s, n_steps - 1)];
+    const bool there = s < n_steps && slot < table[s + 1] - at;
+    return reinterpret_cast<const int*>(prm.probs + (there ? at : 0) + slot) + (threadIdx.x & 1) * (sizeof(finch_problem) / 4 - 1);
+  };
+  FINCH_PHASE_BEGIN();
   for (int s = 0; s < n_steps; ++s) {
-    const int first = step_first[s];
-    if (slot >= step_first[s + 1] - first) break;  // slots are filled from the front
-    const finch_problem pb = prm.probs[first + slot];
-    kept.stay = false;
+#ifdef FINCH_PHASE_TIMERS
+    if (s > 0) phase_last_ = wall_clock64();
+#endif
+    const int t0 = table[s], t1 = table[s + 1], t2 = table[min(s + 2, n_steps)], t3 = table[min(s + 3, n_steps)];
+    if (slot >= t1 - t0) break;  // slots are filled from the front
+    const bool more1 = slot < t2 - t1, more2 = slot < t3 - t2;  // (nobody is present past the last step)
+    const DescriptorPtr next = probs + (more1 ? t1 : t0) + slot, after = probs + (more2 ? t2 : t0) + slot;
+    kept.stay = own_rows_may_stay(probs + t0 + slot, next, after, prm.stay_rows);
+    if (ONCE)
+      est.hidden = more1 && next->scores == probs[t0 + slot].scores && next->c + next->m >= probs[t0 + slot].c + probs[t0 + slot].m;
+    const finch_problem pb = load_problem(prm.probs + t0 + slot);
     // (rows in a cache that an earlier step has moved would be overwritten while they are still wanted)
-    if (prm.stay_rows > 0 && s + 2 < n_steps && slot < step_first[s + 3] - step_first[s + 2] && (s == 0 || pb.c == 0 || kept.mapped))
-      kept.stay = own_rows_may_stay(pb, prm.probs + step_first[s + 1] + slot, prm.probs + step_first[s + 2] + slot, prm.stay_rows);
-    if (own_step_body<D, QBT, ROT, DOC, true>(prm, pb, slot, /*stages=*/1, smem, staged_q, staged_rows, prm.probs + first,
-                                        epoch, kept))
+    kept.stay = kept.stay && more2 && (s == 0 || pb.c == 0 || kept.mapped);
+    est.hidden = est.hidden || !pb.scores;
+    est.ask = descriptor_at(s + 3);
+    FINCH_PHASE(0);
+    if (own_step_body<D, QBT, ROT, DOC, true, ONCE>(prm, pb, slot, /*stages=*/1, smem, staged_q, staged_rows, prm.probs + t0,
+                                        epoch, kept, est))
       ++epoch;
     // the rows this step wrote are the next step's cache: complete before it reads
     __syncthreads();
@@ -920,34 +1218,31 @@ int own_qbt(int row_chunk) {
   return 0;
 }
 
-// Calls f(kernel) for the instantiation that matches (head_dim, qbt, rot); `loop`
-// picks the whole-loop kernel.  Returns false for a combination that is not built.
+// Calls f(kernel) for the instantiation that matches (head_dim, qbt, rot).  Returns false for a
+// combination that is not built.
+#define FINCH_OWN_CASES(KERNEL, ...)                                                      \
+  FINCH_OWN_CASE(128, 2, KERNEL, __VA_ARGS__) FINCH_OWN_CASE(128, 4, KERNEL, __VA_ARGS__) \
+  FINCH_OWN_CASE(128, 6, KERNEL, __VA_ARGS__) FINCH_OWN_CASE(128, 8, KERNEL, __VA_ARGS__) \
+  FINCH_OWN_CASE(64, 2, KERNEL, __VA_ARGS__) FINCH_OWN_CASE(64, 4, KERNEL, __VA_ARGS__)   \
+  FINCH_OWN_CASE(64, 6, KERNEL, __VA_ARGS__) FINCH_OWN_CASE(64, 8, KERNEL, __VA_ARGS__)
+#define FINCH_OWN_CASE(DD, QQ, KERNEL, ...)         \
+  if (head_dim == DD && qbt == QQ) {                \
+    if (rot) f(&KERNEL<DD, QQ, true, __VA_ARGS__>); \
+    else f(&KERNEL<DD, QQ, false, __VA_ARGS__>);    \
+    return true;                                    \
+  }
 template <bool DOC, typename F>
 bool with_step_kernel(int head_dim, int qbt, bool rot, F f) {
-#define FINCH_OWN_CASE(DD, QQ)                                           \
-  if (head_dim == DD && qbt == QQ) {                                     \
-    if (rot) f(&owner_step_bf16<DD, QQ, true, DOC>);                     \
-    else f(&owner_step_bf16<DD, QQ, false, DOC>);                        \
-    return true;                                                         \
-  }
-  FINCH_OWN_CASE(128, 2) FINCH_OWN_CASE(128, 4) FINCH_OWN_CASE(128, 6) FINCH_OWN_CASE(128, 8)
-  FINCH_OWN_CASE(64, 2) FINCH_OWN_CASE(64, 4) FINCH_OWN_CASE(64, 6) FINCH_OWN_CASE(64, 8)
-#undef FINCH_OWN_CASE
+  FINCH_OWN_CASES(owner_step_bf16, DOC)
   return false;
 }
-template <bool DOC, typename F>
+template <bool DOC, bool ONCE, typename F>
 bool with_loop_kernel(int head_dim, int qbt, bool rot, F f) {
-#define FINCH_OWN_CASE(DD, QQ)                                           \
-  if (head_dim == DD && qbt == QQ) {                                     \
-    if (rot) f(&owner_loop_bf16<DD, QQ, true, DOC>);                     \
-    else f(&owner_loop_bf16<DD, QQ, false, DOC>);                        \
-    return true;                                                         \
-  }
-  FINCH_OWN_CASE(128, 2) FINCH_OWN_CASE(128, 4) FINCH_OWN_CASE(128, 6) FINCH_OWN_CASE(128, 8)
-  FINCH_OWN_CASE(64, 2) FINCH_OWN_CASE(64, 4) FINCH_OWN_CASE(64, 6) FINCH_OWN_CASE(64, 8)
-#undef FINCH_OWN_CASE
+  FINCH_OWN_CASES(owner_loop_bf16, DOC, ONCE)
   return false;
 }
+#undef FINCH_OWN_CASE
+#undef FINCH_OWN_CASES
 
 // p.row_chunk and p.lds_bytes must describe this kernel's layout (owner_lds_bytes).
 template <bool DOC>
@@ -963,36 +1258,40 @@ hipError_t launch_owner_impl(int head_dim, const LaunchParams& p, int stages, hi
 
 // The whole loop: n_slots workgroups; step_first is a DEVICE array of n_steps + 1
 // offsets into p.probs.
-template <bool DOC>
+template <bool DOC, bool ONCE>
 hipError_t launch_owner_loop_impl(int head_dim, const LaunchParams& p, const int* step_first, int n_steps,
                                   int n_slots, hipStream_t s) {
   if (n_slots <= 0 || n_steps <= 0) return hipSuccess;
   const dim3 grid(static_cast<unsigned>(n_slots)), block(kOwnThreads);
-  const bool ok = with_loop_kernel<DOC>(head_dim, own_qbt(p.row_chunk), p.rope_pairing != FINCH_ROPE_OFF || p.rank_order,
+  const bool ok = with_loop_kernel<DOC, ONCE>(head_dim, own_qbt(p.row_chunk), p.rope_pairing != FINCH_ROPE_OFF || p.rank_order,
                                         [&](auto kern) {
-                                          hipLaunchKernelGGL(kern, grid, block, p.lds_bytes + 8u * static_cast<unsigned>(p.stay_rows), s,
+                                          hipLaunchKernelGGL(kern, grid, block, p.lds_bytes + 8u * static_cast<unsigned>(p.stay_rows) + 4u * static_cast<unsigned>(p.est_words), s,
                                                              p, step_first, n_steps);
                                         });
   return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
-template <bool DOC>
-hipError_t set_max_lds_owner_impl(size_t bytes) {
+// with(head_dim, qbt, rot, f): as above.
+template <typename W>
+hipError_t set_max_lds_kernels(size_t bytes, W with) {
   hipError_t err = hipSuccess;
   const int dims[2] = {128, 64}, qbts[4] = {2, 4, 6, 8};
   for (int d = 0; d < 2; ++d)
     for (int q = 0; q < 4; ++q)
-      for (int rot = 0; rot < 2; ++rot) {
-        auto set = [&](auto kern) {
+      for (int rot = 0; rot < 2; ++rot)
+        with(dims[d], qbts[q], rot != 0, [&](auto kern) {
           const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                    hipFuncAttributeMaxDynamicSharedMemorySize,
                                                    static_cast<int>(bytes));
           if (e != hipSuccess) err = e;
-        };
-        with_step_kernel<DOC>(dims[d], qbts[q], rot != 0, set);
-        with_loop_kernel<DOC>(dims[d], qbts[q], rot != 0, set);
-      }
+        });
   return err;
+}
+template <bool DOC>
+hipError_t set_max_lds_owner_impl(size_t bytes) {
+  const hipError_t e = set_max_lds_kernels(bytes, [](int d, int q, bool rot, auto f) { with_step_kernel<DOC>(d, q, rot, f); });
+  if (e != hipSuccess) return e;
+  return set_max_lds_kernels(bytes, [](int d, int q, bool rot, auto f) { with_loop_kernel<DOC, false>(d, q, rot, f); });
 }
 
 }  // namespace

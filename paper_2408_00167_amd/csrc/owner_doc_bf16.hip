@@ -12,7 +12,7 @@ hipError_t launch_owner_doc_bf16(int head_dim, const LaunchParams& p, int stages
 
 hipError_t launch_owner_loop_doc_bf16(int head_dim, const LaunchParams& p, const int* step_first,
                                       int n_steps, int n_slots, hipStream_t s) {
-  return launch_owner_loop_impl<true>(head_dim, p, step_first, n_steps, n_slots, s);
+  return launch_owner_loop_impl<true, false>(head_dim, p, step_first, n_steps, n_slots, s);
 }
 
 hipError_t set_max_lds_owner_doc(size_t bytes) { return set_max_lds_owner_impl<true>(bytes); }

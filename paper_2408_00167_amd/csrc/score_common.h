@@ -74,13 +74,15 @@ __device__ __forceinline__ T* uni(T* p) {
 }
 
 // Where the keys of a problem live: rows [0, c) in `cache`, the rest in `chunk`.  With `mapped` row
-// j < c stands at[j] 16-byte pieces behind `cache` (`at` in LDS).
+// j < c stands at[j] 16-byte pieces behind `cache` (`at` in LDS).  With `list` (LDS) place i of a key
+// block holds row list[i].
 struct KeySource {
   const char* cache;
   const char* chunk;
   int c;
   bool mapped = false;
   const int* at = nullptr;
+  const unsigned short* list = nullptr;
 };
 
 // One 32-key block of K as MFMA A operands: lane (t, h) holds row kbase + t,
@@ -93,7 +95,8 @@ struct KeySource {
 template <int D>
 __device__ __forceinline__ void load_k_block(const KeySource& ks, int N, int kbase, int lane,
                                              bf16x8 (&kf)[D / 16]) {
-  const int key = max(0, min(kbase + (lane & 31), N - 1));
+  int key = max(0, min(kbase + (lane & 31), N - 1));
+  if (ks.list) key = ks.list[key];
   const char* row = key < ks.c ? ks.cache + static_cast<size_t>(key) * (D * 2)
                                : ks.chunk + static_cast<size_t>(key - ks.c) * (D * 2);
   if (ks.mapped && key < ks.c) row = ks.cache + static_cast<long long>(ks.at[key]) * 16;
@@ -163,6 +166,13 @@ __device__ __forceinline__ void stage_q_held(const bf16x8 (&held)[D / 16], int R
     const u32x4 raw = __builtin_bit_cast(u32x4, held[u]);
     if (row < rows) *reinterpret_cast<u32x4*>(lds_q + row * kStride + seg * 16) = row0 + row < R ? raw : zero;
   }
+}
+
+// The buffer holds nothing of use any more.
+template <int D>
+__device__ __forceinline__ void forget(bf16x8 (&kf)[D / 16]) {
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) asm volatile("" : "=v"(kf[s]));
 }
 
 template <int D>

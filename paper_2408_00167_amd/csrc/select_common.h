@@ -34,6 +34,11 @@ __device__ __forceinline__ unsigned order_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// The float of an order key.
+__device__ __forceinline__ float order_value(unsigned key) {
+  return __uint_as_float((key & 0x80000000u) ? key & 0x7fffffffu : ~key);
+}
+
 // Inclusive prefix sum over the 64 lanes of a wave without a trip through LDS: shifts
 // by 1, 2, 4, 8 inside each row of 16 lanes (zeros shifted in), then lane 15 of every
 // even row is added to the row above it and lane 31 to the upper half.
@@ -72,6 +77,16 @@ struct SelLds {  // LDS scratch of a selection
   int digit[4], remaining[4];
   const float* layer_src[kSelMaxLayer];  // LayerScores: the score vectors of a layer's heads
   int layer_gave_up;                     // the wait for the layer's other workgroups expired
+};
+
+// What a selection may be asked beside its result: which candidates lie within a factor `room` of the r-th
+// largest score, for non-negative scores.  thr_lo is the order key of the least score / room, thr_hi
+// that of the most that score can be * room; n_lo candidates are not below the one, n_hi above the other.
+struct SelBand {
+  float room;
+  unsigned thr_lo = 0u, thr_hi = 0u;
+  int n_lo = 0, n_hi = 0;
+  float least = 0.f;  // the r-th largest score is not below this
 };
 
 // Where a selection takes the score of candidate i from: one vector ...
@@ -246,7 +261,7 @@ __device__ __forceinline__ void select_generic(const Src& score_of, int N, int r
 // to `gidx`.  0 < r < N.  Whole workgroup; ends without a barrier.
 template <int NT, int KMAX, bool LDS_OUT>
 __device__ __forceinline__ void select_keys(const unsigned* keys, int N, int r, FINCH_GLOBAL int* gidx, int* lidx,
-                                            SelLds* f, int tid, int lane, int wave) {
+                                            SelLds* f, int tid, int lane, int wave, SelBand* band = nullptr) {
   constexpr int kWavesNT = NT / 64;
   const int K = ((N + NT - 1) / NT) | 1;
   const int i0 = tid * K;
@@ -287,6 +302,7 @@ __device__ __forceinline__ void select_keys(const unsigned* keys, int N, int r, 
   int remaining = r;
   unsigned T = lo;           // keys above T are kept,
   int need_eq = remaining;   // and the first need_eq of those equal to it
+  unsigned kth_hi = lo;      // most that the r-th largest key can be
   for (int round = 0; range != 0u; ++round) {
     int* hist = f->hist[round & 1];
     if (round >= 2) {  // (everyone has read it: the barrier of the round before lies between)
@@ -309,10 +325,12 @@ __device__ __forceinline__ void select_keys(const unsigned* keys, int N, int r, 
     if (count == remaining) {  // the whole bin is kept
       T = lo - 1u;
       need_eq = 0;
+      kth_hi = lo + range;
       break;
     }
     T = lo;
     need_eq = remaining;
+    kth_hi = lo;
     if (range != 0u && count <= kSelCand) {
       unsigned in_bin = 0u;
 #pragma unroll
@@ -342,6 +360,7 @@ __device__ __forceinline__ void select_keys(const unsigned* keys, int N, int r, 
       const int src = m ? __ffsll(static_cast<long long>(m)) - 1 : 0;
       T = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(mine), src));
       need_eq = remaining - __builtin_amdgcn_readlane(above, src);
+      kth_hi = T;
       break;
     }
   }
@@ -350,8 +369,26 @@ __device__ __forceinline__ void select_keys(const unsigned* keys, int N, int r, 
 #pragma unroll
   for (int k = 0; k < KMAX; ++k) mine += (key[k] > T ? 1 : 0) + (key[k] == T ? 0x10000 : 0);
   const int incl = wave_inclusive_scan(mine);
+  if (band) {
+    band->least = order_value(T);
+    band->thr_lo = order_key(band->least / band->room);
+    band->thr_hi = order_key(order_value(kth_hi) * band->room);
+    int in = 0;  // (registers without a candidate hold 0: below any score)
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k) in += (key[k] >= band->thr_lo ? 1 : 0) + (key[k] > band->thr_hi ? 0x10000 : 0);
+    in = wave_inclusive_scan(in);
+    if (lane == 63) f->wave_tot[1][wave] = in;
+  }
   if (lane == 63) f->wave_tot[0][wave] = incl;
   __syncthreads();
+  if (band) {
+#pragma unroll
+    for (int w = 0; w < kWavesNT; ++w) {
+      const int x = f->wave_tot[1][w];
+      band->n_lo += x & 0xFFFF;
+      band->n_hi += x >> 16;
+    }
+  }
   int before = incl - mine;
 #pragma unroll
   for (int w = 0; w < kWavesNT; ++w) {
@@ -377,11 +414,11 @@ __device__ __forceinline__ void select_keys(const unsigned* keys, int N, int r, 
 // select_keys with as many registers as the problem needs.
 template <int NT, bool LDS_OUT>
 __device__ __forceinline__ void select_keys_any(const unsigned* keys, int N, int r, FINCH_GLOBAL int* gidx, int* lidx,
-                                                SelLds* f, int tid, int lane, int wave) {
-  if (N <= NT * 3) select_keys<NT, 3, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave);
-  else if (N <= NT * 7) select_keys<NT, 7, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave);
-  else if (N <= NT * 11) select_keys<NT, 11, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave);
-  else select_keys<NT, kSelRegKeys, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave);
+                                                SelLds* f, int tid, int lane, int wave, SelBand* band = nullptr) {
+  if (N <= NT * 3) select_keys<NT, 3, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave, band);
+  else if (N <= NT * 7) select_keys<NT, 7, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave, band);
+  else if (N <= NT * 11) select_keys<NT, 11, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave, band);
+  else select_keys<NT, kSelRegKeys, LDS_OUT>(keys, N, r, gidx, lidx, f, tid, lane, wave, band);
 }
 
 // Puts the order keys of the N scores into LDS (no barrier).

@@ -1,0 +1,112 @@
+"""Whole loops that select on one pass over the keys in steps whose scores the next step overwrites
+(RowEstimates in csrc/owner_body.h): caches, indices and the last scores must be those of one
+finch_step per chunk, which makes both passes - where no key is near the line, where many are and
+some or all of them have to be scored exactly, where guesses are of no use (rows that find far
+larger logits than before, and rows that are not numbers), and where a step's scores are seen."""
+import pytest
+import torch
+
+import paper_2408_00167_amd as F
+from paper_2408_00167_amd.driver import ChunkLoop
+
+pytestmark = pytest.mark.gpu
+
+
+def _problems(kind, d, group, n_que, tokens, chunk, budget, count, seed, exact):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+
+    def rand(*shape):
+        return torch.randn(*shape, generator=g, device="cuda")
+
+    out = []
+    for _ in range(count):
+        q, k, v = rand(group * n_que, d), rand(tokens, d), rand(tokens, d)
+        a = rand(d)
+        a /= a.norm()
+        if kind == "gap":  # relevant keys, as many in every chunk as the schedule adds, far above the others
+            q += 2.5 * a
+            kept = 0
+            for i, r in enumerate(F.finch_schedule(tokens, chunk, budget)):
+                n = min(chunk, tokens - i * chunk)
+                at = torch.rand(n, generator=g, device="cuda").topk(min(n, r - kept)).indices + i * chunk
+                k[at] += (1.6 + 0.8 * torch.rand(len(at), 1, generator=g, device="cuda")) * d ** 0.5 * a
+                kept = r
+        elif kind == "ties":  # every key many times
+            k = k[:37].repeat(-(-tokens // 37), 1)[:tokens].contiguous()
+        elif kind == "jump":  # half of the rows meet a key from the third chunk on that outweighs all before
+            q[::2] += 4 * a
+            k[2 * chunk::chunk] += 30 * a
+        elif kind == "peaked":  # nearly all scores below the least that fp32 can hold
+            q *= 40
+        elif kind == "nan":
+            q[1, 0] = float("nan")
+        out.append(dict(Q=q.bfloat16(), K=k.bfloat16(), V=v.bfloat16(), n_que=n_que, budget=budget))
+        if exact:
+            out[-1]["K_que"] = rand(n_que, d).bfloat16()
+    return out
+
+
+def _run(kind, d, group, n_que, tokens, chunk, budget, seed=0, rope=False, exact=False, want_scores=True, count=3):
+    probs = _problems(kind, d, group, n_que, tokens, chunk, budget, count, seed, exact)
+    got = []
+    for per_step in (False, True):
+        fin = F.Finch(F.FINCH_BF16, d, group)
+        F.finch_set_option(fin.ctx, F.FINCH_OPT_STEP_PATH, F.FINCH_PATH_OWNER)
+        if rope:
+            fin.set_reposition(F.FINCH_ROPE_HALF, F.FINCH_ORDER_ASCENDING, 10000.0)
+        loop = ChunkLoop(fin, probs, chunk, want_scores=want_scores)
+        for _ in range(2):  # (the second time with what the first has left in the buffers)
+            loop.run(per_step=per_step)
+        torch.cuda.synchronize()
+        got.append([loop.final_cache(p) for p in range(count)] + [loop.idx, loop.scores])
+        got[-1] = [x for y in got[-1] for x in (y if isinstance(y, tuple) else (y,)) if x is not None]
+    bits = {torch.float32: torch.int32, torch.bfloat16: torch.int16, torch.int32: torch.int32}  # (NaN as well)
+    for a, b in zip(*got):
+        assert torch.equal(a.view(bits[a.dtype]), b.view(bits[b.dtype]))
+
+
+@pytest.mark.parametrize("kind", ["gap", "dense", "ties", "jump", "peaked"])
+@pytest.mark.parametrize("d,group,n_que", [(128, 1, 16), (128, 2, 33), (128, 4, 48), (128, 4, 64), (64, 4, 40)])
+def test_as_step_by_step(kind, d, group, n_que):
+    """Row blocks 1, 3, 6, 8 and 5; a last chunk that is shorter (the one before it is seen) and ragged key blocks."""
+    _run(kind, d, group, n_que, tokens=3001, chunk=515, budget=190)
+
+
+@pytest.mark.parametrize("rows", [32, 64, 96, 128, 160, 192, 224, 256])
+@pytest.mark.parametrize("d", [64, 128])
+def test_every_number_of_row_blocks(rows, d):
+    _run("gap", d, 1, rows, tokens=1600, chunk=320, budget=100)
+    _run("dense", d, 1, rows - 31, tokens=1600, chunk=320, budget=100)
+
+
+@pytest.mark.parametrize("kind", ["gap", "dense"])
+def test_options(kind):
+    _run(kind, 128, 4, 24, 2600, 400, 200, rope=True)
+    _run(kind, 128, 4, 24, 2600, 400, 200, exact=True)
+    _run(kind, 128, 4, 24, 2600, 400, 200, want_scores=False)
+    _run(kind, 128, 2, 24, 15000, 2500, 2400)   # many kept rows
+    _run(kind, 64, 1, 8, 1200, 100, 1100)       # nearly all rows are kept
+    _run(kind, 128, 8, 24, 1200, 100, 60)       # small chunks
+
+
+def test_mixed_lengths_in_one_launch():
+    """Slots with other numbers of rows and steps beside each other (a kernel for more row blocks than a slot has)."""
+    probs = [p for i, (t, n) in enumerate([(2900, 64), (2100, 9), (1500, 33), (300, 50)])
+             for p in _problems("gap" if i % 2 else "dense", 128, 4, n, t, 300, max(1, t // 12), 2, 5 + i, False)]
+    outs = []
+    for per_step in (False, True):
+        fin = F.Finch(F.FINCH_BF16, 128, 4)
+        F.finch_set_option(fin.ctx, F.FINCH_OPT_STEP_PATH, F.FINCH_PATH_OWNER)
+        loop = ChunkLoop(fin, probs, 300)
+        loop.run(per_step=per_step)
+        torch.cuda.synchronize()
+        outs.append([t for p in range(len(probs)) for t in loop.final_cache(p)] + [loop.idx, loop.scores])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+
+
+def test_rows_that_are_not_numbers_end_the_same_way():
+    """A row of NaN makes every score NaN; nothing is selected on a spread that is not a number, and the
+    launch ends with the indices of the two passes."""
+    _run("nan", 128, 2, 20, 1500, 300, 100, want_scores=False)

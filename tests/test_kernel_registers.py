@@ -67,3 +67,14 @@ def test_row_statistics_of_many_rows_are_not_spilled():
             seen += 1
             assert meta[".vgpr_spill_count"] == 0, f"{m.groups()}: {meta['.vgpr_spill_count']} spilled"
     assert seen == 4
+
+
+def test_one_pass_loops_keep_their_key_buffers_in_registers():
+    """At most four 4-byte values a lane are spilled, as above."""
+    seen = 0
+    for name, meta in kernels().items():
+        m = re.search(r"owner_loop_bf16ILi(\d+)ELi(\d+)ELb([01])ELb0ELb1E", name)
+        if m:
+            seen += 1
+            assert meta[".vgpr_spill_count"] <= 4, f"{m.groups()}: {meta['.vgpr_spill_count']} spilled"
+    assert seen == 16  # 2 head sizes, 4 numbers of row blocks, with re-positioning and without
