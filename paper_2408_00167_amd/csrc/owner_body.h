@@ -616,6 +616,11 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   const int n_pchunks = (Rp + RC - 1) / RC;
   const int dper = (DOC && pb.q_doc && pb.m > 0) ? (pb.m + RC - 1) / RC : 0;
   const int n_chunks = n_pchunks + prm.group * dper;
+  // With several chunks the sums so far stay in LDS, as the order keys that the selection wants there, and go
+  // to memory at the end: a wave that asked memory for a sum would wait for its next key block, which is on the
+  // way before, as well.  (The loop of 256 problems, 192 rows and 1024-token chunks with document rows: 2295 us, 2225
+  // with the sums in LDS.)
+  const bool lkeys_sum = lkeys && !layered && n_chunks > 1;
   struct RowChunk {
     const void* qsrc;
     int R, row0, lim0, lim_step;
@@ -1001,11 +1006,13 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
             lkeys[key] = order_key(tot);
             return;
           }
-          const float val = first_chunk ? tot : dst[key] + tot;
+          float val = tot;
+          if (!first_chunk) val += lkeys ? order_value(lkeys[key]) : dst[key];
+          if (lkeys) lkeys[key] = order_key(val);
+          if (lkeys_sum) return;
           // (scores other workgroups will read go out past this compute unit's caches)
           if (layered) __hip_atomic_store(dst + key, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           else dst[key] = val;
-          if (lkeys) lkeys[key] = order_key(val);
         }
       };
       // the next key block, or the next chunk's rows when there is none
@@ -1089,6 +1096,8 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     load_k_block<D>(ks2, n2, b * 32, lane, ka);
     }
   }
+  if (lkeys_sum)
+    for (int i = tid; i < N; i += kOwnThreads) dst[i] = order_value(lkeys[i]);
   if (DOC && n_chunks == 0) own_no_rows(gscores, lkeys, N, tid);
   // what the prompt-row region of LDS holds now (selection scratch lies behind it)
   staged_q = (n_chunks == 1) ? pb.q : nullptr;
