@@ -1213,9 +1213,13 @@ finch_status finch_loop(finch_ctx* ctx, const finch_problem* host_desc, const fi
     p.lds_bytes = static_cast<uint32_t>(pl.own_lds);
     // notes of where kept rows lie: as many as fit beside the rest of the LDS (the kernels that move
     // every row are fp32's, and slots by rank put the rows in another order)
-    const size_t est_words = static_cast<size_t>(pl.own_row_chunk) + finch::kEstExtraWords;
-    if (scores_may_be_bounds(ctx, pl, n_steps) && pl.own_lds + est_words * 4 <= ctx->max_lds)
-      p.est_words = static_cast<int32_t>(est_words);
+    // (a guess for every row of any problem if they fit, else for problems whose rows go through in one chunk)
+    for (const int32_t rows : {pl.rpad_max, pl.own_row_chunk}) {
+      const size_t est_words = static_cast<size_t>(rows) + finch::kEstExtraWords;
+      if (p.est_words == 0 && scores_may_be_bounds(ctx, pl, n_steps) && rows <= finch::kEstMaxRows &&
+          pl.own_lds + est_words * 4 <= ctx->max_lds)
+        p.est_words = static_cast<int32_t>(est_words);
+    }
     if (rows_pay_to_stay(ctx, pl, n_steps))
       p.stay_rows = static_cast<int32_t>(
           std::min(static_cast<size_t>(pl.r_max), (ctx->max_lds - pl.own_lds - 4 * static_cast<size_t>(p.est_words)) / 8));

@@ -104,7 +104,8 @@ hipError_t launch_select(LaunchParams p, int n_max, hipStream_t s);
 hipError_t launch_select_layer(LaunchParams p, int group, float* layer_scores, int n_max, hipStream_t s);
 hipError_t set_max_lds_select(size_t bytes);
 hipError_t launch_gather(const LaunchParams& p, int row_bytes, int r_max, hipStream_t s);
-constexpr int kEstExtraWords = 32;  // words of RowEstimates beside one per staged prompt row
+constexpr int kEstExtraWords = 32;  // words of RowEstimates beside one per prompt row
+constexpr int kEstMaxRows = 1024;   // most prompt rows it is kept for (4 KB of LDS)
 size_t owner_lds_bytes(int head_dim, int row_chunk, int n_max, int r_max, bool rank_order, bool stages);
 hipError_t launch_prompt_lse(const LaunchParams& p, int head_dim, bool bf16, int rows_max, hipStream_t s);
 hipError_t launch_reposition(const LaunchParams& p, int row_bytes, bool bf16, int r_max, int pairing,

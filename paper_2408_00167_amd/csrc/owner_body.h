@@ -109,10 +109,12 @@ constexpr float kEstLeast = 0x1p-60f;  // smaller scores may have lost terms bel
 // pass has half the matrix instructions, LDS operands and key bytes of two and two thirds of their
 // vector instructions.  Both sides of the loop of 256 problems, 128 channels: 192 rows, 4096-token chunks of 131072
 // tokens, no key near the line 4700 -> 2880 us, keys spread evenly 4850 -> 3610 (open keys scored
-// exactly); 256 rows, 2048-token chunks 1945 -> 1290; 32 rows, 512-token chunks, 1024 problems 957 -> 877.  Steps that do
+// exactly; with more rows than a chunk, whose open keys start the step over, 360 rows, 2048-token chunks of 32768: 3070 ->
+// 2130 and 3035); 256 rows, 2048-token chunks 1945 -> 1290; 32 rows, 512-token chunks, 1024 problems 957 -> 877.  Steps that do
 // not pay (kEstFixed) make both passes, 1 % slower than the kernels without this.
 struct RowEstimates {
-  float* lse = nullptr;      // LDS: one guess per staged row ...
+  float* lse = nullptr;      // LDS: one guess per row (`cap` of them) ...
+  int cap = 0;
   int* words = nullptr;      // ... and kEstExtraWords words behind them: [0, 16) extremes per wave, [16] counter
   const void* q = nullptr;   // the rows they are for
   int rows = 0;
@@ -642,7 +644,8 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   // 2346 where every chunk asks for its rows when its turn has come (64 channels, 256 rows: 1569 and 1669).
   bf16x8 ka[D / 16], kb[D / 16];
   static_assert(!ONCE || (LOOP && !DOC));
-  bool once = ONCE && est.hidden && est.q == pb.q && est.rows == Rp && n_chunks == 1 && lkeys && !est.dense;
+  bool once = ONCE && est.hidden && est.q == pb.q && est.rows == Rp && Rp <= est.cap && lkeys && !est.dense;
+  unsigned most = 0u, least = 0u;  // largest order key of any row's log2 z, and the smallest one's complement
   Selected chosen = {nullptr, false, false};
   int asked;  // (asked for beside the first key block)
   for (int ch = 0; ch < n_chunks; ++ch) {
@@ -683,11 +686,11 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
 #pragma unroll
       for (int q = 0; q < QBT; ++q) {
         z_run[q] = 0.f;
-        g[q] = q < QB ? est.lse[q * 32 + t] : kInf;
+        g[q] = q < QB ? est.lse[row0 + q * 32 + t] : kInf;
       }
       auto put = [&](float tot, int kbase) {
         const int key = kbase + acc_key(t >> 1, h);
-        if ((t & 1) == 0 && key < N) lkeys[key] = order_key(tot);
+        if ((t & 1) == 0 && key < N) lkeys[key] = order_key(first_chunk ? tot : order_value(lkeys[key]) + tot);
       };
       auto process = [&](const bf16x8(&kf)[D / 16], int blk) {
         const int kbase = blk << 5;
@@ -756,20 +759,20 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
       __syncthreads();
       FINCH_PHASE(2);
       // every row's log-sum-exp takes the place of its guess
-      unsigned most = 0u, least = 0u;  // order keys of log2 z_i, the least one's complement
       if (tid < rows) {
         float l = kInf;
-        if (tid < R) {
+        if (row0 + tid < R) {
           float z = wsum[tid];
 #pragma unroll
           for (int w = 1; w < kOwnWaves; ++w) z += wsum[w * RC + tid];
-          const float guess = est.lse[tid];
+          const float guess = est.lse[row0 + tid];
           l = guess + fast_log2(z);
-          if (pb.lse_extra) l = widen_lse(l, as_global<float>(pb.lse_extra)[tid]);
-          most = order_key(l - guess);
-          least = ~most;
+          if (pb.lse_extra) l = widen_lse(l, as_global<float>(pb.lse_extra)[row0 + tid]);
+          const unsigned key = order_key(l - guess);
+          most = max(most, key);
+          least = max(least, ~key);
         }
-        est.lse[tid] = l;
+        est.lse[row0 + tid] = l;
       }
       most = wave_max_u32(most);
       least = wave_max_u32(least);
@@ -788,6 +791,10 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
       // (rows that are not numbers, or whose sum has moved out of range)
       if (!(spread <= kEstSpread)) {
         once = false;
+        if (ch > 0) {  // (the chunks before have no exact scores)
+          ch = -1;
+          continue;
+        }
         b = wave;
         load_k_block<D>(ks, N, b << 5, lane, ka);
       }
@@ -939,7 +946,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
         }
       }
       lds_lse[i] = l;
-      if (ONCE && n_chunks == 1) est.lse[i] = l;
+      if (ONCE && row0 + i < est.cap) est.lse[row0 + i] = l;
     }
     __syncthreads();
     FINCH_PHASE(3);
@@ -1062,12 +1069,17 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     chosen = own_select(prm, pb, slot, N, dst, sel, sel_bytes, lkeys, step_probs, epoch, layered, sync_words, tid, &band);
     FINCH_PHASE(6);
     const int n_lo = uni(band.n_lo), open = n_lo - uni(band.n_hi);
-    if (turn < 2) est.dense = !lkeys || (n_lo > pb.r && 2 * (open * QB + kEstFixed) > N * QB);
+    if (turn < 2) est.dense = !lkeys || (n_lo > pb.r && (n_chunks > 1 || 2 * (open * QB + kEstFixed) > N * QB));
     est.room = fmaxf(kEstRoom, turn == 1 ? uni(band.room) : 0.5f + 0.5f * est.room);
     if (turn != 1) break;
     // Keys below band.thr_lo are out and those above band.thr_hi are in whatever their exact scores are.
     // (The 0.4 % beside the spread are far more than what fp32 sums of exponentials differ by.)
     if (n_lo == pb.r && band.least >= kEstLeast) break;
+    if (n_chunks > 1) {  // (rows that are no longer staged: the step once more, with both passes)
+      once = false;
+      ch = -1;
+      break;
+    }
     // ---- the others one by one
     const unsigned thr_lo = band.thr_lo, thr_hi = band.thr_hi;
     n2 = open;
@@ -1096,13 +1108,13 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     load_k_block<D>(ks2, n2, b * 32, lane, ka);
     }
   }
-  if (lkeys_sum)
+  if (lkeys_sum && !once)
     for (int i = tid; i < N; i += kOwnThreads) dst[i] = order_value(lkeys[i]);
   if (DOC && n_chunks == 0) own_no_rows(gscores, lkeys, N, tid);
   // what the prompt-row region of LDS holds now (selection scratch lies behind it)
   staged_q = (n_chunks == 1) ? pb.q : nullptr;
   staged_rows = Rp;
-  est.q = staged_q;
+  est.q = Rp <= est.cap ? pb.q : nullptr;
   est.rows = Rp;
   if (!stages) return false;
 
@@ -1181,7 +1193,8 @@ __global__ __launch_bounds__(kOwnThreads) void owner_loop_bf16(LaunchParams prm,
   RowEstimates est;
   if (ONCE) {
     est.lse = reinterpret_cast<float*>(smem + prm.lds_bytes + 8u * static_cast<unsigned>(prm.stay_rows));
-    est.words = reinterpret_cast<int*>(est.lse) + prm.row_chunk;
+    est.cap = prm.est_words - kEstExtraWords;
+    est.words = reinterpret_cast<int*>(est.lse) + est.cap;
   }
   // Descriptors come from memory that this launch has not touched yet, 1 to 2 us away, and a step begins with
   // what it and the two after it say.  So each step asks for the one three steps on (once its own first

@@ -80,6 +80,13 @@ def test_every_number_of_row_blocks(rows, d):
     _run("dense", d, 1, rows - 31, tokens=1600, chunk=320, budget=100)
 
 
+@pytest.mark.parametrize("kind", ["gap", "dense", "ties", "jump", "nan"])
+@pytest.mark.parametrize("d,group,n_que", [(128, 1, 257), (128, 4, 96), (64, 8, 70), (64, 4, 260)])
+def test_several_chunks_of_rows(kind, d, group, n_que):
+    """257, 384 and 560 rows in chunks of 256, and more rows than guesses are kept for; open keys start the step over."""
+    _run(kind, d, group, n_que, tokens=2500, chunk=515, budget=190, want_scores=kind != "nan", count=2)
+
+
 @pytest.mark.parametrize("kind", ["gap", "dense"])
 def test_options(kind):
     _run(kind, 128, 4, 24, 2600, 400, 200, rope=True)
