@@ -40,7 +40,7 @@ MEASURED_TRAFFIC = {"C4": {
     "colsum": 2.0 * 159516.2 * 1024 + 4780.0 * 1024,
     "select": 2.0 * 2557.3 * 1024 + 728.0 * 1024,
     "gather": 2.0 * 47163.0 * 1024 + 92928.0 * 1024,
-    "owner": 2.0 * 9503102.2 * 1024 + 531072.0 * 1024,   # one launch = the whole loop
+    "owner": 2.0 * 6278100.0 * 1024 + 391937.0 * 1024,   # one launch = the whole loop
 }}
 
 
@@ -68,8 +68,8 @@ def algorithmic_bytes(w, loop, rows_stay=False, turned=False):
 
 
 def logit_flops(w, loop):
-    """Multiply-adds x 2 of the logits the method forms: every (prompt row, candidate key)
-    pair once per scoring pass, two passes (document rows, when they are on, not counted)."""
+    """Multiply-adds x 2 of the logits that two scoring passes form: every (prompt row, candidate key)
+    pair once per pass (document rows, when they are on, not counted)."""
     flops = 0
     for i in range(loop.n_steps):
         for p, (c, m, r) in zip(loop.active[i], loop.step_shapes[i]):
@@ -298,15 +298,15 @@ def main() -> int:
                         traffic_source=TRAFFIC_SOURCE.get(dom) if default_options and w.name in MEASURED_TRAFFIC else None,
                         bytes_per_launch=bytes_per_launch, avg_launch_us=kernels[dom]["avg_us"],
                         launches_per_step=launches, profiled_ms_per_step=prof_ms,
-                        note="priced against HBM as the path's contract asks; counters and microbenchmarks "
-                             "(profiles/) show the scoring passes bound by vector/matrix instruction issue, "
-                             "not by memory")
+                        note="priced against HBM as the path's contract asks; counters and trials (profiles/) show "
+                             "the scoring passes bound by the chip's power and by vector/matrix instruction "
+                             "issue, not by memory")
 
     # what the arithmetic side of the same launches amounts to (bf16 runs; information
     # beside the contract's HBM figure: the scoring passes are not bound by memory)
     matrix_pipe = None
     if w.dtype == "bf16" and not args.doc_rows:
-        fl = logit_flops(w, loop)
+        fl = logit_flops(w, loop) / 2  # every logit once: how many steps form them twice depends on the scores
         matrix_pipe = dict(logit_flops=fl, achieved_TFLOPs=fl / (ms * 1e-3) / 1e12, peak_TFLOPs=MFMA_BF16_PEAK_TFLOPS,
                            frac=fl / (ms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS)
     path_gbps = total_bytes / (ms * 1e-3) / 1e9
