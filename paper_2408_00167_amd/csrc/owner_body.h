@@ -111,7 +111,7 @@ constexpr float kEstLeast = 0x1p-60f;  // smaller scores may have lost terms bel
 // tokens, no key near the line 4700 -> 2880 us, keys spread evenly 4850 -> 3610 (open keys scored
 // exactly; with more rows than a chunk, whose open keys start the step over, 360 rows, 2048-token chunks of 32768: 3070 ->
 // 2130 and 3035); 256 rows, 2048-token chunks 1945 -> 1290; 32 rows, 512-token chunks, 1024 problems 957 -> 877.  Steps that do
-// not pay (kEstFixed) make both passes, 1 % slower than the kernels without this.
+// not pay (kEstFixed) make both passes, 2 to 3 us slower than in the kernels without this.
 struct RowEstimates {
   float* lse = nullptr;      // LDS: one guess per row (`cap` of them) ...
   int cap = 0;
