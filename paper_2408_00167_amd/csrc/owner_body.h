@@ -92,7 +92,10 @@ struct KeptRows {
 constexpr int kEstFixed = 300;
 constexpr float kEstRoom = 1.15f;      // factor around the r-th largest score in which a slot without experience looks for others
 constexpr float kEstSpread = 16.f;     // log2 of the largest spread that is of use
-constexpr float kEstLeast = 0x1p-60f;  // smaller scores may have lost terms below the least exponent
+// Largest |log2 z_i|: sums of 1024 rows stay below 2^70, and the terms below 2^-126 that a row's sum of 2^-60 and more has
+// lost are less than 2^-52 of it.
+constexpr float kEstReach = 60.f;
+constexpr float kEstLeast = 0x1p-60f;  // smaller key sums may have lost terms below the least exponent
 
 // Selection on one pass over the keys.  The weight of row i at key j is exp2(logit - lse_i), and lse_i is only known
 // when all keys have been seen: hence two passes.  But with any guess g_i of it, one pass gives S_j = sum_i
@@ -765,10 +768,10 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
           float z = wsum[tid];
 #pragma unroll
           for (int w = 1; w < kOwnWaves; ++w) z += wsum[w * RC + tid];
-          const float guess = est.lse[row0 + tid];
-          l = guess + fast_log2(z);
+          const float guess = est.lse[row0 + tid], moved = fast_log2(z);
+          l = guess + moved;
           if (pb.lse_extra) l = widen_lse(l, as_global<float>(pb.lse_extra)[row0 + tid]);
-          const unsigned key = order_key(l - guess);
+          const unsigned key = order_key(fabsf(moved) <= kEstReach ? l - guess : kInf);
           most = max(most, key);
           least = max(least, ~key);
         }
@@ -788,7 +791,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
       }
       spread = uni(order_value(most) - order_value(~least));
       FINCH_PHASE(3);
-      // (rows that are not numbers, or whose sum has moved out of range)
+      // (rows that are not numbers, or one whose sum is out of range: the spread is infinite or not a number)
       if (!(spread <= kEstSpread)) {
         once = false;
         if (ch > 0) {  // (the chunks before have no exact scores)

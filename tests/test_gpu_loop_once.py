@@ -118,3 +118,65 @@ def test_rows_that_are_not_numbers_end_the_same_way():
     """A row of NaN makes every score NaN; nothing is selected on a spread that is not a number, and the
     launch ends with the indices of the two passes."""
     _run("nan", 128, 2, 20, 1500, 300, 100, want_scores=False)
+
+
+def _free_loop(q, chunks, kept, d, group):
+    """One slot whose steps see these chunks alone, each kept row count of `kept`: indices of all steps and the last
+    scores, of one launch and step by step."""
+    n, big = len(chunks[0]), max(kept)
+    outs = []
+    for per_step in (False, True):
+        fin = F.Finch(F.FINCH_BF16, d, group)
+        F.finch_set_option(fin.ctx, F.FINCH_OPT_STEP_PATH, F.FINCH_PATH_OWNER)
+        scores, idx = torch.zeros(n, device="cuda"), torch.zeros(len(chunks), big, dtype=torch.int32, device="cuda")
+        rows = torch.zeros(2, len(chunks), big, d, dtype=torch.bfloat16, device="cuda")
+        steps = [[dict(q=q, k_cache=None, v_cache=None, k_chunk=k, v_chunk=k, k_out=rows[0, i, :r], v_out=rows[1, i, :r],
+                       scores=scores, idx=idx[i, :r], n_que=len(q) // group, c=0, m=n, r=r)]
+                 for i, (k, r) in enumerate(zip(chunks, kept))]
+        if per_step:
+            for s in steps:
+                batch = F.Batch(s)
+                fin.reserve(batch)
+                fin.step(batch)
+        else:
+            batch = F.LoopBatch(steps)
+            fin.reserve_loop(batch)
+            fin.loop(batch)
+        torch.cuda.synchronize()
+        outs.append([idx, scores, rows])
+        fin.close()
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+    return outs[0][0].cpu()
+
+
+@pytest.mark.parametrize("way", ["up", "down"])
+@pytest.mark.parametrize("rows,first,top", [(192, 0, 34.5), (384, 0, 34.25), (384, 256, 34.75)])
+def test_rows_that_all_move_far_at_once(way, rows, first, top):
+    """All log-sum-exps of two groups of rows (from row `first` on; the others stay) move by one step.  They rise by 2^109
+    and 2^123, so that sums over the rows leave fp32's range while every row's sum is in it (`top`: two keys' sums are
+    infinite, a third's within 5 % below 2^128, which share the selection's highest bin), or fall by 2^120, so that a
+    row's sum loses the many terms below 2^-126.  Guesses are of no use, and the step makes both passes."""
+    d, group, n, half = 128, 4, 2000, (rows - first) // 2
+    q = torch.zeros(rows, d)
+    q[first:first + half, 0] = 32  # (a key's channel counts 32 / sqrt(128) * log2(e) = 4.08 octaves)
+    q[first + half:, 1] = 32
+    noise = 0.05 * torch.randn(3, n, d, generator=torch.Generator().manual_seed(rows + first))
+    noise[:, :, :2] = 0
+    chunks = list(noise)
+    chunks[0][700, :2] = 4.5 if way == "up" else 34.0  # stands clear: the next step tries one pass
+    if way == "up":
+        chunks[1][[10, 20], 0] = top   # two fifths of the first group's weight each ...
+        chunks[1][30, 0] = top - 0.25  # (half of that)
+        chunks[1][1500, 1] = 31.25     # ... and all of the second's
+        want = [10, 1500]
+    else:
+        chunks[1][:, 0] = 2.75         # nearly all of the first group's weight together
+        chunks[1][10, 0] = 4.5
+        chunks[1][[1500, 1600], :2] = torch.tensor([0.0, 4.5])  # half of the second group's each
+        want = [1500, 1600]
+    k = chunks[1].bfloat16().double()
+    exact = torch.softmax(q.double() @ k.T / d ** 0.5, 1).sum(0)
+    assert sorted(torch.sort(exact, descending=True, stable=True).indices[:2].tolist()) == want
+    got = _free_loop(q.bfloat16().cuda(), [c.bfloat16().cuda() for c in chunks], [1, 2, 2], d, group)
+    assert got[0, 0] == 700 and got[1].tolist() == want
