@@ -37,6 +37,7 @@ struct finch_ctx {
   uint64_t loop_checked_hash;
   bool loop_checked;
   bool loop_rows_may_stay;  // what check_slot_overlaps said of that set
+  int32_t* loop_ways;       // LaunchParams::ways of its whole loops
 };
 
 // Scratch of finch_step_static: the workspace of a step, held by the library itself so
@@ -922,6 +923,7 @@ finch_status finch_create(const finch_config* cfg, finch_ctx** out) {
   ctx->loop_checked = false;
   ctx->loop_checked_hash = 0;
   ctx->loop_rows_may_stay = false;
+  ctx->loop_ways = nullptr;
   ctx->meet = nullptr;
   hipError_t e = hipGetDevice(&ctx->device);
   StaticAddresses a = {nullptr, nullptr, nullptr};
@@ -1216,6 +1218,7 @@ finch_status finch_loop(finch_ctx* ctx, const finch_problem* host_desc, const fi
     LaunchParams p = make_params(ctx, dev_desc, n_desc, pl, ws);
     p.row_chunk = pl.own_row_chunk;
     p.lds_bytes = static_cast<uint32_t>(pl.own_lds);
+    p.ways = ctx->loop_ways;
     // notes of where kept rows lie: as many as fit beside the rest of the LDS (the kernels that move
     // every row are fp32's, and slots by rank put the rows in another order)
     // (guesses for all rows of any problem if they fit, else for problems whose rows go through in one chunk)
@@ -1262,6 +1265,15 @@ finch_status finch_workspace_status(finch_ctx* ctx, const void* workspace, void*
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(ctx, e);
   return *flags == 0 ? FINCH_OK : FINCH_ERR_TIMEOUT;
+}
+
+// (Not in finch.h: for tests of the ways a step can take.)  From now on finch_loop writes to `ways`, device memory of n_steps
+// * n_slots words, how every step that may select on one pass did so (kWay...); null: no more.  Other
+// words are left alone: those of steps that a slot does not have, and of loops that run otherwise.
+finch_status finch_debug_loop_ways(finch_ctx* ctx, int32_t* ways) {
+  if (!ctx) return FINCH_ERR_INVALID_ARG;
+  ctx->loop_ways = ways;
+  return FINCH_OK;
 }
 
 // What finch_loop checks before it launches anything, and (not in finch.h: for tests of what the kernels

@@ -90,6 +90,7 @@ struct LaunchParams {
   int32_t stay_rows;           // whole loop: most kept rows a step may leave where they are (0: none; room for as many notes, 8
                                // bytes each, follows the lds_bytes)
   int32_t est_words;           // whole loop: 4-byte words of LDS for RowEstimates, behind the notes (0: every step makes both passes)
+  int32_t* ways;               // whole loop with est_words: one word per step and slot for how the step selected (kWay...), or null
   int64_t spin_ticks;          // longest wait for the other workgroups, in 100 MHz ticks
 };
 
@@ -105,6 +106,10 @@ hipError_t launch_select_layer(LaunchParams p, int group, float* layer_scores, i
 hipError_t set_max_lds_select(size_t bytes);
 hipError_t launch_gather(const LaunchParams& p, int row_bytes, int r_max, hipStream_t s);
 constexpr int kEstExtraWords = 32;  // words of RowEstimates beside one per prompt row
+// how a step of those loops selected: on bounds from one pass (kWayOnce), which settled all keys, or left a list of keys, or
+// left all of them (too small for bounds) to the exact scores, or was of no use (its step made both passes: the rows' sums out of range,
+// or keys open with rows in several chunks).  0: both passes from the start.
+enum : int32_t { kWayOnce = 1, kWaySettled = 2, kWayList = 4, kWayAll = 8, kWayRange = 16, kWayAgain = 32 };
 constexpr int kEstMaxRows = 1024;   // most prompt rows it is kept for (4 KB of LDS)
 size_t owner_lds_bytes(int head_dim, int row_chunk, int n_max, int r_max, bool rank_order, bool stages);
 hipError_t launch_prompt_lse(const LaunchParams& p, int head_dim, bool bf16, int rows_max, hipStream_t s);

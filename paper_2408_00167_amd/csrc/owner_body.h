@@ -124,6 +124,7 @@ struct RowEstimates {
   float room = kEstRoom;     // how far from the r-th largest score keys are taken to stay open: as in the last step that tried, less with every one that does not
   bool dense = true;         // too many keys are that close (by the last step's scores): not worth trying
   bool hidden = false;       // this step's scores are not seen by anybody
+  int way = 0;               // how this step selects (kWay...)
   const int* ask = nullptr;  // (no estimate: memory that a later step begins with)
 };
 
@@ -563,14 +564,13 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   }
   FINCH_PHASE_BEGIN();
   const int Rp = (DOC && !pb.q) ? 0 : prm.group * pb.n_que;  // prompt rows
-  const int tid = own_thread(), lane = tid & 63;
+  const int tid = own_thread();
   // (DOC kernels: in a scalar register, so that the loops over a wave's key blocks are uniform.  A key buffer
   // there lives on past both exits of such a loop; with a loop that lanes may leave at different times the
   // compiler keeps what either exit hands on in registers of its own, 32 more than there are: up to
   // 56 spilled, 789 us in place of 604 for the loop of 256 problems, 200-token chunks, with
   // re-positioning, 808 and 743 for a step of 256 problems of 512 + 1024 candidates.)
   const int wave = DOC || ONCE ? uni(tid >> 6) : tid >> 6;
-  const int t = lane & 31, h = lane >> 5;
   constexpr int kStride = D * 2 + 16;
   const int RC = prm.row_chunk;
   char* lds_q = smem;
@@ -648,6 +648,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   bf16x8 ka[D / 16], kb[D / 16];
   static_assert(!ONCE || (LOOP && !DOC));
   bool once = ONCE && est.hidden && est.q == pb.q && est.rows == Rp && Rp <= est.cap && lkeys && !est.dense;
+  if (ONCE) est.way = once ? kWayOnce : 0;
   unsigned most = 0u, least = 0u;  // largest order key of any row's log2 z, and the smallest one's complement
   Selected chosen = {nullptr, false, false};
   int asked;  // (asked for beside the first key block)
@@ -794,6 +795,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
       // (rows that are not numbers, or one whose sum is out of range: the spread is infinite or not a number)
       if (!(spread <= kEstSpread)) {
         once = false;
+        est.way |= kWayRange;
         if (ch > 0) {  // (the chunks before have no exact scores)
           ch = -1;
           continue;
@@ -1077,9 +1079,13 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     if (turn != 1) break;
     // Keys below band.thr_lo are out and those above band.thr_hi are in whatever their exact scores are.
     // (The 0.4 % beside the spread are far more than what fp32 sums of exponentials differ by.)
-    if (n_lo == pb.r && band.least >= kEstLeast) break;
+    if (n_lo == pb.r && band.least >= kEstLeast) {
+      est.way |= kWaySettled;
+      break;
+    }
     if (n_chunks > 1) {  // (rows that are no longer staged: the step once more, with both passes)
       once = false;
+      est.way |= kWayAgain;
       ch = -1;
       break;
     }
@@ -1089,7 +1095,9 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     unsigned short* const list = reinterpret_cast<unsigned short*>(sel + static_cast<size_t>(RC) * (kOwnWaves * 8 + 4) + 16);
     if (!(band.least >= kEstLeast) || n2 <= 0 || reinterpret_cast<char*>(list + n2) > reinterpret_cast<char*>(lkeys)) {
       n2 = N;
+      est.way |= kWayAll;
     } else {
+      est.way |= kWayList;
       for (int i0 = 0; i0 < N; i0 += kOwnThreads) {
         const int i = i0 + tid;
         const unsigned key = i < N ? lkeys[i] : 0u;
@@ -1224,10 +1232,12 @@ __global__ __launch_bounds__(kOwnThreads) void owner_loop_bf16(LaunchParams prm,
     kept.stay = kept.stay && more2 && (s == 0 || pb.c == 0 || kept.mapped);
     est.hidden = est.hidden || !pb.scores;
     est.ask = descriptor_at(s + 3);
+    est.way = 0;
     FINCH_PHASE(0);
     if (own_step_body<D, QBT, ROT, DOC, true, ONCE>(prm, pb, slot, /*stages=*/1, smem, staged_q, staged_rows, prm.probs + t0,
                                         epoch, kept, est))
       ++epoch;
+    if (ONCE && prm.ways && threadIdx.x == 0) prm.ways[static_cast<size_t>(s) * gridDim.x + slot] = est.way;
     // the rows this step wrote are the next step's cache: complete before it reads
     __syncthreads();
   }

@@ -2,7 +2,10 @@
 (RowEstimates in csrc/owner_body.h): caches, indices and the last scores must be those of one
 finch_step per chunk, which makes both passes - where no key is near the line, where many are and
 some or all of them have to be scored exactly, where guesses are of no use (rows that find far
-larger logits than before, and rows that are not numbers), and where a step's scores are seen."""
+larger logits than before, and rows that are not numbers), and where a step's scores are seen.  The launches
+write down which way each step took, so that a test knows that its data has taken the way it is there for."""
+import ctypes
+
 import pytest
 import torch
 
@@ -10,6 +13,17 @@ import paper_2408_00167_amd as F
 from paper_2408_00167_amd.driver import ChunkLoop
 
 pytestmark = pytest.mark.gpu
+
+# kWay... in csrc/finch_internal.h
+ONCE, SETTLED, LIST, ALL, RANGE, AGAIN = 1, 2, 4, 8, 16, 32
+BITS = {torch.float32: torch.int32, torch.bfloat16: torch.int16, torch.int32: torch.int32}  # (compared so: NaN as well)
+
+
+def _record_ways(fin, steps, slots):
+    """Where the loops of `fin` will write how each step of each slot has selected (-1: not by these kernels, or not there)."""
+    ways = torch.full((steps, slots), -1, dtype=torch.int32, device="cuda")
+    assert F.load_library().finch_debug_loop_ways(fin.ctx, ctypes.c_void_p(ways.data_ptr())) == F.FINCH_OK
+    return ways
 
 
 def _problems(kind, d, group, n_que, tokens, chunk, budget, count, seed, exact):
@@ -47,7 +61,9 @@ def _problems(kind, d, group, n_que, tokens, chunk, budget, count, seed, exact):
     return out
 
 
-def _run(kind, d, group, n_que, tokens, chunk, budget, seed=0, rope=False, exact=False, want_scores=True, count=3):
+def _run(kind, d, group, n_que, tokens, chunk, budget, seed=0, rope=False, exact=False, want_scores=True, count=3,
+         seen=0, once=True):
+    """`seen`: one of these ways has been taken by some step; `once`: the kernels with one pass ran (else: they did not)."""
     probs = _problems(kind, d, group, n_que, tokens, chunk, budget, count, seed, exact)
     got = []
     for per_step in (False, True):
@@ -56,45 +72,51 @@ def _run(kind, d, group, n_que, tokens, chunk, budget, seed=0, rope=False, exact
         if rope:
             fin.set_reposition(F.FINCH_ROPE_HALF, F.FINCH_ORDER_ASCENDING, 10000.0)
         loop = ChunkLoop(fin, probs, chunk, want_scores=want_scores)
+        ways = _record_ways(fin, loop.n_steps, count)
         for _ in range(2):  # (the second time with what the first has left in the buffers)
             loop.run(per_step=per_step)
         torch.cuda.synchronize()
         got.append([loop.final_cache(p) for p in range(count)] + [loop.idx, loop.scores])
         got[-1] = [x for y in got[-1] for x in (y if isinstance(y, tuple) else (y,)) if x is not None]
-    bits = {torch.float32: torch.int32, torch.bfloat16: torch.int16, torch.int32: torch.int32}  # (NaN as well)
+        assert bool((ways[0] >= 0).all()) == (once and not per_step), ways
+        assert per_step or not seen or bool(((ways > 0) & (ways & seen > 0)).any()), ways
     for a, b in zip(*got):
-        assert torch.equal(a.view(bits[a.dtype]), b.view(bits[b.dtype]))
+        assert torch.equal(a.view(BITS[a.dtype]), b.view(BITS[b.dtype]))
 
 
 @pytest.mark.parametrize("kind", ["gap", "dense", "ties", "jump", "peaked"])
 @pytest.mark.parametrize("d,group,n_que", [(128, 1, 16), (128, 2, 33), (128, 4, 48), (128, 4, 64), (64, 4, 40)])
 def test_as_step_by_step(kind, d, group, n_que):
     """Row blocks 1, 3, 6, 8 and 5; a last chunk that is shorter (the one before it is seen) and ragged key blocks."""
-    _run(kind, d, group, n_que, tokens=9401, chunk=2215, budget=600)
+    seen = {"gap": SETTLED, "dense": LIST | ALL, "ties": 0, "jump": LIST | ALL | RANGE, "peaked": RANGE}[kind]
+    _run(kind, d, group, n_que, tokens=9401, chunk=2215, budget=600, seen=seen)
 
 
 @pytest.mark.parametrize("rows", [32, 64, 96, 128, 160, 192, 224, 256])
 @pytest.mark.parametrize("d", [64, 128])
 def test_every_number_of_row_blocks(rows, d):
-    _run("gap", d, 1, rows, tokens=9000, chunk=2600, budget=400, count=2)
+    _run("gap", d, 1, rows, tokens=9000, chunk=2600, budget=400, count=2, seen=SETTLED)
     _run("dense", d, 1, rows - 31, tokens=9000, chunk=2600, budget=400, count=2)
-    _run("gap", d, 1, rows, tokens=1600, chunk=320, budget=100)  # (few rows: below the line, by the kernels for two passes)
+    line = 400 * ((rows + 31) // 32 + 1) * d >= 2600 * 128  # (few rows: below it, by the kernels for two passes)
+    _run("gap", d, 1, rows, tokens=1600, chunk=320, budget=100, once=line)
 
 
 @pytest.mark.parametrize("kind", ["gap", "dense", "ties", "jump", "nan"])
 @pytest.mark.parametrize("d,group,n_que", [(128, 1, 257), (128, 4, 96), (64, 8, 70), (64, 4, 260)])
 def test_several_chunks_of_rows(kind, d, group, n_que):
     """257, 384 and 560 rows in chunks of 256, and more rows than guesses are kept for; open keys start the step over."""
-    _run(kind, d, group, n_que, tokens=2500, chunk=515, budget=190, want_scores=kind != "nan", count=2)
+    _run(kind, d, group, n_que, tokens=2500, chunk=515, budget=190, want_scores=kind != "nan", count=2,
+         seen=SETTLED if kind == "gap" and group * n_que <= 1024 else 0)
 
 
 @pytest.mark.parametrize("kind", ["gap", "dense"])
 def test_options(kind):
     _run(kind, 128, 4, 24, 5600, 900, 400, rope=True)
-    _run(kind, 128, 4, 24, 5600, 900, 400, exact=True)
-    _run(kind, 128, 4, 24, 5600, 900, 400, want_scores=False)
-    _run(kind, 128, 2, 24, 15000, 2500, 2400)   # many kept rows
-    _run(kind, 128, 1, 40, 4800, 400, 4400)     # nearly all rows are kept
+    seen = SETTLED if kind == "gap" else LIST
+    _run(kind, 128, 4, 24, 5600, 900, 400, exact=True, seen=seen)
+    _run(kind, 128, 4, 24, 5600, 900, 400, want_scores=False, seen=seen)
+    _run(kind, 128, 2, 24, 15000, 2500, 2400, seen=seen)   # many kept rows
+    _run(kind, 128, 1, 40, 4800, 400, 4400, seen=seen)     # nearly all rows are kept
     _run(kind, 128, 8, 24, 1500, 400, 60)       # small chunks
 
 
@@ -115,14 +137,15 @@ def test_mixed_lengths_in_one_launch():
 
 
 def test_rows_that_are_not_numbers_end_the_same_way():
-    """A row of NaN makes every score NaN; nothing is selected on a spread that is not a number, and the
-    launch ends with the indices of the two passes."""
-    _run("nan", 128, 2, 20, 1500, 300, 100, want_scores=False)
+    """A row of NaN makes every score NaN; nothing is taken to stand clear, and the launch ends with the
+    indices of the two passes."""
+    _run("nan", 128, 2, 20, 4000, 900, 100, want_scores=False)
+    _run("nan", 128, 2, 20, 1500, 300, 100, want_scores=False, once=False)
 
 
 def _free_loop(q, chunks, kept, d, group):
-    """One slot whose steps see these chunks alone, each kept row count of `kept`: indices of all steps and the last
-    scores, of one launch and step by step."""
+    """One slot whose steps see these chunks alone and keep `kept` rows of them, in one launch and step by step: the
+    indices of all steps, and the ways they took."""
     n, big = len(chunks[0]), max(kept)
     outs = []
     for per_step in (False, True):
@@ -141,13 +164,14 @@ def _free_loop(q, chunks, kept, d, group):
         else:
             batch = F.LoopBatch(steps)
             fin.reserve_loop(batch)
+            ways = _record_ways(fin, len(chunks), 1)
             fin.loop(batch)
         torch.cuda.synchronize()
         outs.append([idx, scores, rows])
         fin.close()
     for a, b in zip(*outs):
-        assert torch.equal(a, b)
-    return outs[0][0].cpu()
+        assert torch.equal(a.view(BITS[a.dtype]), b.view(BITS[b.dtype]))
+    return outs[0][0].cpu(), ways[:, 0].tolist()
 
 
 @pytest.mark.parametrize("way", ["up", "down"])
@@ -178,5 +202,32 @@ def test_rows_that_all_move_far_at_once(way, rows, first, top):
     k = chunks[1].bfloat16().double()
     exact = torch.softmax(q.double() @ k.T / d ** 0.5, 1).sum(0)
     assert sorted(torch.sort(exact, descending=True, stable=True).indices[:2].tolist()) == want
-    got = _free_loop(q.bfloat16().cuda(), [c.bfloat16().cuda() for c in chunks], [1, 2, 2], d, group)
+    got, ways = _free_loop(q.bfloat16().cuda(), [c.bfloat16().cuda() for c in chunks], [1, 2, 2], d, group)
     assert got[0, 0] == 700 and got[1].tolist() == want
+    assert ways[1] == ONCE | RANGE
+
+
+@pytest.mark.parametrize("rows", [31, 192, 384])
+@pytest.mark.parametrize("kind", ["open", "tiny", "nan"])
+def test_keys_that_one_pass_leaves_open(kind, rows):
+    """A step whose first group of rows rises by three octaves, with keys of either group near the line; one that keeps keys
+    whose sums are too small for bounds; and one that meets a key that is not a number.  One chunk of rows and two."""
+    d, n, kept = 128, 2000, 40
+    g = torch.Generator().manual_seed(rows)
+    q = torch.zeros(rows, d)
+    q[:rows // 2, 0] = q[rows // 2:, 1] = 32
+    chunks = list(0.05 * torch.randn(3, n, d, generator=g))
+    chunks[0][700, :2] = 4.5  # stands clear: the next step tries one pass
+    near = torch.randperm(n, generator=g)[:2 * kept]
+    if kind == "tiny":
+        chunks[1][:, :2] = -20 - torch.rand(n, 1, generator=g)
+        chunks[1][near[:kept // 2], :2] = 4.5
+    else:
+        for i in range(2):
+            chunks[1][near[i::2], i] = 3.0 + 0.1 * torch.rand(kept, generator=g)
+        chunks[1][900, 0] = 5.25
+    if kind == "nan":
+        chunks[1][5, 7] = float("nan")
+    got, ways = _free_loop(q.bfloat16().cuda(), [c.bfloat16().cuda() for c in chunks], [1, kept, kept], d, 1)
+    assert got[0, 0] == 700
+    assert ways[1] == ONCE | {"nan": RANGE, "tiny": ALL if rows <= 256 else AGAIN, "open": LIST if rows <= 256 else AGAIN}[kind]
