@@ -1073,9 +1073,12 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     SelBand band = {turn == 1 ? fast_exp2(spread) * 1.004f : est.room};
     chosen = own_select(prm, pb, slot, N, dst, sel, sel_bytes, lkeys, step_probs, epoch, layered, sync_words, tid, &band);
     FINCH_PHASE(6);
+    if (turn == 2) break;
     const int n_lo = uni(band.n_lo), open = n_lo - uni(band.n_hi);
-    if (turn < 2) est.dense = !lkeys || (n_lo > pb.r && (n_chunks > 1 || 2 * (open * QB + kEstFixed) > N * QB));
-    est.room = fmaxf(kEstRoom, turn == 1 ? uni(band.room) : 0.5f + 0.5f * est.room);
+    est.dense = !lkeys || (n_lo > pb.r && (n_chunks > 1 || 2 * (open * QB + kEstFixed) > N * QB));
+    // (a step that has tried and started over keeps what it has learned)
+    if (turn == 1) est.room = fmaxf(kEstRoom, uni(band.room));
+    else if (est.way == 0) est.room = fmaxf(kEstRoom, 0.5f + 0.5f * est.room);
     if (turn != 1) break;
     // Keys below band.thr_lo are out and those above band.thr_hi are in whatever their exact scores are.
     // (The 0.4 % beside the spread are far more than what fp32 sums of exponentials differ by.)

@@ -231,3 +231,19 @@ def test_keys_that_one_pass_leaves_open(kind, rows):
     got, ways = _free_loop(q.bfloat16().cuda(), [c.bfloat16().cuda() for c in chunks], [1, kept, kept], d, 1)
     assert got[0, 0] == 700
     assert ways[1] == ONCE | {"nan": RANGE, "tiny": ALL if rows <= 256 else AGAIN, "open": LIST if rows <= 256 else AGAIN}[kind]
+
+
+def test_what_a_step_has_learned_outlives_it():
+    """Half of 384 rows rise or fall by three octaves each step, and a key two and a half octaves below the kept one is open to
+    the step that tries one pass.  That step starts over; the next one still knows how far it had to look, and
+    leaves it at two passes, and so does the one behind it."""
+    d, n, rows = 128, 900, 384
+    q = torch.zeros(rows, d)
+    q[:rows // 2, 0] = q[rows // 2:, 1] = 32
+    chunks = list(0.05 * torch.randn(6, n, d, generator=torch.Generator().manual_seed(1)))
+    for i, k in enumerate(chunks):
+        k[300, :2], k[400, :2] = 4.5, 4.5 - 0.625
+        k[[300, 400], 0] += 0.75 * (i % 2)
+    _, ways = _free_loop(q.bfloat16().cuda(), [c.bfloat16().cuda() for c in chunks], [1] * 6, d, 1)
+    assert ways[1] == ONCE | AGAIN
+    assert ways[2] == ways[3] == 0
