@@ -145,8 +145,10 @@ def test_rows_that_are_not_numbers_end_the_same_way():
 
 def _free_loop(q, chunks, kept, d, group):
     """One slot whose steps see these chunks alone and keep `kept` rows of them, in one launch and step by step: the
-    indices of all steps, and the ways they took."""
-    n, big = len(chunks[0]), max(kept)
+    indices of all steps, and the ways they took.  (The chunks in one allocation: with some of them more than
+    16 GiB apart, where an allocator may put them, the loop takes the kernels for two passes.)"""
+    q, chunks = q.bfloat16().cuda(), torch.stack(chunks).bfloat16().cuda()
+    n, big = chunks.shape[1], max(kept)
     outs = []
     for per_step in (False, True):
         fin = F.Finch(F.FINCH_BF16, d, group)
@@ -202,7 +204,7 @@ def test_rows_that_all_move_far_at_once(way, rows, first, top):
     k = chunks[1].bfloat16().double()
     exact = torch.softmax(q.double() @ k.T / d ** 0.5, 1).sum(0)
     assert sorted(torch.sort(exact, descending=True, stable=True).indices[:2].tolist()) == want
-    got, ways = _free_loop(q.bfloat16().cuda(), [c.bfloat16().cuda() for c in chunks], [1, 2, 2], d, group)
+    got, ways = _free_loop(q, chunks, [1, 2, 2], d, group)
     assert got[0, 0] == 700 and got[1].tolist() == want
     assert ways[1] == ONCE | RANGE
 
@@ -228,7 +230,7 @@ def test_keys_that_one_pass_leaves_open(kind, rows):
         chunks[1][900, 0] = 5.25
     if kind == "nan":
         chunks[1][5, 7] = float("nan")
-    got, ways = _free_loop(q.bfloat16().cuda(), [c.bfloat16().cuda() for c in chunks], [1, kept, kept], d, 1)
+    got, ways = _free_loop(q, chunks, [1, kept, kept], d, 1)
     assert got[0, 0] == 700
     assert ways[1] == ONCE | {"nan": RANGE, "tiny": ALL if rows <= 256 else AGAIN, "open": LIST if rows <= 256 else AGAIN}[kind]
 
@@ -244,6 +246,6 @@ def test_what_a_step_has_learned_outlives_it():
     for i, k in enumerate(chunks):
         k[300, :2], k[400, :2] = 4.5, 4.5 - 0.625
         k[[300, 400], 0] += 0.75 * (i % 2)
-    _, ways = _free_loop(q.bfloat16().cuda(), [c.bfloat16().cuda() for c in chunks], [1] * 6, d, 1)
+    _, ways = _free_loop(q, chunks, [1] * 6, d, 1)
     assert ways[1] == ONCE | AGAIN
     assert ways[2] == ways[3] == 0
