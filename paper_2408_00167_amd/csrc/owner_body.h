@@ -124,6 +124,8 @@ struct RowEstimates {
   float room = kEstRoom;     // how far from the r-th largest score keys are taken to stay open: as in the last step that tried, less with every one that does not
   bool dense = true;         // too many keys are that close (by the last step's scores): not worth trying
   bool hidden = false;       // this step's scores are not seen by anybody
+  int pause = 0;             // steps worth trying that are still left at two passes after tries of no use ...
+  int longest = 3;           // ... and how many were the last time: 7, 15, 31, ... as long as none is of use
   int way = 0;               // how this step selects (kWay...)
   const int* ask = nullptr;  // (no estimate: memory that a later step begins with)
 };
@@ -648,7 +650,15 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   bf16x8 ka[D / 16], kb[D / 16];
   static_assert(!ONCE || (LOOP && !DOC));
   bool once = ONCE && est.hidden && est.q == pb.q && est.rows == Rp && Rp <= est.cap && lkeys && !est.dense;
+  if (ONCE && once && est.pause > 0) {
+    --est.pause;
+    once = false;
+  }
   if (ONCE) est.way = once ? kWayOnce : 0;
+  auto no_use = [&](int why) {
+    est.way |= why;
+    est.pause = est.longest = 2 * est.longest + 1;
+  };
   unsigned most = 0u, least = 0u;  // largest order key of any row's log2 z, and the smallest one's complement
   Selected chosen = {nullptr, false, false};
   int asked;  // (asked for beside the first key block)
@@ -795,7 +805,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
       // (rows that are not numbers, or one whose sum is out of range: the spread is infinite or not a number)
       if (!(spread <= kEstSpread)) {
         once = false;
-        est.way |= kWayRange;
+        no_use(kWayRange);
         if (ch > 0) {  // (the chunks before have no exact scores)
           ch = -1;
           continue;
@@ -1084,11 +1094,12 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     // (The 0.4 % beside the spread are far more than what fp32 sums of exponentials differ by.)
     if (n_lo == pb.r && band.least >= kEstLeast) {
       est.way |= kWaySettled;
+      est.longest = 3;
       break;
     }
     if (n_chunks > 1) {  // (rows that are no longer staged: the step once more, with both passes)
       once = false;
-      est.way |= kWayAgain;
+      no_use(kWayAgain);
       ch = -1;
       break;
     }
@@ -1098,9 +1109,10 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     unsigned short* const list = reinterpret_cast<unsigned short*>(sel + static_cast<size_t>(RC) * (kOwnWaves * 8 + 4) + 16);
     if (!(band.least >= kEstLeast) || n2 <= 0 || reinterpret_cast<char*>(list + n2) > reinterpret_cast<char*>(lkeys)) {
       n2 = N;
-      est.way |= kWayAll;
+      no_use(kWayAll);
     } else {
       est.way |= kWayList;
+      est.longest = 3;
       for (int i0 = 0; i0 < N; i0 += kOwnThreads) {
         const int i = i0 + tid;
         const unsigned key = i < N ? lkeys[i] : 0u;

@@ -249,3 +249,33 @@ def test_what_a_step_has_learned_outlives_it():
     _, ways = _free_loop(q, chunks, [1] * 6, d, 1)
     assert ways[1] == ONCE | AGAIN
     assert ways[2] == ways[3] == 0
+
+
+@pytest.mark.parametrize("rows", [192, 384])
+@pytest.mark.parametrize("kind", ["range", "open", "tiny"])
+def test_tries_of_no_use_become_rare(kind, rows):
+    """Steps whose guesses never serve - half of the rows rise or fall by 30 octaves each time, by 3 with another key within
+    them of the line, or the scores are too small - and then some whose guesses do.  What a try costs is paid once in
+    the first eight steps and once more in the sixteen after them, and tries that serve are made again."""
+    d, n, steps, calm = 128, 900, 22, 30
+    g = torch.Generator().manual_seed(rows)
+    q = torch.zeros(rows, d)
+    q[:rows // 2, 0] = q[rows // 2:, 1] = 32
+    chunks, kept = list(0.05 * torch.randn(steps + calm, n, d, generator=g)), [1] * (steps + calm)
+    for i, k in enumerate(chunks):
+        k[300, :2] = 4.5  # stands clear
+        if i < steps and kind == "tiny" and i > 0:
+            k[:, :2] = -20 - torch.rand(n, 1, generator=g)
+            k[:20, :2] = 4.5
+            kept[i] = 40
+        elif i < steps and kind != "tiny":
+            k[400, :2] = 4.5 - 0.625  # two and a half octaves below
+            k[[300, 400], 0] += (7.5 if kind == "range" else 0.75) * (i % 2)
+    _, ways = _free_loop(q, chunks, kept, d, 1)
+    no_use = {"range": RANGE, "open": AGAIN, "tiny": ALL if rows <= 256 else AGAIN}[kind]
+    if kind == "open" and rows <= 256:  # a list of two keys: it pays
+        assert all(w == ONCE | LIST for w in ways[1:steps])
+    else:
+        assert ways[1] == ONCE | no_use
+        assert sum(w & no_use > 0 for w in ways[:steps]) <= 2
+    assert sum(w & SETTLED > 0 for w in ways[steps:]) >= calm // 2 - 2
