@@ -538,10 +538,10 @@ bool rows_pay_to_stay(const finch_ctx* ctx, const Plan& pl, int32_t n_steps) {
 
 // Whether a whole loop may leave out a step's scores where the next step overwrites them (owner_loop_bf16 decides
 // step by step): nothing else of the slot touches them, every problem selects for itself, and the
-// order of the kept rows does not depend on them.  Those kernels spend 2 to 3 us a step more than the others, which a
-// pass saves from 2600 candidates * (row blocks + 1) on (128 channels; twice as many for 64).  Time with : without,
-// 48 loops of 1024 to 12000 tokens in chunks of 128 to 2048, 16 to 192 rows, no key near the line: below it 0.91 to 1.22
-// (mostly above 1), from it on 0.82 to 0.97; keys spread evenly: below 1.02 to 1.20, from it on 0.93 to 1.07.
+// order of the kept rows does not depend on them.  Those kernels spend about 1 us a step more than the others, which a
+// pass saves from 2600 candidates * (row blocks + 1) on (128 channels; twice as many for 64).  Time
+// with : without, 48 loops of 1024 to 12000 tokens in chunks of 128 to 2048, 16 to 192 rows, no key near the line: below it
+// 0.95 to 1.18 (mostly above 1), from it on 0.80 to 0.99; keys spread evenly: below 1.03 to 1.12, from it on 0.97 to 1.05.
 bool scores_may_be_bounds(const finch_ctx* ctx, const Plan& pl, int32_t n_steps) {
   if (ctx->cfg.dtype != FINCH_BF16 || pl.has_doc || !ctx->loop_rows_may_stay || ctx->layer_group != 1 ||
       ctx->repos.order != FINCH_ORDER_ASCENDING || n_steps < 3)
@@ -1221,7 +1221,9 @@ finch_status finch_loop(finch_ctx* ctx, const finch_problem* host_desc, const fi
     p.ways = ctx->loop_ways;
     // notes of where kept rows lie: as many as fit beside the rest of the LDS (the kernels that move
     // every row are fp32's, and slots by rank put the rows in another order)
-    // (guesses for all rows of any problem if they fit, else for problems whose rows go through in one chunk)
+    // (guesses for all rows of any problem if they fit, else for problems whose rows go through in one chunk.  They come
+    // first: a pass is most of a step, and where the LDS is full they leave room for half as many notes less as they have words,
+    // 144 with 256 rows; steps that keep more rows than there are notes for move them.)
     for (const int32_t rows : {pl.rpad_max, pl.own_row_chunk}) {
       const size_t est_words = static_cast<size_t>(rows) + finch::kEstExtraWords;
       if (p.est_words == 0 && scores_may_be_bounds(ctx, pl, n_steps) && rows <= finch::kEstMaxRows &&

@@ -87,9 +87,16 @@ struct KeptRows {
   bool stay = false;         // this step leaves its kept rows where they are
 };
 
-// Keys that stay open cost their part of the second pass, and as much as kEstFixed keys of one row block more: finding
-// them, and another selection.  One pass saves most of the other: worth trying up to half of that.
-constexpr int kEstFixed = 300;
+// Keys that stay open cost their part of the second pass, and finding them and another selection 5 to 6 us: the
+// time of 500 (192 rows, long steps) to 1200 keys (32 rows) there.  So a step is worth trying while both come to well less
+// than that pass; half of it for what they may come to, as what is open is known from the step before only.  est_fixed is in
+// keys of one row block.  Loops of 256 problems, time : with two passes at every step, keys spread evenly and relevant keys that
+// stand clear: with this 0.86 to 1.05 and 0.71 to 0.94; with 600 whatever the rows 0.86 to 1.07 and 0.71 to 0.95; with 3000 (6000
+// for 64 channels) 0.87 to 1.05 and 0.72 to 0.98, as tries are left out that would have settled all but a few keys.
+template <int D>
+__device__ constexpr int est_fixed(int qb) {
+  return (300 + 200 * qb) * 128 / D;
+}
 constexpr float kEstRoom = 1.15f;      // factor around the r-th largest score in which a slot without experience looks for others
 constexpr float kEstSpread = 16.f;     // log2 of the largest spread that is of use
 // Largest |log2 z_i|: sums of 1024 rows stay below 2^70, and the terms below 2^-126 that a row's sum of 2^-60 and more has
@@ -102,7 +109,9 @@ constexpr float kEstLeast = 0x1p-60f;  // smaller key sums may have lost terms b
 // exp2(logit - g_i) for every key and z_i = 2^(lse_i - g_i) for every row; all terms are
 // positive, so the true score of every key lies between S_j / max_i z_i and S_j / min_i z_i.  Keys
 // further from the r-th largest S than that spread are in or out whatever their exact scores
-// are; only the others, often none, are scored exactly and chosen among.  The selection is that of the exact scores.
+// are; only the others, often none, are scored exactly and chosen among.  The selection is that of two passes, but for open
+// keys whose exact scores differ by no more than rounding: the log-sum-exps behind them are sums over another
+// reference, and may differ from those of two passes in the last bit.
 // As guesses serve the log-sum-exps of the slot's step before (the same rows over most of the same heavy
 // keys).  The scores themselves are not formed, so this is for steps whose scores nobody can see:
 // the next step of the call overwrites all of them (the host has checked that nothing else of the
@@ -110,11 +119,15 @@ constexpr float kEstLeast = 0x1p-60f;  // smaller key sums may have lost terms b
 // What bounds these loops is the chip's power: with 192 rows a launch runs at 1.72 GHz, at 1.92 GHz with the same
 // cycles when its keys come from L2, at 2.13 GHz without key loads.  So what counts is work not done: one
 // pass has half the matrix instructions, LDS operands and key bytes of two and two thirds of their
-// vector instructions.  Both sides of the loop of 256 problems, 128 channels: 192 rows, 4096-token chunks of 131072
-// tokens, no key near the line 4700 -> 2880 us, keys spread evenly 4850 -> 3610 (open keys scored
-// exactly; with more rows than a chunk, whose open keys start the step over, 360 rows, 2048-token chunks of 32768: 3070 ->
-// 2130 and 3035); 256 rows, 2048-token chunks 1945 -> 1290; 32 rows, 512-token chunks, 1024 problems 957 -> 877.  Steps that do
-// not pay (kEstFixed) make both passes, 2 to 3 us slower than in the kernels without this.
+// vector instructions.  Loops of 256 problems, 128 channels, two passes at every step and this: 192 rows, 4096-token
+// chunks of 131072 tokens, no key near the line 4790 -> 2920 us, keys spread evenly 4820 -> 3610 (open keys scored
+// exactly; rows in several chunks, with which open keys start the step over, 360 rows, 2048-token chunks of 32768: 2565 ->
+// 1670 and 2575); 256 rows, 2048-token chunks 1965 -> 1325 and 1985; 1024 problems of 32 rows, 512-token chunks 952 -> 900.
+// Steps that do not pay (est_fixed) make both passes with code of their own (kOnceNote), which differs from the kernels without
+// this by noting the guesses and how many keys are near the line: 0.6 to 1.4 us a step, 2 where both ways were one code.  A
+// try that turns out of no use costs its pass beside the two, so tries are left out for longer with each that is (pause): log-sum-exps
+// that move apart at every step, 192 rows, 8 steps 1184 us with two passes, 1257, 1604 with a try at every step.
+enum : int { kOnceNote = 1, kOnceTry = 2 };
 struct RowEstimates {
   float* lse = nullptr;      // LDS: one guess per row (`cap` of them) ...
   int cap = 0;
@@ -553,8 +566,9 @@ __device__ __forceinline__ bool own_any(int qb, F f) {
 // and selects on the sum, so that all L arrive at the same indices on their own.
 // `step_probs` are the descriptors of this step, `epoch` counts the exchanges this
 // workgroup has been through in this launch; returns true if the step made one.
-// ONCE: steps whose scores nobody sees may select on one pass (RowEstimates).
-template <int D, int QBT, bool ROT, bool DOC, bool LOOP, bool ONCE>
+// ONCE (RowEstimates): kOnceTry selects on one pass, if that is worth trying; true if the step is done, else it
+// is to be made with kOnceNote, which makes both passes and leaves what the next try needs.
+template <int D, int QBT, bool ROT, bool DOC, bool LOOP, int ONCE>
 __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const finch_problem& pb, int slot,
                                               int stages, char* smem, const void*& staged_q,
                                               int& staged_rows, const finch_problem* step_probs,
@@ -562,7 +576,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   const int N = pb.c + pb.m;
   if (N == 0) {
     kept.mapped = false;
-    return false;
+    return ONCE == kOnceTry;
   }
   FINCH_PHASE_BEGIN();
   const int Rp = (DOC && !pb.q) ? 0 : prm.group * pb.n_que;  // prompt rows
@@ -649,12 +663,14 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   // 2346 where every chunk asks for its rows when its turn has come (64 channels, 256 rows: 1569 and 1669).
   bf16x8 ka[D / 16], kb[D / 16];
   static_assert(!ONCE || (LOOP && !DOC));
-  bool once = ONCE && est.hidden && est.q == pb.q && est.rows == Rp && Rp <= est.cap && lkeys && !est.dense;
-  if (ONCE && once && est.pause > 0) {
-    --est.pause;
-    once = false;
+  if (ONCE == kOnceTry) {
+    if (!est.hidden || est.q != pb.q || est.rows != Rp || Rp > est.cap || !lkeys || est.dense) return false;
+    if (est.pause > 0) {
+      --est.pause;
+      return false;
+    }
+    est.way = kWayOnce;
   }
-  if (ONCE) est.way = once ? kWayOnce : 0;
   auto no_use = [&](int why) {
     est.way |= why;
     est.pause = est.longest = 2 * est.longest + 1;
@@ -694,7 +710,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
 
     // ---- the only pass (RowEstimates): row sums and key sums of exp2(logit - guess), fixed block assignment
     float spread = 0.f;  // log2 of max_i z_i / min_i z_i
-    if (ONCE && once) {
+    if (ONCE == kOnceTry) {
       const int tid = own_thread(), lane = tid & 63, t = lane & 31, h = lane >> 5;
       float z_run[QBT], g[QBT];
 #pragma unroll
@@ -804,18 +820,13 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
       FINCH_PHASE(3);
       // (rows that are not numbers, or one whose sum is out of range: the spread is infinite or not a number)
       if (!(spread <= kEstSpread)) {
-        once = false;
         no_use(kWayRange);
-        if (ch > 0) {  // (the chunks before have no exact scores)
-          ch = -1;
-          continue;
-        }
-        b = wave;
-        load_k_block<D>(ks, N, b << 5, lane, ka);
+        staged_q = (n_chunks == 1) ? pb.q : nullptr;
+        return false;
       }
     }
 
-    if (!ONCE || !once) {
+    if constexpr (ONCE != kOnceTry) {
     // ---- pass 1: running (reference, sum exp2) per prompt row, fixed block assignment
     {
       float m_run[QBT], z_run[QBT];
@@ -972,7 +983,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     if (LOOP) asm volatile("" ::"v"(asked));
     int n2 = N, nb2 = nbc;
     KeySource ks2 = ks;
-    for (int turn = ONCE && once ? 1 : 0; turn < 3; ++turn) {
+    for (int turn = ONCE == kOnceTry ? 1 : 0; turn < 3; ++turn) {
     if (turn != 1) {
       const int tid = own_thread(), lane = tid & 63, t = lane & 31, h = lane >> 5;
       auto process = [&](const bf16x8(&kf)[D / 16], int blk) {
@@ -1023,7 +1034,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
         const float tot = fold16_over32(u, t);
         int key = kbase + acc_key(t >> 1, h);
         if ((t & 1) == 0 && key < n2) {
-          if (ONCE && once) {
+          if (ONCE == kOnceTry) {
             if (ks2.list) key = ks2.list[key];
             lkeys[key] = order_key(tot);
             return;
@@ -1085,7 +1096,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     FINCH_PHASE(6);
     if (turn == 2) break;
     const int n_lo = uni(band.n_lo), open = n_lo - uni(band.n_hi);
-    est.dense = !lkeys || (n_lo > pb.r && (n_chunks > 1 || 2 * (open * QB + kEstFixed) > N * QB));
+    est.dense = !lkeys || (n_lo > pb.r && (n_chunks > 1 || 2 * open * QB + est_fixed<D>(QB) > N * QB));
     // (a step that has tried and started over keeps what it has learned)
     if (turn == 1) est.room = fmaxf(kEstRoom, uni(band.room));
     else if (est.way == 0) est.room = fmaxf(kEstRoom, 0.5f + 0.5f * est.room);
@@ -1097,11 +1108,9 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
       est.longest = 3;
       break;
     }
-    if (n_chunks > 1) {  // (rows that are no longer staged: the step once more, with both passes)
-      once = false;
+    if (n_chunks > 1) {  // (rows that are no longer staged)
       no_use(kWayAgain);
-      ch = -1;
-      break;
+      return false;
     }
     // ---- the others one by one
     const unsigned thr_lo = band.thr_lo, thr_hi = band.thr_hi;
@@ -1134,7 +1143,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
     load_k_block<D>(ks2, n2, b * 32, lane, ka);
     }
   }
-  if (lkeys_sum && !once)
+  if (lkeys_sum && ONCE != kOnceTry)
     for (int i = tid; i < N; i += kOwnThreads) dst[i] = order_value(lkeys[i]);
   if (DOC && n_chunks == 0) own_no_rows(gscores, lkeys, N, tid);
   // what the prompt-row region of LDS holds now (selection scratch lies behind it)
@@ -1147,7 +1156,7 @@ __device__ __forceinline__ bool own_step_body(const LaunchParams& prm, const fin
   // ---- top-r and compaction (the pass-1 statistics are dead)
   if (ONCE) {
     own_compact<D / 8, 8, ROT>(prm, pb, N, chosen, dst, sel, lkeys != nullptr, tid, kept);
-    return layered;
+    return true;
   }
   own_finish_step<D / 8, 8, ROT>(prm, pb, slot, N, dst, sel, sel_bytes, lkeys, step_probs, epoch, layered, sync_words, tid, kept);
   return layered;
@@ -1186,7 +1195,7 @@ __global__ __launch_bounds__(kOwnThreads, own_lean(D, QBT, ROT, DOC) ? 4 : 2) vo
   int staged_rows = 0;
   KeptRows kept;
   RowEstimates est;
-  own_step_body<D, QBT, ROT, DOC, false, false>(prm, pb, p, stages, smem, staged_q, staged_rows, prm.probs, 0, kept, est);
+  own_step_body<D, QBT, ROT, DOC, false, 0>(prm, pb, p, stages, smem, staged_q, staged_rows, prm.probs, 0, kept, est);
 }
 
 // One launch = the whole chunk loop (Method: Document Segmentation): workgroup b
@@ -1240,18 +1249,25 @@ __global__ __launch_bounds__(kOwnThreads) void owner_loop_bf16(LaunchParams prm,
     const bool more1 = slot < t2 - t1, more2 = slot < t3 - t2;  // (nobody is present past the last step)
     const DescriptorPtr next = probs + (more1 ? t1 : t0) + slot, after = probs + (more2 ? t2 : t0) + slot;
     kept.stay = own_rows_may_stay(probs + t0 + slot, next, after, prm.stay_rows);
-    if (ONCE)
-      est.hidden = more1 && next->scores == probs[t0 + slot].scores && next->c + next->m >= probs[t0 + slot].c + probs[t0 + slot].m;
+    if (ONCE) {  // (as above)
+      const DescriptorPtr here = probs + t0 + slot;
+      est.hidden = (more1 & (next->scores == here->scores) & (next->c + next->m >= here->c + here->m)) | !here->scores;
+    }
     const finch_problem pb = load_problem(prm.probs + t0 + slot);
     // (rows in a cache that an earlier step has moved would be overwritten while they are still wanted)
     kept.stay = kept.stay && more2 && (s == 0 || pb.c == 0 || kept.mapped);
-    est.hidden = est.hidden || !pb.scores;
     est.ask = descriptor_at(s + 3);
     est.way = 0;
     FINCH_PHASE(0);
-    if (own_step_body<D, QBT, ROT, DOC, true, ONCE>(prm, pb, slot, /*stages=*/1, smem, staged_q, staged_rows, prm.probs + t0,
-                                        epoch, kept, est))
+    if constexpr (ONCE) {
+      if (!own_step_body<D, QBT, ROT, DOC, true, kOnceTry>(prm, pb, slot, /*stages=*/1, smem, staged_q, staged_rows, prm.probs + t0,
+                                                           epoch, kept, est))
+        own_step_body<D, QBT, ROT, DOC, true, kOnceNote>(prm, pb, slot, /*stages=*/1, smem, staged_q, staged_rows, prm.probs + t0,
+                                                         epoch, kept, est);
+    } else if (own_step_body<D, QBT, ROT, DOC, true, 0>(prm, pb, slot, /*stages=*/1, smem, staged_q, staged_rows, prm.probs + t0,
+                                                        epoch, kept, est)) {
       ++epoch;
+    }
     if (ONCE && prm.ways && threadIdx.x == 0) prm.ways[static_cast<size_t>(s) * gridDim.x + slot] = est.way;
     // the rows this step wrote are the next step's cache: complete before it reads
     __syncthreads();

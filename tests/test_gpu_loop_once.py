@@ -113,8 +113,8 @@ def test_several_chunks_of_rows(kind, d, group, n_que):
 def test_options(kind):
     _run(kind, 128, 4, 24, 5600, 900, 400, rope=True)
     seen = SETTLED if kind == "gap" else LIST
-    _run(kind, 128, 4, 24, 5600, 900, 400, exact=True, seen=seen)
-    _run(kind, 128, 4, 24, 5600, 900, 400, want_scores=False, seen=seen)
+    _run(kind, 128, 4, 24, 11200, 1800, 400, exact=True, seen=seen)
+    _run(kind, 128, 4, 24, 11200, 1800, 400, want_scores=False, seen=seen)
     _run(kind, 128, 2, 24, 15000, 2500, 2400, seen=seen)   # many kept rows
     _run(kind, 128, 1, 40, 4800, 400, 4400, seen=seen)     # nearly all rows are kept
     _run(kind, 128, 8, 24, 1500, 400, 60)       # small chunks
